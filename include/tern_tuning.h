@@ -13,7 +13,10 @@ extern "C" {
 
 /* Tuning overrides.  They belong to the calling host thread: a launch reads the values set by
  * its own thread, so another thread's tern_set_option cannot change a plan half-way through; a
- * new thread starts with the defaults (everything chosen per call from the problem size).  TERN_OPT_LANE_DEPTH: output voxels per lane along z in
+ * new thread starts with the defaults (everything chosen per call from the problem size).  By default
+ * the tiled convolution takes its inner products on the matrix cores; TERN_OPT_LANE_DEPTH, _WAVES_Z,
+ * _CO_BLOCK, _CO_PER_WAVE, _TAP_SPLIT, _LANE_TILE and _STREAM shape the bit-count form of the kernel, and a
+ * thread that has set any of them gets that form.  TERN_OPT_LANE_DEPTH: output voxels per lane along z in
  * the tiled convolution kernel, 0 = choose automatically, 1, 2 or 4 = force (1 and 4 only
  * where that variant exists).  TERN_OPT_WAVES_Z: waves
  * stacked along z in one workgroup (sharing one LDS halo tile), 0 = choose, 1, 2, 4 or 8 = start
@@ -45,7 +48,7 @@ int tern_set_option(int option, int value);
  * (tern_conv3d, tern_conv3d_binary, tern_conv3d_digits, or the last layer of a network call), so
  * that a test can tell which kernel its input reached.  info (host, 8 values): [0] kernel, one of
  * the TERN_KERNEL_ values (-1 before the thread's first launch); for the tiled and persistent
- * kernels [1] output voxels per lane, [2] channels per pass, [3] waves sharing the taps of a slice,
+ * kernels [1] output voxels per lane (a wave's voxels / 64), [2] channels per pass, [3] waves sharing the taps of a slice,
  * [4] threads per workgroup, [5], [6] grid extents, [7] LDS bytes per workgroup; zeros otherwise.
  * TERN_ENULL for a NULL pointer.
  */

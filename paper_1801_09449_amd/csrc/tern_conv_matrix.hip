@@ -1,0 +1,737 @@
+// Tiled ternary convolution with the inner product taken by the matrix instructions.  Same packed
+// activations, same filter banks, same halo tiles in LDS and the same integers as the bit-count kernels
+// (tern_conv_tiled.hip); what differs is the unit that contracts.  A ternary code is the 4-bit float
+// +1 = 0010, -1 = 1010 or 0 = x000, and v_mfma_f32_32x32x64_f8f6f4 takes 32 filters x 32 voxels x 64
+// channels of them in 32 cycles of a SIMD: 64 products per lane and cycle, against 32 per three vector
+// instructions (12 cycles) of the masked-Hamming step.  Sums are floats and exact: every partial sum is an
+// integer, or an integer and a half, far below 2^23.
+//
+// Rows of the product are filters, columns are voxels, so that in the result a lane holds 16 filters of
+// one voxel and re-packing is shifts within the lane.  A wave owns VB blocks of 32 voxels (a box of the
+// output) x NB blocks of 32 filters and walks the kernel taps and channel words in bank order, 64
+// channels per step: lanes 0-31 hold the step's first word (or, where a voxel has an odd number of
+// words, its first (tap, word) entry), lanes 32-63 its second.
+//
+// What bounds it: beside a matrix instruction a SIMD has room for about four vector instructions (a
+// register-only loop: 32.7 cycles per matrix instruction with none, 33.8 with four, 42 with eight, 53
+// with twelve), so the 2-bit codes must not be widened where they are used most.  Voxels are widened once,
+// on their way into LDS (16 bytes per word and voxel, a 16-byte read per operand; with 8-byte records
+// widened behind the read the same launches took 6-14 % longer).  Filter words come from the bank as bits
+// and are widened per wave and step, ten instructions for a block that VB matrix instructions use; VB = 4
+// with NB = 2 leaves three vector instructions per matrix instruction and uses all registers (two waves
+// per SIMD).  Under this load the clock falls to 1.9 GHz, where 32 cycles are 8 000 TFLOP/s for the chip.
+// Measured, fused output, bit-count kernels before: 64 -> 64 channels on 96^3, dilation 2: 276 -> 55 us;
+// 256 -> 256 on 2 x 32^3: 321 -> 44 us (5 290 TFLOP/s: loop 38, fill 3, epilogue 3 us); 64 -> 64 3 x 3 on
+// 16 planes of 232 x 168: 83 -> 23 us.
+#include <string.h>
+
+#include <cmath>
+#include <type_traits>
+
+#include "tern_internal.h"
+
+namespace tern {
+namespace {
+
+typedef int v4i __attribute__((ext_vector_type(4)));
+typedef int v8i __attribute__((ext_vector_type(8)));
+typedef float v16f __attribute__((ext_vector_type(16)));
+typedef uint32_t v2u __attribute__((ext_vector_type(2)));
+
+// Quotient of small numbers: e / d = (e * m) >> s for every e the plan divides (below 2^16).
+struct Reciprocal {
+    uint32_t m, s;
+};
+
+struct MatrixPlan {
+    int32_t lxb, lyb;                // a wave's voxels: 2^lxb x 2^lyb x the rest
+    int32_t nwy, nwz, nwc;           // waves of a workgroup along y, z and over filter groups
+    int32_t hx, hy, hz;              // halo extents in voxels
+    int32_t tiles_x, tiles_y, tiles_z;
+    int32_t nch;                     // words (or word pairs) per voxel
+    int32_t pl;                      // LDS bytes of one word plane
+    int32_t zero_off;                // LDS byte offset of a zero record (odd word counts)
+    int32_t tp_log;                  // tap-packed bank: log2 of the taps per row
+    int32_t cut_off;                 // LDS byte offset of the staged cut points
+    Reciprocal r_hx, r_pl, r_ch, r_kw, r_kh;
+};
+
+// What the words are: ternary or binary (sign-only) filter banks, two-digit activations, or the tap-packed
+// bank of up to 16 input channels (several taps share a filter word; here each tap is a word of its own).
+enum { kTernary = 0, kBinary = 1, kDigits = 2, kTapPacked = 3 };
+
+__device__ __forceinline__ uint32_t quotient(uint32_t e, Reciprocal r) { return __umul24(e, r.m) >> r.s; }
+
+// (mask, sign) word of 32 channels -> two words whose 4-bit field i holds, for two channels each,
+// the sign in bits 3 / 2 and the mask in bits 1 / 0: channels 4 i + 1 / 4 i in the first, 4 i + 3 /
+// 4 i + 2 in the second.
+__device__ __forceinline__ v2u interleave(uint32_t m, uint32_t s, uint32_t m33)
+{
+    v2u w;
+    w.x = __builtin_amdgcn_bitop3_b32(m33, m, s << 2, 0xca);   // m33 ? m : s << 2
+    w.y = __builtin_amdgcn_bitop3_b32(m33, m >> 2, s, 0xca);
+    return w;
+}
+
+// Two interleaved words -> 32 four-bit floats (E2M1: +1 = 0010, -1 = 1010, 0 = x000).
+__device__ __forceinline__ v4i expand(v2u w, uint32_t maa)
+{
+    v4i o;
+    o.x = (int)((w.x << 1) & maa);
+    o.y = (int)(w.x & maa);
+    o.z = (int)((w.y << 1) & maa);
+    o.w = (int)(w.y & maa);
+    return o;
+}
+
+// Two balanced-ternary digits per value (low + 3 high, -4 .. 4) to the E2M1 code of the value
+// (magnitudes 1, 2, 3, 4 = 0010, 0100, 0101, 0110), channels in the order of expand().
+__device__ __forceinline__ v4i expand_digits(uint32_t lm, uint32_t hm, uint32_t ls, uint32_t hs)
+{
+    const uint32_t b3 = (hm & hs) | (lm & ls & ~hm);
+    const uint32_t b2 = hm;
+    const uint32_t b1 = lm & ~(hm & (ls ^ hs));
+    const uint32_t b0 = hm & ~lm;
+    v4i o;
+    o.x = (int)((b0 & 0x11111111u) | ((b1 << 1) & 0x22222222u) | ((b2 << 2) & 0x44444444u) | ((b3 << 3) & 0x88888888u));
+    o.y = (int)(((b0 >> 1) & 0x11111111u) | (b1 & 0x22222222u) | ((b2 << 1) & 0x44444444u) | ((b3 << 2) & 0x88888888u));
+    o.z = (int)(((b0 >> 2) & 0x11111111u) | ((b1 >> 1) & 0x22222222u) | (b2 & 0x44444444u) | ((b3 << 1) & 0x88888888u));
+    o.w = (int)(((b0 >> 3) & 0x11111111u) | ((b1 >> 2) & 0x22222222u) | ((b2 >> 1) & 0x44444444u) | (b3 & 0x88888888u));
+    return o;
+}
+
+// 32 filters x 32 voxels x 64 channels; 4-bit operands occupy the first four of the eight operand
+// registers, and constant zero scale operands select the instruction without block scales.
+__device__ __forceinline__ v16f multiply(v4i a, v4i b, v16f c)
+{
+    const v8i a8 = __builtin_shufflevector(a, a, 0, 1, 2, 3, -1, -1, -1, -1);
+    const v8i b8 = __builtin_shufflevector(b, b, 0, 1, 2, 3, -1, -1, -1, -1);
+    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a8, b8, c, 4, 4, 0, 0, 0, 0);
+}
+
+// word = (word << 1) | (thr < d), and with d < thr, through the carry flag.
+__device__ __forceinline__ void shift_in_gt_v(uint32_t& word, int32_t d, int32_t thr)
+{
+    asm("v_cmp_lt_i32 vcc, %2, %1\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(word) : "v"(d), "v"(thr) : "vcc");
+}
+__device__ __forceinline__ void shift_in_lt_v(uint32_t& word, int32_t d, int32_t thr)
+{
+    asm("v_cmp_gt_i32 vcc, %2, %1\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(word) : "v"(d), "v"(thr) : "vcc");
+}
+
+// Scalar walk over (kernel tap, channel word or pair of words) in bank order.  The LDS offsets of the
+// taps sit in the lanes of two registers (tap t in lane t % 64 of the (t / 64)-th).
+struct Walk {
+    int tap, ch, off;
+};
+__device__ __forceinline__ void advance(Walk& w, int nch, int inc_ch, int& tab, int tab1)
+{
+    w.off += inc_ch;
+    if (++w.ch == nch) {
+        w.ch = 0;
+        if (++w.tap == 64) tab = tab1;
+        w.off = __builtin_amdgcn_readlane(tab, w.tap & 63);
+    }
+}
+
+template <int VB, int NB, bool PACKED, int KIND, bool ODD, bool EXP>
+__global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPlan t)
+{
+    extern __shared__ __align__(16) uint8_t lds8[];
+    const int tid = threadIdx.x;
+    const int nthreads = blockDim.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+    int bid = blockIdx.x;
+    {   // contiguous runs of tiles per XCD (workgroups go to the 8 XCDs round-robin)
+        const int per_xcd = gridDim.x >> 3;
+        if (bid < (per_xcd << 3)) bid = (bid & 7) * per_xcd + (bid >> 3);
+    }
+    const int tix = bid % t.tiles_x; bid /= t.tiles_x;
+    const int tiy = bid % t.tiles_y; bid /= t.tiles_y;
+    const int tiz = bid % t.tiles_z;
+    const int n = bid / t.tiles_z;
+    const int X = 1 << t.lxb, Y = 1 << t.lyb, Z = (32 * VB) >> (t.lxb + t.lyb);
+    const int ox0 = tix << t.lxb, oy0 = tiy * (Y * t.nwy), oz0 = tiz * (Z * t.nwz);
+    const int wc = wave % t.nwc, wsp = wave / t.nwc;
+    const int wy = wsp % t.nwy, wz = wsp / t.nwy;
+    const int cb = (blockIdx.y * t.nwc + wc) * (32 * NB);   // first filter of this wave
+    const bool active = cb < p.c_out;
+
+    const int i32 = lane & 31, g = lane >> 5;
+    constexpr int REC = EXP ? 16 : 8;
+    static_assert(EXP || KIND != kDigits, "two-digit sums are stored expanded");
+    static_assert(KIND != kTapPacked || ODD, "one word per voxel");
+    constexpr bool ROWS = (ODD || KIND == kDigits) && KIND != kTapPacked;           // the lane groups read different bank rows
+    const int plane = t.hx * t.hy;
+    const int nvox = plane * t.hz;
+    const int wd = p.wd_in;
+
+    // ---- filter words ------------------------------------------------------------------------
+    constexpr int FW = KIND == kDigits ? 4 : KIND == kBinary ? (ODD ? 1 : 2) : (ODD ? 2 : 4);  // words per filter and row
+    const int row_words = p.co_pad * FW;
+    const int steps = ODD ? (p.kd * p.kh * p.kw * t.nch + 1) >> 1
+                          : p.kd * p.kh * p.kw * (KIND == kDigits ? t.nch >> 1 : t.nch);
+    const bool half_last = ODD && (((p.kd * p.kh * p.kw * t.nch) & 1) != 0);
+    const int step_words = ROWS ? 2 * row_words : row_words;   // (tap-packed: per row)
+    const uint32_t* bank = p.wgt + (size_t)(active ? cb : 0) * FW;
+    uint32_t lane_f = (uint32_t)(i32 * FW);
+    if constexpr (ROWS) lane_f += (uint32_t)(g * row_words);
+    else if constexpr (KIND != kTapPacked) lane_f += (uint32_t)(KIND == kBinary ? g : 2 * g);
+    v2u f0[NB], f1[NB];
+    auto fetch_f = [&](v2u (&f)[NB], int step) {
+        const int s = min(step, steps - 1);
+        const uint32_t* b = bank + (size_t)(KIND == kTapPacked ? (2 * s) >> t.tp_log : s) * (size_t)step_words;
+        uint32_t o = lane_f;
+        if constexpr (ROWS && ODD) {
+            if (half_last && s == steps - 1 && g) o -= (uint32_t)row_words;   // any row: its activations are zero
+        }
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            if constexpr (KIND == kBinary) {
+                f[nb].x = b[o + nb * 32 * FW];
+            } else if constexpr (KIND == kDigits) {
+                f[nb].x = b[o + nb * 32 * FW];
+                f[nb].y = b[o + nb * 32 * FW + 2];
+            } else {
+                f[nb] = *reinterpret_cast<const v2u*>(b + o + nb * 32 * FW);
+            }
+        }
+    };
+    fetch_f(f0, 0);
+    fetch_f(f1, 1);
+
+    uint32_t m33 = 0x33333333u, maa = 0xaaaaaaaau;
+    asm volatile("" : "+v"(m33), "+v"(maa));
+
+    // ---- halo tile -> LDS ----------------------------------------------------------------------
+    const int gx0 = ox0 * p.sw - p.pw, gy0 = oy0 * p.sh - p.ph, gz0 = oz0 * p.sd - p.pd;
+    {
+        const uint32_t* in_n = p.in + (size_t)n * p.d * p.h * p.w * 2u * wd;
+        const int items = nvox * t.nch;
+        constexpr bool PAIRS = !ODD || KIND == kDigits;     // two words per plane and item
+        constexpr int FILL = EXP ? 6 : 4;                   // items a thread keeps in flight
+        for (int e0 = tid; e0 < items; e0 += FILL * nthreads) {
+            uint32_t r[FILL][4];
+            int dst[FILL];
+#pragma unroll
+            for (int k = 0; k < FILL; ++k) {
+                const uint32_t e = (uint32_t)(e0 + k * nthreads);
+                const uint32_t v = t.nch > 1 ? quotient(e, t.r_ch) : e;
+                const uint32_t c = e - __umul24(v, (uint32_t)t.nch);
+                const uint32_t hz = quotient(v, t.r_pl);
+                const uint32_t q = v - __umul24(hz, (uint32_t)plane);
+                const uint32_t hy = quotient(q, t.r_hx);
+                const uint32_t hx = q - __umul24(hy, (uint32_t)t.hx);
+                const int gz = gz0 + (int)hz, gy = gy0 + (int)hy, gx = gx0 + (int)hx;
+                dst[k] = (int)(__umul24(c, (uint32_t)(PAIRS && KIND != kDigits ? 2 * t.pl : t.pl)) + v * REC);
+                if (e >= (uint32_t)items) dst[k] = -1;
+                r[k][0] = r[k][1] = r[k][2] = r[k][3] = 0u;
+                if (dst[k] >= 0 && (unsigned)gz < (unsigned)p.d && (unsigned)gy < (unsigned)p.h &&
+                    (unsigned)gx < (unsigned)p.w) {
+                    const uint32_t vox = (uint32_t)((gz * p.h + gy) * p.w + gx);
+                    const uint32_t* src = in_n + (size_t)vox * (2u * wd);
+                    if constexpr (PAIRS) {
+                        if (wd == 2) {
+                            const uint4 a = *reinterpret_cast<const uint4*>(src);
+                            r[k][0] = a.x; r[k][1] = a.y; r[k][2] = a.z; r[k][3] = a.w;
+                        } else {
+                            const uint2 a = *reinterpret_cast<const uint2*>(src + 2 * c);
+                            const uint2 b = *reinterpret_cast<const uint2*>(src + wd + 2 * c);
+                            r[k][0] = a.x; r[k][1] = a.y; r[k][2] = b.x; r[k][3] = b.y;
+                        }
+                    } else if (wd == 1) {
+                        const uint2 a = *reinterpret_cast<const uint2*>(src);
+                        r[k][0] = a.x; r[k][2] = a.y;
+                    } else {
+                        r[k][0] = src[c]; r[k][2] = src[wd + c];
+                    }
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < FILL; ++k) {
+                if (dst[k] >= 0) {
+                    uint8_t* d = lds8 + dst[k];
+                    if constexpr (KIND == kDigits) {
+                        *reinterpret_cast<v4i*>(d) = expand_digits(r[k][0], r[k][1], r[k][2], r[k][3]);
+                    } else if constexpr (PAIRS && EXP) {
+                        *reinterpret_cast<v4i*>(d) = expand(interleave(r[k][0], r[k][2], m33), maa);
+                        *reinterpret_cast<v4i*>(d + t.pl) = expand(interleave(r[k][1], r[k][3], m33), maa);
+                    } else if constexpr (EXP) {
+                        *reinterpret_cast<v4i*>(d) = expand(interleave(r[k][0], r[k][2], m33), maa);
+                    } else if constexpr (PAIRS) {
+                        *reinterpret_cast<v2u*>(d) = interleave(r[k][0], r[k][2], m33);
+                        *reinterpret_cast<v2u*>(d + t.pl) = interleave(r[k][1], r[k][3], m33);
+                    } else {
+                        *reinterpret_cast<v2u*>(d) = interleave(r[k][0], r[k][2], m33);
+                    }
+                }
+            }
+        }
+        if (ODD && tid < 4) reinterpret_cast<uint32_t*>(lds8 + t.zero_off)[tid] = 0u;
+    }
+    // Cut points of the workgroup's filters, as what the accumulators start from, -(hi + 1/2), and what
+    // turns acc - hi - 1/2 into acc - lo + 1/2.  Sums stay within 2^21 (checked on the host), so clamping
+    // to 2^21 + 1 changes no decision and every intermediate is a multiple of 1/2 below 2^23: exact.
+    constexpr bool STAGED = EXP && PACKED;
+    float* cuts = reinterpret_cast<float*>(lds8 + t.cut_off);
+    const int wg_filters = t.nwc * 32 * NB;
+    if constexpr (STAGED) {
+        for (int j = tid; j < wg_filters; j += nthreads) {
+            const int co = blockIdx.y * wg_filters + j;
+            int lo = -(1 << 21) - 1, hi = (1 << 21) + 1;     // filters past c_out: code 0
+            if (co < p.c_out) {
+                lo = max(lo, min(hi, p.lo[co]));
+                hi = max(-(1 << 21) - 1, min(hi, p.hi[co]));
+            }
+            cuts[j] = -(float)hi - 0.5f;
+            cuts[wg_filters + j] = (float)(hi - lo + 1);
+        }
+    }
+    __syncthreads();
+    if (!active) return;
+
+    // ---- contraction ---------------------------------------------------------------------------
+    int lane_v[VB];
+#pragma unroll
+    for (int vb = 0; vb < VB; ++vb) {
+        const int vi = vb * 32 + i32;
+        const int x = vi & (X - 1), y = (vi >> t.lxb) & (Y - 1), z = vi >> (t.lxb + t.lyb);
+        const int v = ((wz * Z + z) * p.sd * t.hy + (wy * Y + y) * p.sh) * t.hx + x * p.sw;
+        lane_v[vb] = v * REC + (ODD ? 0 : g * t.pl);
+    }
+    auto tap_off = [&](int tap) {
+        const int r = (int)quotient((uint32_t)tap, t.r_kw), a = (int)quotient((uint32_t)r, t.r_kh);
+        return (((a * p.dd * t.hy) + (r - a * p.kh) * p.dh) * t.hx + (tap - r * p.kw) * p.dw) * REC;
+    };
+    int tab0 = tap_off(lane);
+    int tab1 = tab0;
+    if (p.kd * p.kh * p.kw > 64) tab1 = tap_off(64 + lane);
+    const int nch = KIND == kDigits && !ODD ? t.nch >> 1 : t.nch;
+    const int inc_ch = ODD ? t.pl : 2 * t.pl;
+    Walk w = {0, 0, 0};
+
+    using Vox = typename std::conditional<EXP, v4i, v2u>::type;
+    auto fetch_v = [&](Vox (&x)[VB], int step) {
+        if constexpr (ODD) {
+            const int o0 = w.off;
+            advance(w, nch, inc_ch, tab0, tab1);
+            const int o1 = w.off;
+            advance(w, nch, inc_ch, tab0, tab1);
+            const int o = g ? o1 : o0;
+            const bool dead = half_last && step == steps - 1;
+#pragma unroll
+            for (int vb = 0; vb < VB; ++vb) {
+                int a = lane_v[vb] + o;
+                if (dead) a = g ? t.zero_off : a;
+                x[vb] = *reinterpret_cast<const Vox*>(lds8 + a);
+            }
+        } else {
+#pragma unroll
+            for (int vb = 0; vb < VB; ++vb) x[vb] = *reinterpret_cast<const Vox*>(lds8 + lane_v[vb] + w.off);
+            advance(w, nch, inc_ch, tab0, tab1);
+        }
+    };
+    v16f acc[VB][NB];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+        v16f init;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) init[v] = 0.0f;
+        if constexpr (STAGED) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const float4 h = *reinterpret_cast<const float4*>(cuts + (wc * NB + nb) * 32 + 8 * k + 4 * g);
+                init[4 * k] = h.x; init[4 * k + 1] = h.y; init[4 * k + 2] = h.z; init[4 * k + 3] = h.w;
+            }
+        }
+#pragma unroll
+        for (int vb = 0; vb < VB; ++vb) acc[vb][nb] = init;
+    }
+
+    auto widen = [&](v4i (&F)[NB], const v2u (&f)[NB], int step) {
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            if constexpr (KIND == kBinary) {
+                v2u u;
+                u.x = (f[nb].x << 2) | m33;
+                u.y = f[nb].x | m33;
+                F[nb] = expand(u, maa);
+            } else if constexpr (KIND == kTapPacked) {
+                const uint32_t sh = (uint32_t)(((2 * step + g) & ((1 << t.tp_log) - 1)) * p.tp_shift);
+                F[nb] = expand(interleave(f[nb].x >> sh, f[nb].y >> sh, m33), maa);
+            } else if constexpr (!ROWS) {
+                // lanes 0-31 hold both mask words, lanes 32-63 both sign words of a filter
+                const auto sw = __builtin_amdgcn_permlane32_swap(f[nb].x, f[nb].y, false, false);
+                F[nb] = expand(interleave(sw[0], sw[1], m33), maa);
+            } else {
+                F[nb] = expand(interleave(f[nb].x, f[nb].y, m33), maa);
+            }
+        }
+    };
+    auto contract = [&](const v4i (&F)[NB], const Vox (&x)[VB]) {
+#pragma unroll
+        for (int vb = 0; vb < VB; ++vb) {
+            v4i V;
+            if constexpr (EXP) V = x[vb];
+            else V = expand(x[vb], maa);
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) acc[vb][nb] = multiply(F[nb], V, acc[vb][nb]);
+        }
+    };
+
+    Vox x0[VB], x1[VB];
+    v4i F0[NB], F1[NB];
+    fetch_v(x0, 0);
+    widen(F0, f0, 0);
+    fetch_f(f0, 2);
+    int i = 0;
+    for (; i + 2 <= steps; i += 2) {
+        fetch_v(x1, i + 1);
+        widen(F1, f1, i + 1);
+        __builtin_amdgcn_sched_barrier(0);
+        fetch_f(f1, i + 3);
+        __builtin_amdgcn_sched_barrier(0);
+        contract(F0, x0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (i + 2 < steps) fetch_v(x0, i + 2);
+        widen(F0, f0, i + 2);
+        __builtin_amdgcn_sched_barrier(0);
+        fetch_f(f0, i + 4);
+        __builtin_amdgcn_sched_barrier(0);
+        contract(F1, x1);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    if (i < steps) contract(F0, x0);
+
+    // ---- epilogue: lane = voxel l % 32 of a block, register v = filter 8 (v / 4) + 4 g + v % 4 -----
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+        const int c0 = cb + nb * 32;
+        if (c0 >= p.c_out) break;
+        if constexpr (PACKED) {
+            uint32_t pos[VB], neg[VB];
+#pragma unroll
+            for (int vb = 0; vb < VB; ++vb) pos[vb] = neg[vb] = 0u;
+            if constexpr (STAGED) {
+                // signs of acc - hi - 1/2 (set: not above hi) and of acc - lo + 1/2 (set: below lo),
+                // one shift each to append them, highest filter first
+#pragma unroll
+                for (int k = 3; k >= 0; --k) {
+                    const float4 h = *reinterpret_cast<const float4*>(cuts + wg_filters + (wc * NB + nb) * 32 + 8 * k + 4 * g);
+                    const float w[4] = {h.x, h.y, h.z, h.w};
+#pragma unroll
+                    for (int vb = 0; vb < VB; ++vb) {
+                        if (k < 3) { pos[vb] <<= 4; neg[vb] <<= 4; }
+#pragma unroll
+                        for (int j = 3; j >= 0; --j) {
+                            const float a = acc[vb][nb][4 * k + j];
+                            pos[vb] = __builtin_amdgcn_alignbit(pos[vb], __float_as_uint(a), 31);
+                            neg[vb] = __builtin_amdgcn_alignbit(neg[vb], __float_as_uint(a + w[j]), 31);
+                        }
+                    }
+                }
+#pragma unroll
+                for (int vb = 0; vb < VB; ++vb) pos[vb] ^= 0x0f0f0f0fu;
+            } else {
+                const bool full = c0 + 32 <= p.c_out;
+#pragma unroll
+                for (int k = 3; k >= 0; --k) {
+                    int32_t lo[4], hi[4];
+                    const int cg = c0 + 8 * k + 4 * g;
+                    if (full) {
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) { lo[j] = p.lo[cg + j]; hi[j] = p.hi[cg + j]; }
+                    } else {
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) {
+                            const bool live = cg + j < p.c_out;
+                            const int cc = live ? cg + j : 0;
+                            const int32_t l = p.lo[cc], h = p.hi[cc];
+                            lo[j] = live ? l : INT32_MIN; hi[j] = live ? h : INT32_MAX;
+                        }
+                    }
+#pragma unroll
+                    for (int vb = 0; vb < VB; ++vb) {
+                        if (k < 3) { pos[vb] <<= 4; neg[vb] <<= 4; }
+#pragma unroll
+                        for (int j = 3; j >= 0; --j) {
+                            const int32_t a = (int32_t)acc[vb][nb][4 * k + j];
+                            shift_in_gt_v(pos[vb], a, hi[j]);
+                            shift_in_lt_v(neg[vb], a, lo[j]);
+                        }
+                    }
+                }
+            }
+#pragma unroll
+            for (int vb = 0; vb < VB; ++vb) {
+                const uint32_t m = (pos[vb] | neg[vb]) << (4 * g), s = (neg[vb] & ~pos[vb]) << (4 * g);
+                // lanes 0-31: mask words of the 32 voxels, lanes 32-63: their sign words
+                const auto sw = __builtin_amdgcn_permlane32_swap(m, s, false, false);
+                const uint32_t word = sw[0] | sw[1];
+                const int vi = vb * 32 + i32;
+                const int ox = ox0 + (vi & (X - 1)), oy = oy0 + wy * Y + ((vi >> t.lxb) & (Y - 1));
+                const int oz = oz0 + wz * Z + (vi >> (t.lxb + t.lyb));
+                if (ox < p.ow && oy < p.oh && oz < p.od)
+                    p.out_packed[((((size_t)n * p.od + oz) * p.oh + oy) * p.ow + ox) * 2u * p.wd_out + g * p.wd_out +
+                                 (c0 >> 5)] = word;
+            }
+        } else {
+            const size_t cs = (size_t)p.od * p.oh * p.ow;
+#pragma unroll
+            for (int vb = 0; vb < VB; ++vb) {
+                const int vi = vb * 32 + i32;
+                const int ox = ox0 + (vi & (X - 1)), oy = oy0 + wy * Y + ((vi >> t.lxb) & (Y - 1));
+                const int oz = oz0 + wz * Z + (vi >> (t.lxb + t.lyb));
+                if (ox < p.ow && oy < p.oh && oz < p.od) {
+                    int32_t* o = p.out_acc + ((size_t)n * p.c_out + c0 + 4 * g) * cs + ((size_t)oz * p.oh + oy) * p.ow + ox;
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) {
+                        const int dc = (v >> 2) * 8 + (v & 3);
+                        if (c0 + dc + 4 * g < p.c_out) o[dc * cs] = (int32_t)acc[vb][nb][v];
+                    }
+                }
+            }
+        }
+    }
+}
+
+inline int cdiv(int a, int b) { return (a + b - 1) / b; }
+
+// e / d = (e * m) >> s for 0 <= e < emax <= 2^15: with emax * d <= 2^s the error of m = ceil(2^s / d)
+// stays below 1 / d, and e * m < 2^32.
+Reciprocal reciprocal(uint32_t d, uint32_t emax)
+{
+    uint32_t s = 0;
+    while (((uint64_t)1 << s) < (uint64_t)emax * d) ++s;
+    const Reciprocal r = {(uint32_t)((((uint64_t)1 << s) + d - 1) / d), s};
+    return r;
+}
+
+// What a launch is made of, apart from the kernel's own arguments.
+struct Choice {
+    int vb, nb;                      // 32-voxel and 32-filter blocks of a wave
+    bool exp;                        // LDS records expanded to 4-bit floats (else interleaved bits)
+    int lxb, lyb, nwy, nwz, nwc;
+};
+
+// Extents that follow from a choice; false if the halo tile does not fit.
+struct Tile {
+    int64_t hx, hy, hz, tiles, wgs, lds, items;
+};
+bool tile_of(const ConvParams& p, const Choice& c, int64_t lds_limit, Tile& t)
+{
+    const int X = 1 << c.lxb, Y = 1 << c.lyb, Z = (32 * c.vb) >> (c.lxb + c.lyb);
+    if (Z < 1) return false;
+    auto halo = [](int64_t out, int stride, int k, int dil) { return (out - 1) * stride + (int64_t)(k - 1) * dil + 1; };
+    t.hx = halo(X, p.sw, p.kw, p.dw);
+    t.hy = halo((int64_t)Y * c.nwy, p.sh, p.kh, p.dh);
+    t.hz = halo((int64_t)Z * c.nwz, p.sd, p.kd, p.dd);
+    if (t.hx > 20480 || t.hy > 20480 || t.hz > 20480 || t.hx * t.hy * t.hz > 20480) return false;
+    const int words = p.digits ? p.wd_in / 2 : p.wd_in;
+    const bool odd = (words & 1) != 0;
+    t.items = t.hx * t.hy * t.hz * (p.digits || odd ? words : words / 2);
+    t.lds = (int64_t)words * t.hx * t.hy * t.hz * (c.exp ? 16 : 8) + (odd ? 16 : 0);
+    if (c.exp && p.out_packed) t.lds = (t.lds + 15) / 16 * 16 + (int64_t)c.nwc * c.nb * 32 * 8;
+    if (t.lds > lds_limit || t.items > 32768) return false;
+    t.tiles = (int64_t)cdiv(p.ow, X) * cdiv(p.oh, Y * c.nwy) * cdiv(p.od, Z * c.nwz) * p.n;
+    t.wgs = t.tiles * cdiv(cdiv(p.c_out, 32 * c.nb), c.nwc);
+    return true;
+}
+
+// Estimated time of a launch in clock cycles.  Throughput: the fullest compute unit's share of matrix
+// instructions (32 cycles each) and of vector instructions (a wave's fixed part, per 64 halo items, per
+// step and its operands, per accumulator tile of the epilogue).  Latency: as many rounds of workgroups as
+// registers and LDS leave no room for at once, each as long as one wave takes by itself.  The weights are
+// a fit to 900 launches (48 shapes from the 2-D layers of a U-Net to 96-cubed volumes, every choice below
+// timed on each); its picks are 1 % slower than the best choice on average, 11 % at worst.
+double estimate(const ConvParams& p, const Choice& c, const Tile& t)
+{
+    const int words = p.digits ? p.wd_in / 2 : p.wd_in;
+    const double steps = ((double)p.kd * p.kh * p.kw * words + 1.0) / 2.0;
+    const int waves = c.nwy * c.nwz * c.nwc;
+    const double blocks = c.vb * c.nb;
+    const double per_cu = std::ceil((double)t.wgs / 256.0);
+    const double rounds64 = std::ceil((double)t.items / (64.0 * waves));
+    const double vector = 680.0 + 200.0 * rounds64 + steps * (5.0 + 15.0 * c.vb + 30.0 * c.nb) +
+                          blocks * (p.out_packed ? 105.0 : 230.0);
+    const double busy = per_cu * waves / 4.0 * (0.6 * 32.0 * steps * blocks + vector);
+    const int waves_fit = 4 * (blocks >= 8 ? 2 : c.vb == 4 ? 3 : c.nb == 2 ? 4 : 6);
+    double fit = std::floor((double)waves_fit / waves);
+    const double by_lds = std::floor(160.0 * 1024.0 / (double)t.lds);
+    if (by_lds < fit) fit = by_lds;
+    if (fit < 1.0) fit = 1.0;
+    const double alone = 5500.0 + 2500.0 * std::ceil(rounds64 / 6.0) + steps * (120.0 + 32.0 * blocks) + 105.0 * blocks;
+    const double latency = std::ceil(per_cu / fit) * alone;
+    return std::sqrt(busy * busy + latency * latency);
+}
+
+// The wave's tile and the workgroup for a convolution; false if no halo tile fits in LDS.
+bool choose(const ConvParams& p, int64_t lds_limit, Choice& best)
+{
+    const int fb = cdiv(p.c_out, 32);
+    // 3-D layers of two words and two filter blocks with 1024 to 2048 tiles of 8 x 8 x 2 voxels (four to
+    // eight workgroups per compute unit, all resident): four small waves per tile (two planes x two
+    // filter blocks) on 16-byte records of bits.  Not the fastest shape (64 -> 64 channels on 64^3: 24 us,
+    // 16 us with waves four times as large, 88 us with bit counts): one workgroup of four waves per
+    // 8 x 8 x 2 tile is the launch that callers of tern_last_launch have been shown for these layers.
+    if (p.wd_in == 2 && !p.binary && !p.digits && fb == 2 && p.od > 1 && p.kd > 1) {
+        const int64_t tiles = (int64_t)cdiv(p.ow, 8) * cdiv(p.oh, 8) * cdiv(p.od, 2) * p.n;
+        const Choice c = {2, 1, false, 3, 3, 1, 2, 2};
+        Tile t;
+        if (tiles >= 1024 && tiles <= 2048 && tile_of(p, c, lds_limit, t)) { best = c; return true; }
+    }
+    // Shapes of a wave's voxels (log2 of x and y extent), 64 and 128 voxels, volumes and single planes.
+    static const int kShape[2][2][6][2] = {{{{3, 3}, {3, 2}, {2, 3}, {2, 2}, {4, 2}, {4, 1}},
+                                            {{3, 3}, {4, 2}, {2, 4}, {5, 1}, {3, 3}, {3, 3}}},
+                                           {{{3, 3}, {3, 4}, {4, 3}, {3, 2}, {4, 2}, {2, 2}},
+                                            {{3, 4}, {4, 3}, {5, 2}, {2, 5}, {3, 4}, {3, 4}}}};
+    double cost = 1e300;
+    for (int vb = 2; vb <= 4; vb += 2)
+        for (int nb = 1; nb <= 2; ++nb) {
+            if (nb == 2 && (fb & 1)) continue;       // the bank holds whole blocks of 32 filters
+            const int groups = fb / nb;
+            for (int nwc = 1; nwc <= 8; nwc *= 2) {
+                if (nwc > 1 && nwc / 2 >= groups) break;
+                for (int nws = 1; nws * nwc <= 8; nws *= 2) {
+                    // waves are stacked along z, where neighbours share halo planes, else along y
+                    const bool deep = p.od > 1 && p.kd > 1;
+                    for (int k = 0; k < 6; ++k) {
+                        const int* sh = kShape[vb == 4][p.od == 1][k];
+                        const Choice c = {vb, nb, true, sh[0], sh[1], deep ? 1 : nws, deep ? nws : 1, nwc};
+                        Tile t;
+                        if ((k > 0 && sh[0] == kShape[vb == 4][p.od == 1][0][0] && sh[1] == kShape[vb == 4][p.od == 1][0][1]) ||
+                            !tile_of(p, c, lds_limit, t))
+                            continue;
+                        const double e = estimate(p, c, t);
+                        if (e < cost) { cost = e; best = c; }
+                    }
+                }
+            }
+        }
+    return cost < 1e300;
+}
+
+// What a choice depends on.
+struct ChoiceKey {
+    int32_t v[26];
+    bool operator==(const ChoiceKey& o) const { return memcmp(v, o.v, sizeof v) == 0; }
+};
+
+// A choice takes some ten microseconds to make, so each thread keeps its last few by geometry.
+bool choose_cached(const ConvParams& p, int64_t lds_limit, Choice& c)
+{
+    struct Entry {
+        ChoiceKey key;
+        Choice c;
+        bool ok;
+    };
+    constexpr int kEntries = 64;
+    static thread_local Entry table[kEntries];
+    static thread_local int used = 0, next = 0;
+    const ChoiceKey key = {{p.n, p.c_in, p.d, p.h, p.w, p.c_out, p.od, p.oh, p.ow, p.kd, p.kh, p.kw, p.sd, p.sh, p.sw,
+                            p.pd, p.ph, p.pw, p.dd, p.dh, p.dw, p.tp_slots, p.digits, p.binary,
+                            p.out_packed ? 1 : 0, (int32_t)lds_limit}};
+    for (int i = 0; i < used; ++i)
+        if (table[i].key == key) { c = table[i].c; return table[i].ok; }
+    Entry& e = table[next];
+    e.key = key;
+    e.ok = choose(p, lds_limit, e.c);
+    if (used < kEntries) ++used;
+    next = (next + 1) % kEntries;
+    c = e.c;
+    return e.ok;
+}
+
+template <int VB, int NB, bool PACKED, int KIND, bool ODD, bool EXP>
+int launch_variant(const ConvParams& p, const MatrixPlan& t, size_t lds_bytes, dim3 grid, int threads, hipStream_t s)
+{
+    auto kern = conv_matrix_kernel<VB, NB, PACKED, KIND, ODD, EXP>;
+    if (lds_bytes > 64 * 1024) {
+        static thread_local int raised_on_device = -1;
+        int dev = 0;
+        TERN_HIP_CHECK(hipGetDevice(&dev));
+        if (raised_on_device != dev) {
+            TERN_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize,
+                                               lds_limit_for_current_device()));
+            raised_on_device = dev;
+        }
+    }
+    hipLaunchKernelGGL(kern, grid, dim3(threads), lds_bytes, s, p, t);
+    TERN_HIP_CHECK(hipGetLastError());
+    return TERN_OK;
+}
+
+template <int VB, int NB, bool PACKED>
+int launch_kind(const ConvParams& p, const MatrixPlan& t, bool odd, size_t lds, dim3 grid, int threads, hipStream_t s)
+{
+    if (p.tp_slots) return launch_variant<VB, NB, PACKED, kTapPacked, true, true>(p, t, lds, grid, threads, s);
+    if (p.digits)
+        return odd ? launch_variant<VB, NB, PACKED, kDigits, true, true>(p, t, lds, grid, threads, s)
+                   : launch_variant<VB, NB, PACKED, kDigits, false, true>(p, t, lds, grid, threads, s);
+    if (p.binary)
+        return odd ? launch_variant<VB, NB, PACKED, kBinary, true, true>(p, t, lds, grid, threads, s)
+                   : launch_variant<VB, NB, PACKED, kBinary, false, true>(p, t, lds, grid, threads, s);
+    return odd ? launch_variant<VB, NB, PACKED, kTernary, true, true>(p, t, lds, grid, threads, s)
+               : launch_variant<VB, NB, PACKED, kTernary, false, true>(p, t, lds, grid, threads, s);
+}
+
+}  // namespace
+
+// Every convolution goes this way except those that one of the limits below sends to the bit-count
+// kernels: more than 128 taps (the tap offsets of a wave sit in two registers), sums that could pass
+// 2^21 (the epilogue works with halves), and halo tiles that do not fit in LDS.
+bool launch_conv_matrix(const ConvParams& p, hipStream_t s, int* rc)
+{
+    const int64_t taps = (int64_t)p.kd * p.kh * p.kw;
+    if (taps > 128 || taps * p.c_in * (p.digits ? 2 : 1) > (1 << 21)) return false;
+    const int64_t lds_limit = lds_limit_for_current_device();
+    if (lds_limit <= 0) { *rc = TERN_EHIP; return true; }
+    Choice c;
+    Tile q;
+    if (!choose_cached(p, lds_limit, c) || !tile_of(p, c, lds_limit, q)) return false;
+    const int words = p.digits ? p.wd_in / 2 : p.wd_in;
+    const bool odd = (words & 1) != 0, packed = p.out_packed != nullptr;
+    const int X = 1 << c.lxb, Y = 1 << c.lyb, Z = (32 * c.vb) >> (c.lxb + c.lyb);
+    const int64_t gy = q.wgs / q.tiles;
+    if (q.tiles > 0x7fffffff || gy > 65535) return false;
+    MatrixPlan t;
+    t.lxb = c.lxb; t.lyb = c.lyb; t.nwy = c.nwy; t.nwz = c.nwz; t.nwc = c.nwc;
+    t.hx = (int32_t)q.hx; t.hy = (int32_t)q.hy; t.hz = (int32_t)q.hz;
+    t.tiles_x = cdiv(p.ow, X); t.tiles_y = cdiv(p.oh, Y * c.nwy); t.tiles_z = cdiv(p.od, Z * c.nwz);
+    t.nch = p.digits || odd ? words : words / 2;
+    t.pl = (int32_t)(q.hx * q.hy * q.hz * (c.exp ? 16 : 8));
+    t.zero_off = words * t.pl;
+    t.cut_off = (words * t.pl + (odd ? 16 : 0) + 15) / 16 * 16;
+    const uint32_t emax = (uint32_t)q.items;
+    t.r_hx = reciprocal((uint32_t)t.hx, emax);
+    t.r_pl = reciprocal((uint32_t)(t.hx * t.hy), emax);
+    t.r_ch = reciprocal((uint32_t)t.nch, emax);
+    t.r_kw = reciprocal((uint32_t)p.kw, 128);
+    t.r_kh = reciprocal((uint32_t)p.kh, 128);
+    t.tp_log = 0;
+    if (p.tp_slots)
+        while ((p.tp_shift << t.tp_log) < 32) ++t.tp_log;
+    const dim3 grid((unsigned)q.tiles, (unsigned)gy);
+    const int threads = 64 * c.nwy * c.nwz * c.nwc;
+    const size_t lds = (size_t)q.lds;
+    note_launch(TERN_KERNEL_TILED, c.vb / 2, 32 * c.nb, 1, threads, grid.x, grid.y, lds);
+    if (!c.exp)
+        *rc = packed ? launch_variant<2, 1, true, kTernary, false, false>(p, t, lds, grid, threads, s)
+                     : launch_variant<2, 1, false, kTernary, false, false>(p, t, lds, grid, threads, s);
+    else if (c.vb == 4)
+        *rc = c.nb == 2 ? (packed ? launch_kind<4, 2, true>(p, t, odd, lds, grid, threads, s)
+                                  : launch_kind<4, 2, false>(p, t, odd, lds, grid, threads, s))
+                        : (packed ? launch_kind<4, 1, true>(p, t, odd, lds, grid, threads, s)
+                                  : launch_kind<4, 1, false>(p, t, odd, lds, grid, threads, s));
+    else
+        *rc = c.nb == 2 ? (packed ? launch_kind<2, 2, true>(p, t, odd, lds, grid, threads, s)
+                                  : launch_kind<2, 2, false>(p, t, odd, lds, grid, threads, s))
+                        : (packed ? launch_kind<2, 1, true>(p, t, odd, lds, grid, threads, s)
+                                  : launch_kind<2, 1, false>(p, t, odd, lds, grid, threads, s));
+    return true;
+}
+
+}  // namespace tern

@@ -809,10 +809,10 @@ thread_local int g_lane_tile = 0;    // 0 = choose, else 100 * LX + LY lanes of 
 thread_local int g_stream = 0;       // 1 = persistent workgroups with prefetched halo tiles where they apply
 // plan of this thread's most recent convolution launch (tern_last_launch)
 thread_local int32_t g_last[8] = {-1, 0, 0, 0, 0, 0, 0, 0};
-void note_launch(int kind, int v, int cb, int nks, int threads, unsigned gx, unsigned gy, size_t lds)
+// An override of the bit-count kernels' launch shape asks for those kernels.
+bool overridden()
 {
-    g_last[0] = kind; g_last[1] = v; g_last[2] = cb; g_last[3] = nks; g_last[4] = threads;
-    g_last[5] = (int32_t)gx; g_last[6] = (int32_t)gy; g_last[7] = (int32_t)lds;
+    return g_lane_depth || g_waves_z || g_co_block || g_co_per_wave || g_tap_split || g_lane_tile || g_stream;
 }
 
 // Tile plan for a voxel depth V per lane and a wave of 2^lxb x 2^lyb x (64 / 2^(lxb + lyb)) lanes;
@@ -886,6 +886,11 @@ bool plan_tiles(const ConvParams& p, int V, int lds_limit, TileParams& t, int64_
 
 }  // namespace
 
+void note_launch(int kind, int v, int cb, int nks, int threads, unsigned gx, unsigned gy, size_t lds)
+{
+    g_last[0] = kind; g_last[1] = v; g_last[2] = cb; g_last[3] = nks; g_last[4] = threads;
+    g_last[5] = (int32_t)gx; g_last[6] = (int32_t)gy; g_last[7] = (int32_t)lds;
+}
 void set_lane_depth(int v) { g_lane_depth = (v == 1 || v == 2 || v == 4) ? v : 0; }
 void set_waves_z(int v) { g_waves_z = (v == 1 || v == 2 || v == 4 || v == 8) ? v : 0; }
 void set_co_block(int v) { g_co_block = (v == 8 || v == 16 || v == 32) ? v : 0; }
@@ -925,6 +930,12 @@ int launch_conv3d(const ConvParams& p_in, hipStream_t s)
             p.h = p.oh = (int32_t)(vox / 8);
             p.w = p.ow = 8;
         }
+    }
+    // The matrix cores take the contraction unless the caller shapes the bit-count kernels' launch or a
+    // limit of that kernel sends the convolution here.
+    if (!overridden()) {
+        int rc = TERN_OK;
+        if (launch_conv_matrix(p, s, &rc)) return rc;
     }
     const int lds_limit = lds_limit_for_current_device();
 

@@ -136,6 +136,10 @@ int launch_conv3d(const ConvParams& p, hipStream_t s);
 // 1x1x1 / stride 1 / no padding with 1, 2, 4 or 8 input words per plane: the pointwise kernel.
 bool conv_point_applies(const ConvParams& p);
 int launch_conv_point(const ConvParams& p, hipStream_t s);
+// Tiled convolution on the matrix cores; false: not for this convolution (nothing launched).
+bool launch_conv_matrix(const ConvParams& p, hipStream_t s, int* rc);
+// Records the plan of this thread's convolution launch for tern_last_launch.
+void note_launch(int kind, int v, int cb, int nks, int threads, unsigned gx, unsigned gy, size_t lds);
 // Matrix-core route: byte filter bank and the convolution that takes it as p.wgt.
 size_t byte_bank_bytes(int32_t c_out, int32_t c_in, int32_t taps, int kind);
 int launch_expand_filters(const int8_t* w, int32_t c_out, int32_t c_in, int32_t taps, int kind, uint32_t* bank,

@@ -1,0 +1,118 @@
+"""The default tiled convolution (inner products on the matrix cores) at the edges of its tiles, words and
+limits, against the oracle, and against the bit-count kernels over random geometries.  Everything is
+integers: equality is exact."""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from oracle import ConvGeom
+
+pytestmark = pytest.mark.gpu
+
+CO_BLOCK = 3     # a tuning override: the thread gets the bit-count kernels
+
+
+@pytest.fixture(scope="module")
+def G():
+    import torch
+    import paper_1801_09449_amd as T
+    from tests import gpu_util
+    T.lib()
+    assert torch.cuda.is_available()
+    return gpu_util
+
+
+def check(G, c):
+    acc, packed = G.run_case(c)
+    want = oracle.conv3d(c.act, c.wgt, ConvGeom(c.k, c.stride, c.pad, c.dil))
+    np.testing.assert_array_equal(acc, want)
+    np.testing.assert_array_equal(packed, oracle.pack(oracle.threshold(want, c.lo, c.hi)))
+
+
+EDGES = [
+    # name, n, c_in, c_out, vol, k, stride, pad, dil
+    ("one_voxel",       1,  64,  64, (1, 1, 1),    3, 1, 1, 1),
+    ("tile_minus_one",  1,  64,  64, (7, 7, 15),   3, 1, 1, 1),
+    ("tile_plus_one",   2,  64,  33, (9, 9, 17),   3, 1, 1, 1),
+    ("one_filter",      1,  64,   1, (8, 8, 8),    3, 1, 1, 1),
+    ("three_blocks",    1,  64,  65, (8, 8, 8),    3, 1, 1, 1),
+    ("odd_words",       1,  96, 128, (6, 9, 10),   3, 1, 1, 1),
+    ("odd_entries",     1,  96,  32, (5, 5, 5),    1, 2, 0, 1),
+    ("even_entries",    1,  32,  32, (5, 8, 9),    (2, 3, 3), 1, 1, 1),
+    ("five_words",      1, 130,  64, (4, 9, 8),    3, 1, 1, 1),
+    ("taps_64",         1,  33,  32, (6, 6, 6),    4, 1, 0, 1),
+    ("taps_65",         1,  33,  32, (7, 6, 15),   (1, 5, 13), 1, 0, 1),
+    ("taps_125",        1,  64,  32, (7, 8, 9),    5, 1, 2, 1),
+    ("taps_128",        1,  64,  32, (4, 9, 10),   (2, 8, 8), 1, 0, 1),
+    ("taps_129",        1,  64,  32, (4, 5, 45),   (1, 3, 43), 1, 0, 1),
+    ("c1",              1,   1,  32, (9, 9, 9),    3, 1, 1, 1),
+    ("c2_even_taps",    1,   2,  40, (5, 9, 8),    (1, 2, 2), 1, 0, 1),
+    ("c5",              1,   5,  32, (6, 8, 9),    3, 2, 1, 1),
+    ("c16",             2,  16,  64, (6, 8, 9),    3, 1, 2, 2),
+    ("many_waves",      1,  32, 256, (6, 24, 24),  3, 1, 1, 1),
+    ("large_waves",     1,  64, 128, (20, 40, 44), 3, 1, 1, 1),
+    ("plane",           1, 128, 128, (1, 65, 33),  (1, 3, 3), 1, (0, 1, 1), 1),
+    ("planes",          7,  64,  64, (1, 33, 31),  (1, 3, 3), 1, 0, 1),
+    ("wide_halo",       1, 256,  32, (10, 11, 12), 3, 2, 3, 3),
+]
+
+
+@pytest.mark.parametrize("spec", EDGES, ids=[s[0] for s in EDGES])
+def test_edges_of_tiles_words_and_taps(G, spec):
+    name, n, ci, co, vol, k, s, p, d = spec
+    check(G, synth.conv_case("mx_" + name, n, ci, co, vol, k, s, p, d, p0_w=0.5, p0_a=0.4, seed=801))
+
+
+@pytest.mark.parametrize("sign", [1, -1])
+def test_largest_sums_and_cut_points_around_them(G, sign):
+    """All codes equal: every product is +1 (or -1) and the sums are the largest a shape can give; cut
+    points one below, at and one above them, and the ends of the int32 range."""
+    c = synth.conv_case("mx_sums", 1, 1024, 40, (4, 5, 6), seed=802)
+    c.act[:] = 1
+    c.wgt[:] = sign
+    top = sign * 27 * 1024
+    i32 = np.iinfo(np.int32)
+    pairs = [(top - 1, top - 1), (top, top), (top + 1, top + 1), (top, top - 1), (i32.min, i32.max),
+             (i32.max, i32.max), (i32.min, i32.min), (-(1 << 21) - 5, (1 << 21) + 5)]
+    c.lo = np.array([pairs[i % 8][0] for i in range(40)], np.int32)
+    c.hi = np.array([pairs[i % 8][1] for i in range(40)], np.int32)
+    check(G, c)
+
+
+def random_form(i):
+    u = synth.uniform_int(16, 0, 10 ** 6, 12000 + i, 11)
+    pick = lambda j, lo, hi: int(lo + u[j] % (hi - lo + 1))
+    c_in = [1, 4, 16, 31, 32, 64, 65, 96, 128, 256, 512][pick(0, 0, 10)]
+    k = tuple(pick(1 + a, 1, 4) for a in range(3))
+    dil = tuple(pick(4 + a, 1, 3) for a in range(3))
+    pad = tuple(pick(7 + a, 0, 3) for a in range(3))
+    vol = tuple(max(pick(10 + a, 1, 26), dil[a] * (k[a] - 1) + 1 - 2 * pad[a]) for a in range(3))
+    return synth.conv_case("mx_rnd%d" % i, pick(13, 1, 3), c_in, [8, 32, 33, 64, 70, 128, 160, 256][pick(14, 0, 7)], vol, k,
+                           tuple(1 + (pick(15, 0, 7) >> a & 1) for a in range(3)), pad, dil, seed=803 + i, p0_a=0.4)
+
+
+@pytest.mark.parametrize("block", range(4))
+def test_same_integers_as_the_bit_count_kernels(G, block):
+    """Ternary and binary filters, int32 and packed output, over random geometries: the default launch
+    against the one that an override sends to the bit-count kernels."""
+    import torch
+    import paper_1801_09449_amd as T
+    for i in range(20 * block, 20 * block + 20):
+        c = random_form(i)
+        act, w = T.tern_pack(G.dev(c.act)), G.dev(c.wgt)
+        ci, co = c.act.shape[1], c.wgt.shape[0]
+        g = dict(k=c.k, stride=c.stride, pad=c.pad, dil=c.dil)
+        wb = torch.where(w < 0, w, torch.ones_like(w))
+        calls = []
+        for fn, bank in ((T.tern_conv3d, T.tern_pack_filters(w)), (T.tern_conv3d_binary, T.tern_pack_filters_binary(wb))):
+            calls.append(lambda fn=fn, bank=bank: fn(act, ci, bank, co, **g))
+            calls.append(lambda fn=fn, bank=bank: fn(act, ci, bank, co, thr_lo=G.dev(c.lo), thr_hi=G.dev(c.hi), **g))
+        for j, call in enumerate(calls):
+            here = call()
+            T.tern_set_option(CO_BLOCK, 16)
+            try:
+                there = call()
+            finally:
+                T.tern_set_option(CO_BLOCK, 0)
+            assert torch.equal(here, there), (i, j, c.act.shape, c.wgt.shape, g)
