@@ -29,14 +29,10 @@
 #include <type_traits>
 
 #include "tern_internal.h"
+#include "tern_matrix_common.h"
 
 namespace tern {
 namespace {
-
-typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v8i __attribute__((ext_vector_type(8)));
-typedef float v16f __attribute__((ext_vector_type(16)));
-typedef uint32_t v2u __attribute__((ext_vector_type(2)));
 
 // Quotient of small numbers: e / d = (e * m) >> s for every e the plan divides (below 2^16).
 struct Reciprocal {
@@ -62,28 +58,6 @@ enum { kTernary = 0, kBinary = 1, kDigits = 2, kTapPacked = 3 };
 
 __device__ __forceinline__ uint32_t quotient(uint32_t e, Reciprocal r) { return __umul24(e, r.m) >> r.s; }
 
-// (mask, sign) word of 32 channels -> two words whose 4-bit field i holds, for two channels each,
-// the sign in bits 3 / 2 and the mask in bits 1 / 0: channels 4 i + 1 / 4 i in the first, 4 i + 3 /
-// 4 i + 2 in the second.
-__device__ __forceinline__ v2u interleave(uint32_t m, uint32_t s, uint32_t m33)
-{
-    v2u w;
-    w.x = __builtin_amdgcn_bitop3_b32(m33, m, s << 2, 0xca);   // m33 ? m : s << 2
-    w.y = __builtin_amdgcn_bitop3_b32(m33, m >> 2, s, 0xca);
-    return w;
-}
-
-// Two interleaved words -> 32 four-bit floats (E2M1: +1 = 0010, -1 = 1010, 0 = x000).
-__device__ __forceinline__ v4i expand(v2u w, uint32_t maa)
-{
-    v4i o;
-    o.x = (int)((w.x << 1) & maa);
-    o.y = (int)(w.x & maa);
-    o.z = (int)((w.y << 1) & maa);
-    o.w = (int)(w.y & maa);
-    return o;
-}
-
 // Two balanced-ternary digits per value (low + 3 high, -4 .. 4) to the E2M1 code of the value
 // (magnitudes 1, 2, 3, 4 = 0010, 0100, 0101, 0110), channels in the order of expand().
 __device__ __forceinline__ v4i expand_digits(uint32_t lm, uint32_t hm, uint32_t ls, uint32_t hs)
@@ -98,15 +72,6 @@ __device__ __forceinline__ v4i expand_digits(uint32_t lm, uint32_t hm, uint32_t 
     o.z = (int)(((b0 >> 2) & 0x11111111u) | ((b1 >> 1) & 0x22222222u) | (b2 & 0x44444444u) | ((b3 << 1) & 0x88888888u));
     o.w = (int)(((b0 >> 3) & 0x11111111u) | ((b1 >> 2) & 0x22222222u) | ((b2 >> 1) & 0x44444444u) | (b3 & 0x88888888u));
     return o;
-}
-
-// 32 filters x 32 voxels x 64 channels; 4-bit operands occupy the first four of the eight operand
-// registers, and constant zero scale operands select the instruction without block scales.
-__device__ __forceinline__ v16f multiply(v4i a, v4i b, v16f c)
-{
-    const v8i a8 = __builtin_shufflevector(a, a, 0, 1, 2, 3, -1, -1, -1, -1);
-    const v8i b8 = __builtin_shufflevector(b, b, 0, 1, 2, 3, -1, -1, -1, -1);
-    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a8, b8, c, 4, 4, 0, 0, 0, 0);
 }
 
 // word = (word << 1) | (thr < d), and with d < thr, through the carry flag.
@@ -271,22 +236,17 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
         }
         if (ODD && tid < 4) reinterpret_cast<uint32_t*>(lds8 + t.zero_off)[tid] = 0u;
     }
-    // Cut points of the workgroup's filters, as what the accumulators start from, -(hi + 1/2), and what
-    // turns acc - hi - 1/2 into acc - lo + 1/2.  Sums stay within 2^21 (checked on the host), so clamping
-    // to 2^21 + 1 changes no decision and every intermediate is a multiple of 1/2 below 2^23: exact.
+    // Cut points of the workgroup's filters: start values, then widths.
     constexpr bool STAGED = EXP && PACKED;
     float* cuts = reinterpret_cast<float*>(lds8 + t.cut_off);
     const int wg_filters = t.nwc * 32 * NB;
     if constexpr (STAGED) {
         for (int j = tid; j < wg_filters; j += nthreads) {
             const int co = blockIdx.y * wg_filters + j;
-            int lo = -(1 << 21) - 1, hi = (1 << 21) + 1;     // filters past c_out: code 0
-            if (co < p.c_out) {
-                lo = max(lo, min(hi, p.lo[co]));
-                hi = max(-(1 << 21) - 1, min(hi, p.hi[co]));
-            }
-            cuts[j] = -(float)hi - 0.5f;
-            cuts[wg_filters + j] = (float)(hi - lo + 1);
+            const bool live = co < p.c_out;
+            const Cut cut = cut_of(live ? p.lo[co] : 0, live ? p.hi[co] : 0, live);
+            cuts[j] = cut.start;
+            cuts[wg_filters + j] = cut.width;
         }
     }
     __syncthreads();
@@ -415,8 +375,7 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
 #pragma unroll
             for (int vb = 0; vb < VB; ++vb) pos[vb] = neg[vb] = 0u;
             if constexpr (STAGED) {
-                // signs of acc - hi - 1/2 (set: not above hi) and of acc - lo + 1/2 (set: below lo),
-                // one shift each to append them, highest filter first
+                // highest filter first
 #pragma unroll
                 for (int k = 3; k >= 0; --k) {
                     const float4 h = *reinterpret_cast<const float4*>(cuts + wg_filters + (wc * NB + nb) * 32 + 8 * k + 4 * g);
@@ -425,15 +384,9 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
                     for (int vb = 0; vb < VB; ++vb) {
                         if (k < 3) { pos[vb] <<= 4; neg[vb] <<= 4; }
 #pragma unroll
-                        for (int j = 3; j >= 0; --j) {
-                            const float a = acc[vb][nb][4 * k + j];
-                            pos[vb] = __builtin_amdgcn_alignbit(pos[vb], __float_as_uint(a), 31);
-                            neg[vb] = __builtin_amdgcn_alignbit(neg[vb], __float_as_uint(a + w[j]), 31);
-                        }
+                        for (int j = 3; j >= 0; --j) decide(pos[vb], neg[vb], acc[vb][nb][4 * k + j], w[j]);
                     }
                 }
-#pragma unroll
-                for (int vb = 0; vb < VB; ++vb) pos[vb] ^= 0x0f0f0f0fu;
             } else {
                 const bool full = c0 + 32 <= p.c_out;
 #pragma unroll
@@ -466,10 +419,7 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
             }
 #pragma unroll
             for (int vb = 0; vb < VB; ++vb) {
-                const uint32_t m = (pos[vb] | neg[vb]) << (4 * g), s = (neg[vb] & ~pos[vb]) << (4 * g);
-                // lanes 0-31: mask words of the 32 voxels, lanes 32-63: their sign words
-                const auto sw = __builtin_amdgcn_permlane32_swap(m, s, false, false);
-                const uint32_t word = sw[0] | sw[1];
+                const uint32_t word = block_word(STAGED ? pos[vb] : pos[vb] ^ 0x0f0f0f0fu, neg[vb], g);
                 const int vi = vb * 32 + i32;
                 const int ox = ox0 + (vi & (X - 1)), oy = oy0 + wy * Y + ((vi >> t.lxb) & (Y - 1));
                 const int oz = oz0 + wz * Z + (vi >> (t.lxb + t.lyb));
@@ -686,7 +636,7 @@ int launch_kind(const ConvParams& p, const MatrixPlan& t, bool odd, size_t lds, 
 bool launch_conv_matrix(const ConvParams& p, hipStream_t s, int* rc)
 {
     const int64_t taps = (int64_t)p.kd * p.kh * p.kw;
-    if (taps > 128 || taps * p.c_in * (p.digits ? 2 : 1) > (1 << 21)) return false;
+    if (taps > 128 || taps * p.c_in * (p.digits ? 2 : 1) > kMatrixSumLimit) return false;
     const int64_t lds_limit = lds_limit_for_current_device();
     if (lds_limit <= 0) { *rc = TERN_EHIP; return true; }
     Choice c;

@@ -1,18 +1,22 @@
 // Pointwise ternary convolution for gfx950: a 1x1x1 kernel with unit stride and no padding
 // (paper section 2, Eq. 9; the 1x1 rows of Table 1; also the second half of a one-channel first
-// layer whose taps were gathered into one word per voxel).
+// layer whose taps were gathered into a bit string per voxel).
 //
-// An output voxel depends on one input voxel only, so there is no halo and nothing to share:
-// the volume is a flat list of voxels, a lane owns V of them (64 apart, so that a wave's loads
-// and stores are contiguous runs), reads their packed words from global memory once into
-// registers, and then walks the output channels CO_BLK at a time with the filter words coming
-// through the scalar cache -- the same four vector instructions per word pair and the same
-// epilogue as the tiled kernel, without its LDS tile, barrier and tap walk, whose fixed cost per
-// wave would dominate here (a single-tap wave has only a few hundred instructions of real work).
+// An output voxel depends on one input voxel only, so there is no halo, no LDS and no barrier: the volume
+// is a flat list of voxels.  A wave holds the filters of 32 NB channels in registers, widened to 4-bit
+// floats once, and their cut points; it walks blocks of 32 voxels, each fetched from global memory straight
+// into the matrix instruction's lanes (a block's records are one contiguous run: lanes 0-31 take the mask
+// words of a voxel's word pair, lanes 32-63 the sign words, and one half-wave swap sorts them), four
+// blocks ahead of their use (two blocks ahead, cut points in registers instead of LDS and accumulators that
+// the compiler put into accumulation registers: 21 us where this takes 12).  Bound by memory where the
+// output is int32, by the epilogue's three vector instructions per output where it is packed.  Measured
+// against one lane per voxel with bit counts: 64 -> 64 channels on 96^3 24.5 -> 12.0 us packed (28 MB,
+// 2.4 TB/s) and 39.0 -> 36.9 us int32 (6.5 TB/s), 128 -> 128 on 64^3 22.0 -> 8.9, 256 -> 256 on 609
+// voxels 9.2 -> 2.9, 32 -> 32 on 64^3 4.7 -> 3.9.
 #include <type_traits>
 
-#include "tern_conv_common.h"
 #include "tern_internal.h"
+#include "tern_matrix_common.h"
 
 namespace tern {
 namespace {
@@ -20,142 +24,199 @@ namespace {
 constexpr int kPointThreads = 256;
 
 struct PointParams {
-    const uint32_t* in;      // packed [voxels][2][WC*NCH] (batch items folded for packed output)
-    const uint32_t* wgt;     // filter bank [NCH][co_pad][2][WC]
+    const uint32_t* in;      // packed [voxels][2][wd] (batch items folded for packed output)
+    const uint32_t* wgt;     // filter bank [words or pairs][co_pad][2][wc]; binary: [..][co_pad][wc]
     const int32_t* lo;
     const int32_t* hi;
     int32_t* out_acc;        // [n][c_out][voxels] or null
     uint32_t* out_packed;    // [voxels][2][wd_out] or null
-    int64_t voxels;          // per grid.z slice
+    int32_t voxels;          // per grid.z slice
+    int32_t blocks_per_wave;
     int32_t c_out, wd_out, co_pad;
-    int32_t co_per_wave;     // multiple of 32 (or everything)
 };
 
-template <int WC, int NCH, int V, int CO_BLK, bool PACKED>
-__global__ __launch_bounds__(kPointThreads) void conv_point_kernel(PointParams p)
+// S: steps of 64 channels (word pairs); ODD: an odd number of words per voxel (the last pair is half
+// empty, bank and records are read word by word); BIN: sign-only filters.
+template <int S, int NB, bool PACKED, bool BIN, bool ODD>
+__global__ __launch_bounds__(kPointThreads) __attribute__((amdgpu_waves_per_eu(3))) void conv_point_kernel(PointParams p)
 {
-    constexpr int WD = WC * NCH;
-    constexpr int KG = GroupOf<CO_BLK>::value;
-    constexpr int NG = CO_BLK / KG;
-    const int lane = threadIdx.x & 63;
+    constexpr int WD = ODD ? 2 * S - 1 : 2 * S;
+    constexpr int REC = 2 * WD;                          // words of a voxel record
+    const int lane = threadIdx.x & 63, i32 = lane & 31, g = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t wid = (int64_t)blockIdx.x * (kPointThreads / 64) + wave;
-    const int64_t v0 = wid * (64 * V) + lane;           // this lane's first voxel
-    if (wid * (64 * V) >= p.voxels) return;             // whole wave past the end
-    const int n = blockIdx.z;
-    const uint32_t* in_n = p.in + (size_t)n * p.voxels * 2u * WD;
-
-    // ---- this lane's voxels, all chunks, straight into registers -----------------------------
-    ActChunk<WC> A[NCH][V];
-#pragma unroll
-    for (int v = 0; v < V; ++v) {
-        const int64_t vox = v0 + 64 * v;
-        const bool live = vox < p.voxels;
-        const uint32_t* src = in_n + (size_t)(live ? vox : 0) * 2u * WD;
-        if constexpr (WD == 1) {
-            uint2 r = *reinterpret_cast<const uint2*>(src);
-            A[0][v].m[0] = live ? r.x : 0u;
-            A[0][v].s[0] = live ? r.y : 0u;
-        } else if constexpr (WC == 1) {   // odd word counts: records are only 8-byte aligned
-#pragma unroll
-            for (int ch = 0; ch < NCH; ++ch) {
-                const uint32_t m = src[ch], sg = src[WD + ch];
-                A[ch][v].m[0] = live ? m : 0u;
-                A[ch][v].s[0] = live ? sg : 0u;
-            }
-        } else {
-#pragma unroll
-            for (int ch = 0; ch < NCH; ++ch) {
-                const uint2 m = *reinterpret_cast<const uint2*>(src + 2 * ch);
-                const uint2 sg = *reinterpret_cast<const uint2*>(src + WD + 2 * ch);
-                A[ch][v].m[0] = live ? m.x : 0u; A[ch][v].m[1] = live ? m.y : 0u;
-                A[ch][v].s[0] = live ? sg.x : 0u; A[ch][v].s[1] = live ? sg.y : 0u;
-            }
+    const int blocks = (int)(((uint32_t)p.voxels + 31u) >> 5);
+    const int c0 = blockIdx.y * (32 * NB);
+    const uint32_t* in_n = p.in + (size_t)blockIdx.z * (size_t)p.voxels * REC;
+    // cut points of the workgroup's filters: start values, then widths
+    __shared__ __align__(16) float cuts[PACKED ? 64 * NB : 4];
+    if constexpr (PACKED) {
+        if (threadIdx.x < 32 * NB) {
+            const int co = c0 + (int)threadIdx.x;
+            const bool live = co < p.c_out;
+            const Cut c = cut_of(live ? p.lo[co] : 0, live ? p.hi[co] : 0, live);
+            cuts[threadIdx.x] = c.start;
+            cuts[32 * NB + threadIdx.x] = c.width;
         }
     }
+    const int64_t first64 = ((int64_t)blockIdx.x * (kPointThreads / 64) + wave) * p.blocks_per_wave;
+    const int first = (int)min(first64, (int64_t)blocks);
+    const int last = min(blocks, first + p.blocks_per_wave) - 1;   // before first: nothing to do
 
-    const int co_begin = blockIdx.y * p.co_per_wave;
-    const int co_end = min(p.c_out, co_begin + p.co_per_wave);
-    const int step_words = p.co_pad * 2 * WC;            // filter-bank words per chunk
-    uint32_t pos_w[V], neg_w[V];
+    uint32_t m33 = 0x33333333u, maa = 0xaaaaaaaau;
+    asm volatile("" : "+v"(m33), "+v"(maa));
+
+    // One block's words, (mask, sign) per step once sorted.  Voxels past the end repeat the last one.
+    auto fetch = [&](v2u (&x)[S], int b) {
+        const int v0 = b * 32;
+        const uint32_t lane_v = (uint32_t)min(i32, p.voxels - 1 - v0);
+        const uint32_t* src = in_n + (size_t)v0 * REC + lane_v * REC;
 #pragma unroll
-    for (int v = 0; v < V; ++v) pos_w[v] = neg_w[v] = 0u;
-
-    for (int cb = co_begin; cb < co_end; cb += CO_BLK) {
-        int32_t acc_m[V][CO_BLK], acc_n[V][CO_BLK];   // set by the first chunk, added to by the rest
-
-        // (chunk, channel group) pairs in order, two filter-word groups in flight
-        scalar_ptr wbase = (scalar_ptr)(uintptr_t)p.wgt + (size_t)cb * 2 * WC;
-        WGroup<WC, KG> g[2];
-        load_wgroup<WC, KG>(g[0], wbase);
-        auto group_step = [&](int idx, auto init) {
-            const int ch = idx / NG, gi = idx % NG;
-            settle<WC, KG>(g[idx & 1]);
-            __builtin_amdgcn_sched_barrier(0);
-            if (idx + 1 < NCH * NG) {
-                const int nch = (idx + 1) / NG, ngi = (idx + 1) % NG;
-                load_wgroup<WC, KG>(g[(idx + 1) & 1], wbase + (size_t)nch * step_words + ngi * KG * 2 * WC);
+        for (int s = 0; s < S; ++s) {
+            if constexpr (!ODD) {
+                x[s] = *reinterpret_cast<const v2u*>(src + g * WD + 2 * s);
+            } else {
+                const bool live = 2 * s + 1 < WD || g == 0;
+                const int q = live ? 2 * s + g : 2 * s;
+                x[s].x = src[q];
+                x[s].y = src[WD + q];
+                if (!live) x[s].x = x[s].y = 0u;
             }
-            __builtin_amdgcn_sched_barrier(0);
-            mac_group<WC, V, CO_BLK, KG, decltype(init)::value>(A[ch], g[idx & 1], gi * KG, acc_m, acc_n);
-            __builtin_amdgcn_sched_barrier(0);
-        };
+        }
+    };
+    constexpr int AHEAD = 4;
+    v2u x[AHEAD][S];
 #pragma unroll
-        for (int idx = 0; idx < NG; ++idx) group_step(idx, std::true_type{});
-#pragma unroll
-        for (int idx = NG; idx < NCH * NG; ++idx) group_step(idx, std::false_type{});
+    for (int k = 0; k < AHEAD; ++k) fetch(x[k], max(0, min(first + k, last)));
 
-        int32_t d[V][CO_BLK];
+    // ---- filters and cut points ----------------------------------------------------------------
+    v4i F[NB][S];
 #pragma unroll
-        for (int v = 0; v < V; ++v)
+    for (int nb = 0; nb < NB; ++nb) {
+        const int co = c0 + nb * 32 + i32;               // below co_pad: whole blocks of 32 exist
 #pragma unroll
-            for (int j = 0; j < CO_BLK; ++j) d[v][j] = acc_m[v][j] - 2 * acc_n[v][j];
+        for (int s = 0; s < S; ++s) {
+            v2u w;
+            if constexpr (!ODD) {
+                const uint32_t* row = p.wgt + (size_t)s * p.co_pad * (BIN ? 2 : 4);
+                if constexpr (BIN) {
+                    w.y = row[co * 2 + g];
+                } else {
+                    const v2u r = *reinterpret_cast<const v2u*>(row + co * 4 + 2 * g);
+                    const auto sw = __builtin_amdgcn_permlane32_swap(r.x, r.y, false, false);
+                    w.x = sw[0]; w.y = sw[1];
+                }
+            } else {
+                const int q = min(2 * s + g, WD - 1);     // (past the end: any word, the voxel's is zero)
+                if constexpr (BIN) w.y = p.wgt[((size_t)q * p.co_pad + co)];
+                else w = *reinterpret_cast<const v2u*>(p.wgt + ((size_t)q * p.co_pad + co) * 2);
+            }
+            if constexpr (BIN) w.x = 0xffffffffu;
+            F[nb][s] = expand(interleave(w.x, w.y, m33), maa);
+        }
+    }
+    if constexpr (PACKED) __syncthreads();
+    if (first > last) return;
+    v16f start[NB];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            float4 h = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            if constexpr (PACKED) h = *reinterpret_cast<const float4*>(cuts + nb * 32 + 8 * k + 4 * g);
+            start[nb][4 * k] = h.x; start[nb][4 * k + 1] = h.y; start[nb][4 * k + 2] = h.z; start[nb][4 * k + 3] = h.w;
+        }
 
-        const int co_left = co_end - cb;
+    // ---- blocks of 32 voxels -------------------------------------------------------------------
+    auto block = [&](v2u (&x)[S], int b) {
+        v4i V[S];
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            if constexpr (ODD) {
+                V[s] = expand(interleave(x[s].x, x[s].y, m33), maa);
+            } else {
+                const auto sw = __builtin_amdgcn_permlane32_swap(x[s].x, x[s].y, false, false);
+                V[s] = expand(interleave(sw[0], sw[1], m33), maa);
+            }
+        }
+        fetch(x, min(b + AHEAD, last));
+        v16f acc[NB];
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            acc[nb] = multiply(F[nb][0], V[0], start[nb]);
+#pragma unroll
+            for (int s = 1; s < S; ++s) acc[nb] = multiply(F[nb][s], V[s], acc[nb]);
+        }
+        const int vox = b * 32 + i32;
         if constexpr (PACKED) {
-            uint32_t pp[V], pn[V];
-            ternarise_pass<V, CO_BLK>(d, (scalar_ptr)(uintptr_t)p.lo, (scalar_ptr)(uintptr_t)p.hi, cb,
-                                      co_left, p.c_out, pp, pn);
-            const int sh = cb & 31;
+            uint32_t word[NB];
 #pragma unroll
-            for (int v = 0; v < V; ++v) { pos_w[v] |= pp[v] << sh; neg_w[v] |= pn[v] << sh; }
-            // a wave's channel slice starts at a multiple of 32, so it always owns whole words
-            if (((cb + CO_BLK) & 31) == 0 || cb + CO_BLK >= co_end) {
-                const int q = cb >> 5;
+            for (int nb = 0; nb < NB; ++nb) {
+                uint32_t pos = 0u, neg = 0u;
 #pragma unroll
-                for (int v = 0; v < V; ++v) {
-                    const int64_t vox = v0 + 64 * v;
-                    if (vox < p.voxels) {
-                        uint32_t* o = p.out_packed + (size_t)vox * 2u * p.wd_out;
-                        o[q] = pos_w[v] | neg_w[v];
-                        o[p.wd_out + q] = neg_w[v] & ~pos_w[v];    // +1 wins if lo > hi
-                    }
-                    pos_w[v] = neg_w[v] = 0u;
+                for (int k = 3; k >= 0; --k) {
+                    const float4 h = *reinterpret_cast<const float4*>(cuts + 32 * NB + nb * 32 + 8 * k + 4 * g);
+                    const float w[4] = {h.x, h.y, h.z, h.w};
+                    if (k < 3) { pos <<= 4; neg <<= 4; }
+#pragma unroll
+                    for (int j = 3; j >= 0; --j) decide(pos, neg, acc[nb][4 * k + j], w[j]);
+                }
+                word[nb] = block_word(pos, neg, g);
+            }
+            if (vox < p.voxels) {
+                uint32_t* o = p.out_packed + ((size_t)(b * 32) * 2u + (uint32_t)(i32 * 2)) * p.wd_out + g * p.wd_out + (c0 >> 5);
+                if (NB == 2 && (p.wd_out & 1) == 0) {
+                    *reinterpret_cast<v2u*>(o) = v2u{word[0], word[NB - 1]};
+                } else {
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb)
+                        if (c0 + nb * 32 < p.c_out) o[nb] = word[nb];
                 }
             }
         } else {
+            if (vox < p.voxels) {
 #pragma unroll
-            for (int v = 0; v < V; ++v) {
-                const int64_t vox = v0 + 64 * v;
-                if (vox < p.voxels) {
-                    int32_t* o = p.out_acc + (size_t)n * p.c_out * p.voxels + vox;
+                for (int nb = 0; nb < NB; ++nb) {
+                    const int cb = c0 + nb * 32 + 4 * g;
+                    int32_t* o = p.out_acc + ((size_t)blockIdx.z * p.c_out + cb) * (size_t)p.voxels + vox;
 #pragma unroll
-                    for (int j = 0; j < CO_BLK; ++j)
-                        if (j < co_left) o[(size_t)(cb + j) * p.voxels] = d[v][j];
+                    for (int v = 0; v < 16; ++v) {
+                        const int dc = (v >> 2) * 8 + (v & 3);
+                        if (cb + dc < p.c_out) o[(size_t)dc * p.voxels] = (int32_t)acc[nb][v];
+                    }
                 }
             }
         }
+    };
+    for (int b = first; b <= last; b += AHEAD) {
+#pragma unroll
+        for (int k = 0; k < AHEAD; ++k)
+            if (b + k <= last) block(x[k], b + k);
     }
+}
+
+template <int S, bool ODD>
+void launch_steps(const PointParams& p, bool packed, bool binary, int nb, dim3 grid, hipStream_t s)
+{
+    const dim3 block(kPointThreads);
+#define TERN_POINT(NB_, BIN_)                                                                              \
+    do {                                                                                                   \
+        if (packed) hipLaunchKernelGGL((conv_point_kernel<S, NB_, true, BIN_, ODD>), grid, block, 0, s, p);  \
+        else hipLaunchKernelGGL((conv_point_kernel<S, NB_, false, BIN_, ODD>), grid, block, 0, s, p);        \
+    } while (0)
+    if (nb == 2) { if (binary) TERN_POINT(2, true); else TERN_POINT(2, false); }
+    else { if (binary) TERN_POINT(1, true); else TERN_POINT(1, false); }
+#undef TERN_POINT
 }
 
 }  // namespace
 
+// Up to eight words per voxel (the filters of a wave stay in registers) and, with several taps' worth of
+// channels packed into a word (c_in <= 16), never: a single tap has a plain bank.
 bool conv_point_applies(const ConvParams& p)
 {
     if (p.kd * p.kh * p.kw != 1) return false;
     if (p.sd != 1 || p.sh != 1 || p.sw != 1 || p.pd != 0 || p.ph != 0 || p.pw != 0) return false;
-    if (p.tp_slots != 0) return false;
-    return p.wd_in == 1 || p.wd_in == 2 || p.wd_in == 3 || p.wd_in == 4 || p.wd_in == 5 || p.wd_in == 8;
+    return p.tp_slots == 0 && p.wd_in <= 8;
 }
 
 int launch_conv_point(const ConvParams& c, hipStream_t s)
@@ -165,48 +226,35 @@ int launch_conv_point(const ConvParams& c, hipStream_t s)
     p.in = c.in; p.wgt = c.wgt; p.lo = c.lo; p.hi = c.hi;
     p.out_acc = c.out_acc; p.out_packed = c.out_packed;
     // packed output: batch items are just more voxels; int32 output keeps them apart (grid.z)
-    const int64_t spatial = (int64_t)c.d * c.h * c.w;
-    p.voxels = packed ? spatial * c.n : spatial;
+    const int64_t voxels = (int64_t)c.d * c.h * c.w * (packed ? c.n : 1);
     const int gz = packed ? 1 : c.n;
     if (gz > 65535) return TERN_ESHAPE;
+    p.voxels = (int32_t)voxels;                          // at most 2^31 - 1 per tensor
     p.c_out = c.c_out; p.wd_out = c.wd_out; p.co_pad = c.co_pad;
-
-    constexpr int V = 2;
-    const int64_t waves0 = (p.voxels + 64 * V - 1) / (64 * V) * gz;
-    // 32 channels per pass on large problems (half the passes), 16 on small ones or when the
-    // last pass would be mostly padding
-    const int tail = c.c_out % 32;
-    const int co_blk = (waves0 * ((c.c_out + 31) / 32) >= 4096 && (tail == 0 || tail > 16)) ? 32 : 16;
-    // One wave walks all output channels (its voxels are read once) unless that leaves the chip
-    // short of waves; slices are whole 32-channel words.
-    const int words = (c.c_out + 31) / 32;
-    int slices = 1;
-    if (waves0 < 2048) {
-        slices = (int)((2048 + waves0 - 1) / waves0);
-        if (slices > words) slices = words;
-    }
-    const int words_per_slice = (words + slices - 1) / slices;
-    slices = (words + words_per_slice - 1) / words_per_slice;
-    p.co_per_wave = words_per_slice * 32;
-
-    const int64_t blocks = (waves0 / gz + kPointThreads / 64 - 1) / (kPointThreads / 64);
-    if (blocks > 0x7fffffff || slices > 65535) return TERN_ESHAPE;
-    const dim3 grid((unsigned)blocks, (unsigned)slices, (unsigned)gz), block(kPointThreads);
-#define TERN_POINT(WC_, NCH_, CB_)                                                                        \
-    do {                                                                                                  \
-        if (packed) hipLaunchKernelGGL((conv_point_kernel<WC_, NCH_, V, CB_, true>), grid, block, 0, s, p); \
-        else hipLaunchKernelGGL((conv_point_kernel<WC_, NCH_, V, CB_, false>), grid, block, 0, s, p);       \
-    } while (0)
+    const int fb = (c.c_out + 31) / 32;
+    const int64_t blocks = (voxels + 31) / 32;
+    // Two filter blocks per wave where they come in pairs, fit the registers (up to four words) and the
+    // launch still has a wave per SIMD; then
+    // as many blocks per wave as leave four waves per SIMD: setting a wave up (filters, cut points) costs
+    // as much as two blocks.
+    const int nb = fb % 2 == 0 && c.wd_in <= 4 && blocks * gz * (fb / 2) >= 1024 ? 2 : 1;
+    const int groups = fb / nb;
+    if (groups > 65535) return TERN_ESHAPE;
+    int64_t per = (blocks * gz * groups + 4095) / 4096;
+    if (per > 64) per = 64;
+    p.blocks_per_wave = (int32_t)per;
+    const int64_t waves = (blocks + per - 1) / per;
+    const dim3 grid((unsigned)((waves + kPointThreads / 64 - 1) / (kPointThreads / 64)), (unsigned)groups, (unsigned)gz);
     switch (c.wd_in) {
-        case 1: if (co_blk == 32) TERN_POINT(1, 1, 32); else TERN_POINT(1, 1, 16); break;
-        case 2: if (co_blk == 32) TERN_POINT(2, 1, 32); else TERN_POINT(2, 1, 16); break;
-        case 3: if (co_blk == 32) TERN_POINT(1, 3, 32); else TERN_POINT(1, 3, 16); break;
-        case 4: if (co_blk == 32) TERN_POINT(2, 2, 32); else TERN_POINT(2, 2, 16); break;
-        case 5: if (co_blk == 32) TERN_POINT(1, 5, 32); else TERN_POINT(1, 5, 16); break;
-        case 8: if (co_blk == 32) TERN_POINT(2, 4, 32); else TERN_POINT(2, 4, 16); break;
-        default: return TERN_EARG;
+        case 1: launch_steps<1, true>(p, packed, c.binary != 0, nb, grid, s); break;
+        case 2: launch_steps<1, false>(p, packed, c.binary != 0, nb, grid, s); break;
+        case 3: launch_steps<2, true>(p, packed, c.binary != 0, nb, grid, s); break;
+        case 4: launch_steps<2, false>(p, packed, c.binary != 0, nb, grid, s); break;
+        case 5: launch_steps<3, true>(p, packed, c.binary != 0, nb, grid, s); break;
+        case 6: launch_steps<3, false>(p, packed, c.binary != 0, nb, grid, s); break;
+        case 7: launch_steps<4, true>(p, packed, c.binary != 0, nb, grid, s); break;
+        default: launch_steps<4, false>(p, packed, c.binary != 0, nb, grid, s); break;
     }
-#undef TERN_POINT
     TERN_HIP_CHECK(hipGetLastError());
     return TERN_OK;
 }

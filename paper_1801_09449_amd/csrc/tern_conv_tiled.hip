@@ -903,7 +903,7 @@ void last_launch(int32_t* info) { for (int i = 0; i < 8; ++i) info[i] = g_last[i
 
 int launch_conv3d(const ConvParams& p_in, hipStream_t s)
 {
-    if (g_point && !p_in.digits && !p_in.binary && conv_point_applies(p_in)) {
+    if (g_point && !p_in.digits && conv_point_applies(p_in)) {
         note_launch(TERN_KERNEL_POINTWISE, 0, 0, 0, 0, 0, 0, 0);
         return launch_conv_point(p_in, s);
     }

@@ -133,7 +133,7 @@ int launch_threshold_pack_i32(const int32_t* src, tern_dims dims, const int32_t*
 int launch_threshold_pack_f32(const float* src, tern_dims dims, const float* lo, const float* hi,
                               uint32_t* dst, hipStream_t s);
 int launch_conv3d(const ConvParams& p, hipStream_t s);
-// 1x1x1 / stride 1 / no padding with 1, 2, 4 or 8 input words per plane: the pointwise kernel.
+// 1x1x1 / stride 1 / no padding with up to 8 input words per plane: the pointwise kernel.
 bool conv_point_applies(const ConvParams& p);
 int launch_conv_point(const ConvParams& p, hipStream_t s);
 // Tiled convolution on the matrix cores; false: not for this convolution (nothing launched).

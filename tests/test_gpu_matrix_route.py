@@ -116,3 +116,26 @@ def test_same_integers_as_the_bit_count_kernels(G, block):
             finally:
                 T.tern_set_option(CO_BLOCK, 0)
             assert torch.equal(here, there), (i, j, c.act.shape, c.wgt.shape, g)
+
+
+@pytest.mark.parametrize("words", range(1, 10))
+@pytest.mark.parametrize("vox", [(1, 1, 1), (1, 1, 31), (1, 3, 11), (5, 16, 27)], ids=["1", "31", "33", "2160"])
+def test_pointwise_blocks_and_words(G, words, vox):
+    """Single-tap convolutions: every word count the pointwise kernel takes (and the first it does not),
+    blocks of 32 voxels with and without a remainder, a batch (folded for packed output), filter counts
+    with one block, two and a remainder, ternary and binary filters."""
+    import torch
+    import paper_1801_09449_amd as T
+    for co, n in ((1, 1), (33, 2), (64, 3), (200, 1)):
+        c = synth.conv_case("px", n, 32 * words - (words & 3), co, vox, k=1, pad=0, seed=830 + words, p0_a=0.4)
+        check(G, c)
+        assert (T.tern_last_launch()["kernel"] == T.KERNEL_POINTWISE) == (words <= 8)
+        w = np.where(c.wgt < 0, -1, 1).astype(np.int8)
+        got = T.tern_conv3d_binary(T.tern_pack(G.dev(c.act)), c.act.shape[1], T.tern_pack_filters_binary(G.dev(w)), co, 1, 1, 0, 1)
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(got.cpu().numpy(), oracle.conv3d(c.act, w, ConvGeom(c.k, c.stride, c.pad, c.dil)))
+
+
+def test_pointwise_many_blocks_per_wave(G):
+    """More blocks than waves: a wave walks several, the last one fewer and a part of one."""
+    check(G, synth.conv_case("px_many", 1, 64, 64, (64, 65, 67), k=1, pad=0, seed=829, p0_a=0.4))
