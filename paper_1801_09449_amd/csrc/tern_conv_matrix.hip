@@ -177,12 +177,13 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
         const int items = nvox * t.nch;
         constexpr bool PAIRS = !ODD || KIND == kDigits;     // two words per plane and item
         constexpr int FILL = EXP ? 6 : 4;                   // items a thread keeps in flight
-        for (int e0 = tid; e0 < items; e0 += FILL * nthreads) {
+        for (int base = 0; base < items; base += FILL * nthreads) {
             uint32_t r[FILL][4];
             int dst[FILL];
 #pragma unroll
             for (int k = 0; k < FILL; ++k) {
-                const uint32_t e = (uint32_t)(e0 + k * nthreads);
+                if (EXP && !ODD && base + k * nthreads >= items) break;   // (the same for every thread)
+                const uint32_t e = (uint32_t)(base + k * nthreads + tid);
                 const uint32_t v = t.nch > 1 ? quotient(e, t.r_ch) : e;
                 const uint32_t c = e - __umul24(v, (uint32_t)t.nch);
                 const uint32_t hz = quotient(v, t.r_pl);
@@ -216,6 +217,7 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
             }
 #pragma unroll
             for (int k = 0; k < FILL; ++k) {
+                if (EXP && !ODD && base + k * nthreads >= items) break;
                 if (dst[k] >= 0) {
                     uint8_t* d = lds8 + dst[k];
                     if constexpr (KIND == kDigits) {
@@ -293,21 +295,18 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
             advance(w, nch, inc_ch, tab0, tab1);
         }
     };
-    v16f acc[VB][NB];
+    v16f acc[VB][NB], start[NB];
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
-        v16f init;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) init[v] = 0.0f;
+        for (int v = 0; v < 16; ++v) start[nb][v] = 0.0f;
         if constexpr (STAGED) {
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const float4 h = *reinterpret_cast<const float4*>(cuts + (wc * NB + nb) * 32 + 8 * k + 4 * g);
-                init[4 * k] = h.x; init[4 * k + 1] = h.y; init[4 * k + 2] = h.z; init[4 * k + 3] = h.w;
+                start[nb][4 * k] = h.x; start[nb][4 * k + 1] = h.y; start[nb][4 * k + 2] = h.z; start[nb][4 * k + 3] = h.w;
             }
         }
-#pragma unroll
-        for (int vb = 0; vb < VB; ++vb) acc[vb][nb] = init;
     }
 
     auto widen = [&](v4i (&F)[NB], const v2u (&f)[NB], int step) {
@@ -330,116 +329,133 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
             }
         }
     };
-    auto contract = [&](const v4i (&F)[NB], const Vox (&x)[VB]) {
+    auto contract = [&](const v4i (&F)[NB], const Vox (&x)[VB], auto first) {
 #pragma unroll
         for (int vb = 0; vb < VB; ++vb) {
             v4i V;
             if constexpr (EXP) V = x[vb];
             else V = expand(x[vb], maa);
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb) acc[vb][nb] = multiply(F[nb], V, acc[vb][nb]);
+            for (int nb = 0; nb < NB; ++nb)
+                acc[vb][nb] = multiply(F[nb], V, decltype(first)::value ? start[nb] : acc[vb][nb]);
         }
     };
 
+    // Operands of step i + 1 are fetched and widened in front of step i's matrix instructions, filter words
+    // two steps further ahead.  (The barriers keep the compiler from moving those loads above the use of
+    // the registers they replace, which made it copy them and wait for loads it had just issued.)
     Vox x0[VB], x1[VB];
     v4i F0[NB], F1[NB];
     fetch_v(x0, 0);
     widen(F0, f0, 0);
     fetch_f(f0, 2);
-    int i = 0;
+    if (steps > 1) {
+        fetch_v(x1, 1);
+        widen(F1, f1, 1);
+        fetch_f(f1, 3);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    contract(F0, x0, std::true_type{});
+    int i = 1;
     for (; i + 2 <= steps; i += 2) {
-        fetch_v(x1, i + 1);
-        widen(F1, f1, i + 1);
+        fetch_v(x0, i + 1);
+        widen(F0, f0, i + 1);
         __builtin_amdgcn_sched_barrier(0);
-        fetch_f(f1, i + 3);
+        fetch_f(f0, i + 3);
         __builtin_amdgcn_sched_barrier(0);
-        contract(F0, x0);
+        contract(F1, x1, std::false_type{});
         __builtin_amdgcn_sched_barrier(0);
-        if (i + 2 < steps) fetch_v(x0, i + 2);
-        widen(F0, f0, i + 2);
+        if (i + 2 < steps) fetch_v(x1, i + 2);
+        widen(F1, f1, i + 2);
         __builtin_amdgcn_sched_barrier(0);
-        fetch_f(f0, i + 4);
+        fetch_f(f1, i + 4);
         __builtin_amdgcn_sched_barrier(0);
-        contract(F1, x1);
+        contract(F0, x0, std::false_type{});
         __builtin_amdgcn_sched_barrier(0);
     }
-    if (i < steps) contract(F0, x0);
+    if (i < steps) contract(F1, x1, std::false_type{});
 
     // ---- epilogue: lane = voxel l % 32 of a block, register v = filter 8 (v / 4) + 4 g + v % 4 -----
+    // A block's voxels differ from block 0's by the same box offset in every lane.
+    const int lx = i32 & (X - 1), ly = (i32 >> t.lxb) & (Y - 1), lz = i32 >> (t.lxb + t.lyb);
+    const int bx = ox0, by = oy0 + wy * Y, bz = oz0 + wz * Z;
+    auto offset_of = [&](int vb, int& dx, int& dy, int& dz) {
+        dx = (vb * 32) & (X - 1);
+        dy = ((vb * 32) >> t.lxb) & (Y - 1);
+        dz = (vb * 32) >> (t.lxb + t.lyb);
+        return lx < p.ow - bx - dx && ly < p.oh - by - dy && lz < p.od - bz - dz;
+    };
+    const size_t row = (size_t)p.ow, slab = (size_t)p.oh * p.ow;
+    const size_t vox0 = (((size_t)n * p.od + bz + lz) * p.oh + by + ly) * p.ow + bx + lx;
+    if constexpr (PACKED) {
+        uint32_t* out = p.out_packed + vox0 * 2u * p.wd_out + g * p.wd_out + (cb >> 5);
+        const bool pair = NB == 2 && (p.wd_out & 1) == 0;      // (cb >> 5 is even then)
+        int32_t lo[16], hi[16];
+        if constexpr (!STAGED) {                               // all at once: one round trip
+            static_assert(STAGED || NB == 1, "one filter block");
+            if (cb + 32 <= p.c_out) {
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-        const int c0 = cb + nb * 32;
-        if (c0 >= p.c_out) break;
-        if constexpr (PACKED) {
-            uint32_t pos[VB], neg[VB];
-#pragma unroll
-            for (int vb = 0; vb < VB; ++vb) pos[vb] = neg[vb] = 0u;
-            if constexpr (STAGED) {
-                // highest filter first
-#pragma unroll
-                for (int k = 3; k >= 0; --k) {
-                    const float4 h = *reinterpret_cast<const float4*>(cuts + wg_filters + (wc * NB + nb) * 32 + 8 * k + 4 * g);
-                    const float w[4] = {h.x, h.y, h.z, h.w};
-#pragma unroll
-                    for (int vb = 0; vb < VB; ++vb) {
-                        if (k < 3) { pos[vb] <<= 4; neg[vb] <<= 4; }
-#pragma unroll
-                        for (int j = 3; j >= 0; --j) decide(pos[vb], neg[vb], acc[vb][nb][4 * k + j], w[j]);
-                    }
+                for (int v = 0; v < 16; ++v) {
+                    const int co = cb + (v >> 2) * 8 + 4 * g + (v & 3);
+                    lo[v] = p.lo[co]; hi[v] = p.hi[co];
                 }
             } else {
-                const bool full = c0 + 32 <= p.c_out;
 #pragma unroll
-                for (int k = 3; k >= 0; --k) {
-                    int32_t lo[4], hi[4];
-                    const int cg = c0 + 8 * k + 4 * g;
-                    if (full) {
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) { lo[j] = p.lo[cg + j]; hi[j] = p.hi[cg + j]; }
-                    } else {
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) {
-                            const bool live = cg + j < p.c_out;
-                            const int cc = live ? cg + j : 0;
-                            const int32_t l = p.lo[cc], h = p.hi[cc];
-                            lo[j] = live ? l : INT32_MIN; hi[j] = live ? h : INT32_MAX;
-                        }
-                    }
-#pragma unroll
-                    for (int vb = 0; vb < VB; ++vb) {
-                        if (k < 3) { pos[vb] <<= 4; neg[vb] <<= 4; }
-#pragma unroll
-                        for (int j = 3; j >= 0; --j) {
-                            const int32_t a = (int32_t)acc[vb][nb][4 * k + j];
-                            shift_in_gt_v(pos[vb], a, hi[j]);
-                            shift_in_lt_v(neg[vb], a, lo[j]);
-                        }
-                    }
+                for (int v = 0; v < 16; ++v) {
+                    const int co = cb + (v >> 2) * 8 + 4 * g + (v & 3);
+                    const bool live = co < p.c_out;
+                    const int32_t l = p.lo[live ? co : 0], h = p.hi[live ? co : 0];
+                    lo[v] = live ? l : INT32_MIN; hi[v] = live ? h : INT32_MAX;
                 }
             }
+        }
 #pragma unroll
-            for (int vb = 0; vb < VB; ++vb) {
-                const uint32_t word = block_word(STAGED ? pos[vb] : pos[vb] ^ 0x0f0f0f0fu, neg[vb], g);
-                const int vi = vb * 32 + i32;
-                const int ox = ox0 + (vi & (X - 1)), oy = oy0 + wy * Y + ((vi >> t.lxb) & (Y - 1));
-                const int oz = oz0 + wz * Z + (vi >> (t.lxb + t.lyb));
-                if (ox < p.ow && oy < p.oh && oz < p.od)
-                    p.out_packed[((((size_t)n * p.od + oz) * p.oh + oy) * p.ow + ox) * 2u * p.wd_out + g * p.wd_out +
-                                 (c0 >> 5)] = word;
+        for (int vb = 0; vb < VB; ++vb) {
+            uint32_t word[NB];
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) {
+                uint32_t pos = 0u, neg = 0u;
+                if constexpr (STAGED) {
+                    decide_block(pos, neg, acc[vb][nb], cuts + wg_filters + (wc * NB + nb) * 32 + 4 * g);
+                } else {
+#pragma unroll
+                    for (int v = 15; v >= 0; --v) {
+                        const int32_t a = (int32_t)acc[vb][nb][v];
+                        shift_in_gt_v(pos, a, hi[v]);
+                        shift_in_lt_v(neg, a, lo[v]);
+                        if ((v & 3) == 0 && v > 0) { pos <<= 4; neg <<= 4; }
+                    }
+                    pos = ~pos;
+                }
+                word[nb] = block_word(pos, neg);
             }
-        } else {
-            const size_t cs = (size_t)p.od * p.oh * p.ow;
+            int dx, dy, dz;
+            if (offset_of(vb, dx, dy, dz)) {
+                uint32_t* o = out + (dz * slab + dy * row + dx) * 2u * p.wd_out;
+                if (pair) {
+                    *reinterpret_cast<v2u*>(o) = v2u{word[0], word[NB - 1]};
+                } else {
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb)
+                        if (cb + nb * 32 < p.c_out) o[nb] = word[nb];
+                }
+            }
+        }
+    } else {
+        const size_t cs = (size_t)p.od * slab;
+        const size_t in_item = vox0 - (size_t)n * cs;
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            const int c0 = cb + nb * 32 + 4 * g;
 #pragma unroll
             for (int vb = 0; vb < VB; ++vb) {
-                const int vi = vb * 32 + i32;
-                const int ox = ox0 + (vi & (X - 1)), oy = oy0 + wy * Y + ((vi >> t.lxb) & (Y - 1));
-                const int oz = oz0 + wz * Z + (vi >> (t.lxb + t.lyb));
-                if (ox < p.ow && oy < p.oh && oz < p.od) {
-                    int32_t* o = p.out_acc + ((size_t)n * p.c_out + c0 + 4 * g) * cs + ((size_t)oz * p.oh + oy) * p.ow + ox;
+                int dx, dy, dz;
+                if (offset_of(vb, dx, dy, dz)) {
+                    int32_t* o = p.out_acc + ((size_t)n * p.c_out + c0) * cs + in_item + dz * slab + dy * row + dx;
 #pragma unroll
                     for (int v = 0; v < 16; ++v) {
                         const int dc = (v >> 2) * 8 + (v & 3);
-                        if (c0 + dc + 4 * g < p.c_out) o[dc * cs] = (int32_t)acc[vb][nb][v];
+                        if (c0 + dc < p.c_out) o[dc * cs] = (int32_t)acc[vb][nb][v];
                     }
                 }
             }

@@ -151,16 +151,9 @@ __global__ __launch_bounds__(kPointThreads) __attribute__((amdgpu_waves_per_eu(3
             uint32_t word[NB];
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) {
-                uint32_t pos = 0u, neg = 0u;
-#pragma unroll
-                for (int k = 3; k >= 0; --k) {
-                    const float4 h = *reinterpret_cast<const float4*>(cuts + 32 * NB + nb * 32 + 8 * k + 4 * g);
-                    const float w[4] = {h.x, h.y, h.z, h.w};
-                    if (k < 3) { pos <<= 4; neg <<= 4; }
-#pragma unroll
-                    for (int j = 3; j >= 0; --j) decide(pos, neg, acc[nb][4 * k + j], w[j]);
-                }
-                word[nb] = block_word(pos, neg, g);
+                uint32_t pos, neg;
+                decide_block(pos, neg, acc[nb], cuts + 32 * NB + nb * 32 + 4 * g);
+                word[nb] = block_word(pos, neg);
             }
             if (vox < p.voxels) {
                 uint32_t* o = p.out_packed + ((size_t)(b * 32) * 2u + (uint32_t)(i32 * 2)) * p.wd_out + g * p.wd_out + (c0 >> 5);

@@ -61,21 +61,39 @@ __device__ __forceinline__ Cut cut_of(int lo, int hi, bool live)
 }
 
 // Appends to pos / neg the signs of acc - hi - 1/2 (set: not above hi) and of acc - lo + 1/2 (set: below
-// lo): one vector instruction and two.
+// lo): one vector instruction and two.  BITS = 5 leaves a gap of four (undefined) bits behind them.
+template <int BITS>
 __device__ __forceinline__ void decide(uint32_t& pos, uint32_t& neg, float acc, float width)
 {
-    pos = __builtin_amdgcn_alignbit(pos, __float_as_uint(acc), 31);
-    neg = __builtin_amdgcn_alignbit(neg, __float_as_uint(acc + width), 31);
+    pos = __builtin_amdgcn_alignbit(pos, __float_as_uint(acc), 32 - BITS);
+    neg = __builtin_amdgcn_alignbit(neg, __float_as_uint(acc + width), 32 - BITS);
 }
 
-// pos / neg of a 32 x 32 block, lane = voxel l % 32: bit 8 k + j for filter 8 k + 4 g + j, pos inverted as
-// decide() leaves it.  Lanes 0-31 get the voxels' mask words, lanes 32-63 their sign words.
-__device__ __forceinline__ uint32_t block_word(uint32_t pos, uint32_t neg, int g)
+// The decisions of a 32 x 32 block, register v = filter 8 (v / 4) + 4 g + v % 4: widths come four at a
+// time from LDS (for the lane's own half g), highest filter first, so that filter 8 k + 4 g + j ends up at
+// bit 8 k + j.
+__device__ __forceinline__ void decide_block(uint32_t& pos, uint32_t& neg, const v16f& acc, const float* widths)
 {
-    pos ^= 0x0f0f0f0fu;
-    const uint32_t m = (pos | neg) << (4 * g), s = (neg & ~pos) << (4 * g);
+    pos = neg = 0u;
+#pragma unroll
+    for (int k = 3; k >= 0; --k) {
+        const float4 w = *reinterpret_cast<const float4*>(widths + 8 * k);
+        decide<1>(pos, neg, acc[4 * k + 3], w.w);
+        decide<1>(pos, neg, acc[4 * k + 2], w.z);
+        decide<1>(pos, neg, acc[4 * k + 1], w.y);
+        if (k > 0) decide<5>(pos, neg, acc[4 * k], w.x);
+        else decide<1>(pos, neg, acc[4 * k], w.x);
+    }
+}
+
+// pos / neg as decide_block leaves them to packed words, lane = voxel l % 32: lanes 0-31 get the voxels'
+// mask words, lanes 32-63 their sign words (+1 wins where both decisions hold).
+__device__ __forceinline__ uint32_t block_word(uint32_t pos, uint32_t neg)
+{
+    const uint32_t m = __builtin_amdgcn_bitop3_b32(pos, neg, 0x0f0f0f0fu, 0x8a);   // (~pos | neg) & mask
+    const uint32_t s = __builtin_amdgcn_bitop3_b32(pos, neg, 0x0f0f0f0fu, 0x80);   // pos & neg & mask
     const auto sw = __builtin_amdgcn_permlane32_swap(m, s, false, false);
-    return sw[0] | sw[1];
+    return sw[0] | (sw[1] << 4);                                                   // both halves' filters
 }
 
 }  // namespace
