@@ -16,6 +16,7 @@ import torch
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_NAME = "libtern.so"
 _lib = None
+_native = None      # the compiled per-call path (csrc/tern_torch.cpp); False where it is not built
 
 
 class TernError(RuntimeError):
@@ -115,7 +116,26 @@ def lib():
     L.tern_probe_valu.argtypes = [I, I, I, I, P, P]; L.tern_probe_valu.restype = C.c_int
     L.tern_last_launch.argtypes = [C.POINTER(C.c_int32)]; L.tern_last_launch.restype = C.c_int
     _lib = L
+    global _native
+    if os.path.exists(os.path.join(_HERE, "_tern_torch.so")):
+        from . import _tern_torch
+        _native = _tern_torch
+    else:
+        _native = False
     return L
+
+
+def _plain(name: str, what: str, *args):
+    """The compiled path of an entry point: its output, or None where the arguments are not the plain
+    case (the caller's own checks then say what is wrong, or handle it)."""
+    if _native is None:
+        lib()
+    if not _native:
+        return None
+    r = getattr(_native, name)(*args)
+    if r.__class__ is int:
+        _check(r, what)
+    return r
 
 
 # ---- helpers -----------------------------------------------------------------------------------
@@ -200,6 +220,9 @@ def _empty_packed(shape, device) -> torch.Tensor:
 # ---- entry points ------------------------------------------------------------------------------
 def tern_pack(src: torch.Tensor, out: Optional[torch.Tensor] = None) -> torch.Tensor:
     """int8 ternary [N][C][D][H][W] -> packed planes [N][D][H][W][2][ceil(C/32)] (int32 bits)."""
+    done = _plain("pack", "tern_pack", src, out)
+    if done is not None:
+        return done
     _dev(src, torch.int8, "src")
     if src.dim() != 5:
         raise ValueError("src must be [N][C][D][H][W]")
@@ -300,6 +323,11 @@ def tern_conv3d(in_packed: torch.Tensor, c_in: int, w_bank: torch.Tensor, c_out:
     a multiple of 64) and w_bank the bank of tern_digits_weights' output (tern_conv3d_digits).
     mfma="i8" / "f4" (True = "i8"): w_bank is the bank of tern_expand_filters for that kind
     (tern_conv3d_mfma)."""
+    if not digits and not mfma:
+        done = _plain("conv", "tern_conv3d", bool(binary), in_packed, c_in, w_bank, c_out, k, stride, pad, dil,
+                      thr_lo, thr_hi, out)
+        if done is not None:
+            return done
     kind = "i8" if mfma is True else mfma
     if binary and (digits or mfma):
         raise ValueError("binary filters go with neither digits nor mfma")
@@ -397,6 +425,9 @@ def tern_digits_weights(w):
 def tern_threshold_pack(src: torch.Tensor, thr_lo: torch.Tensor, thr_hi: torch.Tensor,
                         out: Optional[torch.Tensor] = None) -> torch.Tensor:
     """int32 or float32 [N][C][D][H][W] -> packed ternary codes (+1 if v > hi[c], -1 if v < lo[c])."""
+    done = _plain("threshold_pack", "tern_threshold_pack", src, thr_lo, thr_hi, out)
+    if done is not None:
+        return done
     if not isinstance(src, torch.Tensor) or src.dtype not in (torch.int32, torch.float32):
         raise TypeError("src must be an int32 or float32 torch tensor")
     _dev(src, src.dtype, "src")
@@ -459,6 +490,10 @@ def tern_fcn_forward(x: torch.Tensor, in_lo: torch.Tensor, in_hi: torch.Tensor,
     calls tern_fcn_forward_static: no workspace, the activations between layers go to the
     library's fixed device array (return_layers then gives views of that array, valid until the
     next such call on this GPU)."""
+    if not return_layers and not static_scratch:
+        done = _plain("fcn", "tern_fcn_forward", x, in_lo, in_hi, layers, workspace, out)
+        if done is not None:
+            return done
     _dev(x, torch.float32, "x")
     if x.dim() != 5:
         raise ValueError("x must be [N][C0][D][H][W]")
@@ -676,6 +711,11 @@ def tern_net_forward(x: torch.Tensor, in_lo: torch.Tensor, in_hi: torch.Tensor, 
     """Float input -> Eq. 6 -> modules with skips -> optional float-weight prediction layer.
     Returns the prediction maps (or None without a head) and, if return_modules, a list of
     (packed module output viewing the workspace, logical dims)."""
+    if not return_modules and head_w is not None:
+        done = _plain("net", "tern_net_forward", x, in_lo, in_hi, mods, head_w, head_b, head_stride, head_pad, head_dil,
+                      workspace, head_out)
+        if done is not None:
+            return done
     _dev(x, torch.float32, "x")
     if x.dim() != 5:
         raise ValueError("x must be [N][C][D][H][W]")

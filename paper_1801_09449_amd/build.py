@@ -1,4 +1,5 @@
-"""Compile the gfx950 library (csrc/*.hip -> paper_1801_09449_amd/libtern.so) with hipcc.
+"""Compile the gfx950 library (csrc/*.hip -> paper_1801_09449_amd/libtern.so) with hipcc, and the
+binding's per-call path (csrc/tern_torch.cpp -> _tern_torch.so, host code only) with g++.
 
 hipcc cross-compiles without a GPU present.  The library is built in-tree so that it travels with
 the source tree; it is not installed anywhere.  Every call recompiles every source (one hipcc
@@ -16,6 +17,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libtern.so")
+NATIVE = os.path.join(HERE, "_tern_torch.so")
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
@@ -41,6 +43,27 @@ def _run(cmd, verbose):
         print(out, flush=True)
 
 
+def _build_native(verbose):
+    """The torch side of the binding, linked against libtern.so beside it."""
+    import sysconfig
+    from torch.utils import cpp_extension
+    tmp = NATIVE + ".tmp.%d" % os.getpid()
+    libs = cpp_extension.library_paths()
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-I", os.path.join(ROOT, "include")]
+    for p in cpp_extension.include_paths() + [sysconfig.get_paths()["include"]]:
+        cmd += ["-isystem", p]
+    cmd += ["-o", tmp, os.path.join(CSRC, "tern_torch.cpp"), "-L", HERE, "-l:libtern.so"]
+    for p in libs:
+        cmd += ["-L", p]
+    cmd += ["-ltorch_python", "-ltorch_cpu", "-ltorch", "-lc10", "-Wl,-rpath,$ORIGIN"]
+    try:
+        _run(cmd, verbose)
+        os.replace(tmp, NATIVE)
+    finally:
+        if os.path.exists(tmp):
+            os.remove(tmp)
+
+
 def build(verbose: bool = False, jobs: int = 0) -> str:
     """Always recompiles (under a minute with a few cores)."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -58,6 +81,7 @@ def build(verbose: bool = False, jobs: int = 0) -> str:
         finally:
             if os.path.exists(tmp):
                 os.remove(tmp)
+        _build_native(verbose)
     finally:
         shutil.rmtree(tmpdir, ignore_errors=True)
     return LIB

@@ -57,6 +57,7 @@ class UNetPlan:
         self.head_b = dev(np.asarray(head_b, np.float32)) if head_b is not None else None
         self._ws = None
         self._chosen: Dict[tuple, List[B.NetModule]] = {}
+        self._need: Dict[tuple, int] = {}          # workspace bytes by input shape
 
     # A pooled module whose folded convolution is at least this many ternary MACs runs through
     # two digits instead (half the word pairs for one more small launch; measured break-even
@@ -77,7 +78,10 @@ class UNetPlan:
         return self._chosen[key]
 
     def workspace(self, x: torch.Tensor) -> torch.Tensor:
-        need = B.tern_net_workspace_bytes(x.shape, self.modules(x.shape))
+        key = tuple(x.shape)
+        need = self._need.get(key)
+        if need is None:
+            need = self._need[key] = B.tern_net_workspace_bytes(x.shape, self.modules(x.shape))
         if self._ws is None or self._ws.numel() < need or self._ws.device != x.device:
             self._ws = torch.empty((need,), dtype=torch.uint8, device=x.device)
         return self._ws

@@ -1,0 +1,121 @@
+"""The binding's compiled per-call path: it gives what the Python path gives, and leaves every call that is
+not plain to it (same errors, nothing launched)."""
+import numpy as np
+import pytest
+import torch
+
+import synth
+
+
+@pytest.fixture
+def B():
+    from paper_1801_09449_amd import binding as B
+    B.lib()
+    assert B._native, "built together with the library"
+    yield B
+    B.lib()
+
+
+def test_host_tensors_and_odd_arguments_are_left_to_the_python_checks(B):
+    n = B._native
+    x = torch.zeros(1, 32, 2, 2, 2, dtype=torch.int8)
+    assert n.pack(x, None) is None and n.pack(3, None) is None and n.pack(None, x) is None
+    assert n.threshold_pack(x.float(), None, None, None) is None
+    assert n.fcn(x, x, x, [], None, None) is None and n.fcn(None, None, None, (), None, None) is None
+    assert n.net(x, x, x, [object()], None, None, 1, 0, 1, None, None) is None
+    assert n.conv(False, x, 32, x, 32, 3, 1, 1, 1, None, None, None) is None
+    with pytest.raises(TypeError):
+        n.conv(x)
+    with pytest.raises(ValueError, match="GPU"):
+        B.tern_pack(x)
+
+
+def both(B, call):
+    """Results (or the exceptions) of the compiled and of the Python path."""
+    got = []
+    keep = B._native
+    for native in (keep, False):
+        B._native = native
+        try:
+            got.append(call())
+        except Exception as e:          # noqa: BLE001 -- compared below
+            got.append((type(e), str(e)))
+        finally:
+            B._native = keep
+    return got
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("fused", [True, False])
+@pytest.mark.parametrize("binary", [True, False])
+def test_convolution_same_results_and_same_errors(B, fused, binary):
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    c = synth.conv_case("native", 2, 40, 33, (5, 6, 7), k=(3, 1, 3), stride=(1, 2, 1), pad=(1, 0, 1), seed=901)
+    a, w = B.tern_pack(dev(c.act)), dev(c.wgt)
+    bank = B.tern_pack_filters_binary(w) if binary else B.tern_pack_filters(w)
+    lo, hi = (dev(c.lo), dev(c.hi)) if fused else (None, None)
+    kw = dict(k=c.k, stride=c.stride, pad=c.pad, dil=1, thr_lo=lo, thr_hi=hi, binary=binary)
+    x, y = both(B, lambda: B.tern_conv3d(a, 40, bank, 33, **kw))
+    assert x.dtype == y.dtype and x.shape == y.shape and torch.equal(x, y)
+    out = torch.empty_like(x)
+    assert B.tern_conv3d(a, 40, bank, 33, out=out, **kw) is out and torch.equal(out, y)
+    lists = dict(kw, k=list(c.k), pad=[1, 0, 1])
+    x, z = both(B, lambda: B.tern_conv3d(a, 40, bank, 33, **lists))
+    assert torch.equal(x, y) and torch.equal(z, y)
+    bad = [dict(in_packed=a.float()), dict(in_packed=a.cpu()), dict(in_packed=a[:, :, :, ::2]), dict(c_in=70),
+           dict(w_bank=bank[:-1]), dict(c_out=65), dict(k=(3, 3, 3)), dict(stride=0), dict(pad=-1), dict(k="3"),
+           dict(k=2 ** 40), dict(out=out[:1]), dict(out=out.float()), dict(thr_lo=torch.zeros(2, dtype=torch.int32).cuda(), thr_hi=None)]
+    for change in bad:
+        args = dict(dict(in_packed=a, c_in=40, w_bank=bank, c_out=33), **kw)
+        args.update(change)
+        p, q = both(B, lambda: B.tern_conv3d(**args))
+        assert isinstance(p, tuple) and p == q, change
+
+
+@pytest.mark.gpu
+def test_packers_and_networks_same_results_and_same_errors(B):
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    src = dev(synth.ternary((2, 33, 3, 4, 5), 0.4, 902, synth.T_ACT))
+    for call in (lambda: B.tern_pack(src), lambda: B.tern_pack(src.transpose(2, 3)), lambda: B.tern_pack(src[0]),
+                 lambda: B.tern_pack(src, torch.empty(3, dtype=torch.int32).cuda()),
+                 lambda: B.tern_threshold_pack(src.float(), torch.full((33,), -0.5).cuda(), torch.full((33,), 0.5).cuda()),
+                 lambda: B.tern_threshold_pack(src.int(), torch.full((33,), -0.5).cuda(), torch.full((33,), 0.5).cuda()),
+                 lambda: B.tern_threshold_pack(src.double(), src, src)):
+        x, y = both(B, call)
+        assert (torch.equal(x, y) if isinstance(x, torch.Tensor) else x == y)
+    f = synth.config2(seed=3, vol=(16, 16, 8), channels=(16, 32, 40), strides=(1, 2, 1))
+    layers = [B.FcnLayer(L["w"].shape[1], L["w"].shape[0], B.tern_pack_filters(dev(L["w"])), dev(L["lo"]), dev(L["hi"]),
+                         L["k"], L["stride"], L["pad"], L["dil"]) for L in f.layers]
+    mods = [B.NetModule(L["w"].shape[0], B.tern_pack_filters(dev(L["w"])), dev(L["lo"]), dev(L["hi"]), k=L["k"],
+                        stride=L["stride"], pad=L["pad"], dil=L["dil"]) for L in f.layers]
+    mods.append(B.NetModule(8, B.tern_pack_filters(dev(synth.ternary((8, 56, 3, 3, 3), 0.5, 904, 2))), dev(np.zeros(8, np.int32)),
+                            dev(np.ones(8, np.int32)), k=3, pad=1, skip_from=0, up=2))
+    x, lo, hi = dev(f.x), dev(f.in_lo), dev(f.in_hi)
+    hw = torch.randn(3, 8, 1, 3, 3, device="cuda", generator=torch.Generator("cuda").manual_seed(5))
+    small = torch.empty(16, dtype=torch.uint8, device="cuda")
+    for call in (lambda: B.tern_fcn_forward(x, lo, hi, layers), lambda: B.tern_fcn_forward(x, lo, hi, tuple(layers)),
+                 lambda: B.tern_fcn_forward(x, lo, hi, layers[1:]), lambda: B.tern_fcn_forward(x, lo, hi, layers, workspace=small),
+                 lambda: B.tern_net_forward(x, lo, hi, mods, hw, hw[:, 0, 0, 0, 0].contiguous()),
+                 lambda: B.tern_net_forward(x, lo, hi, mods, hw, workspace=small), lambda: B.tern_net_forward(x, lo, hi, mods),
+                 lambda: B.tern_net_forward(x, lo, hi, mods[2:], hw)):
+        p, q = both(B, call)
+        assert (torch.equal(p, q) if isinstance(p, torch.Tensor) else p == q)
+
+
+@pytest.mark.gpu
+def test_calls_go_to_the_current_stream(B):
+    src = torch.from_numpy(synth.ternary((1, 64, 8, 8, 8), 0.4, 903, synth.T_ACT)).cuda()
+    want = B.tern_pack(src)
+    s = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(s):
+        g = torch.cuda.CUDAGraph()
+        out = torch.zeros_like(want)
+        torch.cuda.synchronize()
+        with torch.cuda.graph(g, stream=s):      # captured only if it went to this stream
+            B.tern_pack(src, out)
+    for _ in range(3):
+        out.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
