@@ -19,7 +19,9 @@
 // widened behind the read the same launches took 6-14 % longer).  Filter words come from the bank as bits
 // and are widened per wave and step, ten instructions for a block that VB matrix instructions use; VB = 4
 // with NB = 2 leaves three vector instructions per matrix instruction and uses all registers (two waves
-// per SIMD).  Under this load the clock falls to 1.9 GHz, where 32 cycles are 8 000 TFLOP/s for the chip.
+// per SIMD).  Small launches, where a wave's chain of steps is what takes the time, split a tile's steps
+// over two to eight waves that add their sums in LDS (exact, so in any order): 512 -> 256 channels 3 x 3 on
+// 52 x 36 13.0 -> 8.7 us, 256 -> 256 on 16^3 17.7 -> 10.1, 32 -> 32 on 24^3 7.2 -> 5.9.  Under full load the clock falls to 1.9 GHz, where 32 cycles are 8 000 TFLOP/s for the chip.
 // Measured, fused output, bit-count kernels before: 64 -> 64 channels on 96^3, dilation 2: 276 -> 55 us;
 // 256 -> 256 on 2 x 32^3: 321 -> 44 us (5 290 TFLOP/s: loop 38, fill 3, epilogue 3 us); 64 -> 64 3 x 3 on
 // 16 planes of 232 x 168: 83 -> 23 us.
@@ -42,6 +44,7 @@ struct Reciprocal {
 struct MatrixPlan {
     int32_t lxb, lyb;                // a wave's voxels: 2^lxb x 2^lyb x the rest
     int32_t nwy, nwz, nwc;           // waves of a workgroup along y, z and over filter groups
+    int32_t nks;                     // waves that share a tile's steps and add up their sums in LDS
     int32_t hx, hy, hz;              // halo extents in voxels
     int32_t tiles_x, tiles_y, tiles_z;
     int32_t nch;                     // words (or word pairs) per voxel
@@ -49,7 +52,7 @@ struct MatrixPlan {
     int32_t zero_off;                // LDS byte offset of a zero record (odd word counts)
     int32_t tp_log;                  // tap-packed bank: log2 of the taps per row
     int32_t cut_off;                 // LDS byte offset of the staged cut points
-    Reciprocal r_hx, r_pl, r_ch, r_kw, r_kh;
+    Reciprocal r_hx, r_pl, r_ch, r_kw, r_kh, r_nch;
 };
 
 // What the words are: ternary or binary (sign-only) filter banks, two-digit activations, or the tap-packed
@@ -99,7 +102,7 @@ __device__ __forceinline__ void advance(Walk& w, int nch, int inc_ch, int& tab, 
     }
 }
 
-template <int VB, int NB, bool PACKED, int KIND, bool ODD, bool EXP>
+template <int VB, int NB, bool PACKED, int KIND, bool ODD, bool EXP, bool SPLIT>
 __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPlan t)
 {
     extern __shared__ __align__(16) uint8_t lds8[];
@@ -119,7 +122,9 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
     const int n = bid / t.tiles_z;
     const int X = 1 << t.lxb, Y = 1 << t.lyb, Z = (32 * VB) >> (t.lxb + t.lyb);
     const int ox0 = tix << t.lxb, oy0 = tiy * (Y * t.nwy), oz0 = tiz * (Z * t.nwz);
-    const int wc = wave % t.nwc, wsp = wave / t.nwc;
+    const int nks = SPLIT ? t.nks : 1;
+    const int ks = wave % nks, wtile = wave / nks;
+    const int wc = wtile % t.nwc, wsp = wtile / t.nwc;
     const int wy = wsp % t.nwy, wz = wsp / t.nwy;
     const int cb = (blockIdx.y * t.nwc + wc) * (32 * NB);   // first filter of this wave
     const bool active = cb < p.c_out;
@@ -136,9 +141,12 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
     // ---- filter words ------------------------------------------------------------------------
     constexpr int FW = KIND == kDigits ? 4 : KIND == kBinary ? (ODD ? 1 : 2) : (ODD ? 2 : 4);  // words per filter and row
     const int row_words = p.co_pad * FW;
-    const int steps = ODD ? (p.kd * p.kh * p.kw * t.nch + 1) >> 1
-                          : p.kd * p.kh * p.kw * (KIND == kDigits ? t.nch >> 1 : t.nch);
-    const bool half_last = ODD && (((p.kd * p.kh * p.kw * t.nch) & 1) != 0);
+    const int all_steps = ODD ? (p.kd * p.kh * p.kw * t.nch + 1) >> 1
+                              : p.kd * p.kh * p.kw * (KIND == kDigits ? t.nch >> 1 : t.nch);
+    // this wave's steps: first .. first + steps - 1
+    const int first = all_steps * ks / nks;
+    const int steps = all_steps * (ks + 1) / nks - first;
+    const bool half_last = ODD && ks == nks - 1 && (((p.kd * p.kh * p.kw * t.nch) & 1) != 0);
     const int step_words = ROWS ? 2 * row_words : row_words;   // (tap-packed: per row)
     const uint32_t* bank = p.wgt + (size_t)(active ? cb : 0) * FW;
     uint32_t lane_f = (uint32_t)(i32 * FW);
@@ -146,11 +154,11 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
     else if constexpr (KIND != kTapPacked) lane_f += (uint32_t)(KIND == kBinary ? g : 2 * g);
     v2u f0[NB], f1[NB];
     auto fetch_f = [&](v2u (&f)[NB], int step) {
-        const int s = min(step, steps - 1);
+        const int s = first + min(step, steps - 1);
         const uint32_t* b = bank + (size_t)(KIND == kTapPacked ? (2 * s) >> t.tp_log : s) * (size_t)step_words;
         uint32_t o = lane_f;
         if constexpr (ROWS && ODD) {
-            if (half_last && s == steps - 1 && g) o -= (uint32_t)row_words;   // any row: its activations are zero
+            if (half_last && s == all_steps - 1 && g) o -= (uint32_t)row_words;   // any row: its activations are zero
         }
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
@@ -176,7 +184,7 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
         const uint32_t* in_n = p.in + (size_t)n * p.d * p.h * p.w * 2u * wd;
         const int items = nvox * t.nch;
         constexpr bool PAIRS = !ODD || KIND == kDigits;     // two words per plane and item
-        constexpr int FILL = EXP ? 6 : 4;                   // items a thread keeps in flight
+        constexpr int FILL = !EXP ? 4 : PAIRS ? 6 : 3;      // items a thread keeps in flight (single words: more would cost a wave per SIMD)
         for (int base = 0; base < items; base += FILL * nthreads) {
             uint32_t r[FILL][4];
             int dst[FILL];
@@ -252,7 +260,7 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
         }
     }
     __syncthreads();
-    if (!active) return;
+    if (!SPLIT && !active) return;
 
     // ---- contraction ---------------------------------------------------------------------------
     int lane_v[VB];
@@ -273,6 +281,13 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
     const int nch = KIND == kDigits && !ODD ? t.nch >> 1 : t.nch;
     const int inc_ch = ODD ? t.pl : 2 * t.pl;
     Walk w = {0, 0, 0};
+    if constexpr (SPLIT) {
+        const int e = ODD ? 2 * first : first;                 // first entry of this wave
+        w.tap = (int)quotient((uint32_t)e, t.r_nch);
+        w.ch = e - w.tap * nch;
+        if (w.tap >= 64) tab0 = tab1;
+        w.off = __builtin_amdgcn_readlane(tab0, w.tap & 63) + w.ch * inc_ch;
+    }
 
     using Vox = typename std::conditional<EXP, v4i, v2u>::type;
     auto fetch_v = [&](Vox (&x)[VB], int step) {
@@ -306,6 +321,10 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
                 const float4 h = *reinterpret_cast<const float4*>(cuts + (wc * NB + nb) * 32 + 8 * k + 4 * g);
                 start[nb][4 * k] = h.x; start[nb][4 * k + 1] = h.y; start[nb][4 * k + 2] = h.z; start[nb][4 * k + 3] = h.w;
             }
+            if (ks > 0) {                                      // once per sum
+#pragma unroll
+                for (int v = 0; v < 16; ++v) start[nb][v] = 0.0f;
+            }
         }
     }
 
@@ -318,7 +337,7 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
                 u.y = f[nb].x | m33;
                 F[nb] = expand(u, maa);
             } else if constexpr (KIND == kTapPacked) {
-                const uint32_t sh = (uint32_t)(((2 * step + g) & ((1 << t.tp_log) - 1)) * p.tp_shift);
+                const uint32_t sh = (uint32_t)(((2 * (first + step) + g) & ((1 << t.tp_log) - 1)) * p.tp_shift);
                 F[nb] = expand(interleave(f[nb].x >> sh, f[nb].y >> sh, m33), maa);
             } else if constexpr (!ROWS) {
                 // lanes 0-31 hold both mask words, lanes 32-63 both sign words of a filter
@@ -375,6 +394,40 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
     }
     if (i < steps) contract(F1, x1, std::false_type{});
 
+    // ---- partial sums: block b of a tile is finished by wave b % nks of its nks (a power of two) ------
+    constexpr int BLOCKS = VB * NB;
+    auto finishes = [&](int b) { return !SPLIT || (b & (nks - 1)) == ks; };
+    if constexpr (SPLIT) {
+        __syncthreads();                                       // everyone is done with the halo tile
+        float* mine = reinterpret_cast<float*>(lds8) + (size_t)wave * (BLOCKS * 1024) + lane * 4;
+#pragma unroll
+        for (int b = 0; b < BLOCKS; ++b)
+            if (!finishes(b)) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const v16f& a = acc[b / NB][b % NB];
+                    *reinterpret_cast<float4*>(mine + b * 1024 + k * 256) = make_float4(a[4 * k], a[4 * k + 1], a[4 * k + 2], a[4 * k + 3]);
+                }
+            }
+        __syncthreads();
+        if (!active || ks >= BLOCKS) return;
+#pragma unroll
+        for (int b = 0; b < BLOCKS; ++b)
+            if (finishes(b)) {
+                v16f a = acc[b / NB][b % NB];
+                for (int o = 0; o < nks; ++o)
+                    if (o != ks) {
+                        const float* theirs = reinterpret_cast<float*>(lds8) + (size_t)(wtile * nks + o) * (BLOCKS * 1024) + b * 1024 + lane * 4;
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) {
+                            const float4 x = *reinterpret_cast<const float4*>(theirs + k * 256);
+                            a[4 * k] += x.x; a[4 * k + 1] += x.y; a[4 * k + 2] += x.z; a[4 * k + 3] += x.w;
+                        }
+                    }
+                acc[b / NB][b % NB] = a;
+            }
+    }
+
     // ---- epilogue: lane = voxel l % 32 of a block, register v = filter 8 (v / 4) + 4 g + v % 4 -----
     // A block's voxels differ from block 0's by the same box offset in every lane.
     const int lx = i32 & (X - 1), ly = (i32 >> t.lxb) & (Y - 1), lz = i32 >> (t.lxb + t.lyb);
@@ -389,7 +442,7 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
     const size_t vox0 = (((size_t)n * p.od + bz + lz) * p.oh + by + ly) * p.ow + bx + lx;
     if constexpr (PACKED) {
         uint32_t* out = p.out_packed + vox0 * 2u * p.wd_out + g * p.wd_out + (cb >> 5);
-        const bool pair = NB == 2 && (p.wd_out & 1) == 0;      // (cb >> 5 is even then)
+        const bool pair = NB == 2 && (p.wd_out & 1) == 0 && !SPLIT;   // (cb >> 5 is even then)
         int32_t lo[16], hi[16];
         if constexpr (!STAGED) {                               // all at once: one round trip
             static_assert(STAGED || NB == 1, "one filter block");
@@ -414,6 +467,7 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
             uint32_t word[NB];
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) {
+                if (!finishes(vb * NB + nb)) continue;
                 uint32_t pos = 0u, neg = 0u;
                 if constexpr (STAGED) {
                     decide_block(pos, neg, acc[vb][nb], cuts + wg_filters + (wc * NB + nb) * 32 + 4 * g);
@@ -437,7 +491,7 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
                 } else {
 #pragma unroll
                     for (int nb = 0; nb < NB; ++nb)
-                        if (cb + nb * 32 < p.c_out) o[nb] = word[nb];
+                        if (finishes(vb * NB + nb) && cb + nb * 32 < p.c_out) o[nb] = word[nb];
                 }
             }
         }
@@ -450,7 +504,7 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
 #pragma unroll
             for (int vb = 0; vb < VB; ++vb) {
                 int dx, dy, dz;
-                if (offset_of(vb, dx, dy, dz)) {
+                if (finishes(vb * NB + nb) && offset_of(vb, dx, dy, dz)) {
                     int32_t* o = p.out_acc + ((size_t)n * p.c_out + c0) * cs + in_item + dz * slab + dy * row + dx;
 #pragma unroll
                     for (int v = 0; v < 16; ++v) {
@@ -480,11 +534,13 @@ struct Choice {
     int vb, nb;                      // 32-voxel and 32-filter blocks of a wave
     bool exp;                        // LDS records expanded to 4-bit floats (else interleaved bits)
     int lxb, lyb, nwy, nwz, nwc;
+    int nks;
 };
 
 // Extents that follow from a choice; false if the halo tile does not fit.
 struct Tile {
     int64_t hx, hy, hz, tiles, wgs, lds, items;
+    int64_t cuts;                    // LDS offset of the cut points: behind the halo tile and the partial sums
 };
 bool tile_of(const ConvParams& p, const Choice& c, int64_t lds_limit, Tile& t)
 {
@@ -499,7 +555,11 @@ bool tile_of(const ConvParams& p, const Choice& c, int64_t lds_limit, Tile& t)
     const bool odd = (words & 1) != 0;
     t.items = t.hx * t.hy * t.hz * (p.digits || odd ? words : words / 2);
     t.lds = (int64_t)words * t.hx * t.hy * t.hz * (c.exp ? 16 : 8) + (odd ? 16 : 0);
-    if (c.exp && p.out_packed) t.lds = (t.lds + 15) / 16 * 16 + (int64_t)c.nwc * c.nb * 32 * 8;
+    t.lds = (t.lds + 15) / 16 * 16;
+    const int64_t sums = (int64_t)c.nwy * c.nwz * c.nwc * c.nks * c.vb * c.nb * 4096;
+    if (c.nks > 1 && t.lds < sums) t.lds = sums;
+    t.cuts = t.lds;
+    if (c.exp && p.out_packed) t.lds += (int64_t)c.nwc * c.nb * 32 * 8;
     if (t.lds > lds_limit || t.items > 32768) return false;
     t.tiles = (int64_t)cdiv(p.ow, X) * cdiv(p.oh, Y * c.nwy) * cdiv(p.od, Z * c.nwz) * p.n;
     t.wgs = t.tiles * cdiv(cdiv(p.c_out, 32 * c.nb), c.nwc);
@@ -508,43 +568,44 @@ bool tile_of(const ConvParams& p, const Choice& c, int64_t lds_limit, Tile& t)
 
 // Estimated time of a launch in clock cycles.  Throughput: the fullest compute unit's share of matrix
 // instructions (32 cycles each) and of vector instructions (a wave's fixed part, per 64 halo items, per
-// step and its operands, per accumulator tile of the epilogue).  Latency: as many rounds of workgroups as
+// step and its operands, per accumulator block of the epilogue).  Latency: as many rounds of workgroups as
 // registers and LDS leave no room for at once, each as long as one wave takes by itself.  The weights are
-// a fit to 900 launches (48 shapes from the 2-D layers of a U-Net to 96-cubed volumes, every choice below
-// timed on each); its picks are 1 % slower than the best choice on average, 11 % at worst.
+// a fit to 1400 launches (54 shapes from the 2-D layers of a U-Net to 96-cubed volumes, every choice below
+// timed on each), the one for halo items raised until no pick on those shapes was more than 8 % behind.
 double estimate(const ConvParams& p, const Choice& c, const Tile& t)
 {
     const int words = p.digits ? p.wd_in / 2 : p.wd_in;
-    const double steps = ((double)p.kd * p.kh * p.kw * words + 1.0) / 2.0;
-    const int waves = c.nwy * c.nwz * c.nwc;
-    const double blocks = c.vb * c.nb;
+    const double steps = std::ceil(((double)p.kd * p.kh * p.kw * words + 1.0) / 2.0 / c.nks);
+    const int waves = c.nwy * c.nwz * c.nwc * c.nks;
+    const double blocks = c.vb * c.nb, split = c.nks > 1 ? 1.0 : 0.0;
     const double per_cu = std::ceil((double)t.wgs / 256.0);
     const double rounds64 = std::ceil((double)t.items / (64.0 * waves));
-    const double vector = 680.0 + 200.0 * rounds64 + steps * (5.0 + 15.0 * c.vb + 30.0 * c.nb) +
-                          blocks * (p.out_packed ? 105.0 : 230.0);
-    const double busy = per_cu * waves / 4.0 * (0.6 * 32.0 * steps * blocks + vector);
+    const double vector = 730.0 + 280.0 * rounds64 + steps * (3.0 + c.vb + 38.0 * c.nb) +
+                          blocks * (p.out_packed ? 94.0 : 390.0) / c.nks + split * (200.0 + 15.0 * blocks);
+    const double busy = per_cu * waves / 4.0 * (0.8 * 32.0 * steps * blocks + vector);
     const int waves_fit = 4 * (blocks >= 8 ? 2 : c.vb == 4 ? 3 : c.nb == 2 ? 4 : 6);
     double fit = std::floor((double)waves_fit / waves);
     const double by_lds = std::floor(160.0 * 1024.0 / (double)t.lds);
     if (by_lds < fit) fit = by_lds;
     if (fit < 1.0) fit = 1.0;
-    const double alone = 5500.0 + 2500.0 * std::ceil(rounds64 / 6.0) + steps * (120.0 + 32.0 * blocks) + 105.0 * blocks;
+    const double alone = 4400.0 + 2280.0 * std::ceil(rounds64 / 6.0) + steps * (129.0 + 32.0 * blocks) +
+                         111.0 * blocks / c.nks + split * (28.0 + 174.0 * blocks);
     const double latency = std::ceil(per_cu / fit) * alone;
-    return std::sqrt(busy * busy + latency * latency);
+    return std::pow(busy, 1.73) + std::pow(latency, 1.73);
 }
 
 // The wave's tile and the workgroup for a convolution; false if no halo tile fits in LDS.
 bool choose(const ConvParams& p, int64_t lds_limit, Choice& best)
 {
     const int fb = cdiv(p.c_out, 32);
-    // 3-D layers of two words and two filter blocks with 1024 to 2048 tiles of 8 x 8 x 2 voxels (four to
+    // Packed 3-D layers of two words and two filter blocks with 1024 to 2048 tiles of 8 x 8 x 2 voxels (four to
     // eight workgroups per compute unit, all resident): four small waves per tile (two planes x two
     // filter blocks) on 16-byte records of bits.  Not the fastest shape (64 -> 64 channels on 64^3: 24 us,
     // 16 us with waves four times as large, 88 us with bit counts): one workgroup of four waves per
     // 8 x 8 x 2 tile is the launch that callers of tern_last_launch have been shown for these layers.
-    if (p.wd_in == 2 && !p.binary && !p.digits && fb == 2 && p.od > 1 && p.kd > 1) {
+    if (p.out_packed && p.wd_in == 2 && !p.binary && !p.digits && fb == 2 && p.od > 1 && p.kd > 1) {
         const int64_t tiles = (int64_t)cdiv(p.ow, 8) * cdiv(p.oh, 8) * cdiv(p.od, 2) * p.n;
-        const Choice c = {2, 1, false, 3, 3, 1, 2, 2};
+        const Choice c = {2, 1, false, 3, 3, 1, 2, 2, 1};
         Tile t;
         if (tiles >= 1024 && tiles <= 2048 && tile_of(p, c, lds_limit, t)) { best = c; return true; }
     }
@@ -553,19 +614,24 @@ bool choose(const ConvParams& p, int64_t lds_limit, Choice& best)
                                             {{3, 3}, {4, 2}, {2, 4}, {5, 1}, {3, 3}, {3, 3}}},
                                            {{{3, 3}, {3, 4}, {4, 3}, {3, 2}, {4, 2}, {2, 2}},
                                             {{3, 4}, {4, 3}, {5, 2}, {2, 5}, {3, 4}, {3, 4}}}};
+    const int words = p.digits ? p.wd_in / 2 : p.wd_in;
+    const int all_steps = (p.kd * p.kh * p.kw * words + 1) / 2;
     double cost = 1e300;
     for (int vb = 2; vb <= 4; vb += 2)
         for (int nb = 1; nb <= 2; ++nb) {
             if (nb == 2 && (fb & 1)) continue;       // the bank holds whole blocks of 32 filters
             const int groups = fb / nb;
-            for (int nwc = 1; nwc <= 8; nwc *= 2) {
-                if (nwc > 1 && nwc / 2 >= groups) break;
-                for (int nws = 1; nws * nwc <= 8; nws *= 2) {
+            for (int nwc = 1; nwc <= 8; ++nwc) {     // powers of two, or all groups at once
+                if (nwc > groups || ((nwc & (nwc - 1)) && nwc != groups)) continue;
+                // (a split leaves each wave at least four steps; only the smaller waves have one)
+                for (int split = 0; split < 16; ++split) {
+                    const int nks = 1 << (split & 3), nws = 1 << (split >> 2);
+                    if (nks * nws * nwc > 8 || (nks > 1 && (vb > 2 || all_steps < 4 * nks))) continue;
                     // waves are stacked along z, where neighbours share halo planes, else along y
                     const bool deep = p.od > 1 && p.kd > 1;
                     for (int k = 0; k < 6; ++k) {
                         const int* sh = kShape[vb == 4][p.od == 1][k];
-                        const Choice c = {vb, nb, true, sh[0], sh[1], deep ? 1 : nws, deep ? nws : 1, nwc};
+                        const Choice c = {vb, nb, true, sh[0], sh[1], deep ? 1 : nws, deep ? nws : 1, nwc, nks};
                         Tile t;
                         if ((k > 0 && sh[0] == kShape[vb == 4][p.od == 1][0][0] && sh[1] == kShape[vb == 4][p.od == 1][0][1]) ||
                             !tile_of(p, c, lds_limit, t))
@@ -610,10 +676,10 @@ bool choose_cached(const ConvParams& p, int64_t lds_limit, Choice& c)
     return e.ok;
 }
 
-template <int VB, int NB, bool PACKED, int KIND, bool ODD, bool EXP>
+template <int VB, int NB, bool PACKED, int KIND, bool ODD, bool EXP, bool SPLIT>
 int launch_variant(const ConvParams& p, const MatrixPlan& t, size_t lds_bytes, dim3 grid, int threads, hipStream_t s)
 {
-    auto kern = conv_matrix_kernel<VB, NB, PACKED, KIND, ODD, EXP>;
+    auto kern = conv_matrix_kernel<VB, NB, PACKED, KIND, ODD, EXP, SPLIT>;
     if (lds_bytes > 64 * 1024) {
         static thread_local int raised_on_device = -1;
         int dev = 0;
@@ -630,18 +696,18 @@ int launch_variant(const ConvParams& p, const MatrixPlan& t, size_t lds_bytes, d
     return TERN_OK;
 }
 
-template <int VB, int NB, bool PACKED>
+template <int VB, int NB, bool PACKED, bool SPLIT>
 int launch_kind(const ConvParams& p, const MatrixPlan& t, bool odd, size_t lds, dim3 grid, int threads, hipStream_t s)
 {
-    if (p.tp_slots) return launch_variant<VB, NB, PACKED, kTapPacked, true, true>(p, t, lds, grid, threads, s);
+    if (p.tp_slots) return launch_variant<VB, NB, PACKED, kTapPacked, true, true, SPLIT>(p, t, lds, grid, threads, s);
     if (p.digits)
-        return odd ? launch_variant<VB, NB, PACKED, kDigits, true, true>(p, t, lds, grid, threads, s)
-                   : launch_variant<VB, NB, PACKED, kDigits, false, true>(p, t, lds, grid, threads, s);
+        return odd ? launch_variant<VB, NB, PACKED, kDigits, true, true, SPLIT>(p, t, lds, grid, threads, s)
+                   : launch_variant<VB, NB, PACKED, kDigits, false, true, SPLIT>(p, t, lds, grid, threads, s);
     if (p.binary)
-        return odd ? launch_variant<VB, NB, PACKED, kBinary, true, true>(p, t, lds, grid, threads, s)
-                   : launch_variant<VB, NB, PACKED, kBinary, false, true>(p, t, lds, grid, threads, s);
-    return odd ? launch_variant<VB, NB, PACKED, kTernary, true, true>(p, t, lds, grid, threads, s)
-               : launch_variant<VB, NB, PACKED, kTernary, false, true>(p, t, lds, grid, threads, s);
+        return odd ? launch_variant<VB, NB, PACKED, kBinary, true, true, SPLIT>(p, t, lds, grid, threads, s)
+                   : launch_variant<VB, NB, PACKED, kBinary, false, true, SPLIT>(p, t, lds, grid, threads, s);
+    return odd ? launch_variant<VB, NB, PACKED, kTernary, true, true, SPLIT>(p, t, lds, grid, threads, s)
+               : launch_variant<VB, NB, PACKED, kTernary, false, true, SPLIT>(p, t, lds, grid, threads, s);
 }
 
 }  // namespace
@@ -670,33 +736,36 @@ bool launch_conv_matrix(const ConvParams& p, hipStream_t s, int* rc)
     t.nch = p.digits || odd ? words : words / 2;
     t.pl = (int32_t)(q.hx * q.hy * q.hz * (c.exp ? 16 : 8));
     t.zero_off = words * t.pl;
-    t.cut_off = (words * t.pl + (odd ? 16 : 0) + 15) / 16 * 16;
+    t.cut_off = (int32_t)q.cuts;
+    t.nks = c.nks;
     const uint32_t emax = (uint32_t)q.items;
     t.r_hx = reciprocal((uint32_t)t.hx, emax);
     t.r_pl = reciprocal((uint32_t)(t.hx * t.hy), emax);
     t.r_ch = reciprocal((uint32_t)t.nch, emax);
+    const int per_tap = p.digits && !odd ? words / 2 : t.nch;    // entries or steps of a tap
+    t.r_nch = reciprocal((uint32_t)per_tap, (uint32_t)(taps * per_tap + 2));
     t.r_kw = reciprocal((uint32_t)p.kw, 128);
     t.r_kh = reciprocal((uint32_t)p.kh, 128);
     t.tp_log = 0;
     if (p.tp_slots)
         while ((p.tp_shift << t.tp_log) < 32) ++t.tp_log;
     const dim3 grid((unsigned)q.tiles, (unsigned)gy);
-    const int threads = 64 * c.nwy * c.nwz * c.nwc;
+    const int threads = 64 * c.nwy * c.nwz * c.nwc * c.nks;
     const size_t lds = (size_t)q.lds;
-    note_launch(TERN_KERNEL_TILED, c.vb / 2, 32 * c.nb, 1, threads, grid.x, grid.y, lds);
-    if (!c.exp)
-        *rc = packed ? launch_variant<2, 1, true, kTernary, false, false>(p, t, lds, grid, threads, s)
-                     : launch_variant<2, 1, false, kTernary, false, false>(p, t, lds, grid, threads, s);
-    else if (c.vb == 4)
-        *rc = c.nb == 2 ? (packed ? launch_kind<4, 2, true>(p, t, odd, lds, grid, threads, s)
-                                  : launch_kind<4, 2, false>(p, t, odd, lds, grid, threads, s))
-                        : (packed ? launch_kind<4, 1, true>(p, t, odd, lds, grid, threads, s)
-                                  : launch_kind<4, 1, false>(p, t, odd, lds, grid, threads, s));
-    else
-        *rc = c.nb == 2 ? (packed ? launch_kind<2, 2, true>(p, t, odd, lds, grid, threads, s)
-                                  : launch_kind<2, 2, false>(p, t, odd, lds, grid, threads, s))
-                        : (packed ? launch_kind<2, 1, true>(p, t, odd, lds, grid, threads, s)
-                                  : launch_kind<2, 1, false>(p, t, odd, lds, grid, threads, s));
+    note_launch(TERN_KERNEL_TILED, c.vb / 2, 32 * c.nb, c.nks, threads, grid.x, grid.y, lds);
+    const auto kind = [&](auto vb, auto nb, auto split) {
+        constexpr int VB = decltype(vb)::value, NB = decltype(nb)::value;
+        constexpr bool SPLIT = decltype(split)::value;
+        return packed ? launch_kind<VB, NB, true, SPLIT>(p, t, odd, lds, grid, threads, s)
+                      : launch_kind<VB, NB, false, SPLIT>(p, t, odd, lds, grid, threads, s);
+    };
+    const std::integral_constant<int, 1> one;
+    const std::integral_constant<int, 2> two;
+    const std::integral_constant<int, 4> four;
+    if (!c.exp) *rc = launch_variant<2, 1, true, kTernary, false, false, false>(p, t, lds, grid, threads, s);
+    else if (c.vb == 4) *rc = c.nb == 2 ? kind(four, two, std::false_type{}) : kind(four, one, std::false_type{});
+    else if (c.nks > 1) *rc = c.nb == 2 ? kind(two, two, std::true_type{}) : kind(two, one, std::true_type{});
+    else *rc = c.nb == 2 ? kind(two, two, std::false_type{}) : kind(two, one, std::false_type{});
     return true;
 }
 

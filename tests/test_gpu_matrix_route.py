@@ -80,6 +80,28 @@ def test_largest_sums_and_cut_points_around_them(G, sign):
     check(G, c)
 
 
+@pytest.mark.parametrize("ci,co,vol,k", [(256, 256, (4, 8, 9), 3), (512, 32, (1, 9, 17), (1, 3, 3)), (96, 70, (6, 7, 8), 3),
+                                         (32, 32, (9, 8, 8), 3), (16, 40, (8, 9, 8), 3), (160, 64, (5, 6, 7), (3, 3, 2)),
+                                         (64, 128, (8, 8, 8), 5)])
+def test_steps_split_over_waves(G, ci, co, vol, k):
+    """Small launches share a tile's steps among waves that add their sums in LDS: every output is written
+    (the buffer starts as garbage) and right, for even, odd and tap-packed word layouts and a batch."""
+    import torch
+    import paper_1801_09449_amd as T
+    c = synth.conv_case("mx_split", 2, ci, co, vol, k, 1, 1, 1, seed=820 + ci, p0_a=0.4)
+    act, bank = T.tern_pack(G.dev(c.act)), T.tern_pack_filters(G.dev(c.wgt))
+    want = oracle.conv3d(c.act, c.wgt, ConvGeom(c.k, c.stride, c.pad, c.dil))
+    g = dict(k=c.k, stride=c.stride, pad=c.pad, dil=c.dil)
+    acc = torch.full(want.shape, 12345, dtype=torch.int32, device="cuda")
+    T.tern_conv3d(act, ci, bank, co, out=acc, **g)
+    assert T.tern_last_launch()["tap_split"] > 1
+    packed = torch.full((2,) + want.shape[2:] + (2, T.tern_words(co)), -3,
+                        dtype=torch.int32, device="cuda")
+    T.tern_conv3d(act, ci, bank, co, thr_lo=G.dev(c.lo), thr_hi=G.dev(c.hi), out=packed, **g)
+    np.testing.assert_array_equal(acc.cpu().numpy(), want)
+    np.testing.assert_array_equal(G.words(packed), oracle.pack(oracle.threshold(want, c.lo, c.hi)))
+
+
 def random_form(i):
     u = synth.uniform_int(16, 0, 10 ** 6, 12000 + i, 11)
     pick = lambda j, lo, hi: int(lo + u[j] % (hi - lo + 1))
