@@ -1,14 +1,15 @@
 #!/usr/bin/env python3
 """Benchmark of the ternary 3D convolution on one MI355X.
 
-One step = one call of the fused ternary convolution (halo staging, masked-Hamming contraction,
-threshold + re-pack epilogue) on BASELINE config[1]: batch 1, C_in = C_out = 64, 64^3 volume, 3^3
+One step = one call of the fused ternary convolution (halo staging, contraction, threshold + re-pack
+epilogue) on BASELINE config[1]: batch 1, C_in = C_out = 64, 64^3 volume, 3^3
 kernel, stride 1, pad 1, seeded synthetic ternary data already resident in HBM and already packed
 (as it is between layers of a network).  Prints ONE JSON line.
 
-Besides the headline the line carries: the roofline of the timed kernel (issued vector
-instructions against the ALU ceiling derived from unit counts and clock, with the rate of the same
-instruction sequence measured in this run beside it), a
+Besides the headline the line carries: the roofline of the timed kernel (matrix-core rate against the
+4-bit peak), the same layer through the bit-count kernel with its issued vector instructions against the
+ALU ceiling derived from unit counts and clock (and the rate of the same instruction sequence measured in
+this run beside it), a
 check of the timed output against the CPU oracle, per-launch statistics, one compact row for each
 of the other BASELINE configurations, and the oracle timed on the host cores.
 """
@@ -35,7 +36,10 @@ SIMDS, CLOCK_HZ = 256 * 4, 2.4e9
 PEAK_LANE_OPS_TERNARY = SIMDS * CLOCK_HZ / 3.0 * 64      # 52.43e12 issued lane-ops/s = 419 TMAC/s
 PEAK_LANE_OPS_BINARY = SIMDS * CLOCK_HZ / 3.0 * 64       # 2 instructions in 6 cycles: the same 3.0
 NOMINAL_LANE_OPS = 256 * 64 * 2.4e9       # 39.32e12: one wave instruction per SIMD every four cycles
-# The kernels issue four vector instructions per 32-bit word pair (32 MACs): and, popcount-
+# Matrix cores: a SIMD finishes a 32 x 32 x 64 product of 4-bit floats (65 536 ternary MACs) in 32
+# cycles, dense.
+PEAK_MATRIX_MACS = SIMDS * CLOCK_HZ * 65536 / 32         # 5.03e15 MAC/s = 10.07 PFLOP/s
+# The bit-count kernels issue four vector instructions per 32-bit word pair (32 MACs): and, popcount-
 # accumulate, three-input bit operation, popcount-accumulate.  Counted from the kernel's code: 94.5 %
 # of the instructions of a config[1] wave are these.
 ISSUED_OPS_PER_MAC = 4.0 / 32.0
@@ -340,7 +344,7 @@ def extras(T, synth, dev, case, act_i8, act, bank, lo, hi, out_acc, out_packed, 
     return ex
 
 
-def config_rows(T, synth, dev, peak_issue):
+def config_rows(T, synth, dev):
     """One compact row per other BASELINE configuration (fused call, HBM-resident packed input)."""
     import numpy as np
     import torch
@@ -350,8 +354,7 @@ def config_rows(T, synth, dev, peak_issue):
         f, a = conv_times(T, dev, c, steps=steps, warmup=3)
         r = {"gmac": round(c.macs / 1e9, 3), "fused_ms": round(f, 5), "int32_out_ms": round(a, 5),
              "TMACs": round(c.macs / (f * 1e-3) / 1e12, 2)}
-        if peak_issue:
-            r["issued_frac_of_alu_peak"] = round(ISSUED_OPS_PER_MAC * c.macs / (f * 1e-3) / peak_issue, 3)
+        r["frac_of_matrix_peak"] = round(c.macs / (f * 1e-3) / PEAK_MATRIX_MACS, 3)
         return r
 
     rows["config0"] = row(synth.config0(), steps=100)
@@ -388,8 +391,9 @@ def config_rows(T, synth, dev, peak_issue):
 
 
 def binary_row(T, synth, dev, probe_rate):
-    """The binary special case (Eq. 8) at config[1]'s shape on inputs without zeros: two issued
-    vector instructions per word pair against the rate of that pair in a register-only loop."""
+    """The binary special case (Eq. 8) at config[1]'s shape on inputs without zeros, by default (matrix
+    cores) and through the bit-count kernel: two issued vector instructions per word pair against the rate
+    of that pair in a register-only loop."""
     import torch
     c = synth.conv_case("cfg1_binary", 1, 64, 64, 64, p0_w=0.0, p0_a=0.0, seed=0, thr_range=(-24, 24))
     a = T.tern_pack(dev(c.act))
@@ -397,8 +401,13 @@ def binary_row(T, synth, dev, probe_rate):
     lo, hi = dev(c.lo), dev(c.hi)
     out = T.tern_conv3d_binary(a, 64, bank, 64, thr_lo=lo, thr_hi=hi)
     ms, _ = timed(lambda: T.tern_conv3d_binary(a, 64, bank, 64, thr_lo=lo, thr_hi=hi, out=out), 100, 5)
+    T.tern_set_option(3, 32)
+    try:
+        ms_bits, _ = timed(lambda: T.tern_conv3d_binary(a, 64, bank, 64, thr_lo=lo, thr_hi=hi, out=out), 100, 5)
+    finally:
+        T.tern_set_option(3, 0)
     peak = probe_rate(10)
-    issued = (2.0 / 32.0) * c.macs / (ms * 1e-3)
+    issued = (2.0 / 32.0) * c.macs / (ms_bits * 1e-3)
     torch.cuda.synchronize()
     # the same kernel on the shapes of config[3] and config[4] (3^3, dilation 1): longer launches
     larger = {}
@@ -410,12 +419,13 @@ def binary_row(T, synth, dev, probe_rate):
         ms_l, _ = timed(lambda: T.tern_conv3d_binary(al, ch, bl, ch, thr_lo=ll, thr_hi=hl, out=ol), 30, 3)
         larger[name] = {"gmac": round(cl.macs / 1e9, 3), "fused_ms": round(ms_l, 5),
                         "TMACs": round(cl.macs / (ms_l * 1e-3) / 1e12, 2),
-                        "issued_frac_of_alu_peak": round((2.0 / 32.0) * cl.macs / (ms_l * 1e-3) / PEAK_LANE_OPS_BINARY, 3)}
+                        "frac_of_matrix_peak": round(cl.macs / (ms_l * 1e-3) / PEAK_MATRIX_MACS, 3)}
         del al, bl, ol
     torch.cuda.empty_cache()
     return {"workload": "tern_conv3d_binary, config[1]'s shape, +-1 weights and activations, fused cut points",
             "gmac": round(c.macs / 1e9, 3), "fused_ms": round(ms, 5), "TMACs": round(c.macs / (ms * 1e-3) / 1e12, 2),
-            "roofline": {"bound": "alu", "achieved": issued / 1e12, "peak": PEAK_LANE_OPS_BINARY / 1e12,
+            "frac_of_matrix_peak": round(c.macs / (ms * 1e-3) / PEAK_MATRIX_MACS, 3),
+            "bit_count_kernel": {"ms": round(ms_bits, 5), "bound": "alu", "achieved": issued / 1e12, "peak": PEAK_LANE_OPS_BINARY / 1e12,
                          "unit": "T lane-op/s", "frac": issued / PEAK_LANE_OPS_BINARY,
                          "basis": "2 issued vector lane-ops per 32 MACs (three-input bit op 2 cycles, popcount-"
                                   "accumulate 4) against 1024 SIMDs x 2.4 GHz x 64 lanes / 3.0 = 839 TMAC/s",
@@ -475,11 +485,19 @@ def main():
 
     ms, wall_ms = timed(step, args.steps, args.warmup)
     settle_ms = timed.last_settle_ms
+    launch_plan = T.tern_last_launch()
+    # the same layer with an override that sends it to the bit-count kernel (32 channels per pass, the
+    # choice it makes for this layer by itself)
+    T.tern_set_option(3, 32)
+    try:
+        ms_bits, _ = timed(step, max(20, min(args.steps, 100)), 5)
+    finally:
+        T.tern_set_option(3, args.co_block)
     singles = per_launch(step, max(10, min(args.steps, 200)))
     macs = case.macs
     tmacs = macs / (ms * 1e-3) / 1e12
-    issued = ISSUED_OPS_PER_MAC * macs / (ms * 1e-3)
-    algorithmic = ALGORITHMIC_OPS_PER_MAC * macs / (ms * 1e-3)
+    issued = ISSUED_OPS_PER_MAC * macs / (ms_bits * 1e-3)
+    algorithmic = ALGORITHMIC_OPS_PER_MAC * macs / (ms_bits * 1e-3)
 
     if args.calib_copy:
         src = torch.empty(256 << 20, dtype=torch.uint8, device="cuda")
@@ -503,14 +521,28 @@ def main():
         "metric": "ternary MAC/s (TMAC/s) + ms per volume; % of int/popcount peak",
         "value": tmacs, "unit": "TMAC/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
         "ms_per_step": ms, "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
-        "dtype": "u32 bit-planes, int32 accumulate", "data": "synthetic",
+        "dtype": "2-bit codes as 4-bit floats, exact integer sums in fp32", "data": "synthetic",
         "config": {"workload": "config[1]: fused ternary conv3d, N=1, C_in=C_out=64, 64^3, k=3^3, "
                                "s=1, p=1, packed in -> packed out", "gmac": macs / 1e9,
                    "wall_ms_per_step": wall_ms, "settle_ms_before_timing": round(settle_ms, 1),
                    "settle_rule": "at least %g ms, then until four bursts of 50 launches agree within 1 %% (at most 400 ms)" % SETTLE_MS},
         "launch_ms": {"mean": ms, "median": statistics.median(singles), "min": min(singles),
                       "single_launches": len(singles)},
+        "launch": launch_plan,
         "roofline": {
+            "bound": "vector instructions around the matrix cores", "achieved": 2.0 * macs / (ms * 1e-3) / 1e12,
+            "peak": 2.0 * PEAK_MATRIX_MACS / 1e12, "unit": "TFLOP/s", "frac": macs / (ms * 1e-3) / PEAK_MATRIX_MACS,
+            "basis": "achieved = 2 x MAC/s (zeros and padded taps counted); peak = 1024 SIMDs x 2.4 GHz x 65536 MACs "
+                     "per 32 cycles (dense 4-bit products; the clock falls to about 1.9 GHz under them)",
+            "traffic": TRAFFIC_BYTES_CFG1,
+            "traffic_basis": "rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE of the bit-count kernel on the same tiles, "
+                             "profiles/conv3d_fused_config1.md (a profiler run, not this run)",
+            "algorithmic_bytes": ALGORITHMIC_BYTES_CFG1,
+            "hbm_GBps": TRAFFIC_BYTES_CFG1 / (ms * 1e-3) / 1e9,
+        },
+        # the paper's scheme on this layer: percent of int/popcount peak
+        "bit_count_kernel": {
+            "ms": ms_bits, "TMACs": macs / (ms_bits * 1e-3) / 1e12,
             "bound": "alu", "achieved": issued / 1e12, "peak": PEAK_LANE_OPS_TERNARY / 1e12, "unit": "T lane-op/s",
             "frac": issued / PEAK_LANE_OPS_TERNARY,
             "basis": "achieved = 4 issued 32-bit vector lane-ops per 32 MACs (and, popcount-accumulate, "
@@ -531,16 +563,11 @@ def main():
                                                 "note": "256 CU x 64 lanes x 2.4 GHz is not a ceiling for integer "
                                                         "ops on vector registers (they retire in two cycles); the "
                                                         "paper's five operations per word pair against it exceed 1"},
-            "traffic": TRAFFIC_BYTES_CFG1,
-            "traffic_basis": "rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE of this kernel, profiles/conv3d_fused_config1.md "
-                             "(a profiler run of the same command, not this run)",
-            "algorithmic_bytes": ALGORITHMIC_BYTES_CFG1,
-            "hbm_GBps": TRAFFIC_BYTES_CFG1 / (ms * 1e-3) / 1e9,
         },
     }
 
     if not args.no_configs:
-        result["configs"] = config_rows(T, synth, dev, PEAK_LANE_OPS_TERNARY)
+        result["configs"] = config_rows(T, synth, dev)
         result["binary_eq8"] = binary_row(T, synth, dev, probe_rate)
 
     if args.extras:
