@@ -7,6 +7,8 @@ pointers plus the current torch stream.  No arithmetic happens here.
 from __future__ import annotations
 
 import ctypes as C
+import functools
+import math
 import os
 from dataclasses import dataclass
 from typing import List, Optional, Sequence, Tuple
@@ -711,11 +713,11 @@ def tern_net_forward(x: torch.Tensor, in_lo: torch.Tensor, in_hi: torch.Tensor, 
     """Float input -> Eq. 6 -> modules with skips -> optional float-weight prediction layer.
     Returns the prediction maps (or None without a head) and, if return_modules, a list of
     (packed module output viewing the workspace, logical dims)."""
-    if not return_modules and head_w is not None:
+    if not return_modules:
         done = _plain("net", "tern_net_forward", x, in_lo, in_hi, mods, head_w, head_b, head_stride, head_pad, head_dil,
                       workspace, head_out)
         if done is not None:
-            return done
+            return None if head_w is None else done
     _dev(x, torch.float32, "x")
     if x.dim() != 5:
         raise ValueError("x must be [N][C][D][H][W]")
@@ -725,6 +727,7 @@ def tern_net_forward(x: torch.Tensor, in_lo: torch.Tensor, in_hi: torch.Tensor, 
     need = int(lib().tern_net_workspace_bytes(_dims(x.shape), arr, len(mods)))
     if need == 0:
         raise TernError(-3, "tern_net_workspace_bytes (invalid module list)")
+    last = _net_sizes(x.shape, in_lo, in_hi, mods)
     if workspace is None:
         workspace = torch.empty((need,), dtype=torch.uint8, device=x.device)
     _dev(workspace, torch.uint8, "workspace")
@@ -741,13 +744,12 @@ def tern_net_forward(x: torch.Tensor, in_lo: torch.Tensor, in_hi: torch.Tensor, 
         hk = _geom(tuple(int(v) for v in head_w.shape[2:]), head_stride, head_pad, head_dil)
         if head_b is not None:
             _dev(head_b, torch.float32, "head_b")
+        ho = _head_sizes(last, head_w, head_b, head_stride, head_pad, head_dil)
         if head_out is None:
-            # extents of the last module, then of the head
-            dims_list = _net_dims(x.shape, mods)
-            ho = tern_conv_out_dims(dims_list[-1], head_c_out, tuple(int(v) for v in head_w.shape[2:]),
-                                    head_stride, head_pad, head_dil)
             head_out = torch.empty(ho, dtype=torch.float32, device=x.device)
         _dev(head_out, torch.float32, "head_out")
+        if head_out.numel() < math.prod(ho):
+            raise ValueError("head_out is too small")
     _check(lib().tern_net_forward(_ptr(x), _dims(x.shape), _ptr(in_lo), _ptr(in_hi), arr, len(mods),
                                   _ptr(head_w) if head_w is not None else None,
                                   _ptr(head_b) if head_b is not None else None, head_c_out, hk,
@@ -768,20 +770,53 @@ def tern_net_forward(x: torch.Tensor, in_lo: torch.Tensor, in_hi: torch.Tensor, 
     return head_out, views
 
 
-def _net_dims(in_shape, mods):
-    """Logical dims of every module's output (host arithmetic mirroring the library's)."""
+def _net_walk(in_shape, mods):
+    """(input channels, logical dims of the output) of every module (host arithmetic mirroring the library's)."""
     out = []
     cur = tuple(int(v) for v in in_shape)
     for m in mods:
         n, c, d, h, w = cur
         d, h, w = d * m.up[0], h * m.up[1], w * m.up[2]
         if m.skip_from >= 0:
-            c += out[m.skip_from][1]
+            c += out[m.skip_from][1][1]
         if max(m.pool) > 1:
             c, d, h, w = 64 * tern_words(c), d // m.pool[0], h // m.pool[1], w // m.pool[2]
         cur = tern_conv_out_dims((n, c, d, h, w), m.c_out, m.k, m.stride, m.pad, m.dil)
-        out.append(cur)
+        out.append((c, cur))
     return out
+
+
+@functools.lru_cache(maxsize=1024)
+def _bank_bytes(c_out, c_in, k):
+    return tern_filter_bank_bytes(c_out, c_in, k)
+
+
+def _net_dims(in_shape, mods):
+    """Logical dims of every module's output."""
+    return [dims for _, dims in _net_walk(in_shape, mods)]
+
+
+def _net_sizes(in_shape, in_lo, in_hi, mods):
+    """Raises where a parameter tensor holds less than the library reads of it (it gets bare pointers; what
+    is larger was always accepted).  Returns the dims of the last module's output."""
+    if in_lo.numel() < in_shape[1] or in_hi.numel() < in_shape[1]:
+        raise ValueError("input cut points must have C entries")
+    walk = _net_walk(in_shape, mods)
+    for i, (m, (c_in, _)) in enumerate(zip(mods, walk)):
+        if m.w_bank.numel() * 4 < _bank_bytes(m.c_out, c_in, m.k):
+            raise ValueError(f"module {i}: w_bank size does not match (c_out, c_in, k)")
+        if m.thr_lo.numel() < m.c_out or m.thr_hi.numel() < m.c_out:
+            raise ValueError(f"module {i}: cut points must have c_out entries")
+    return walk[-1][1]
+
+
+def _head_sizes(last, head_w, head_b, stride, pad, dil):
+    """The same for the prediction layer behind a module output of dims `last`; its output dims."""
+    if head_w.shape[1] != last[1]:
+        raise ValueError(f"head_w must have {last[1]} input channels")
+    if head_b is not None and head_b.numel() < head_w.shape[0]:
+        raise ValueError("head_b must have C_out entries")
+    return tern_conv_out_dims(last, head_w.shape[0], tuple(int(v) for v in head_w.shape[2:]), stride, pad, dil)
 
 
 def tern_count_codes(in_packed: torch.Tensor, c: int):

@@ -4,7 +4,8 @@
 // fourteen modules 80 us more.  Every function here handles the plain case only: plain tensors of the
 // right type, device, layout and size.  For anything else it returns None before anything is launched, and
 // the Python function that called it goes through its own checks, which name what is wrong.
-// Results: the output tensor; None (not the plain case); or an int, the C entry point's negative status.
+// Results: the output tensor (0 from a network without a prediction layer); None (not the plain case); or an
+// int, the C entry point's negative status.
 // Nothing is kept between calls.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
@@ -301,7 +302,7 @@ PyObject* net(PyObject*, PyObject* const* a, Py_ssize_t nargs)
         const at::Tensor& lo = tensor(a[1], at::kFloat);
         const at::Tensor& hi = tensor(a[2], at::kFloat);
         const tern_dims d = dims5(x);
-        if (!PyList_CheckExact(a[3])) throw Other();
+        if (lo.numel() < d.c || hi.numel() < d.c || !PyList_CheckExact(a[3])) throw Other();
         const Py_ssize_t n = PyList_GET_SIZE(a[3]);
         if (n < 1 || n > 1024) throw Other();
         std::vector<tern_module> mods((size_t)n);
@@ -317,9 +318,12 @@ PyObject* net(PyObject*, PyObject* const* a, Py_ssize_t nargs)
             attr_triple(M, g_names.up, m.up); attr_triple(M, g_names.pool, m.pool);
             Ref bank(PyObject_GetAttr(M, g_names.w_bank)), tl(PyObject_GetAttr(M, g_names.thr_lo)),
                 th(PyObject_GetAttr(M, g_names.thr_hi));
-            m.w_bank = (const uint32_t*)tensor(bank.o, at::kInt).data_ptr();
-            m.thr_lo = (const int32_t*)tensor(tl.o, at::kInt).data_ptr();
-            m.thr_hi = (const int32_t*)tensor(th.o, at::kInt).data_ptr();
+            const at::Tensor& b = tensor(bank.o, at::kInt);
+            const at::Tensor& t0 = tensor(tl.o, at::kInt);
+            const at::Tensor& t1 = tensor(th.o, at::kInt);
+            m.w_bank = (const uint32_t*)b.data_ptr();
+            m.thr_lo = (const int32_t*)t0.data_ptr();
+            m.thr_hi = (const int32_t*)t1.data_ptr();
             // extents, as the library walks them
             if (m.skip_from >= i || m.skip_from < -1) throw Other();
             int64_t e[4] = {cur.c, cur.d, cur.h, cur.w};
@@ -335,6 +339,10 @@ PyObject* net(PyObject*, PyObject* const* a, Py_ssize_t nargs)
             const tern_dims in = {cur.n, dim32(e[0]), dim32(e[1]), dim32(e[2]), dim32(e[3])};
             if (tern_conv_out_dims(in, m.c_out, m.g, &cur) != TERN_OK) throw Other();
             outs[(size_t)i] = cur;
+            // the library reads this much of each (larger ones were always accepted)
+            if ((size_t)b.numel() * 4 < tern_filter_bank_bytes(m.c_out, in.c, m.g.k[0], m.g.k[1], m.g.k[2]) ||
+                t0.numel() < m.c_out || t1.numel() < m.c_out)
+                throw Other();
         }
         const size_t need = tern_net_workspace_bytes(d, mods.data(), (int32_t)n);
         if (need == 0) throw Other();
@@ -353,11 +361,20 @@ PyObject* net(PyObject*, PyObject* const* a, Py_ssize_t nargs)
             head_c_out = wd.n;
             g.k[0] = wd.d; g.k[1] = wd.h; g.k[2] = wd.w;
             triple(a[6], g.stride); triple(a[7], g.pad); triple(a[8], g.dil);
-            if (a[5] != Py_None) pb = (const float*)tensor(a[5], at::kFloat).data_ptr();
+            if (wd.c != cur.c) throw Other();
+            if (a[5] != Py_None) {
+                const at::Tensor& bias = tensor(a[5], at::kFloat);
+                if (bias.numel() < head_c_out) throw Other();
+                pb = (const float*)bias.data_ptr();
+            }
             tern_dims o;
             if (tern_conv_out_dims(cur, head_c_out, g, &o) != TERN_OK) throw Other();
-            if (a[10] == Py_None) out = at::empty({o.n, o.c, o.d, o.h, o.w}, x.options());
-            else out = tensor(a[10], at::kFloat);
+            if (a[10] == Py_None) {
+                out = at::empty({o.n, o.c, o.d, o.h, o.w}, x.options());
+            } else {
+                out = tensor(a[10], at::kFloat);
+                if (out.numel() < (int64_t)o.n * o.c * o.d * o.h * o.w) throw Other();
+            }
             pw = (const float*)w.data_ptr();
             po = (float*)out.data_ptr();
         }

@@ -102,6 +102,69 @@ def test_packers_and_networks_same_results_and_same_errors(B):
         assert (torch.equal(p, q) if isinstance(p, torch.Tensor) else p == q)
 
 
+def small_net(B, dev):
+    """Two modules, the second behind pooling, upsampling and a skip, and a prediction layer."""
+    w0, w1 = synth.ternary((40, 2, 3, 3, 3), 0.5, 905, 2), synth.ternary((24, 64 * 3, 1, 3, 3), 0.5, 906, 2)
+    bank = lambda w: B.tern_pack_filters(dev(w)) if dev(w).is_cuda else torch.zeros(B.tern_filter_bank_bytes(w.shape[0], w.shape[1], w.shape[2:]) // 4, dtype=torch.int32)
+    cut = lambda c, v: dev(np.full(c, v, np.int32))
+    class Mod:                          # host stand-in for NetModule, which takes device tensors only
+        def __init__(self, c_out, w_bank, thr_lo, thr_hi, k, stride=(1, 1, 1), pad=(0, 0, 0), dil=(1, 1, 1), skip_from=-1, up=(1, 1, 1), pool=(1, 1, 1)):
+            self.__dict__.update({n: v for n, v in locals().items() if n != "self"})
+    M = B.NetModule if dev(w0).is_cuda else Mod
+    mods = [M(40, bank(w0), cut(40, -1), cut(40, 1), k=(3, 3, 3), pad=(1, 1, 1)),
+            M(24, bank(w1), cut(24, -2), cut(24, 2), k=(1, 3, 3), skip_from=0, up=(1, 1, 1), pool=(1, 2, 2))]
+    g = np.random.default_rng(7)
+    return dict(x=dev(g.standard_normal((2, 2, 3, 10, 12)).astype(np.float32)), in_lo=dev(np.full(2, -0.5, np.float32)),
+                in_hi=dev(np.full(2, 0.5, np.float32)), mods=mods, head_w=dev(g.standard_normal((3, 24, 1, 2, 2)).astype(np.float32)),
+                head_b=dev(np.zeros(3, np.float32)))
+
+
+def undersized(B, net):
+    """Changes to a network's tensors that leave one of them smaller than what the library reads of it."""
+    import copy
+    yield "in_lo", dict(net, in_lo=net["in_lo"][:1]), "C entries"
+    yield "in_hi", dict(net, in_hi=net["in_hi"][:1]), "C entries"
+    for i in (0, 1):
+        for name, match in (("w_bank", "module %d: w_bank" % i), ("thr_lo", "module %d: cut" % i), ("thr_hi", "module %d: cut" % i)):
+            mods = [copy.copy(m) for m in net["mods"]]
+            setattr(mods[i], name, getattr(mods[i], name)[:-1])
+            yield "%s %d" % (name, i), dict(net, mods=mods), match
+    yield "head_b", dict(net, head_b=net["head_b"][:2]), "head_b"
+    yield "head_w", dict(net, head_w=net["head_w"][:, :23].contiguous()), "24 input channels"
+
+
+def test_network_parameters_smaller_than_what_is_read_are_refused_on_the_host(B):
+    """The library gets bare pointers, so the binding compares sizes (here on host tensors, through the
+    function that stands in front of the call)."""
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a))
+
+    def sizes(n):
+        return B._head_sizes(B._net_sizes(n["x"].shape, n["in_lo"], n["in_hi"], n["mods"]), n["head_w"], n["head_b"], 1, 0, 1)
+    net = small_net(B, dev)
+    assert sizes(net) == (2, 3, 3, 2, 3)
+    for name, bad, match in undersized(B, net):
+        with pytest.raises(ValueError, match=match):
+            sizes(bad)
+    large = dict(net, in_lo=torch.zeros(9), head_b=torch.zeros(9))     # as before: more than needed is fine
+    assert sizes(large) == sizes(net)
+
+
+@pytest.mark.gpu
+def test_network_parameters_smaller_than_what_is_read_raise_before_a_launch(B):
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    net = small_net(B, dev)
+    want, other = both(B, lambda: B.tern_net_forward(**net))
+    assert torch.equal(want, other) and want.shape == (2, 3, 3, 2, 3)
+    out = torch.empty(want.numel() + 5, device="cuda")
+    for case in [net, dict(net, head_w=None, head_b=None)]:
+        p, q = both(B, lambda: B.tern_net_forward(**case))
+        assert p is q is None or torch.equal(p, q)
+    assert B.tern_net_forward(**net, head_out=out) is out and torch.equal(out[:want.numel()].view_as(want), want)
+    for name, bad, match in list(undersized(B, net)) + [("head_out", dict(net, head_out=out[:want.numel() - 1]), "head_out")]:
+        p, q = both(B, lambda: B.tern_net_forward(**bad))
+        assert isinstance(p, tuple) and p[0] is ValueError and match in p[1] and p == q, (name, p, q)
+
+
 @pytest.mark.gpu
 def test_calls_go_to_the_current_stream(B):
     src = torch.from_numpy(synth.ternary((1, 64, 8, 8, 8), 0.4, 903, synth.T_ACT)).cuda()
