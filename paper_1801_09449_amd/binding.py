@@ -117,13 +117,19 @@ def lib():
     L.tern_set_option.argtypes = [C.c_int, C.c_int]; L.tern_set_option.restype = C.c_int
     L.tern_probe_valu.argtypes = [I, I, I, I, P, P]; L.tern_probe_valu.restype = C.c_int
     L.tern_last_launch.argtypes = [C.POINTER(C.c_int32)]; L.tern_last_launch.restype = C.c_int
-    _lib = L
+    # An extension that is there has to load (every call fails where it does not, not the first one only);
+    # `_lib` is set last, so that a failure is not taken for a library without it.
     global _native
     if os.path.exists(os.path.join(_HERE, "_tern_torch.so")):
-        from . import _tern_torch
+        try:
+            from . import _tern_torch
+        except ImportError as e:
+            raise ImportError("_tern_torch.so beside the library does not load: build both again with "
+                              "`python -m paper_1801_09449_amd.build`, or remove it") from e
         _native = _tern_torch
     else:
         _native = False
+    _lib = L
     return L
 
 

@@ -30,6 +30,28 @@ def test_host_tensors_and_odd_arguments_are_left_to_the_python_checks(B):
         B.tern_pack(x)
 
 
+def test_an_extension_that_does_not_load_fails_every_call_and_a_missing_one_none(B, tmp_path):
+    """Not the first call only, with every later one silently on the slow path."""
+    import os
+    import shutil
+    import subprocess
+    import sys
+    src = os.path.dirname(B.__file__)
+    pkg = tmp_path / "paper_1801_09449_amd"
+    pkg.mkdir()
+    for f in os.listdir(src):
+        if f.endswith(".py") or f == "libtern.so":
+            shutil.copy(os.path.join(src, f), pkg / f)
+    code = ("import paper_1801_09449_amd as T\n"
+            "for _ in range(3):\n"
+            "    try: print(T.tern_words(33))\n"
+            "    except ImportError as e: print('ImportError', 'build both again' in str(e))\n")
+    run = lambda: subprocess.run([sys.executable, "-c", code], cwd=tmp_path, text=True, capture_output=True, check=True).stdout.split("\n")[:3]
+    assert run() == ["2"] * 3
+    (pkg / "_tern_torch.so").write_bytes(b"of another build")
+    assert run() == ["ImportError True"] * 3
+
+
 def both(B, call):
     """Results (or the exceptions) of the compiled and of the Python path."""
     got = []
