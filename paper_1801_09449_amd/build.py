@@ -10,7 +10,9 @@ import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 import tempfile
+import warnings
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -38,14 +40,37 @@ def _run(cmd, verbose):
     # the host pass warns that it does not know the packed-fp32 target feature: harmless
     out = "\n".join(l for l in res.stdout.splitlines() if "packed-fp32-ops" not in l)
     if res.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + " ".join(cmd) + "\n" + out)
+        raise RuntimeError(cmd[0] + " failed:\n" + " ".join(cmd) + "\n" + out)
     if verbose and out.strip():
         print(out, flush=True)
 
 
+def _native_lacks():
+    """What is not there for compiling the torch side of the binding, or None."""
+    if shutil.which("g++") is None:
+        return "g++"
+    if not os.path.exists(os.path.join(sysconfig.get_paths()["include"], "Python.h")):
+        return "Python.h"
+    try:
+        from torch.utils import cpp_extension
+        paths = cpp_extension.include_paths()
+    except Exception as e:                      # torch itself, or something that its build tools import
+        return "torch (%s)" % e
+    if not any(os.path.exists(os.path.join(p, "torch", "csrc", "autograd", "python_variable.h")) for p in paths):
+        return "torch's headers"
+    return None
+
+
 def _build_native(verbose):
-    """The torch side of the binding, linked against libtern.so beside it."""
-    import sysconfig
+    """The torch side of the binding, linked against libtern.so beside it.  Where its tools are missing there
+    is no such file afterwards (the binding then makes its calls through ctypes); a source that does not
+    compile is an error."""
+    lacks = _native_lacks()
+    if lacks:
+        if os.path.exists(NATIVE):
+            os.remove(NATIVE)                   # of another build
+        warnings.warn("_tern_torch.so is not built, %s is missing: calls take some microseconds more" % lacks)
+        return
     from torch.utils import cpp_extension
     tmp = NATIVE + ".tmp.%d" % os.getpid()
     libs = cpp_extension.library_paths()

@@ -52,6 +52,37 @@ def test_an_extension_that_does_not_load_fails_every_call_and_a_missing_one_none
     assert run() == ["ImportError True"] * 3
 
 
+@pytest.mark.parametrize("missing", ["g++", "Python.h", "torch's headers", None])
+def test_library_builds_without_the_tools_of_the_extension(monkeypatch, tmp_path, missing):
+    """build() compiles the library first; what the extension lacks is a warning, no failure, and no
+    extension of another build stays beside the new library."""
+    from torch.utils import cpp_extension
+    from paper_1801_09449_amd import build
+    ran = []
+
+    def run(cmd, verbose):
+        ran.append(cmd)
+        (tmp_path / cmd[cmd.index("-o") + 1].split("/")[-1]).write_text("built")
+    monkeypatch.setattr(build, "_run", run)
+    monkeypatch.setattr(build, "LIB", str(tmp_path / "libtern.so"))
+    monkeypatch.setattr(build, "NATIVE", str(tmp_path / "_tern_torch.so"))
+    (tmp_path / "_tern_torch.so").write_text("old")
+    if missing == "g++":
+        monkeypatch.setattr(build.shutil, "which", lambda name: None)
+    elif missing == "Python.h":
+        monkeypatch.setattr(build.sysconfig, "get_paths", lambda: {"include": str(tmp_path)})
+    elif missing:
+        monkeypatch.setattr(cpp_extension, "include_paths", lambda: [str(tmp_path)])
+    if missing:
+        with pytest.warns(UserWarning, match=missing.replace("+", "[+]")):
+            assert build.build() == str(tmp_path / "libtern.so")
+    else:
+        build.build()
+    assert (tmp_path / "libtern.so").read_text() == "built"
+    assert (tmp_path / "_tern_torch.so").exists() == (missing is None)
+    assert missing or (tmp_path / "_tern_torch.so").read_text() == "built"
+
+
 def both(B, call):
     """Results (or the exceptions) of the compiled and of the Python path."""
     got = []
