@@ -56,32 +56,40 @@ class UNetPlan:
         self.head_w = dev(np.asarray(head_w, np.float32)) if head_w is not None else None
         self.head_b = dev(np.asarray(head_b, np.float32)) if head_b is not None else None
         self._ws = None
-        self._chosen: Dict[tuple, List[B.NetModule]] = {}
-        self._need: Dict[tuple, int] = {}          # workspace bytes by input shape
+        self._shapes: Dict[tuple, list] = {}       # by input shape: [module list, workspace bytes or None]
 
     # A pooled module whose folded convolution is at least this many ternary MACs runs through
     # two digits instead (half the word pairs for one more small launch; measured break-even
     # between 1 and 3 GMAC on MI355X).
     DIGITS_FROM_MACS = 1.5e9
 
-    def modules(self, in_shape) -> List[B.NetModule]:
-        """The module list for an input of this shape (cached)."""
-        key = tuple(int(v) for v in in_shape)
-        if key not in self._chosen:
+    KEPT_SHAPES = 256                              # a program that sees more starts over: a choice takes 0.1 ms
+
+    def _of_shape(self, in_shape) -> list:
+        key = tuple(in_shape)
+        kept = self._shapes.get(key)
+        if kept is None:
             dims = B._net_dims(key, self.mods)       # same extents either way
             mods = list(self.mods)
             for i, m in self._digit_mods.items():
                 n, _, d, h, w = dims[i]
                 if n * d * h * w * self._macs[i] >= self.DIGITS_FROM_MACS:
                     mods[i] = m
-            self._chosen[key] = mods
-        return self._chosen[key]
+            kept = [mods, None]
+            if len(self._shapes) >= self.KEPT_SHAPES:
+                self._shapes.clear()
+            self._shapes[key] = kept
+        return kept
+
+    def modules(self, in_shape) -> List[B.NetModule]:
+        """The module list for an input of this shape."""
+        return self._of_shape(in_shape)[0]
 
     def workspace(self, x: torch.Tensor) -> torch.Tensor:
-        key = tuple(x.shape)
-        need = self._need.get(key)
-        if need is None:
-            need = self._need[key] = B.tern_net_workspace_bytes(x.shape, self.modules(x.shape))
+        kept = self._of_shape(x.shape)
+        if kept[1] is None:
+            kept[1] = B.tern_net_workspace_bytes(x.shape, kept[0])
+        need = kept[1]
         if self._ws is None or self._ws.numel() < need or self._ws.device != x.device:
             self._ws = torch.empty((need,), dtype=torch.uint8, device=x.device)
         return self._ws

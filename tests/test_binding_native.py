@@ -202,6 +202,21 @@ def test_network_parameters_smaller_than_what_is_read_are_refused_on_the_host(B)
     assert sizes(large) == sizes(net)
 
 
+def test_what_a_unet_plan_keeps_by_input_shape_is_bounded(B, monkeypatch):
+    from paper_1801_09449_amd import unet
+    plan = unet.UNetPlan.__new__(unet.UNetPlan)
+    net = small_net(B, lambda a: torch.from_numpy(np.ascontiguousarray(a)))
+    plan.mods, plan._digit_mods, plan._macs, plan._ws = net["mods"], {}, {}, None
+    plan._shapes, plan._chosen, plan._need = {}, {}, {}
+    monkeypatch.setattr(B, "tern_net_workspace_bytes", lambda shape, mods: 16)
+    held = lambda: sum(len(d) for d in vars(plan).values() if isinstance(d, dict))
+    for i in range(1000):
+        x = torch.empty(1, 2, 3, 8 + i, 8, device="meta")
+        assert plan.workspace(x).numel() == 16 and plan.modules(x.shape) == net["mods"]
+        assert held() <= 256
+    assert held() > 0 and plan.modules(x.shape) is plan.modules((1, 2, 3, 8 + i, 8))
+
+
 @pytest.mark.gpu
 def test_network_parameters_smaller_than_what_is_read_raise_before_a_launch(B):
     dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
