@@ -204,9 +204,11 @@ void launch_steps(const PointParams& p, bool packed, bool binary, int nb, dim3 g
 }  // namespace
 
 // Up to eight words per voxel (the filters of a wave stay in registers) and, with several taps' worth of
-// channels packed into a word (c_in <= 16), never: a single tap has a plain bank.
+// channels packed into a word (c_in <= 16), never: a single tap has a plain bank.  int32 output has a grid
+// layer per batch item: batches beyond the grid's 65535 layers go through the tiled kernel.
 bool conv_point_applies(const ConvParams& p)
 {
+    if (!p.out_packed && p.n > 65535) return false;
     if (p.kd * p.kh * p.kw != 1) return false;
     if (p.sd != 1 || p.sh != 1 || p.sw != 1 || p.pd != 0 || p.ph != 0 || p.pw != 0) return false;
     return p.tp_slots == 0 && p.wd_in <= 8;
@@ -221,7 +223,6 @@ int launch_conv_point(const ConvParams& c, hipStream_t s)
     // packed output: batch items are just more voxels; int32 output keeps them apart (grid.z)
     const int64_t voxels = (int64_t)c.d * c.h * c.w * (packed ? c.n : 1);
     const int gz = packed ? 1 : c.n;
-    if (gz > 65535) return TERN_ESHAPE;
     p.voxels = (int32_t)voxels;                          // at most 2^31 - 1 per tensor
     p.c_out = c.c_out; p.wd_out = c.wd_out; p.co_pad = c.co_pad;
     const int fb = (c.c_out + 31) / 32;

@@ -161,3 +161,16 @@ def test_pointwise_blocks_and_words(G, words, vox):
 def test_pointwise_many_blocks_per_wave(G):
     """More blocks than waves: a wave walks several, the last one fewer and a part of one."""
     check(G, synth.conv_case("px_many", 1, 64, 64, (64, 65, 67), k=1, pad=0, seed=829, p0_a=0.4))
+
+
+@pytest.mark.parametrize("ci", [32, 192])
+def test_pointwise_batches_beyond_the_grid(G, ci):
+    """More batch items than a grid has layers, int32 and packed output, binary and ternary filters."""
+    import torch
+    import paper_1801_09449_amd as T
+    c = synth.conv_case("px_batch", 65539, ci, 3, (1, 1, 2), k=1, pad=0, seed=831, p0_a=0.4)
+    check(G, c)
+    w = np.where(c.wgt < 0, -1, 1).astype(np.int8)
+    got = T.tern_conv3d_binary(T.tern_pack(G.dev(c.act)), ci, T.tern_pack_filters_binary(G.dev(w)), 3, 1, 1, 0, 1)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(got.cpu().numpy(), oracle.conv3d(c.act, w, ConvGeom(c.k, c.stride, c.pad, c.dil)))
