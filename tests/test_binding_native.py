@@ -115,6 +115,12 @@ def test_convolution_same_results_and_same_errors(B, fused, binary):
     lists = dict(kw, k=list(c.k), pad=[1, 0, 1])
     x, z = both(B, lambda: B.tern_conv3d(a, 40, bank, 33, **lists))
     assert torch.equal(x, y) and torch.equal(z, y)
+    # lists and numpy integers stay with the compiled path (to leave it costs more than it saves)
+    for k, ci in ((list(c.k), 40), (np.array(c.k, np.int64).tolist(), np.int64(40)), (tuple(np.int32(v) for v in c.k), 40), (torch.Size(c.k), 40)):
+        got = B._native.conv(binary, a, ci, bank, np.int32(33), k, [1, 2, 1], [1, 0, True], True, lo, hi, None)
+        assert got is not None and torch.equal(got, y)
+    for k in ((3, 1), (3.0, 1, 3), "313", np.array(c.k), None):
+        assert B._native.conv(binary, a, 40, bank, 33, k, 1, 1, 1, lo, hi, None) is None
     bad = [dict(in_packed=a.float()), dict(in_packed=a.cpu()), dict(in_packed=a[:, :, :, ::2]), dict(c_in=70),
            dict(w_bank=bank[:-1]), dict(c_out=65), dict(k=(3, 3, 3)), dict(stride=0), dict(pad=-1), dict(k="3"),
            dict(k=2 ** 40), dict(out=out[:1]), dict(out=out.float()), dict(thr_lo=torch.zeros(2, dtype=torch.int32).cuda(), thr_hi=None)]
@@ -144,6 +150,9 @@ def test_packers_and_networks_same_results_and_same_errors(B):
     mods.append(B.NetModule(8, B.tern_pack_filters(dev(synth.ternary((8, 56, 3, 3, 3), 0.5, 904, 2))), dev(np.zeros(8, np.int32)),
                             dev(np.ones(8, np.int32)), k=3, pad=1, skip_from=0, up=2))
     x, lo, hi = dev(f.x), dev(f.in_lo), dev(f.in_hi)
+    as_lists = [B.FcnLayer(l.c_in, l.c_out, l.w_bank, l.thr_lo, l.thr_hi, list(l.k), list(l.stride), list(l.pad), list(l.dil)) for l in layers]
+    for form in (tuple(layers), as_lists, tuple(as_lists)):
+        assert torch.equal(B._native.fcn(x, lo, hi, form, None, None), B.tern_fcn_forward(x, lo, hi, layers))
     hw = torch.randn(3, 8, 1, 3, 3, device="cuda", generator=torch.Generator("cuda").manual_seed(5))
     small = torch.empty(16, dtype=torch.uint8, device="cuda")
     for call in (lambda: B.tern_fcn_forward(x, lo, hi, layers), lambda: B.tern_fcn_forward(x, lo, hi, tuple(layers)),
