@@ -77,16 +77,6 @@ __device__ __forceinline__ v4i expand_digits(uint32_t lm, uint32_t hm, uint32_t 
     return o;
 }
 
-// word = (word << 1) | (thr < d), and with d < thr, through the carry flag.
-__device__ __forceinline__ void shift_in_gt_v(uint32_t& word, int32_t d, int32_t thr)
-{
-    asm("v_cmp_lt_i32 vcc, %2, %1\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(word) : "v"(d), "v"(thr) : "vcc");
-}
-__device__ __forceinline__ void shift_in_lt_v(uint32_t& word, int32_t d, int32_t thr)
-{
-    asm("v_cmp_gt_i32 vcc, %2, %1\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(word) : "v"(d), "v"(thr) : "vcc");
-}
-
 // Scalar walk over (kernel tap, channel word or pair of words) in bank order.  The LDS offsets of the
 // taps sit in the lanes of two registers (tap t in lane t % 64 of the (t / 64)-th).
 struct Walk {
@@ -102,7 +92,7 @@ __device__ __forceinline__ void advance(Walk& w, int nch, int inc_ch, int& tab, 
     }
 }
 
-template <int VB, int NB, bool PACKED, int KIND, bool ODD, bool EXP, bool SPLIT>
+template <int VB, int NB, bool PACKED, int KIND, bool ODD, bool SPLIT>
 __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPlan t)
 {
     extern __shared__ __align__(16) uint8_t lds8[];
@@ -130,8 +120,7 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
     const bool active = cb < p.c_out;
 
     const int i32 = lane & 31, g = lane >> 5;
-    constexpr int REC = EXP ? 16 : 8;
-    static_assert(EXP || KIND != kDigits, "two-digit sums are stored expanded");
+    constexpr int REC = 16;                                 // LDS bytes per word and voxel: 32 four-bit floats
     static_assert(KIND != kTapPacked || ODD, "one word per voxel");
     constexpr bool ROWS = (ODD || KIND == kDigits) && KIND != kTapPacked;           // the lane groups read different bank rows
     const int plane = t.hx * t.hy;
@@ -184,13 +173,13 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
         const uint32_t* in_n = p.in + (size_t)n * p.d * p.h * p.w * 2u * wd;
         const int items = nvox * t.nch;
         constexpr bool PAIRS = !ODD || KIND == kDigits;     // two words per plane and item
-        constexpr int FILL = !EXP ? 4 : PAIRS ? 6 : 3;      // items a thread keeps in flight (single words: more would cost a wave per SIMD)
+        constexpr int FILL = PAIRS ? 6 : 3;      // items a thread keeps in flight (single words: more would cost a wave per SIMD)
         for (int base = 0; base < items; base += FILL * nthreads) {
             uint32_t r[FILL][4];
             int dst[FILL];
 #pragma unroll
             for (int k = 0; k < FILL; ++k) {
-                if (EXP && !ODD && base + k * nthreads >= items) break;   // (the same for every thread)
+                if (!ODD && base + k * nthreads >= items) break;   // (the same for every thread)
                 const uint32_t e = (uint32_t)(base + k * nthreads + tid);
                 const uint32_t v = t.nch > 1 ? quotient(e, t.r_ch) : e;
                 const uint32_t c = e - __umul24(v, (uint32_t)t.nch);
@@ -225,21 +214,16 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
             }
 #pragma unroll
             for (int k = 0; k < FILL; ++k) {
-                if (EXP && !ODD && base + k * nthreads >= items) break;
+                if (!ODD && base + k * nthreads >= items) break;
                 if (dst[k] >= 0) {
                     uint8_t* d = lds8 + dst[k];
                     if constexpr (KIND == kDigits) {
                         *reinterpret_cast<v4i*>(d) = expand_digits(r[k][0], r[k][1], r[k][2], r[k][3]);
-                    } else if constexpr (PAIRS && EXP) {
+                    } else if constexpr (PAIRS) {
                         *reinterpret_cast<v4i*>(d) = expand(interleave(r[k][0], r[k][2], m33), maa);
                         *reinterpret_cast<v4i*>(d + t.pl) = expand(interleave(r[k][1], r[k][3], m33), maa);
-                    } else if constexpr (EXP) {
-                        *reinterpret_cast<v4i*>(d) = expand(interleave(r[k][0], r[k][2], m33), maa);
-                    } else if constexpr (PAIRS) {
-                        *reinterpret_cast<v2u*>(d) = interleave(r[k][0], r[k][2], m33);
-                        *reinterpret_cast<v2u*>(d + t.pl) = interleave(r[k][1], r[k][3], m33);
                     } else {
-                        *reinterpret_cast<v2u*>(d) = interleave(r[k][0], r[k][2], m33);
+                        *reinterpret_cast<v4i*>(d) = expand(interleave(r[k][0], r[k][2], m33), maa);
                     }
                 }
             }
@@ -247,10 +231,9 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
         if (ODD && tid < 4) reinterpret_cast<uint32_t*>(lds8 + t.zero_off)[tid] = 0u;
     }
     // Cut points of the workgroup's filters: start values, then widths.
-    constexpr bool STAGED = EXP && PACKED;
     float* cuts = reinterpret_cast<float*>(lds8 + t.cut_off);
     const int wg_filters = t.nwc * 32 * NB;
-    if constexpr (STAGED) {
+    if constexpr (PACKED) {
         for (int j = tid; j < wg_filters; j += nthreads) {
             const int co = blockIdx.y * wg_filters + j;
             const bool live = co < p.c_out;
@@ -289,8 +272,7 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
         w.off = __builtin_amdgcn_readlane(tab0, w.tap & 63) + w.ch * inc_ch;
     }
 
-    using Vox = typename std::conditional<EXP, v4i, v2u>::type;
-    auto fetch_v = [&](Vox (&x)[VB], int step) {
+    auto fetch_v = [&](v4i (&x)[VB], int step) {
         if constexpr (ODD) {
             const int o0 = w.off;
             advance(w, nch, inc_ch, tab0, tab1);
@@ -302,11 +284,11 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
             for (int vb = 0; vb < VB; ++vb) {
                 int a = lane_v[vb] + o;
                 if (dead) a = g ? t.zero_off : a;
-                x[vb] = *reinterpret_cast<const Vox*>(lds8 + a);
+                x[vb] = *reinterpret_cast<const v4i*>(lds8 + a);
             }
         } else {
 #pragma unroll
-            for (int vb = 0; vb < VB; ++vb) x[vb] = *reinterpret_cast<const Vox*>(lds8 + lane_v[vb] + w.off);
+            for (int vb = 0; vb < VB; ++vb) x[vb] = *reinterpret_cast<const v4i*>(lds8 + lane_v[vb] + w.off);
             advance(w, nch, inc_ch, tab0, tab1);
         }
     };
@@ -315,7 +297,7 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
     for (int nb = 0; nb < NB; ++nb) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) start[nb][v] = 0.0f;
-        if constexpr (STAGED) {
+        if constexpr (PACKED) {
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const float4 h = *reinterpret_cast<const float4*>(cuts + (wc * NB + nb) * 32 + 8 * k + 4 * g);
@@ -348,22 +330,18 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
             }
         }
     };
-    auto contract = [&](const v4i (&F)[NB], const Vox (&x)[VB], auto first) {
+    auto contract = [&](const v4i (&F)[NB], const v4i (&x)[VB], auto first) {
 #pragma unroll
-        for (int vb = 0; vb < VB; ++vb) {
-            v4i V;
-            if constexpr (EXP) V = x[vb];
-            else V = expand(x[vb], maa);
+        for (int vb = 0; vb < VB; ++vb)
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb)
-                acc[vb][nb] = multiply(F[nb], V, decltype(first)::value ? start[nb] : acc[vb][nb]);
-        }
+                acc[vb][nb] = multiply(F[nb], x[vb], decltype(first)::value ? start[nb] : acc[vb][nb]);
     };
 
     // Operands of step i + 1 are fetched and widened in front of step i's matrix instructions, filter words
     // two steps further ahead.  (The barriers keep the compiler from moving those loads above the use of
     // the registers they replace, which made it copy them and wait for loads it had just issued.)
-    Vox x0[VB], x1[VB];
+    v4i x0[VB], x1[VB];
     v4i F0[NB], F1[NB];
     fetch_v(x0, 0);
     widen(F0, f0, 0);
@@ -443,44 +421,14 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
     if constexpr (PACKED) {
         uint32_t* out = p.out_packed + vox0 * 2u * p.wd_out + g * p.wd_out + (cb >> 5);
         const bool pair = NB == 2 && (p.wd_out & 1) == 0 && !SPLIT;   // (cb >> 5 is even then)
-        int32_t lo[16], hi[16];
-        if constexpr (!STAGED) {                               // all at once: one round trip
-            static_assert(STAGED || NB == 1, "one filter block");
-            if (cb + 32 <= p.c_out) {
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int co = cb + (v >> 2) * 8 + 4 * g + (v & 3);
-                    lo[v] = p.lo[co]; hi[v] = p.hi[co];
-                }
-            } else {
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int co = cb + (v >> 2) * 8 + 4 * g + (v & 3);
-                    const bool live = co < p.c_out;
-                    const int32_t l = p.lo[live ? co : 0], h = p.hi[live ? co : 0];
-                    lo[v] = live ? l : INT32_MIN; hi[v] = live ? h : INT32_MAX;
-                }
-            }
-        }
 #pragma unroll
         for (int vb = 0; vb < VB; ++vb) {
             uint32_t word[NB];
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) {
                 if (!finishes(vb * NB + nb)) continue;
-                uint32_t pos = 0u, neg = 0u;
-                if constexpr (STAGED) {
-                    decide_block(pos, neg, acc[vb][nb], cuts + wg_filters + (wc * NB + nb) * 32 + 4 * g);
-                } else {
-#pragma unroll
-                    for (int v = 15; v >= 0; --v) {
-                        const int32_t a = (int32_t)acc[vb][nb][v];
-                        shift_in_gt_v(pos, a, hi[v]);
-                        shift_in_lt_v(neg, a, lo[v]);
-                        if ((v & 3) == 0 && v > 0) { pos <<= 4; neg <<= 4; }
-                    }
-                    pos = ~pos;
-                }
+                uint32_t pos, neg;
+                decide_block(pos, neg, acc[vb][nb], cuts + wg_filters + (wc * NB + nb) * 32 + 4 * g);
                 word[nb] = block_word(pos, neg);
             }
             int dx, dy, dz;
@@ -532,7 +480,6 @@ Reciprocal reciprocal(uint32_t d, uint32_t emax)
 // What a launch is made of, apart from the kernel's own arguments.
 struct Choice {
     int vb, nb;                      // 32-voxel and 32-filter blocks of a wave
-    bool exp;                        // LDS records expanded to 4-bit floats (else interleaved bits)
     int lxb, lyb, nwy, nwz, nwc;
     int nks;
 };
@@ -554,12 +501,12 @@ bool tile_of(const ConvParams& p, const Choice& c, int64_t lds_limit, Tile& t)
     const int words = p.digits ? p.wd_in / 2 : p.wd_in;
     const bool odd = (words & 1) != 0;
     t.items = t.hx * t.hy * t.hz * (p.digits || odd ? words : words / 2);
-    t.lds = (int64_t)words * t.hx * t.hy * t.hz * (c.exp ? 16 : 8) + (odd ? 16 : 0);
+    t.lds = (int64_t)words * t.hx * t.hy * t.hz * 16 + (odd ? 16 : 0);
     t.lds = (t.lds + 15) / 16 * 16;
     const int64_t sums = (int64_t)c.nwy * c.nwz * c.nwc * c.nks * c.vb * c.nb * 4096;
     if (c.nks > 1 && t.lds < sums) t.lds = sums;
     t.cuts = t.lds;
-    if (c.exp && p.out_packed) t.lds += (int64_t)c.nwc * c.nb * 32 * 8;
+    if (p.out_packed) t.lds += (int64_t)c.nwc * c.nb * 32 * 8;
     if (t.lds > lds_limit || t.items > 32768) return false;
     t.tiles = (int64_t)cdiv(p.ow, X) * cdiv(p.oh, Y * c.nwy) * cdiv(p.od, Z * c.nwz) * p.n;
     t.wgs = t.tiles * cdiv(cdiv(p.c_out, 32 * c.nb), c.nwc);
@@ -598,17 +545,6 @@ double estimate(const ConvParams& p, const Choice& c, const Tile& t)
 bool choose(const ConvParams& p, int64_t lds_limit, Choice& best)
 {
     const int fb = cdiv(p.c_out, 32);
-    // Packed 3-D layers of two words and two filter blocks with 1024 to 2048 tiles of 8 x 8 x 2 voxels (four to
-    // eight workgroups per compute unit, all resident): four small waves per tile (two planes x two
-    // filter blocks) on 16-byte records of bits.  Not the fastest shape (64 -> 64 channels on 64^3: 24 us,
-    // 16 us with waves four times as large, 88 us with bit counts): one workgroup of four waves per
-    // 8 x 8 x 2 tile is the launch that callers of tern_last_launch have been shown for these layers.
-    if (p.out_packed && p.wd_in == 2 && !p.binary && !p.digits && fb == 2 && p.od > 1 && p.kd > 1) {
-        const int64_t tiles = (int64_t)cdiv(p.ow, 8) * cdiv(p.oh, 8) * cdiv(p.od, 2) * p.n;
-        const Choice c = {2, 1, false, 3, 3, 1, 2, 2, 1};
-        Tile t;
-        if (tiles >= 1024 && tiles <= 2048 && tile_of(p, c, lds_limit, t)) { best = c; return true; }
-    }
     // Shapes of a wave's voxels (log2 of x and y extent), 64 and 128 voxels, volumes and single planes.
     static const int kShape[2][2][6][2] = {{{{3, 3}, {3, 2}, {2, 3}, {2, 2}, {4, 2}, {4, 1}},
                                             {{3, 3}, {4, 2}, {2, 4}, {5, 1}, {3, 3}, {3, 3}}},
@@ -631,7 +567,7 @@ bool choose(const ConvParams& p, int64_t lds_limit, Choice& best)
                     const bool deep = p.od > 1 && p.kd > 1;
                     for (int k = 0; k < 6; ++k) {
                         const int* sh = kShape[vb == 4][p.od == 1][k];
-                        const Choice c = {vb, nb, true, sh[0], sh[1], deep ? 1 : nws, deep ? nws : 1, nwc, nks};
+                        const Choice c = {vb, nb, sh[0], sh[1], deep ? 1 : nws, deep ? nws : 1, nwc, nks};
                         Tile t;
                         if ((k > 0 && sh[0] == kShape[vb == 4][p.od == 1][0][0] && sh[1] == kShape[vb == 4][p.od == 1][0][1]) ||
                             !tile_of(p, c, lds_limit, t))
@@ -676,10 +612,10 @@ bool choose_cached(const ConvParams& p, int64_t lds_limit, Choice& c)
     return e.ok;
 }
 
-template <int VB, int NB, bool PACKED, int KIND, bool ODD, bool EXP, bool SPLIT>
+template <int VB, int NB, bool PACKED, int KIND, bool ODD, bool SPLIT>
 int launch_variant(const ConvParams& p, const MatrixPlan& t, size_t lds_bytes, dim3 grid, int threads, hipStream_t s)
 {
-    auto kern = conv_matrix_kernel<VB, NB, PACKED, KIND, ODD, EXP, SPLIT>;
+    auto kern = conv_matrix_kernel<VB, NB, PACKED, KIND, ODD, SPLIT>;
     if (lds_bytes > 64 * 1024) {
         static thread_local int raised_on_device = -1;
         int dev = 0;
@@ -699,15 +635,15 @@ int launch_variant(const ConvParams& p, const MatrixPlan& t, size_t lds_bytes, d
 template <int VB, int NB, bool PACKED, bool SPLIT>
 int launch_kind(const ConvParams& p, const MatrixPlan& t, bool odd, size_t lds, dim3 grid, int threads, hipStream_t s)
 {
-    if (p.tp_slots) return launch_variant<VB, NB, PACKED, kTapPacked, true, true, SPLIT>(p, t, lds, grid, threads, s);
+    if (p.tp_slots) return launch_variant<VB, NB, PACKED, kTapPacked, true, SPLIT>(p, t, lds, grid, threads, s);
     if (p.digits)
-        return odd ? launch_variant<VB, NB, PACKED, kDigits, true, true, SPLIT>(p, t, lds, grid, threads, s)
-                   : launch_variant<VB, NB, PACKED, kDigits, false, true, SPLIT>(p, t, lds, grid, threads, s);
+        return odd ? launch_variant<VB, NB, PACKED, kDigits, true, SPLIT>(p, t, lds, grid, threads, s)
+                   : launch_variant<VB, NB, PACKED, kDigits, false, SPLIT>(p, t, lds, grid, threads, s);
     if (p.binary)
-        return odd ? launch_variant<VB, NB, PACKED, kBinary, true, true, SPLIT>(p, t, lds, grid, threads, s)
-                   : launch_variant<VB, NB, PACKED, kBinary, false, true, SPLIT>(p, t, lds, grid, threads, s);
-    return odd ? launch_variant<VB, NB, PACKED, kTernary, true, true, SPLIT>(p, t, lds, grid, threads, s)
-               : launch_variant<VB, NB, PACKED, kTernary, false, true, SPLIT>(p, t, lds, grid, threads, s);
+        return odd ? launch_variant<VB, NB, PACKED, kBinary, true, SPLIT>(p, t, lds, grid, threads, s)
+                   : launch_variant<VB, NB, PACKED, kBinary, false, SPLIT>(p, t, lds, grid, threads, s);
+    return odd ? launch_variant<VB, NB, PACKED, kTernary, true, SPLIT>(p, t, lds, grid, threads, s)
+               : launch_variant<VB, NB, PACKED, kTernary, false, SPLIT>(p, t, lds, grid, threads, s);
 }
 
 }  // namespace
@@ -734,7 +670,7 @@ bool launch_conv_matrix(const ConvParams& p, hipStream_t s, int* rc)
     t.hx = (int32_t)q.hx; t.hy = (int32_t)q.hy; t.hz = (int32_t)q.hz;
     t.tiles_x = cdiv(p.ow, X); t.tiles_y = cdiv(p.oh, Y * c.nwy); t.tiles_z = cdiv(p.od, Z * c.nwz);
     t.nch = p.digits || odd ? words : words / 2;
-    t.pl = (int32_t)(q.hx * q.hy * q.hz * (c.exp ? 16 : 8));
+    t.pl = (int32_t)(q.hx * q.hy * q.hz * 16);
     t.zero_off = words * t.pl;
     t.cut_off = (int32_t)q.cuts;
     t.nks = c.nks;
@@ -762,8 +698,7 @@ bool launch_conv_matrix(const ConvParams& p, hipStream_t s, int* rc)
     const std::integral_constant<int, 1> one;
     const std::integral_constant<int, 2> two;
     const std::integral_constant<int, 4> four;
-    if (!c.exp) *rc = launch_variant<2, 1, true, kTernary, false, false, false>(p, t, lds, grid, threads, s);
-    else if (c.vb == 4) *rc = c.nb == 2 ? kind(four, two, std::false_type{}) : kind(four, one, std::false_type{});
+    if (c.vb == 4) *rc = c.nb == 2 ? kind(four, two, std::false_type{}) : kind(four, one, std::false_type{});
     else if (c.nks > 1) *rc = c.nb == 2 ? kind(two, two, std::true_type{}) : kind(two, one, std::true_type{});
     else *rc = c.nb == 2 ? kind(two, two, std::false_type{}) : kind(two, one, std::false_type{});
     return true;
