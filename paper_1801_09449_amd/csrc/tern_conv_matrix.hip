@@ -25,12 +25,10 @@
 // Measured, fused output, bit-count kernels before: 64 -> 64 channels on 96^3, dilation 2: 276 -> 55 us;
 // 256 -> 256 on 2 x 32^3: 321 -> 44 us (5 290 TFLOP/s: loop 38, fill 3, epilogue 3 us); 64 -> 64 3 x 3 on
 // 16 planes of 232 x 168: 83 -> 23 us.
-#include <string.h>
-
-#include <cmath>
 #include <type_traits>
 
 #include "tern_internal.h"
+#include "tern_matrix_choice.h"
 #include "tern_matrix_common.h"
 
 namespace tern {
@@ -465,8 +463,6 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
     }
 }
 
-inline int cdiv(int a, int b) { return (a + b - 1) / b; }
-
 // e / d = (e * m) >> s for 0 <= e < emax <= 2^15: with emax * d <= 2^s the error of m = ceil(2^s / d)
 // stays below 1 / d, and e * m < 2^32.
 Reciprocal reciprocal(uint32_t d, uint32_t emax)
@@ -475,141 +471,6 @@ Reciprocal reciprocal(uint32_t d, uint32_t emax)
     while (((uint64_t)1 << s) < (uint64_t)emax * d) ++s;
     const Reciprocal r = {(uint32_t)((((uint64_t)1 << s) + d - 1) / d), s};
     return r;
-}
-
-// What a launch is made of, apart from the kernel's own arguments.
-struct Choice {
-    int vb, nb;                      // 32-voxel and 32-filter blocks of a wave
-    int lxb, lyb, nwy, nwz, nwc;
-    int nks;
-};
-
-// Extents that follow from a choice; false if the halo tile does not fit.
-struct Tile {
-    int64_t hx, hy, hz, tiles, wgs, lds, items;
-    int64_t cuts;                    // LDS offset of the cut points: behind the halo tile and the partial sums
-};
-bool tile_of(const ConvParams& p, const Choice& c, int64_t lds_limit, Tile& t)
-{
-    const int X = 1 << c.lxb, Y = 1 << c.lyb, Z = (32 * c.vb) >> (c.lxb + c.lyb);
-    if (Z < 1) return false;
-    auto halo = [](int64_t out, int stride, int k, int dil) { return (out - 1) * stride + (int64_t)(k - 1) * dil + 1; };
-    t.hx = halo(X, p.sw, p.kw, p.dw);
-    t.hy = halo((int64_t)Y * c.nwy, p.sh, p.kh, p.dh);
-    t.hz = halo((int64_t)Z * c.nwz, p.sd, p.kd, p.dd);
-    if (t.hx > 20480 || t.hy > 20480 || t.hz > 20480 || t.hx * t.hy * t.hz > 20480) return false;
-    const int words = p.digits ? p.wd_in / 2 : p.wd_in;
-    const bool odd = (words & 1) != 0;
-    t.items = t.hx * t.hy * t.hz * (p.digits || odd ? words : words / 2);
-    t.lds = (int64_t)words * t.hx * t.hy * t.hz * 16 + (odd ? 16 : 0);
-    t.lds = (t.lds + 15) / 16 * 16;
-    const int64_t sums = (int64_t)c.nwy * c.nwz * c.nwc * c.nks * c.vb * c.nb * 4096;
-    if (c.nks > 1 && t.lds < sums) t.lds = sums;
-    t.cuts = t.lds;
-    if (p.out_packed) t.lds += (int64_t)c.nwc * c.nb * 32 * 8;
-    if (t.lds > lds_limit || t.items > 32768) return false;
-    t.tiles = (int64_t)cdiv(p.ow, X) * cdiv(p.oh, Y * c.nwy) * cdiv(p.od, Z * c.nwz) * p.n;
-    t.wgs = t.tiles * cdiv(cdiv(p.c_out, 32 * c.nb), c.nwc);
-    return true;
-}
-
-// Estimated time of a launch in clock cycles.  Throughput: the fullest compute unit's share of matrix
-// instructions (32 cycles each) and of vector instructions (a wave's fixed part, per 64 halo items, per
-// step and its operands, per accumulator block of the epilogue).  Latency: as many rounds of workgroups as
-// registers and LDS leave no room for at once, each as long as one wave takes by itself.  The weights are
-// a fit to 1400 launches (54 shapes from the 2-D layers of a U-Net to 96-cubed volumes, every choice below
-// timed on each), the one for halo items raised until no pick on those shapes was more than 8 % behind.
-double estimate(const ConvParams& p, const Choice& c, const Tile& t)
-{
-    const int words = p.digits ? p.wd_in / 2 : p.wd_in;
-    const double steps = std::ceil(((double)p.kd * p.kh * p.kw * words + 1.0) / 2.0 / c.nks);
-    const int waves = c.nwy * c.nwz * c.nwc * c.nks;
-    const double blocks = c.vb * c.nb, split = c.nks > 1 ? 1.0 : 0.0;
-    const double per_cu = std::ceil((double)t.wgs / 256.0);
-    const double rounds64 = std::ceil((double)t.items / (64.0 * waves));
-    const double vector = 730.0 + 280.0 * rounds64 + steps * (3.0 + c.vb + 38.0 * c.nb) +
-                          blocks * (p.out_packed ? 94.0 : 390.0) / c.nks + split * (200.0 + 15.0 * blocks);
-    const double busy = per_cu * waves / 4.0 * (0.8 * 32.0 * steps * blocks + vector);
-    const int waves_fit = 4 * (blocks >= 8 ? 2 : c.vb == 4 ? 3 : c.nb == 2 ? 4 : 6);
-    double fit = std::floor((double)waves_fit / waves);
-    const double by_lds = std::floor(160.0 * 1024.0 / (double)t.lds);
-    if (by_lds < fit) fit = by_lds;
-    if (fit < 1.0) fit = 1.0;
-    const double alone = 4400.0 + 2280.0 * std::ceil(rounds64 / 6.0) + steps * (129.0 + 32.0 * blocks) +
-                         111.0 * blocks / c.nks + split * (28.0 + 174.0 * blocks);
-    const double latency = std::ceil(per_cu / fit) * alone;
-    return std::pow(busy, 1.73) + std::pow(latency, 1.73);
-}
-
-// The wave's tile and the workgroup for a convolution; false if no halo tile fits in LDS.
-bool choose(const ConvParams& p, int64_t lds_limit, Choice& best)
-{
-    const int fb = cdiv(p.c_out, 32);
-    // Shapes of a wave's voxels (log2 of x and y extent), 64 and 128 voxels, volumes and single planes.
-    static const int kShape[2][2][6][2] = {{{{3, 3}, {3, 2}, {2, 3}, {2, 2}, {4, 2}, {4, 1}},
-                                            {{3, 3}, {4, 2}, {2, 4}, {5, 1}, {3, 3}, {3, 3}}},
-                                           {{{3, 3}, {3, 4}, {4, 3}, {3, 2}, {4, 2}, {2, 2}},
-                                            {{3, 4}, {4, 3}, {5, 2}, {2, 5}, {3, 4}, {3, 4}}}};
-    const int words = p.digits ? p.wd_in / 2 : p.wd_in;
-    const int all_steps = (p.kd * p.kh * p.kw * words + 1) / 2;
-    double cost = 1e300;
-    for (int vb = 2; vb <= 4; vb += 2)
-        for (int nb = 1; nb <= 2; ++nb) {
-            if (nb == 2 && (fb & 1)) continue;       // the bank holds whole blocks of 32 filters
-            const int groups = fb / nb;
-            for (int nwc = 1; nwc <= 8; ++nwc) {     // powers of two, or all groups at once
-                if (nwc > groups || ((nwc & (nwc - 1)) && nwc != groups)) continue;
-                // (a split leaves each wave at least four steps; only the smaller waves have one)
-                for (int split = 0; split < 16; ++split) {
-                    const int nks = 1 << (split & 3), nws = 1 << (split >> 2);
-                    if (nks * nws * nwc > 8 || (nks > 1 && (vb > 2 || all_steps < 4 * nks))) continue;
-                    // waves are stacked along z, where neighbours share halo planes, else along y
-                    const bool deep = p.od > 1 && p.kd > 1;
-                    for (int k = 0; k < 6; ++k) {
-                        const int* sh = kShape[vb == 4][p.od == 1][k];
-                        const Choice c = {vb, nb, sh[0], sh[1], deep ? 1 : nws, deep ? nws : 1, nwc, nks};
-                        Tile t;
-                        if ((k > 0 && sh[0] == kShape[vb == 4][p.od == 1][0][0] && sh[1] == kShape[vb == 4][p.od == 1][0][1]) ||
-                            !tile_of(p, c, lds_limit, t))
-                            continue;
-                        const double e = estimate(p, c, t);
-                        if (e < cost) { cost = e; best = c; }
-                    }
-                }
-            }
-        }
-    return cost < 1e300;
-}
-
-// What a choice depends on.
-struct ChoiceKey {
-    int32_t v[26];
-    bool operator==(const ChoiceKey& o) const { return memcmp(v, o.v, sizeof v) == 0; }
-};
-
-// A choice takes some ten microseconds to make, so each thread keeps its last few by geometry.
-bool choose_cached(const ConvParams& p, int64_t lds_limit, Choice& c)
-{
-    struct Entry {
-        ChoiceKey key;
-        Choice c;
-        bool ok;
-    };
-    constexpr int kEntries = 64;
-    static thread_local Entry table[kEntries];
-    static thread_local int used = 0, next = 0;
-    const ChoiceKey key = {{p.n, p.c_in, p.d, p.h, p.w, p.c_out, p.od, p.oh, p.ow, p.kd, p.kh, p.kw, p.sd, p.sh, p.sw,
-                            p.pd, p.ph, p.pw, p.dd, p.dh, p.dw, p.tp_slots, p.digits, p.binary,
-                            p.out_packed ? 1 : 0, (int32_t)lds_limit}};
-    for (int i = 0; i < used; ++i)
-        if (table[i].key == key) { c = table[i].c; return table[i].ok; }
-    Entry& e = table[next];
-    e.key = key;
-    e.ok = choose(p, lds_limit, e.c);
-    if (used < kEntries) ++used;
-    next = (next + 1) % kEntries;
-    c = e.c;
-    return e.ok;
 }
 
 template <int VB, int NB, bool PACKED, int KIND, bool ODD, bool SPLIT>
@@ -657,11 +518,13 @@ bool launch_conv_matrix(const ConvParams& p, hipStream_t s, int* rc)
     if (taps > 128 || taps * p.c_in * (p.digits ? 2 : 1) > kMatrixSumLimit) return false;
     const int64_t lds_limit = lds_limit_for_current_device();
     if (lds_limit <= 0) { *rc = TERN_EHIP; return true; }
-    Choice c;
-    Tile q;
-    if (!choose_cached(p, lds_limit, c) || !tile_of(p, c, lds_limit, q)) return false;
     const int words = p.digits ? p.wd_in / 2 : p.wd_in;
     const bool odd = (words & 1) != 0, packed = p.out_packed != nullptr;
+    const MatrixShape shape = {p.n, p.c_out, p.od, p.oh, p.ow, p.kd, p.kh, p.kw, p.sd, p.sh, p.sw, p.dd, p.dh, p.dw,
+                               words, p.digits, packed ? 1 : 0, (int32_t)lds_limit};
+    Choice c;
+    Tile q;
+    if (!choose_cached(shape, c) || !tile_of(shape, c, q)) return false;
     const int X = 1 << c.lxb, Y = 1 << c.lyb, Z = (32 * c.vb) >> (c.lxb + c.lyb);
     const int64_t gy = q.wgs / q.tiles;
     if (q.tiles > 0x7fffffff || gy > 65535) return false;

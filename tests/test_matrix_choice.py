@@ -1,0 +1,119 @@
+"""The launch chooser of the tiled matrix kernel (csrc/tern_matrix_choice.h, host code): against a plain search
+over every launch with the estimate written out in ordinary divisions, over random geometries."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_1801_09449_amd", "csrc")
+
+SOURCE = r"""
+#include "tern_matrix_choice.h"
+#include <chrono>
+#include <cstdio>
+#include <random>
+#include <vector>
+using namespace tern;
+
+static double up(double x) { return std::ceil(x); }
+
+static double plain_cost(const MatrixShape& s, const Choice& c, const Tile& t)
+{
+    const double steps = up(((double)s.kd * s.kh * s.kw * s.words + 1.0) / 2.0 / c.nks);
+    const int waves = c.nwy * c.nwz * c.nwc * c.nks, groups = (s.c_out + 31) / 32 / c.nb;
+    const int active = waves / c.nwc * (c.nwc < groups ? c.nwc : groups);
+    const double blocks = c.vb * c.nb, split = c.nks > 1 ? 1.0 : 0.0;
+    const double per_cu = up((double)t.wgs / 256.0), rounds = up((double)t.items / (64.0 * waves));
+    const double vector = 730.0 + 280.0 * rounds + steps * (3.0 + c.vb + 38.0 * c.nb) + blocks * (s.packed ? 94.0 : 390.0) / c.nks +
+                          split * (200.0 + 15.0 * blocks);
+    const double busy = per_cu / 4.0 * (active * (25.6 * steps * blocks + vector) + (waves - active) * (100.0 + 280.0 * rounds));
+    double fit = std::floor(4.0 * (blocks >= 8 ? 2 : c.vb == 4 ? 3 : c.nb == 2 ? 4 : 6) / waves);
+    fit = std::fmax(1.0, std::fmin(fit, std::floor(163840.0 / (double)t.lds)));
+    const double alone = 4400.0 + 2280.0 * up(rounds / 6.0) + steps * (129.0 + 32.0 * blocks) + 111.0 * blocks / c.nks +
+                         split * (28.0 + 174.0 * blocks);
+    return std::pow(busy, 1.73) + std::pow(up(per_cu / fit) * alone, 1.73);
+}
+
+// Every launch in the order that decides between equals.
+static bool search(const MatrixShape& s, Choice& best, double& cost)
+{
+    static const int volume[2][6][2] = {{{3, 3}, {3, 2}, {2, 3}, {2, 2}, {4, 2}, {4, 1}}, {{3, 3}, {3, 4}, {4, 3}, {3, 2}, {4, 2}, {2, 2}}};
+    static const int plane[2][6][2] = {{{3, 3}, {4, 2}, {2, 4}, {5, 1}}, {{3, 4}, {4, 3}, {5, 2}, {2, 5}}};
+    const int fb = (s.c_out + 31) / 32, all_steps = (s.kd * s.kh * s.kw * s.words + 1) / 2;
+    const bool deep = s.od > 1 && s.kd > 1;
+    cost = 1e300;
+    for (int vb = 2; vb <= 4; vb += 2)
+        for (int nb = 1; nb <= 2; ++nb)
+            for (int nwc = 1; nwc <= 8; ++nwc)
+                for (int nws = 1; nws <= 8; nws *= 2)
+                    for (int nks = 1; nks <= 8; nks *= 2)
+                        for (int k = 0; k < (s.od == 1 ? 4 : 6); ++k) {
+                            const int* sh = (s.od == 1 ? plane : volume)[vb == 4][k];
+                            const int groups = fb / nb;
+                            if (nb == 2 && (fb & 1)) continue;
+                            if (nwc > groups || ((nwc & (nwc - 1)) && nwc != groups)) continue;
+                            if (nks * nws * nwc > 8 || (nks > 1 && (vb > 2 || all_steps < 4 * nks))) continue;
+                            const Choice c = {vb, nb, sh[0], sh[1], deep ? 1 : nws, deep ? nws : 1, nwc, nks};
+                            Tile t;
+                            if (!tile_of(s, c, t)) continue;
+                            const double x = plain_cost(s, c, t);
+                            if (x < cost) { cost = x; best = c; }
+                        }
+    return cost < 1e300;
+}
+
+int main()
+{
+    std::mt19937_64 r(1);
+    auto log_int = [&](double a, double b) { return (int)std::lround(std::exp(std::uniform_real_distribution<>(std::log(a), std::log(b))(r))); };
+    auto pick = [&](std::initializer_list<int> l) { return *(l.begin() + r() % l.size()); };
+    std::vector<MatrixShape> all;
+    for (int i = 0; i < 20000; ++i) {
+        MatrixShape s = {pick({1, 1, 2, 4, 16, log_int(1, 100000)}), pick({32, 64, 128, 256, 512, log_int(1, 3000)}), log_int(1, 300), log_int(1, 300),
+                         log_int(1, 300), pick({1, 1, 2, 3, 3, 3, 5}), pick({1, 2, 3, 3, 5}), pick({1, 2, 3, 3, 5}), pick({1, 1, 2}),
+                         pick({1, 1, 2, 4}), pick({1, 1, 2}), pick({1, 1, 2, 3}), pick({1, 1, 2, 3}), pick({1, 1, 2, 3}),
+                         pick({1, 2, 3, 4, 8, log_int(1, 60)}), pick({0, 0, 0, 1}), pick({0, 1}), 160 * 1024};
+        if (r() % 3 == 0) s.od = s.kd = 1;
+        if (r() % 9 == 0) s.lds_limit = 64 * 1024;
+        all.push_back(s);
+    }
+    const auto now = [] { return std::chrono::steady_clock::now(); };
+    std::vector<Choice> a(all.size()), b(all.size());
+    std::vector<double> cost(all.size());
+    std::vector<char> ok(all.size());
+    const auto t0 = now();
+    for (size_t i = 0; i < all.size(); ++i) ok[i] = search(all[i], a[i], cost[i]);
+    const auto t1 = now();
+    long differ = 0, none = 0, kept = 0;
+    for (size_t i = 0; i < all.size(); ++i) differ += choose(all[i], b[i]) != (bool)ok[i];
+    const auto t2 = now();
+    for (size_t i = 0; i < all.size(); ++i) {
+        if (!ok[i]) { ++none; continue; }
+        Tile t;
+        if (!tile_of(all[i], b[i], t) || !(plain_cost(all[i], b[i], t) <= cost[i] * (1 + 1e-12))) ++differ;
+        if (b[i].nwy * b[i].nwz * b[i].nwc * b[i].nks > 8 || t.lds > all[i].lds_limit) ++differ;
+    }
+    for (int round = 0; round < 2; ++round)                 // first made, then found or made again
+        for (size_t i = 0; i < 1500; ++i)
+            for (int twice = 0; twice < 2; ++twice) {
+                Choice c;
+                if (choose_cached(all[i], c) != (bool)ok[i] || (ok[i] && memcmp(&c, &b[i], sizeof c) != 0)) ++kept;
+            }
+    printf("differ %ld kept %ld none %ld of %zu ratio %.3f\n", differ, kept, none, all.size(), (double)(t2 - t1).count() / (t1 - t0).count());
+}
+"""
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_cheap_choice_is_the_choice_of_a_plain_search(tmp_path):
+    """Same estimated time for every geometry (bounds put nothing better aside, no division was rounded wrongly),
+    what is kept is found again, and a choice costs a fraction of the search."""
+    (tmp_path / "t.cpp").write_text(SOURCE)
+    subprocess.run(["g++", "-O3", "-std=c++17", "-I", CSRC, str(tmp_path / "t.cpp"), "-o", str(tmp_path / "t")], check=True)
+    out = subprocess.run([str(tmp_path / "t")], check=True, capture_output=True, text=True).stdout.split()
+    got = dict(zip(out[::2], out[1::2]))
+    print(out)
+    assert got["differ"] == "0" and got["kept"] == "0"
+    assert 0 < int(got["none"]) < 4000
+    assert float(out[out.index("ratio") + 1]) < 0.6
