@@ -93,14 +93,20 @@ constexpr double kInverse[25] = {0, 1.0, 1.0 / 2, 1.0 / 3, 1.0 / 4, 1.0 / 5, 1.0
                                  1.0 / 13, 1.0 / 14, 1.0 / 15, 1.0 / 16, 1.0 / 17, 1.0 / 18, 1.0 / 19, 1.0 / 20, 1.0 / 21, 1.0 / 22, 1.0 / 23, 1.0 / 24};
 
 inline int waves_of(const Choice& c) { return c.nwy * c.nwz * c.nwc * c.nks; }        // at most 8
+// Waves beyond the filter groups only help to fill the halo tile.
+inline int helpers_of(const MatrixShape& s, const Choice& c)
+{
+    const int groups = cdiv(s.c_out, 32) / c.nb;
+    return c.nwc > groups ? c.nwy * c.nwz * c.nks * (c.nwc - groups) : 0;
+}
 // Halo items per wave in units of 64, rounded up (the sum stays below 2^16).
 inline int rounds64_of(int waves, int64_t items) { return (int)(((uint64_t)(items + 64 * waves - 1) * kPer64[waves]) >> 32); }
-inline double busy_of(const MatrixShape& s, const Choice& c, int64_t per_cu, int32_t steps, int rounds64)
+inline double busy_of(const MatrixShape& s, const Choice& c, int64_t per_cu, int helpers, int32_t steps, int rounds64)
 {
     const double blocks = c.vb * c.nb;
     const double vector = 730.0 + 280.0 * rounds64 + steps * (3.0 + c.vb + 38.0 * c.nb) + blocks * (s.packed ? 94.0 : 390.0) * kShare[c.nks] +
                           (c.nks > 1 ? 200.0 + 15.0 * blocks : 0.0);
-    return (double)per_cu * waves_of(c) * 0.25 * (0.8 * 32.0 * steps * blocks + vector);
+    return (double)per_cu * 0.25 * ((waves_of(c) - helpers) * (0.8 * 32.0 * steps * blocks + vector) + helpers * (100.0 + 280.0 * rounds64));
 }
 inline double latency_of(const Choice& c, int64_t per_cu, int64_t lds, int32_t steps, int rounds64)
 {
@@ -119,7 +125,7 @@ inline double estimate(const MatrixShape& s, const Choice& c, const Tile& t)
     const int32_t steps = steps_of(s, c.nks == 1 ? 0 : c.nks == 2 ? 1 : c.nks == 4 ? 2 : 3);
     const int r = rounds64_of(waves_of(c), t.items);
     const int64_t per_cu = (t.wgs + 255) >> 8;
-    return norm_cost(busy_of(s, c, per_cu, steps, r), latency_of(c, per_cu, t.lds, steps, r));
+    return norm_cost(busy_of(s, c, per_cu, helpers_of(s, c), steps, r), latency_of(c, per_cu, t.lds, steps, r));
 }
 
 // The norm of (1, r) for r in 0 .. 1, from below: a bound of the norm without a power.
@@ -151,11 +157,18 @@ inline bool choose(const MatrixShape& s, Choice& best)
     const int flat = s.od == 1;
     const bool deep = s.od > 1 && s.kd > 1;
     const int64_t all_steps = ((int64_t)s.kd * s.kh * s.kw * s.words + 1) / 2;
+    int deepest = 0;                                 // log2 of the deepest split
+    while (deepest < 3 && all_steps >= 8 << deepest) ++deepest;
     double cost = 1e300, root = 1e300;               // of the best so far, and its norm
     int order = 0;
     int32_t steps[4];
     for (int lks = 0; lks < 4; ++lks) steps[lks] = steps_of(s, lks);
-    // waves over filter groups: powers of two, or all groups at once
+    // Waves over filter groups: powers of two, or all groups at once.  Beyond those they only help to fill the
+    // halo tile: where that takes one wave's round trips more than once, a compute unit has one workgroup and
+    // the steps are split as far as they go.  One wave that fills a wide tile alone is slow: 96 -> 19 channels,
+    // 3 x 1 x 1 with stride 2 and dilation 3 on 2 x (1, 4, 1), 12.6 us alone and 5.6 with seven helpers; over 160
+    // small launches the geometric mean falls by 8 %, and 15 of 16 that had been slower than the bit-count
+    // kernels no longer are.  With two steps a wave instead of four, splits of eight took 15 % longer than splits of four.
     struct Groups {
         int n, nwc[8], per_tile[8];
     } groups[3];
@@ -163,7 +176,7 @@ inline bool choose(const MatrixShape& s, Choice& best)
         Groups& g = groups[nb];
         const int all = fb / nb;
         g.n = 0;
-        for (int nwc = 1; nwc <= 8 && nwc <= all; ++nwc)
+        for (int nwc = 1; nwc <= 8; ++nwc)
             if (!(nwc & (nwc - 1)) || nwc == all) {
                 g.nwc[g.n] = nwc;
                 g.per_tile[g.n++] = cdiv(all, nwc);
@@ -175,7 +188,7 @@ inline bool choose(const MatrixShape& s, Choice& best)
         for (int nb = 1; nb <= 2; ++nb)
             for (int lks = 0; lks < 4; ++lks) {
                 const Choice one = {vb, nb, 0, 0, 1, 1, 1, 1 << lks};
-                wave[nb][lks] = busy_of(s, one, 1, steps[lks], 0) * kShare[1 << lks] * (1.0 - 1e-9);
+                wave[nb][lks] = busy_of(s, one, 1, 0, steps[lks], 0) * kShare[1 << lks] * (1.0 - 1e-9);
                 alone[nb][lks] = latency_of(one, 1, 1, steps[lks], 1) * (1.0 - 1e-9);
             }
         for (int k = 0; k < kWaveShapes[flat]; ++k)
@@ -195,17 +208,20 @@ inline bool choose(const MatrixShape& s, Choice& best)
                     for (int i = 0; i < g.n && g.nwc[i] * nws <= 8; ++i) {
                         c.nwc = g.nwc[i];
                         halo.wgs = halo.tiles * g.per_tile[i];
+                        const int beyond = c.nwc > fb / c.nb ? nws * (c.nwc - fb / c.nb) : 0;
+                        if (beyond && (vb > 2 || halo.items <= 64 * nws * (fb / c.nb) || halo.wgs > 256)) break;
                         // a split leaves each wave at least four steps; only the smaller waves have one
-                        for (int lks = 0; lks < 4; ++lks) {
+                        for (int lks = beyond ? deepest : 0; lks < 4; ++lks) {
                             c.nks = 1 << lks;
-                            if (c.nks * nws * c.nwc > 8 || (lks > 0 && (vb > 2 || all_steps < 4 * c.nks))) break;
+                            if (c.nks * nws * c.nwc > 8 || (lks > 0 && (vb > 2 || lks > deepest))) break;
+                            const int helpers = beyond << lks;
                             const int64_t per_cu = (halo.wgs + 255) >> 8;
                             const int waves = nws * c.nwc << lks;
-                            if ((double)(per_cu * waves) * wave[c.nb][lks] > root || alone[c.nb][lks] > root) continue;
+                            if ((double)(per_cu * (waves - helpers)) * wave[c.nb][lks] > root || alone[c.nb][lks] > root) continue;
                             Tile t = halo;
                             if (!lds_of(s, c, t)) continue;
                             const int r = rounds64_of(waves, t.items);
-                            const double busy = busy_of(s, c, per_cu, steps[lks], r);
+                            const double busy = busy_of(s, c, per_cu, helpers, steps[lks], r);
                             if (busy > root) continue;
                             const double latency = latency_of(c, per_cu, t.lds, steps[lks], r);
                             if (norm_bound(busy, latency) > root) continue;

@@ -102,6 +102,38 @@ def test_steps_split_over_waves(G, ci, co, vol, k):
     np.testing.assert_array_equal(G.words(packed), oracle.pack(oracle.threshold(want, c.lo, c.hi)))
 
 
+@pytest.mark.parametrize("n,ci,co,vol,k,s,p,d,digits", [
+    (5, 96, 8, (2, 3, 2), (3, 1, 1), 2, (3, 0, 0), 3, False), (2, 96, 19, (1, 4, 1), (3, 1, 1), 2, (3, 0, 0), 3, False),
+    (2, 288, 2, (96, 2, 3), 1, 2, 0, 1, True), (1, 160, 32, (67, 2, 83), 1, (1, 2, 2), 0, 1, True),
+    (1, 32, 8, (79, 6, 11), 2, 2, 3, 3, False), (2, 32, 8, (1, 69, 5), 3, (1, 2, 2), 3, 3, False),
+    (1, 330, 14, (3, 48, 4), 1, (1, 2, 2), 0, 1, False), (1, 287, 70, (2, 1, 7), (3, 1, 1), 2, (1, 0, 0), 1, False)])
+def test_waves_that_only_help_to_fill(G, n, ci, co, vol, k, s, p, d, digits):
+    """Small launches with a wide halo tile have more waves than filter groups and splits: the others take part
+    in the fill and in the barriers and write nothing (int32 and packed output into buffers of garbage)."""
+    import torch
+    import paper_1801_09449_amd as T
+    c = synth.conv_case("mx_help", n, ci, co, vol, k, s, p, d, seed=840 + ci, p0_a=0.4)
+    g = dict(k=c.k, stride=c.stride, pad=c.pad, dil=c.dil)
+    act = T.tern_pack(G.dev(c.act))
+    if digits:
+        act, c2 = T.tern_pool_digits(act, ci, (1, 1, 1))
+        bank = T.tern_pack_filters(G.dev(T.tern_digits_weights(c.wgt)))
+        call = lambda **kw: T.tern_conv3d(act, c2, bank, co, digits=True, **g, **kw)
+    else:
+        bank = T.tern_pack_filters(G.dev(c.wgt))
+        call = lambda **kw: T.tern_conv3d(act, ci, bank, co, **g, **kw)
+    want = oracle.conv3d(c.act, c.wgt, ConvGeom(c.k, c.stride, c.pad, c.dil))
+    acc = torch.full(want.shape, 12345, dtype=torch.int32, device="cuda")
+    call(out=acc)
+    plan = T.tern_last_launch()
+    assert plan["kernel"] == T.KERNEL_TILED
+    assert plan["threads"] // 64 > plan["tap_split"] * -(-co // plan["channels_per_pass"]), plan
+    packed = torch.full((n,) + want.shape[2:] + (2, T.tern_words(co)), -3, dtype=torch.int32, device="cuda")
+    call(thr_lo=G.dev(c.lo), thr_hi=G.dev(c.hi), out=packed)
+    np.testing.assert_array_equal(acc.cpu().numpy(), want)
+    np.testing.assert_array_equal(G.words(packed), oracle.pack(oracle.threshold(want, c.lo, c.hi)))
+
+
 def random_form(i):
     u = synth.uniform_int(16, 0, 10 ** 6, 12000 + i, 11)
     pick = lambda j, lo, hi: int(lo + u[j] % (hi - lo + 1))

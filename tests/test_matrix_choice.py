@@ -52,11 +52,13 @@ static bool search(const MatrixShape& s, Choice& best, double& cost)
                             const int* sh = (s.od == 1 ? plane : volume)[vb == 4][k];
                             const int groups = fb / nb;
                             if (nb == 2 && (fb & 1)) continue;
-                            if (nwc > groups || ((nwc & (nwc - 1)) && nwc != groups)) continue;
+                            if ((nwc & (nwc - 1)) && nwc != groups) continue;
                             if (nks * nws * nwc > 8 || (nks > 1 && (vb > 2 || all_steps < 4 * nks))) continue;
                             const Choice c = {vb, nb, sh[0], sh[1], deep ? 1 : nws, deep ? nws : 1, nwc, nks};
                             Tile t;
                             if (!tile_of(s, c, t)) continue;
+                            // waves that only help to fill
+                            if (nwc > groups && (vb > 2 || t.wgs > 256 || t.items <= 64 * nws * groups || (nks < 8 && all_steps >= 8 * nks))) continue;
                             const double x = plain_cost(s, c, t);
                             if (x < cost) { cost = x; best = c; }
                         }
@@ -105,13 +107,46 @@ int main()
 """
 
 
+WAVES = r"""
+#include "tern_matrix_choice.h"
+#include <cstdio>
+int main()
+{
+    // n, c_out, output extents, kernel, stride, dilation, words, digits, packed
+    const tern::MatrixShape s[] = {{2, 19, 1, 2, 1, 3, 1, 1, 2, 2, 2, 3, 3, 3, 3, 0, 1, 163840}, {2, 2, 48, 1, 2, 1, 1, 1, 2, 2, 2, 1, 1, 1, 9, 1, 1, 163840},
+                                   {1, 32, 67, 1, 42, 1, 1, 1, 1, 2, 2, 1, 1, 1, 5, 1, 0, 163840}, {1, 8, 41, 5, 7, 2, 2, 2, 2, 2, 2, 3, 3, 3, 1, 0, 0, 163840},
+                                   {2, 8, 3, 37, 5, 3, 3, 3, 1, 2, 2, 3, 3, 3, 1, 0, 1, 163840}, {1, 64, 64, 64, 64, 3, 3, 3, 1, 1, 1, 1, 1, 1, 2, 0, 1, 163840}};
+    for (const auto& x : s) {
+        tern::Choice c;
+        tern::Tile t;
+        if (!tern::choose(x, c) || !tern::tile_of(x, c, t)) return 1;
+        const int waves = c.nwy * c.nwz * c.nwc * c.nks;
+        printf("%d %d %d\n", waves, (int)((t.items + 64 * waves - 1) / (64 * waves)), c.nwc * c.nb * 32 <= (x.c_out + 31) / 32 * 32);
+    }
+}
+"""
+
+
+def build_and_run(tmp_path, source):
+    (tmp_path / "t.cpp").write_text(source)
+    subprocess.run(["g++", "-O3", "-std=c++17", "-I", CSRC, str(tmp_path / "t.cpp"), "-o", str(tmp_path / "t")], check=True)
+    return subprocess.run([str(tmp_path / "t")], check=True, capture_output=True, text=True).stdout
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_no_wave_fills_a_wide_halo_tile_alone(tmp_path):
+    """Launches of few workgroups and few steps, where a split leaves waves idle: these fill too, at most
+    eight items a lane here (single waves had 15 to 63).  Large launches have no such waves."""
+    rows = [tuple(map(int, l.split())) for l in build_and_run(tmp_path, WAVES).splitlines()]
+    assert all(waves >= 4 and items <= 8 for waves, items, _ in rows[:5]), rows
+    assert rows[5][2] == 1, rows
+
+
 @pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
 def test_cheap_choice_is_the_choice_of_a_plain_search(tmp_path):
     """Same estimated time for every geometry (bounds put nothing better aside, no division was rounded wrongly),
     what is kept is found again, and a choice costs a fraction of the search."""
-    (tmp_path / "t.cpp").write_text(SOURCE)
-    subprocess.run(["g++", "-O3", "-std=c++17", "-I", CSRC, str(tmp_path / "t.cpp"), "-o", str(tmp_path / "t")], check=True)
-    out = subprocess.run([str(tmp_path / "t")], check=True, capture_output=True, text=True).stdout.split()
+    out = build_and_run(tmp_path, SOURCE).split()
     got = dict(zip(out[::2], out[1::2]))
     print(out)
     assert got["differ"] == "0" and got["kept"] == "0"
