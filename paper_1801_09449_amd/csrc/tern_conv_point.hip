@@ -83,10 +83,19 @@ __global__ __launch_bounds__(kPointThreads) __attribute__((amdgpu_waves_per_eu(3
             }
         }
     };
+    // Past the end of a wave's run the last block is fetched again, except word by word (three, five and seven
+    // words): there each load touches 32 lines, and short runs spent their time on repeats (7 words -> 256
+    // channels on 14 208 voxels 12.5 -> 6.7 us).  Elsewhere the branch costs more than the loads (1 word -> 256
+    // channels on 196 608 voxels 10.6 us, 12.6 with it; 8 words on 53 350 12.0 and 13.0).
     constexpr int AHEAD = 4;
+    auto fetch_within = [&](v2u (&x)[S], int b) {
+        if constexpr (!ODD || S == 1) fetch(x, max(0, min(b, last)));
+        else if (b <= last) fetch(x, b);
+    };
     v2u x[AHEAD][S];
 #pragma unroll
-    for (int k = 0; k < AHEAD; ++k) fetch(x[k], max(0, min(first + k, last)));
+    for (int k = 0; k < AHEAD; ++k)
+        fetch_within(x[k], first + k);
 
     // ---- filters and cut points ----------------------------------------------------------------
     v4i F[NB][S];
@@ -138,7 +147,7 @@ __global__ __launch_bounds__(kPointThreads) __attribute__((amdgpu_waves_per_eu(3
                 V[s] = expand(interleave(sw[0], sw[1], m33), maa);
             }
         }
-        fetch(x, min(b + AHEAD, last));
+        fetch_within(x, b + AHEAD);
         v16f acc[NB];
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
@@ -228,13 +237,15 @@ int launch_conv_point(const ConvParams& c, hipStream_t s)
     const int fb = (c.c_out + 31) / 32;
     const int64_t blocks = (voxels + 31) / 32;
     // Two filter blocks per wave where they come in pairs, fit the registers (up to four words) and the
-    // launch still has a wave per SIMD; then
-    // as many blocks per wave as leave four waves per SIMD: setting a wave up (filters, cut points) costs
-    // as much as two blocks.
+    // launch still has a wave per SIMD; then as many blocks per wave as leave four waves per SIMD: setting a
+    // wave up (filters, cut points) costs as much as two blocks.  Eight where several groups write int32 from up
+    // to three words: a block's stores take longer than that (32 -> 256 channels on 2 x 26 675 voxels 16.4 us
+    // with four, 12.4; one group of few filters 3.9 and 4.3, eight words -> 128 channels 19.7 and 22.0).
     const int nb = fb % 2 == 0 && c.wd_in <= 4 && blocks * gz * (fb / 2) >= 1024 ? 2 : 1;
     const int groups = fb / nb;
     if (groups > 65535) return TERN_ESHAPE;
-    int64_t per = (blocks * gz * groups + 4095) / 4096;
+    const int64_t waves_wanted = !packed && groups > 1 && c.wd_in <= 3 ? 8192 : 4096;
+    int64_t per = (blocks * gz * groups + waves_wanted - 1) / waves_wanted;
     if (per > 64) per = 64;
     p.blocks_per_wave = (int32_t)per;
     const int64_t waves = (blocks + per - 1) / per;

@@ -195,6 +195,13 @@ def test_pointwise_many_blocks_per_wave(G):
     check(G, synth.conv_case("px_many", 1, 64, 64, (64, 65, 67), k=1, pad=0, seed=829, p0_a=0.4))
 
 
+@pytest.mark.parametrize("ci,co", [(32, 100), (96, 64), (130, 200), (224, 129), (256, 96)])
+@pytest.mark.parametrize("vol", [(1, 41, 99), (19, 50, 53)], ids=["one_or_two_blocks", "several"])
+def test_pointwise_runs_shorter_and_longer_than_the_fetch_is_ahead(G, ci, co, vol):
+    """Waves with fewer blocks than are fetched ahead, and with more and a remainder."""
+    check(G, synth.conv_case("px_runs", 2, ci, co, vol, k=1, pad=0, seed=832 + ci, p0_a=0.4))
+
+
 @pytest.mark.parametrize("ci", [32, 192])
 def test_pointwise_batches_beyond_the_grid(G, ci):
     """More batch items than a grid has layers, int32 and packed output, binary and ternary filters."""
