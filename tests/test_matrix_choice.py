@@ -51,7 +51,7 @@ static bool search(const MatrixShape& s, Choice& best, double& cost)
                         for (int k = 0; k < (s.od == 1 ? 4 : 6); ++k) {
                             const int* sh = (s.od == 1 ? plane : volume)[vb == 4][k];
                             const int groups = fb / nb;
-                            if (nb == 2 && (fb & 1)) continue;
+                            if (nb == 2 && ((fb & 1) || (s.digits && !s.packed && all_steps > 1 && all_steps <= 8))) continue;
                             if ((nwc & (nwc - 1)) && nwc != groups) continue;
                             if (nks * nws * nwc > 8 || (nks > 1 && (vb > 2 || all_steps < 4 * nks))) continue;
                             const Choice c = {vb, nb, sh[0], sh[1], deep ? 1 : nws, deep ? nws : 1, nwc, nks};
@@ -75,7 +75,7 @@ int main()
         MatrixShape s = {pick({1, 1, 2, 4, 16, log_int(1, 100000)}), pick({32, 64, 128, 256, 512, log_int(1, 3000)}), log_int(1, 300), log_int(1, 300),
                          log_int(1, 300), pick({1, 1, 2, 3, 3, 3, 5}), pick({1, 2, 3, 3, 5}), pick({1, 2, 3, 3, 5}), pick({1, 1, 2}),
                          pick({1, 1, 2, 4}), pick({1, 1, 2}), pick({1, 1, 2, 3}), pick({1, 1, 2, 3}), pick({1, 1, 2, 3}),
-                         pick({1, 2, 3, 4, 8, log_int(1, 60)}), pick({0, 0, 0, 1}), pick({0, 1}), 160 * 1024};
+                         pick({1, 2, 3, 4, 8, log_int(1, 60)}), pick({0, 0, 1}), pick({0, 1}), 160 * 1024};
         if (r() % 3 == 0) s.od = s.kd = 1;
         if (r() % 9 == 0) s.lds_limit = 64 * 1024;
         all.push_back(s);
