@@ -168,8 +168,8 @@ inline bool choose(const MatrixShape& s, Choice& best)
     int32_t steps[4];
     for (int lks = 0; lks < 4; ++lks) steps[lks] = steps_of(s, lks);
     // Waves over filter groups: powers of two, or all groups at once.  Beyond those they only help to fill the
-    // halo tile: where that takes one wave's round trips more than once, a compute unit has one workgroup and
-    // the steps are split as far as they go.  One wave that fills a wide tile alone is slow: 96 -> 19 channels,
+    // halo tile: with the smallest waves, where that takes one wave's round trips more than once, a compute unit
+    // has one workgroup and the steps are split as far as they go.  One wave that fills a wide tile alone is slow: 96 -> 19 channels,
     // 3 x 1 x 1 with stride 2 and dilation 3 on 2 x (1, 4, 1), 12.6 us alone and 5.6 with seven helpers; over 160
     // small launches the geometric mean falls by 8 %, and 15 of 16 that had been slower than the bit-count
     // kernels no longer are.  With two steps a wave instead of four, splits of eight took 15 % longer than splits of four.
@@ -213,7 +213,7 @@ inline bool choose(const MatrixShape& s, Choice& best)
                         c.nwc = g.nwc[i];
                         halo.wgs = halo.tiles * g.per_tile[i];
                         const int beyond = c.nwc > fb / c.nb ? nws * (c.nwc - fb / c.nb) : 0;
-                        if (beyond && (vb > 2 || halo.items <= 64 * nws * (fb / c.nb) || halo.wgs > 256)) break;
+                        if (beyond && (vb > 2 || c.nb > 1 || halo.items <= 64 * nws * (fb / c.nb) || halo.wgs > 256)) break;
                         // a split leaves each wave at least four steps; only the smaller waves have one
                         for (int lks = beyond ? deepest : 0; lks < 4; ++lks) {
                             c.nks = 1 << lks;

@@ -58,7 +58,7 @@ static bool search(const MatrixShape& s, Choice& best, double& cost)
                             Tile t;
                             if (!tile_of(s, c, t)) continue;
                             // waves that only help to fill
-                            if (nwc > groups && (vb > 2 || t.wgs > 256 || t.items <= 64 * nws * groups || (nks < 8 && all_steps >= 8 * nks))) continue;
+                            if (nwc > groups && (vb > 2 || nb > 1 || t.wgs > 256 || t.items <= 64 * nws * groups || (nks < 8 && all_steps >= 8 * nks))) continue;
                             const double x = plain_cost(s, c, t);
                             if (x < cost) { cost = x; best = c; }
                         }
