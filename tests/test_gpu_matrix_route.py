@@ -98,8 +98,88 @@ def test_steps_split_over_waves(G, ci, co, vol, k):
     packed = torch.full((2,) + want.shape[2:] + (2, T.tern_words(co)), -3,
                         dtype=torch.int32, device="cuda")
     T.tern_conv3d(act, ci, bank, co, thr_lo=G.dev(c.lo), thr_hi=G.dev(c.hi), out=packed, **g)
+    assert T.tern_last_launch()["tap_split"] > 1
     np.testing.assert_array_equal(acc.cpu().numpy(), want)
     np.testing.assert_array_equal(G.words(packed), oracle.pack(oracle.threshold(want, c.lo, c.hi)))
+
+
+ONE_SIDED = [  # n, c_in, c_out, vol, k, pad: split, tiled in small and in large waves, pointwise with even and odd words
+    (1, 256, 64, (4, 8, 9), 3, 1), (1, 16, 40, (8, 9, 8), 3, 1), (2, 128, 64, (24, 40, 41), 3, 1), (1, 33, 32, (30, 33, 31), 3, 1),
+    (1, 64, 128, (20, 40, 44), 3, 1), (2, 64, 64, (5, 9, 31), 1, 0), (1, 160, 40, (5, 9, 31), 1, 0), (1, 300, 40, (5, 9, 31), 1, 0)]
+
+
+@pytest.mark.parametrize("kind", ["ternary", "binary", "digits"])
+@pytest.mark.parametrize("n,ci,co,vol,k,pad", ONE_SIDED)
+def test_one_cut_point_out_of_reach_and_the_other_among_the_sums(G, kind, n, ci, co, vol, k, pad):
+    """The sums start from the upper cut point, clamped beyond every sum: with that one at the end of its range
+    and the lower one among the sums, codes are right only if no product added to a start of 2^21 loses its
+    last bit (and the other way round)."""
+    import torch
+    import paper_1801_09449_amd as T
+    c = synth.conv_case("mx_one", n, ci, co, vol, k, 1, pad, 1, seed=850 + ci, p0_a=0.4)
+    w = np.where(c.wgt < 0, -1, 1).astype(np.int8) if kind == "binary" else c.wgt
+    act, g = T.tern_pack(G.dev(c.act)), dict(k=c.k, stride=c.stride, pad=c.pad, dil=c.dil)
+    if kind == "binary":
+        call = lambda **kw: T.tern_conv3d(act, ci, T.tern_pack_filters_binary(G.dev(w)), co, binary=True, **g, **kw)
+    elif kind == "digits":
+        pooled, c2 = T.tern_pool_digits(act, ci, (1, 1, 1))
+        call = lambda **kw: T.tern_conv3d(pooled, c2, T.tern_pack_filters(G.dev(T.tern_digits_weights(w))), co, digits=True, **g, **kw)
+    else:
+        call = lambda **kw: T.tern_conv3d(act, ci, T.tern_pack_filters(G.dev(w)), co, **g, **kw)
+    want = oracle.conv3d(c.act, w, ConvGeom(c.k, c.stride, c.pad, c.dil))
+    i32 = np.iinfo(np.int32)
+    mid = np.median(want.transpose(1, 0, 2, 3, 4).reshape(co, -1), axis=1).astype(np.int32) + np.arange(co, dtype=np.int32) % 3 - 1
+    ends = [(mid, i32.max), (mid, (1 << 21) + 1), (mid, (1 << 21) - 1), (i32.min, mid), (-(1 << 21) - 1, mid), (mid, mid), (mid + 1, mid)]
+    for lo, hi in ends:
+        lo, hi = (np.broadcast_to(np.asarray(v, np.int32), (co,)).copy() for v in (lo, hi))
+        got = call(thr_lo=G.dev(lo), thr_hi=G.dev(hi))
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(G.words(got), oracle.pack(oracle.threshold(want, lo, hi)), err_msg=str((lo[:3], hi[:3])))
+
+
+def reference(act, w, pad):
+    """Cross-correlation at stride 1 by one float32 product per tap (sums below 2^24: exact), int32 on the GPU."""
+    import torch
+    a, wt = act.float(), w.float()
+    x = torch.nn.functional.pad(a, (pad[2], pad[2], pad[1], pad[1], pad[0], pad[0]))
+    o = [x.shape[2 + i] - w.shape[2 + i] + 1 for i in range(3)]
+    out = torch.zeros((act.shape[0], w.shape[0], o[0] * o[1] * o[2]), device="cuda")
+    for z in range(w.shape[2]):
+        for y in range(w.shape[3]):
+            for v in range(w.shape[4]):
+                tap = wt[:, :, z, y, v].contiguous()
+                for i in range(act.shape[0]):
+                    out[i] += tap @ x[i, :, z:z + o[0], y:y + o[1], v:v + o[2]].reshape(w.shape[1], -1)
+    return out.view(act.shape[0], w.shape[0], *o).int()
+
+
+@pytest.mark.parametrize("binary", [False, True])
+@pytest.mark.parametrize("n,ci,co,vol,k", [
+    (1, 64, 32, (8, 9, 10), (5, 5, 6)), (1, 96, 70, (7, 20, 21), (5, 5, 6)), (1, 64, 70, (24, 40, 40), (3, 5, 9)), (2, 64, 128, (20, 40, 40), (3, 5, 9)),
+    (1, 64, 64, (64, 64, 64), (1, 3, 43)), (1, 32, 128, (48, 64, 72), (3, 5, 9)), (1, 32, 20, (64, 64, 72), (3, 5, 9)),
+    (1, 1, 32, (16, 16, 16), (5, 5, 6)), (1, 4, 70, (40, 40, 40), (5, 5, 6)), (1, 16, 128, (64, 64, 64), (5, 5, 6)), (20, 64, 64, (1, 90, 84), (1, 12, 12))])
+def test_bit_count_plans_where_the_matrix_kernel_does_not_go(G, n, ci, co, vol, k, binary):
+    """More than 128 taps, without an override: the plans that the bit-count kernels choose by themselves for
+    small, middling and large launches, whole and ragged filter counts, one word, several and several taps to
+    a word, volumes and stacks of planes."""
+    import torch
+    import paper_1801_09449_amd as T
+    gen = torch.Generator("cuda").manual_seed(860 + ci)
+    act = torch.randint(-1, 2, (n, ci) + vol, generator=gen, device="cuda", dtype=torch.int8)
+    w = torch.randint(-1, 2, (co, ci) + k, generator=gen, device="cuda", dtype=torch.int8)
+    if binary:
+        w = torch.where(w < 0, w, torch.ones_like(w))
+    pad = tuple(x // 2 for x in k)
+    want = reference(act, w, pad)
+    a, bank = T.tern_pack(act), T.tern_pack_filters_binary(w) if binary else T.tern_pack_filters(w)
+    got = T.tern_conv3d(a, ci, bank, co, k=k, pad=pad, binary=binary)
+    assert T.tern_last_launch()["kernel"] == T.KERNEL_TILED
+    assert torch.equal(got, want)
+    lo, hi = torch.full((co,), -3, dtype=torch.int32, device="cuda"), torch.arange(co, device="cuda", dtype=torch.int32) % 7
+    packed = T.tern_conv3d(a, ci, bank, co, k=k, pad=pad, thr_lo=lo, thr_hi=hi, binary=binary)
+    v = (1, -1, 1, 1, 1)
+    codes = (want > hi.view(v)).to(torch.int8) - ((want < lo.view(v)) & ~(want > hi.view(v))).to(torch.int8)
+    assert torch.equal(packed, T.tern_pack(codes))
 
 
 @pytest.mark.parametrize("n,ci,co,vol,k,s,p,d,digits", [
