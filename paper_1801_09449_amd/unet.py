@@ -6,8 +6,9 @@ call of the library (Eq. 6 on the float stack, fused ternary convolutions, upsam
 concatenation on packed planes, float-weight prediction layer).  2x2 average pooling is exact
 either way it is done here: small problems fold it into the filters of the module that follows
 (tern_fold_avgpool: taps repeated over the pooling window, stride multiplied: no extra launch,
-four times the word pairs of the pooled convolution); large ones pool into two balanced-ternary
-digits first (tern_pool_digits, one small launch) and convolve those (twice the word pairs).
+four times the products of the pooled convolution); large ones pool into two balanced-ternary
+digits first (tern_pool_digits, one small launch) and convolve those (as many products as the
+pooled convolution has).
 """
 from typing import Dict, List, Sequence
 
@@ -26,7 +27,7 @@ class UNetPlan:
         saved: Dict[str, int] = {}
         self.mods: List[B.NetModule] = []          # pooling folded into the filters everywhere
         self._digit_mods: Dict[int, B.NetModule] = {}   # pooled modules in their two-digit form
-        self._macs: Dict[int, float] = {}          # folded word-pair work per output voxel of such a module
+        self._macs: Dict[int, float] = {}          # folded MACs per output voxel of such a module
         for i, L in enumerate(layers):
             w = np.ascontiguousarray(L["w"], dtype=np.int8)
             stride = tuple(int(v) for v in (L.get("stride") or (1, 1, 1)))
@@ -58,10 +59,13 @@ class UNetPlan:
         self._ws = None
         self._shapes: Dict[tuple, list] = {}       # by input shape: [module list, workspace bytes or None]
 
-    # A pooled module whose folded convolution is at least this many ternary MACs runs through
-    # two digits instead (half the word pairs for one more small launch; measured break-even
-    # between 1 and 3 GMAC on MI355X).
-    DIGITS_FROM_MACS = 1.5e9
+    # A pooled module whose folded convolution is at least this many ternary MACs runs through two digits
+    # instead: a quarter of the matrix products (a window sum is one 4-bit float) for one more launch of 2 to
+    # 6 us.  Measured, folded and digits, 3 x 3 behind 2 x 2: 64 -> 128 channels 2.7 GMAC 8.4 and 9.7 us, 5.4 GMAC
+    # 10.7 and 9.9; 128 -> 256 channels 5.3 GMAC 10.7 and 11.1, 10.8 GMAC 14.2 and 13.2, 173 GMAC 82 and 45.
+    # Single taps gain nothing at any size tried but lose little above the line (256 -> 256 channels, 2.5 GMAC
+    # 6.6 and 8.9, 40 GMAC 31.8 and 33.7).
+    DIGITS_FROM_MACS = 6e9
 
     KEPT_SHAPES = 256                              # a program that sees more starts over: a choice takes 0.1 ms
 
