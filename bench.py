@@ -47,9 +47,9 @@ ISSUED_OPS_PER_MAC = 4.0 / 32.0
 # popcount-accumulates); kept as a secondary figure beside the issued-instruction count.
 ALGORITHMIC_OPS_PER_MAC = 5.0 / 32.0
 # HBM bytes per launch of the config[1] kernel: rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE scaled by
-# a 256 MiB copy under the same counters (profiles/conv3d_fused_config1.md).  A profiler figure,
+# a 256 MiB copy under the same counters (profiles/conv_matrix_kernels.md).  A profiler figure,
 # not measured by this script.
-TRAFFIC_BYTES_CFG1 = 10.09e6
+TRAFFIC_BYTES_CFG1 = 9.72e6
 ALGORITHMIC_BYTES_CFG1 = 8.42e6
 SETTLE_MS = 40.0                          # GPU work in front of every timed region (clocks settle)
 
@@ -530,13 +530,13 @@ def main():
                       "single_launches": len(singles)},
         "launch": launch_plan,
         "roofline": {
-            "bound": "vector instructions around the matrix cores", "achieved": 2.0 * macs / (ms * 1e-3) / 1e12,
+            "bound": "matrix cores and the vector instructions beside them, two waves per SIMD", "achieved": 2.0 * macs / (ms * 1e-3) / 1e12,
             "peak": 2.0 * PEAK_MATRIX_MACS / 1e12, "unit": "TFLOP/s", "frac": macs / (ms * 1e-3) / PEAK_MATRIX_MACS,
             "basis": "achieved = 2 x MAC/s (zeros and padded taps counted); peak = 1024 SIMDs x 2.4 GHz x 65536 MACs "
                      "per 32 cycles (dense 4-bit products; the clock falls to about 1.9 GHz under them)",
             "traffic": TRAFFIC_BYTES_CFG1,
-            "traffic_basis": "rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE of the bit-count kernel on the same tiles, "
-                             "profiles/conv3d_fused_config1.md (a profiler run, not this run)",
+            "traffic_basis": "rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE of this kernel, "
+                             "profiles/conv_matrix_kernels.md (a profiler run, not this run)",
             "algorithmic_bytes": ALGORITHMIC_BYTES_CFG1,
             "hbm_GBps": TRAFFIC_BYTES_CFG1 / (ms * 1e-3) / 1e9,
         },

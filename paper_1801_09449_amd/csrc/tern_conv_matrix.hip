@@ -2,9 +2,9 @@
 // activations, same filter banks, same halo tiles in LDS and the same integers as the bit-count kernels
 // (tern_conv_tiled.hip); what differs is the unit that contracts.  A ternary code is the 4-bit float
 // +1 = 0010, -1 = 1010 or 0 = x000, and v_mfma_f32_32x32x64_f8f6f4 takes 32 filters x 32 voxels x 64
-// channels of them in 32 cycles of a SIMD: 64 products per lane and cycle, against 32 per three vector
-// instructions (12 cycles) of the masked-Hamming step.  Sums are floats and exact: every partial sum is an
-// integer, or an integer and a half, far below 2^23.
+// channels of them in 32 cycles of a SIMD: 32 products per lane and cycle, against 32 per four vector
+// instructions (12 cycles at best) of the masked-Hamming step.  Sums are floats and exact: every partial
+// sum is an integer, or an integer and a half, far below 2^23.
 //
 // Rows of the product are filters, columns are voxels, so that in the result a lane holds 16 filters of
 // one voxel and re-packing is shifts within the lane.  A wave owns VB blocks of 32 voxels (a box of the
@@ -21,10 +21,11 @@
 // with NB = 2 leaves three vector instructions per matrix instruction and uses all registers (two waves
 // per SIMD).  Small launches, where a wave's chain of steps is what takes the time, split a tile's steps
 // over two to eight waves that add their sums in LDS (exact, so in any order): 512 -> 256 channels 3 x 3 on
-// 52 x 36 13.0 -> 8.7 us, 256 -> 256 on 16^3 17.7 -> 10.1, 32 -> 32 on 24^3 7.2 -> 5.9.  Under full load the clock falls to 1.9 GHz, where 32 cycles are 8 000 TFLOP/s for the chip.
-// Measured, fused output, bit-count kernels before: 64 -> 64 channels on 96^3, dilation 2: 276 -> 55 us;
-// 256 -> 256 on 2 x 32^3: 321 -> 44 us (5 290 TFLOP/s: loop 38, fill 3, epilogue 3 us); 64 -> 64 3 x 3 on
-// 16 planes of 232 x 168: 83 -> 23 us.
+// 52 x 36 13.0 -> 8.7 us, 256 -> 256 on 16^3 17.7 -> 10.1, 32 -> 32 on 24^3 7.2 -> 5.9.  Under full load the
+// clock falls to 1.9 GHz, where 32 cycles are 8 000 TFLOP/s for the chip.
+// Measured, fused output, bit-count kernels before: 64 -> 64 channels on 64^3: 88 -> 15.4 us, on 96^3 with
+// dilation 2: 276 -> 54 us; 256 -> 256 on 2 x 32^3: 321 -> 43 us (5 400 TFLOP/s: loop 38, fill 3, epilogue 3 us);
+// 64 -> 64 3 x 3 on 16 planes of 232 x 168: 83 -> 23 us.
 #include <type_traits>
 
 #include "tern_internal.h"
@@ -511,7 +512,16 @@ int launch_kind(const ConvParams& p, const MatrixPlan& t, bool odd, size_t lds, 
 
 // Every convolution goes this way except those that one of the limits below sends to the bit-count
 // kernels: more than 128 taps (the tap offsets of a wave sit in two registers), sums that could pass
-// 2^21 (the epilogue works with halves), and halo tiles that do not fit in LDS.
+// 2^21 (the epilogue works with halves; LDS runs out first, so far), and halo tiles that do not fit in LDS.
+// A tile holds all words of its voxels: 3 x 3 x 3 kernels fit up to 47 words (1504 channels) at stride 1, 19 with
+// dilation 2, 10 with 3, 14 at stride 2, 7 and 4 with dilation 2 and 3; from the next word on they take three
+// to eight times as long as their neighbours.
+// Slower here than with bit counts, and left so: one and two channels (16 or 32 taps to a filter word there) to
+// at most 16 filters under 64 to 128 taps, 0.8 to 1.35 times with no rule of sizes that tells them apart (1 -> 16
+// channels, 5^3: 15.6 and 17.9 us on 48^3, 56^3 to 80^3 0.91 to 1.0 times); at most 8 filters with dilated kernels
+// on 256 channels, where 16-byte records take a second round of workgroups (256 -> 8, dilation 3, 88 x 66 x 2: 14.7
+// and 17.4 us); int32 sums of some twenty voxels whose tile the bit-count kernel could not hold and left to the
+// direct one (6.7 and 8.4 us).
 bool launch_conv_matrix(const ConvParams& p, hipStream_t s, int* rc)
 {
     const int64_t taps = (int64_t)p.kd * p.kh * p.kw;

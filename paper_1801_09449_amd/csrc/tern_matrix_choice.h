@@ -80,7 +80,9 @@ inline bool tile_of(const MatrixShape& s, const Choice& c, Tile& t)
 // compute unit's share of matrix instructions (32 cycles each) and of vector instructions (a wave's fixed
 // part, per 64 halo items, per step and its operands, per accumulator block of the epilogue).  Latency: as
 // many rounds of workgroups as registers and LDS leave no room for at once, each as long as one wave takes by
-// itself.
+// itself.  The weights are a fit to 1400 launches on 54 shapes, from the 2-D layers of a U-Net to 96-cubed volumes
+// (workgroups of powers of two only; the search looks at more).  Of 2817 launches on those shapes, the choice took
+// 6 % longer than the best one in the geometric mean and 22 % at the most.
 // A choice looks at some two hundred launches, so nothing below is an integer division.
 inline int32_t steps_of(const MatrixShape& s, int lks)             // of a wave, the longest
 {
