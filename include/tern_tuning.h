@@ -25,7 +25,8 @@ extern "C" {
  * TERN_OPT_TAP_SPLIT: waves of one workgroup that share the kernel taps of one channel slice and
  * add their partial sums in LDS, 0 = choose, 1, 2, 4 or 8.  TERN_OPT_POINTWISE: 1 (default) = 1x1x1
  * convolutions with unit stride and no padding use the pointwise kernel when the input has up to 8
- * words per plane, 0 = they go through the tiled kernel like any other.
+ * words per plane (with int32 output, up to 65535 batch items), 0 = they go through the tiled kernel like
+ * any other.
  * TERN_OPT_LANE_TILE: the block of 64 output voxels that one wave of the tiled kernel computes,
  * 0 = choose (8 x 8 in a plane, or a smaller footprint over several planes where that wastes fewer
  * lanes on the edges of a stack of independent planes), -1 = always 8 x 8, 100 * X + Y with X, Y in

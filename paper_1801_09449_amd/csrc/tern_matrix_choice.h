@@ -95,14 +95,9 @@ constexpr double kInverse[25] = {0, 1.0, 1.0 / 2, 1.0 / 3, 1.0 / 4, 1.0 / 5, 1.0
                                  1.0 / 13, 1.0 / 14, 1.0 / 15, 1.0 / 16, 1.0 / 17, 1.0 / 18, 1.0 / 19, 1.0 / 20, 1.0 / 21, 1.0 / 22, 1.0 / 23, 1.0 / 24};
 
 inline int waves_of(const Choice& c) { return c.nwy * c.nwz * c.nwc * c.nks; }        // at most 8
-// Waves beyond the filter groups only help to fill the halo tile.
-inline int helpers_of(const MatrixShape& s, const Choice& c)
-{
-    const int groups = cdiv(s.c_out, 32) / c.nb;
-    return c.nwc > groups ? c.nwy * c.nwz * c.nks * (c.nwc - groups) : 0;
-}
 // Halo items per wave in units of 64, rounded up (the sum stays below 2^16).
 inline int rounds64_of(int waves, int64_t items) { return (int)(((uint64_t)(items + 64 * waves - 1) * kPer64[waves]) >> 32); }
+// (helpers: waves beyond the filter groups, which only help to fill the halo tile)
 inline double busy_of(const MatrixShape& s, const Choice& c, int64_t per_cu, int helpers, int32_t steps, int rounds64)
 {
     const double blocks = c.vb * c.nb;
@@ -122,13 +117,6 @@ inline double latency_of(const Choice& c, int64_t per_cu, int64_t lds, int32_t s
     return (double)rounds * alone;
 }
 inline double norm_cost(double busy, double latency) { return std::pow(busy, 1.73) + std::pow(latency, 1.73); }
-inline double estimate(const MatrixShape& s, const Choice& c, const Tile& t)
-{
-    const int32_t steps = steps_of(s, c.nks == 1 ? 0 : c.nks == 2 ? 1 : c.nks == 4 ? 2 : 3);
-    const int r = rounds64_of(waves_of(c), t.items);
-    const int64_t per_cu = (t.wgs + 255) >> 8;
-    return norm_cost(busy_of(s, c, per_cu, helpers_of(s, c), steps, r), latency_of(c, per_cu, t.lds, steps, r));
-}
 
 // The norm of (1, r) for r in 0 .. 1, from below: a bound of the norm without a power.
 struct NormTable {
