@@ -23,6 +23,11 @@
 // over two to eight waves that add their sums in LDS (exact, so in any order): 512 -> 256 channels 3 x 3 on
 // 52 x 36 13.0 -> 8.7 us, 256 -> 256 on 16^3 17.7 -> 10.1, 32 -> 32 on 24^3 7.2 -> 5.9.  Under full load the
 // clock falls to 1.9 GHz, where 32 cycles are 8 000 TFLOP/s for the chip.
+// What stands in front of the first matrix instruction counts for a launch of 5 to 9 us: workgroup and wave numbers
+// are divided by multiplication (ten integer divisions were 250 instructions before the first load), cut points
+// and halo items are fetched at once, and halo voxels go through a buffer descriptor that returns zeros outside the
+// volume.  Together: 32 -> 32 on 24^3 5.46 -> 4.99 us, 96 -> 70 stride 2 on 2 x 45 x 53 x 37 13.9 -> 12.5, 64 -> 64
+// on 96^3 with dilation 2 53.8 -> 51.5, a U-Net's fifteen launches 125.6 -> 113.3.
 // Measured, fused output, bit-count kernels before: 64 -> 64 channels on 64^3: 88 -> 15.4 us, on 96^3 with
 // dilation 2: 276 -> 54 us; 256 -> 256 on 2 x 32^3: 321 -> 43 us (5 400 TFLOP/s: loop 38, fill 3, epilogue 3 us);
 // 64 -> 64 3 x 3 on 16 planes of 232 x 168: 83 -> 23 us.
@@ -35,23 +40,19 @@
 namespace tern {
 namespace {
 
-// Quotient of small numbers: e / d = (e * m) >> s for every e the plan divides (below 2^16).
-struct Reciprocal {
-    uint32_t m, s;
-};
-
 struct MatrixPlan {
     int32_t lxb, lyb;                // a wave's voxels: 2^lxb x 2^lyb x the rest
-    int32_t nwy, nwz, nwc;           // waves of a workgroup along y, z and over filter groups
-    int32_t nks;                     // waves that share a tile's steps and add up their sums in LDS
+    int32_t lwy, lwz, nwc;           // waves of a workgroup along y and z (log2) and over filter groups
+    int32_t lks;                     // waves that share a tile's steps and add up their sums in LDS (log2)
     int32_t hx, hy, hz;              // halo extents in voxels
-    int32_t tiles_x, tiles_y, tiles_z;
+    Divisor tiles_x, tiles_y, tiles_z;
+    uint32_t reach;                  // bytes of input from a tile's first plane to its last
     int32_t nch;                     // words (or word pairs) per voxel
     int32_t pl;                      // LDS bytes of one word plane
     int32_t zero_off;                // LDS byte offset of a zero record (odd word counts)
     int32_t tp_log;                  // tap-packed bank: log2 of the taps per row
     int32_t cut_off;                 // LDS byte offset of the staged cut points
-    Reciprocal r_hx, r_pl, r_ch, r_kw, r_kh, r_nch;
+    Reciprocal r_hx, r_pl, r_ch, r_kw, r_kh, r_nch, r_nwc;
 };
 
 // What the words are: ternary or binary (sign-only) filter banks, two-digit activations, or the tap-packed
@@ -59,6 +60,7 @@ struct MatrixPlan {
 enum { kTernary = 0, kBinary = 1, kDigits = 2, kTapPacked = 3 };
 
 __device__ __forceinline__ uint32_t quotient(uint32_t e, Reciprocal r) { return __umul24(e, r.m) >> r.s; }
+__device__ __forceinline__ int quotient(int e, Divisor d) { return (int)(((uint64_t)(uint32_t)e * d.m) >> d.s); }
 
 // Two balanced-ternary digits per value (low + 3 high, -4 .. 4) to the E2M1 code of the value
 // (magnitudes 1, 2, 3, 4 = 0010, 0100, 0101, 0110), channels in the order of expand().
@@ -105,16 +107,15 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
         const int per_xcd = gridDim.x >> 3;
         if (bid < (per_xcd << 3)) bid = (bid & 7) * per_xcd + (bid >> 3);
     }
-    const int tix = bid % t.tiles_x; bid /= t.tiles_x;
-    const int tiy = bid % t.tiles_y; bid /= t.tiles_y;
-    const int tiz = bid % t.tiles_z;
-    const int n = bid / t.tiles_z;
+    const int row = quotient(bid, t.tiles_x), tix = bid - row * t.tiles_x.d;
+    const int layer = quotient(row, t.tiles_y), tiy = row - layer * t.tiles_y.d;
+    const int n = quotient(layer, t.tiles_z), tiz = layer - n * t.tiles_z.d;
     const int X = 1 << t.lxb, Y = 1 << t.lyb, Z = (32 * VB) >> (t.lxb + t.lyb);
-    const int ox0 = tix << t.lxb, oy0 = tiy * (Y * t.nwy), oz0 = tiz * (Z * t.nwz);
-    const int nks = SPLIT ? t.nks : 1;
-    const int ks = wave % nks, wtile = wave / nks;
-    const int wc = wtile % t.nwc, wsp = wtile / t.nwc;
-    const int wy = wsp % t.nwy, wz = wsp / t.nwy;
+    const int ox0 = tix << t.lxb, oy0 = tiy << (t.lyb + t.lwy), oz0 = tiz * (Z << t.lwz);
+    const int lks = SPLIT ? t.lks : 0, nks = 1 << lks;
+    const int ks = wave & (nks - 1), wtile = wave >> lks;
+    const int wsp = (int)quotient((uint32_t)wtile, t.r_nwc), wc = wtile - wsp * t.nwc;
+    const int wy = wsp & ((1 << t.lwy) - 1), wz = wsp >> t.lwy;
     const int cb = (blockIdx.y * t.nwc + wc) * (32 * NB);   // first filter of this wave
     const bool active = cb < p.c_out;
 
@@ -132,8 +133,8 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
     const int all_steps = ODD ? (p.kd * p.kh * p.kw * t.nch + 1) >> 1
                               : p.kd * p.kh * p.kw * (KIND == kDigits ? t.nch >> 1 : t.nch);
     // this wave's steps: first .. first + steps - 1
-    const int first = all_steps * ks / nks;
-    const int steps = all_steps * (ks + 1) / nks - first;
+    const int first = (all_steps * ks) >> lks;
+    const int steps = ((all_steps * (ks + 1)) >> lks) - first;
     const bool half_last = ODD && ks == nks - 1 && (((p.kd * p.kh * p.kw * t.nch) & 1) != 0);
     const int step_words = ROWS ? 2 * row_words : row_words;   // (tap-packed: per row)
     const uint32_t* bank = p.wgt + (size_t)(active ? cb : 0) * FW;
@@ -163,57 +164,65 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
     fetch_f(f0, 0);
     fetch_f(f1, 1);
 
+    // Cut points of the workgroup's filters, thread j those of filter j (a workgroup has at least as many
+    // threads).  Fetched here, with the first loads, and staged behind the halo tile: fetched there they cost
+    // another round trip in front of the barrier (0.4 to 0.9 us of a launch of 5 to 9).
+    const int wg_filters = t.nwc * 32 * NB;
+    int cut_lo = 0, cut_hi = 0;
+    if constexpr (PACKED) {
+        const int co = min((int)blockIdx.y * wg_filters + min(tid, wg_filters - 1), p.c_out - 1);
+        cut_lo = p.lo[co];
+        cut_hi = p.hi[co];
+    }
+
     uint32_t m33 = 0x33333333u, maa = 0xaaaaaaaau;
     asm volatile("" : "+v"(m33), "+v"(maa));
 
     // ---- halo tile -> LDS ----------------------------------------------------------------------
     const int gx0 = ox0 * p.sw - p.pw, gy0 = oy0 * p.sh - p.ph, gz0 = oz0 * p.sd - p.pd;
     {
-        const uint32_t* in_n = p.in + (size_t)n * p.d * p.h * p.w * 2u * wd;
+        // Offsets from the tile's first plane within the volume, in bytes and modulo 2^32; voxels outside the
+        // volume get one past the end, which reads as zeros.
+        const int zb = max(gz0, 0);
+        const uint32_t rec = 8u * (uint32_t)wd, line = (uint32_t)p.w * rec, slice = (uint32_t)p.h * line;
+        const __amdgpu_buffer_rsrc_t src = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<uint32_t*>(p.in + ((size_t)n * p.d + zb) * ((size_t)p.h * p.w * 2u * wd)), 0, t.reach, 0x00020000);
+        const uint32_t origin = (uint32_t)(gz0 - zb) * slice + (uint32_t)gy0 * line + (uint32_t)gx0 * rec;
+        constexpr uint32_t OUTSIDE = 0xfffffff0u;
         const int items = nvox * t.nch;
         constexpr bool PAIRS = !ODD || KIND == kDigits;     // two words per plane and item
         constexpr int FILL = PAIRS ? 6 : 3;      // items a thread keeps in flight (single words: more would cost a wave per SIMD)
-        for (int base = 0; base < items; base += FILL * nthreads) {
+        auto round = [&](int base) {
             uint32_t r[FILL][4];
             int dst[FILL];
 #pragma unroll
             for (int k = 0; k < FILL; ++k) {
-                if (!ODD && base + k * nthreads >= items) break;   // (the same for every thread)
+                if (!ODD && k > 0 && base + k * nthreads >= items) break;   // (the same for every thread)
                 const uint32_t e = (uint32_t)(base + k * nthreads + tid);
-                const uint32_t v = t.nch > 1 ? quotient(e, t.r_ch) : e;
+                const uint32_t v = quotient(e, t.r_ch);
                 const uint32_t c = e - __umul24(v, (uint32_t)t.nch);
                 const uint32_t hz = quotient(v, t.r_pl);
                 const uint32_t q = v - __umul24(hz, (uint32_t)plane);
                 const uint32_t hy = quotient(q, t.r_hx);
                 const uint32_t hx = q - __umul24(hy, (uint32_t)t.hx);
-                const int gz = gz0 + (int)hz, gy = gy0 + (int)hy, gx = gx0 + (int)hx;
-                dst[k] = (int)(__umul24(c, (uint32_t)(PAIRS && KIND != kDigits ? 2 * t.pl : t.pl)) + v * REC);
-                if (e >= (uint32_t)items) dst[k] = -1;
-                r[k][0] = r[k][1] = r[k][2] = r[k][3] = 0u;
-                if (dst[k] >= 0 && (unsigned)gz < (unsigned)p.d && (unsigned)gy < (unsigned)p.h &&
-                    (unsigned)gx < (unsigned)p.w) {
-                    const uint32_t vox = (uint32_t)((gz * p.h + gy) * p.w + gx);
-                    const uint32_t* src = in_n + (size_t)vox * (2u * wd);
-                    if constexpr (PAIRS) {
-                        if (wd == 2) {
-                            const uint4 a = *reinterpret_cast<const uint4*>(src);
-                            r[k][0] = a.x; r[k][1] = a.y; r[k][2] = a.z; r[k][3] = a.w;
-                        } else {
-                            const uint2 a = *reinterpret_cast<const uint2*>(src + 2 * c);
-                            const uint2 b = *reinterpret_cast<const uint2*>(src + wd + 2 * c);
-                            r[k][0] = a.x; r[k][1] = a.y; r[k][2] = b.x; r[k][3] = b.y;
-                        }
-                    } else if (wd == 1) {
-                        const uint2 a = *reinterpret_cast<const uint2*>(src);
-                        r[k][0] = a.x; r[k][2] = a.y;
-                    } else {
-                        r[k][0] = src[c]; r[k][2] = src[wd + c];
-                    }
+                const bool live = e < (uint32_t)items;
+                dst[k] = live ? (int)(__umul24(c, (uint32_t)(PAIRS && KIND != kDigits ? 2 * t.pl : t.pl)) + v * REC) : -1;
+                const bool inside = live & ((uint32_t)(gz0 + (int)hz) < (uint32_t)p.d) & ((uint32_t)(gy0 + (int)hy) < (uint32_t)p.h) &
+                                    ((uint32_t)(gx0 + (int)hx) < (uint32_t)p.w);
+                uint32_t o = origin + hz * slice + hy * line + __umul24(hx, rec) + (PAIRS ? 8u : 4u) * c;
+                o = inside ? o : OUTSIDE;
+                if constexpr (PAIRS) {
+                    const v2u a = __builtin_amdgcn_raw_buffer_load_b64(src, o, 0, 0);
+                    const v2u b = __builtin_amdgcn_raw_buffer_load_b64(src, o, 4 * wd, 0);
+                    r[k][0] = a.x; r[k][1] = a.y; r[k][2] = b.x; r[k][3] = b.y;
+                } else {
+                    r[k][0] = __builtin_amdgcn_raw_buffer_load_b32(src, o, 0, 0);
+                    r[k][2] = __builtin_amdgcn_raw_buffer_load_b32(src, o, 4 * wd, 0);
                 }
             }
 #pragma unroll
             for (int k = 0; k < FILL; ++k) {
-                if (!ODD && base + k * nthreads >= items) break;
+                if (!ODD && k > 0 && base + k * nthreads >= items) break;
                 if (dst[k] >= 0) {
                     uint8_t* d = lds8 + dst[k];
                     if constexpr (KIND == kDigits) {
@@ -226,19 +235,19 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
                     }
                 }
             }
-        }
+        };
+        // The first round by itself: in front of a loop the compiler waits for every load that is under way.
+        round(0);
+        for (int base = FILL * nthreads; base < items; base += FILL * nthreads) round(base);
         if (ODD && tid < 4) reinterpret_cast<uint32_t*>(lds8 + t.zero_off)[tid] = 0u;
     }
-    // Cut points of the workgroup's filters: start values, then widths.
+    // Cut points in LDS: start values, then widths.
     float* cuts = reinterpret_cast<float*>(lds8 + t.cut_off);
-    const int wg_filters = t.nwc * 32 * NB;
     if constexpr (PACKED) {
-        for (int j = tid; j < wg_filters; j += nthreads) {
-            const int co = blockIdx.y * wg_filters + j;
-            const bool live = co < p.c_out;
-            const Cut cut = cut_of(live ? p.lo[co] : 0, live ? p.hi[co] : 0, live);
-            cuts[j] = cut.start;
-            cuts[wg_filters + j] = cut.width;
+        if (tid < wg_filters) {
+            const Cut cut = cut_of(cut_lo, cut_hi, (int)blockIdx.y * wg_filters + tid < p.c_out);
+            cuts[tid] = cut.start;
+            cuts[wg_filters + tid] = cut.width;
         }
     }
     __syncthreads();
@@ -415,7 +424,7 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
         dz = (vb * 32) >> (t.lxb + t.lyb);
         return lx < p.ow - bx - dx && ly < p.oh - by - dy && lz < p.od - bz - dz;
     };
-    const size_t row = (size_t)p.ow, slab = (size_t)p.oh * p.ow;
+    const size_t line = (size_t)p.ow, slab = (size_t)p.oh * p.ow;
     const size_t vox0 = (((size_t)n * p.od + bz + lz) * p.oh + by + ly) * p.ow + bx + lx;
     if constexpr (PACKED) {
         uint32_t* out = p.out_packed + vox0 * 2u * p.wd_out + g * p.wd_out + (cb >> 5);
@@ -432,7 +441,7 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
             }
             int dx, dy, dz;
             if (offset_of(vb, dx, dy, dz)) {
-                uint32_t* o = out + (dz * slab + dy * row + dx) * 2u * p.wd_out;
+                uint32_t* o = out + (dz * slab + dy * line + dx) * 2u * p.wd_out;
                 if (pair) {
                     *reinterpret_cast<v2u*>(o) = v2u{word[0], word[NB - 1]};
                 } else {
@@ -452,7 +461,7 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
             for (int vb = 0; vb < VB; ++vb) {
                 int dx, dy, dz;
                 if (finishes(vb * NB + nb) && offset_of(vb, dx, dy, dz)) {
-                    int32_t* o = p.out_acc + ((size_t)n * p.c_out + c0) * cs + in_item + dz * slab + dy * row + dx;
+                    int32_t* o = p.out_acc + ((size_t)n * p.c_out + c0) * cs + in_item + dz * slab + dy * line + dx;
 #pragma unroll
                     for (int v = 0; v < 16; ++v) {
                         const int dc = (v >> 2) * 8 + (v & 3);
@@ -462,16 +471,6 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
             }
         }
     }
-}
-
-// e / d = (e * m) >> s for 0 <= e < emax <= 2^15: with emax * d <= 2^s the error of m = ceil(2^s / d)
-// stays below 1 / d, and e * m < 2^32.
-Reciprocal reciprocal(uint32_t d, uint32_t emax)
-{
-    uint32_t s = 0;
-    while (((uint64_t)1 << s) < (uint64_t)emax * d) ++s;
-    const Reciprocal r = {(uint32_t)((((uint64_t)1 << s) + d - 1) / d), s};
-    return r;
 }
 
 template <int VB, int NB, bool PACKED, int KIND, bool ODD, bool SPLIT>
@@ -538,15 +537,22 @@ bool launch_conv_matrix(const ConvParams& p, hipStream_t s, int* rc)
     const int X = 1 << c.lxb, Y = 1 << c.lyb, Z = (32 * c.vb) >> (c.lxb + c.lyb);
     const int64_t gy = q.wgs / q.tiles;
     if (q.tiles > 0x7fffffff || gy > 65535) return false;
+    // A tile's planes within 4 GB (a volume's may be more).
+    const int64_t plane_bytes = 8 * (int64_t)p.wd_in * p.h * p.w;
+    if (plane_bytes > 0xffff0000ll) return false;
+    const int64_t reach = plane_bytes * (q.hz < p.d ? q.hz : p.d);
+    if (reach > 0xffff0000ll) return false;
     MatrixPlan t;
-    t.lxb = c.lxb; t.lyb = c.lyb; t.nwy = c.nwy; t.nwz = c.nwz; t.nwc = c.nwc;
+    t.lxb = c.lxb; t.lyb = c.lyb; t.lwy = log2_up(c.nwy); t.lwz = log2_up(c.nwz); t.nwc = c.nwc;
     t.hx = (int32_t)q.hx; t.hy = (int32_t)q.hy; t.hz = (int32_t)q.hz;
-    t.tiles_x = cdiv(p.ow, X); t.tiles_y = cdiv(p.oh, Y * c.nwy); t.tiles_z = cdiv(p.od, Z * c.nwz);
+    t.tiles_x = divisor(cdiv(p.ow, X)); t.tiles_y = divisor(cdiv(p.oh, Y * c.nwy)); t.tiles_z = divisor(cdiv(p.od, Z * c.nwz));
+    t.reach = (uint32_t)reach;
     t.nch = p.digits || odd ? words : words / 2;
     t.pl = (int32_t)(q.hx * q.hy * q.hz * 16);
     t.zero_off = words * t.pl;
     t.cut_off = (int32_t)q.cuts;
-    t.nks = c.nks;
+    t.lks = log2_up(c.nks);
+    t.r_nwc = reciprocal((uint32_t)c.nwc, 8);
     const uint32_t emax = (uint32_t)q.items;
     t.r_hx = reciprocal((uint32_t)t.hx, emax);
     t.r_pl = reciprocal((uint32_t)(t.hx * t.hy), emax);

@@ -127,6 +127,33 @@ int main()
 """
 
 
+DIVISIONS = r"""
+#include "tern_matrix_choice.h"
+#include <cstdio>
+#include <random>
+int main()
+{
+    long wrong = 0;
+    std::mt19937_64 r(2);
+    const auto quotient = [](uint32_t e, tern::Divisor d) { return (uint32_t)(((uint64_t)e * d.m) >> d.s); };
+    for (int i = 0; i < 400000; ++i) {
+        const int32_t d = i < 2000 ? i + 1 : i < 2100 ? 0x7fffffff - (i - 2000) : (int32_t)(r() % 0x7fffffff >> (r() % 31)) + 1;
+        const tern::Divisor q = tern::divisor(d);
+        const uint32_t last = 0x7fffffffu / (uint32_t)d * (uint32_t)d;        // the largest multiple
+        for (uint32_t e : {0u, (uint32_t)d - 1, (uint32_t)d, last - 1, last, 0x7fffffffu, (uint32_t)(r() & 0x7fffffffu)})
+            wrong += quotient(e, q) != e / (uint32_t)d;
+    }
+    for (uint32_t d = 1; d <= 8; ++d)                                          // waves of a workgroup over filter groups
+        for (uint32_t e = 0; e < 8; ++e) wrong += (e * tern::reciprocal(d, 8).m) >> tern::reciprocal(d, 8).s != e / d;
+    for (uint32_t d = 1; d < 600; ++d) {
+        const tern::Reciprocal q = tern::reciprocal(d, 32768);
+        for (uint32_t e = 0; e < 32768; ++e) wrong += (e * q.m) >> q.s != e / d;
+    }
+    printf("%ld\n", wrong);
+}
+"""
+
+
 def build_and_run(tmp_path, source):
     (tmp_path / "t.cpp").write_text(source)
     subprocess.run(["g++", "-O3", "-std=c++17", "-I", CSRC, str(tmp_path / "t.cpp"), "-o", str(tmp_path / "t")], check=True)
@@ -152,3 +179,9 @@ def test_cheap_choice_is_the_choice_of_a_plain_search(tmp_path):
     assert got["differ"] == "0" and got["kept"] == "0"
     assert 0 < int(got["none"]) < 4000
     assert float(out[out.index("ratio") + 1]) < 0.6
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_divisions_by_multiplication(tmp_path):
+    """The launch's reciprocals give the quotients of the integers, at multiples and beside them up to 2^31."""
+    assert build_and_run(tmp_path, DIVISIONS).strip() == "0"
