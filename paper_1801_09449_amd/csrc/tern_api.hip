@@ -657,6 +657,26 @@ struct NetWalk {
     uint32_t** module_out; tern_dims* module_dims;
 };
 
+// Sources of whole words with factors that are powers of two, as launch_conv3d_pair takes them.
+inline bool pair_of(const tern_source* src, int n_src, ConvPair* pair)
+{
+    if (src[0].dims.c % 32 != 0) return false;
+    for (int i = 0; i < 2; ++i) {
+        const tern_source& a = src[i < n_src ? i : 0];
+        PairSource& q = pair->s[i];
+        q.p = a.packed;
+        q.d = a.dims.d; q.h = a.dims.h; q.w = a.dims.w;
+        q.wd = i < n_src ? tern_words(a.dims.c) : 0;
+        for (int k = 0; k < 3; ++k) {
+            q.up_log[k] = 0;
+            while (1 << q.up_log[k] < a.up[k]) ++q.up_log[k];
+            if (1 << q.up_log[k] != a.up[k]) return false;
+            q.first[k] = a.first[k];
+        }
+    }
+    return true;
+}
+
 inline size_t region(const tern_dims& d) { return (tern_packed_bytes(d) + 255u) & ~(size_t)255u; }
 
 int net_walk(tern_dims in_dims, const tern_module* mods, int32_t n_mods, NetWalk* w, size_t* total,
@@ -715,6 +735,9 @@ int net_walk(tern_dims in_dims, const tern_module* mods, int32_t n_mods, NetWalk
     size_t cur_off = in_off;
     for (int i = 0; i < n_mods; ++i) {
         const tern_module& m = mods[i];
+        // a module's joined input: written by tern_concat unless the convolution reads its parts
+        tern_source src[2];
+        int n_src = 0;
         if (m.skip_from >= i || m.skip_from < -1) return TERN_EARG;
         for (int a = 0; a < 3; ++a)
             if (m.up[a] < 1 || m.up[a] > 1024) return TERN_EARG;
@@ -723,11 +746,10 @@ int net_walk(tern_dims in_dims, const tern_module* mods, int32_t n_mods, NetWalk
             const int64_t ud = (int64_t)cur.d * m.up[0], uh = (int64_t)cur.h * m.up[1], uw = (int64_t)cur.w * m.up[2];
             if (ud > INT32_MAX || uh > INT32_MAX || uw > INT32_MAX) return TERN_ESHAPE;
             tern_dims cat = {cur.n, cur.c, (int32_t)ud, (int32_t)uh, (int32_t)uw};
-            tern_source src[2];
             src[0].packed = w && w->run ? (const uint32_t*)(w->ws + cur_off) : nullptr;
             src[0].dims = cur;
             for (int a = 0; a < 3; ++a) { src[0].up[a] = m.up[a]; src[0].first[a] = 0; }
-            int n_src = 1;
+            n_src = 1;
             if (m.skip_from >= 0) {
                 const tern_dims& sd = odims[(size_t)m.skip_from];
                 const int32_t first[3] = {(sd.d - cat.d) / 2, (sd.h - cat.h) / 2, (sd.w - cat.w) / 2};
@@ -742,15 +764,25 @@ int net_walk(tern_dims in_dims, const tern_module* mods, int32_t n_mods, NetWalk
             if (!sizes_ok(cat)) return TERN_ESHAPE;
             const size_t cat_off = off;
             off += region(cat);
-            if (w && w->run) {
-                int rc = tern_concat(src, n_src, cat, (uint32_t*)(w->ws + cat_off), w->stream);
-                if (rc != TERN_OK) return rc;
-            }
             cur = cat;
             cur_off = cat_off;
         }
         // sum pooling in front of the module: two balanced-ternary digits per channel
         const bool pooled = m.pool[0] > 1 || m.pool[1] > 1 || m.pool[2] > 1;
+        bool joined = false;
+        if (n_src > 0 && w && w->run) {
+            int rc = TERN_OK;
+            tern_dims o;
+            if (!pooled && aligned16(m.w_bank) && geom_check(cur, m.c_out, m.g, &o) == TERN_OK) {
+                ConvPair pair;
+                joined = pair_of(src, n_src, &pair) &&
+                         launch_conv3d_pair(conv_params(nullptr, cur, m.w_bank, m.c_out, m.g, o, m.thr_lo, m.thr_hi, nullptr,
+                                                        (uint32_t*)(w->ws + off)),
+                                            pair, w->stream, &rc);
+            }
+            if (!joined) rc = tern_concat(src, n_src, cur, (uint32_t*)(w->ws + cur_off), w->stream);
+            if (rc != TERN_OK) return rc;
+        }
         if (pooled) {
             for (int a = 0; a < 3; ++a)
                 if (m.pool[a] < 1 || m.pool[a] > 4) return TERN_EARG;
@@ -777,7 +809,9 @@ int net_walk(tern_dims in_dims, const tern_module* mods, int32_t n_mods, NetWalk
         off += region(o);
         if (w && w->run) {
             if (!m.w_bank || !m.thr_lo || !m.thr_hi) return TERN_ENULL;
-            if (i == 0 && gathered && !fused) {
+            if (joined) {
+                // (launched above)
+            } else if (i == 0 && gathered && !fused) {
                 // single-tap convolution over the gathered words
                 const int32_t taps = m.g.k[0] * m.g.k[1] * m.g.k[2];
                 const tern_dims pin = {o.n, taps, o.d, o.h, o.w};

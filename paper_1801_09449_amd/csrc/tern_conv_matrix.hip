@@ -40,6 +40,18 @@
 namespace tern {
 namespace {
 
+// Where a tile's words come from when the input lies in two tensors (ConvPair): byte offsets from the first
+// of the two in memory.
+struct PairPlan {
+    const uint32_t* base;
+    uint32_t reach;                  // bytes from there to the end of both
+    uint32_t start[2], item[2];      // first byte, bytes per batch item
+    uint32_t line[2], rec[2];        // bytes per row and per voxel
+    int32_t h[2];
+    int32_t up[2][3], first[2][3];
+    int32_t nch0;                    // word pairs of source 0
+};
+
 struct MatrixPlan {
     int32_t lxb, lyb;                // a wave's voxels: 2^lxb x 2^lyb x the rest
     int32_t lwy, lwz, nwc;           // waves of a workgroup along y and z (log2) and over filter groups
@@ -53,11 +65,14 @@ struct MatrixPlan {
     int32_t tp_log;                  // tap-packed bank: log2 of the taps per row
     int32_t cut_off;                 // LDS byte offset of the staged cut points
     Reciprocal r_hx, r_pl, r_ch, r_kw, r_kh, r_nch, r_nwc;
+    PairPlan pair;                   // (kPair)
 };
 
 // What the words are: ternary or binary (sign-only) filter banks, two-digit activations, or the tap-packed
-// bank of up to 16 input channels (several taps share a filter word; here each tap is a word of its own).
-enum { kTernary = 0, kBinary = 1, kDigits = 2, kTapPacked = 3 };
+// bank of up to 16 input channels (several taps share a filter word; here each tap is a word of its own), or
+// ternary banks with the activations in two tensors (an upsampled one and a cropped one behind it: joining
+// them in memory first took a launch of 4 us at 15 to 90 thousand voxels and 12 to 13 us at sixteen times as many).
+enum { kTernary = 0, kBinary = 1, kDigits = 2, kTapPacked = 3, kPair = 4 };
 
 __device__ __forceinline__ uint32_t quotient(uint32_t e, Reciprocal r) { return __umul24(e, r.m) >> r.s; }
 __device__ __forceinline__ int quotient(int e, Divisor d) { return (int)(((uint64_t)(uint32_t)e * d.m) >> d.s); }
@@ -185,8 +200,13 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
         // volume get one past the end, which reads as zeros.
         const int zb = max(gz0, 0);
         const uint32_t rec = 8u * (uint32_t)wd, line = (uint32_t)p.w * rec, slice = (uint32_t)p.h * line;
-        const __amdgpu_buffer_rsrc_t src = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<uint32_t*>(p.in + ((size_t)n * p.d + zb) * ((size_t)p.h * p.w * 2u * wd)), 0, t.reach, 0x00020000);
+        const uint32_t* from = KIND == kPair ? t.pair.base : p.in + ((size_t)n * p.d + zb) * ((size_t)p.h * p.w * 2u * wd);
+        const __amdgpu_buffer_rsrc_t src = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(from), 0, t.reach, 0x00020000);
+        uint32_t pair0 = 0, pair1 = 0;                      // the batch item's first bytes; word pair c of source 1 is pair c - nch0 there
+        if constexpr (KIND == kPair) {
+            pair0 = t.pair.start[0] + (uint32_t)n * t.pair.item[0];
+            pair1 = t.pair.start[1] + (uint32_t)n * t.pair.item[1] - 8u * (uint32_t)t.pair.nch0;
+        }
         const uint32_t origin = (uint32_t)(gz0 - zb) * slice + (uint32_t)gy0 * line + (uint32_t)gx0 * rec;
         constexpr uint32_t OUTSIDE = 0xfffffff0u;
         const int items = nvox * t.nch;
@@ -209,6 +229,22 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
                 dst[k] = live ? (int)(__umul24(c, (uint32_t)(PAIRS && KIND != kDigits ? 2 * t.pl : t.pl)) + v * REC) : -1;
                 const bool inside = live & ((uint32_t)(gz0 + (int)hz) < (uint32_t)p.d) & ((uint32_t)(gy0 + (int)hy) < (uint32_t)p.h) &
                                     ((uint32_t)(gx0 + (int)hx) < (uint32_t)p.w);
+                if constexpr (KIND == kPair) {
+                    const PairPlan& u = t.pair;
+                    const bool a = c < (uint32_t)u.nch0;
+                    const int iz = gz0 + (int)hz, iy = gy0 + (int)hy, ix = gx0 + (int)hx;
+                    const int z = a ? (iz + u.first[0][0]) >> u.up[0][0] : (iz + u.first[1][0]) >> u.up[1][0];
+                    const int y = a ? (iy + u.first[0][1]) >> u.up[0][1] : (iy + u.first[1][1]) >> u.up[1][1];
+                    const int x = a ? (ix + u.first[0][2]) >> u.up[0][2] : (ix + u.first[1][2]) >> u.up[1][2];
+                    const uint32_t plane_row = __umul24((uint32_t)z, (uint32_t)(a ? u.h[0] : u.h[1])) + (uint32_t)y;
+                    const uint32_t vrec = a ? u.rec[0] : u.rec[1];
+                    uint32_t o = (a ? pair0 : pair1) + __umul24(plane_row, a ? u.line[0] : u.line[1]) + __umul24((uint32_t)x, vrec) + 8u * c;
+                    o = inside ? o : OUTSIDE;
+                    const v2u m = __builtin_amdgcn_raw_buffer_load_b64(src, o, 0, 0);
+                    const v2u sg = __builtin_amdgcn_raw_buffer_load_b64(src, inside ? o + (vrec >> 1) : OUTSIDE, 0, 0);
+                    r[k][0] = m.x; r[k][1] = m.y; r[k][2] = sg.x; r[k][3] = sg.y;
+                    continue;
+                }
                 uint32_t o = origin + hz * slice + hy * line + __umul24(hx, rec) + (PAIRS ? 8u : 4u) * c;
                 o = inside ? o : OUTSIDE;
                 if constexpr (PAIRS) {
@@ -496,6 +532,8 @@ int launch_variant(const ConvParams& p, const MatrixPlan& t, size_t lds_bytes, d
 template <int VB, int NB, bool PACKED, bool SPLIT>
 int launch_kind(const ConvParams& p, const MatrixPlan& t, bool odd, size_t lds, dim3 grid, int threads, hipStream_t s)
 {
+    if constexpr (PACKED)
+        if (t.pair.base) return launch_variant<VB, NB, PACKED, kPair, false, SPLIT>(p, t, lds, grid, threads, s);
     if (p.tp_slots) return launch_variant<VB, NB, PACKED, kTapPacked, true, SPLIT>(p, t, lds, grid, threads, s);
     if (p.digits)
         return odd ? launch_variant<VB, NB, PACKED, kDigits, true, SPLIT>(p, t, lds, grid, threads, s)
@@ -509,6 +547,33 @@ int launch_kind(const ConvParams& p, const MatrixPlan& t, bool odd, size_t lds, 
 
 }  // namespace
 
+// Two tensors as one buffer: both within 4 GB, rows and row numbers within the kernel's 24-bit products.
+static bool pair_plan(const ConvPair& pair, int32_t n, PairPlan& u)
+{
+    const bool both = pair.s[1].wd > 0;
+    const uintptr_t a = (uintptr_t)pair.s[0].p, b = both ? (uintptr_t)pair.s[1].p : a, base = a < b ? a : b;
+    uint64_t end = 0;
+    for (int i = 0; i < 2; ++i) {
+        const PairSource& q = pair.s[i];
+        const bool there = i == 0 || both;
+        const int64_t rec = 8 * (int64_t)q.wd, line = there ? q.w * rec : 0, rows = there ? (int64_t)q.d * q.h : 0;
+        if (line >= 1 << 24 || rows >= 1 << 24 || q.d >= 1 << 24) return false;
+        const uint64_t start = (i == 0 ? a : b) - base, bytes = (uint64_t)n * (uint64_t)(rows * line);
+        if (start > 0xffff0000u || bytes > 0xffff0000u || start + bytes > 0xffff0000u) return false;
+        if (start + bytes > end) end = start + bytes;
+        u.start[i] = (uint32_t)start;
+        u.item[i] = (uint32_t)(rows * line);
+        u.line[i] = (uint32_t)line;
+        u.rec[i] = (uint32_t)rec;
+        u.h[i] = q.h;
+        for (int k = 0; k < 3; ++k) { u.up[i][k] = q.up_log[k]; u.first[i][k] = q.first[k]; }
+    }
+    u.base = (const uint32_t*)base;
+    u.reach = (uint32_t)end;
+    u.nch0 = pair.s[0].wd / 2;
+    return true;
+}
+
 // Every convolution goes this way except those that one of the limits below sends to the bit-count
 // kernels: more than 128 taps (the tap offsets of a wave sit in two registers), sums that could pass
 // 2^21 (the epilogue works with halves; LDS runs out first, so far), and halo tiles that do not fit in LDS.
@@ -521,8 +586,11 @@ int launch_kind(const ConvParams& p, const MatrixPlan& t, bool odd, size_t lds, 
 // on 256 channels, where 16-byte records take a second round of workgroups (256 -> 8, dilation 3, 88 x 66 x 2: 14.7
 // and 17.4 us); int32 sums of some twenty voxels whose tile the bit-count kernel could not hold and left to the
 // direct one (6.7 and 8.4 us).
-bool launch_conv_matrix(const ConvParams& p, hipStream_t s, int* rc)
+bool launch_conv_matrix(const ConvParams& p, const ConvPair* pair, hipStream_t s, int* rc)
 {
+    MatrixPlan t;
+    t.pair.base = nullptr;
+    if (pair && !pair_plan(*pair, p.n, t.pair)) return false;
     const int64_t taps = (int64_t)p.kd * p.kh * p.kw;
     if (taps > 128 || taps * p.c_in * (p.digits ? 2 : 1) > kMatrixSumLimit) return false;
     const int64_t lds_limit = lds_limit_for_current_device();
@@ -539,10 +607,9 @@ bool launch_conv_matrix(const ConvParams& p, hipStream_t s, int* rc)
     if (q.tiles > 0x7fffffff || gy > 65535) return false;
     // A tile's planes within 4 GB (a volume's may be more).
     const int64_t plane_bytes = 8 * (int64_t)p.wd_in * p.h * p.w;
-    if (plane_bytes > 0xffff0000ll) return false;
-    const int64_t reach = plane_bytes * (q.hz < p.d ? q.hz : p.d);
+    if (!pair && plane_bytes > 0xffff0000ll) return false;
+    const int64_t reach = pair ? t.pair.reach : plane_bytes * (q.hz < p.d ? q.hz : p.d);
     if (reach > 0xffff0000ll) return false;
-    MatrixPlan t;
     t.lxb = c.lxb; t.lyb = c.lyb; t.lwy = log2_up(c.nwy); t.lwz = log2_up(c.nwz); t.nwc = c.nwc;
     t.hx = (int32_t)q.hx; t.hy = (int32_t)q.hy; t.hz = (int32_t)q.hz;
     t.tiles_x = divisor(cdiv(p.ow, X)); t.tiles_y = divisor(cdiv(p.oh, Y * c.nwy)); t.tiles_z = divisor(cdiv(p.od, Z * c.nwz));

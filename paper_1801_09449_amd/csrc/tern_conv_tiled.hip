@@ -901,6 +901,28 @@ void set_lane_tile(int v) { g_lane_tile = v; }
 void set_stream(int v) { g_stream = v ? 1 : 0; }
 void last_launch(int32_t* info) { for (int i = 0; i < 8; ++i) info[i] = g_last[i]; }
 
+// Only the tiled matrix kernel reads two tensors, and only whole pairs of words of one of them at a time.
+bool launch_conv3d_pair(const ConvParams& p_in, const ConvPair& pair_in, hipStream_t s, int* rc)
+{
+    ConvParams p = p_in;
+    ConvPair pair = pair_in;
+    if (overridden() || !p.out_packed || p.digits || p.binary || p.tp_slots || (pair.s[0].wd & 1) || (pair.s[1].wd & 1) ||
+        (g_point && conv_point_applies(p)))
+        return false;
+    // planes without depth neighbours: batch items are more planes, as below, if each source has them in a row
+    if (p.n > 1 && p.kd == 1 && p.sd == 1 && p.pd == 0 && (int64_t)p.n * p.d <= INT32_MAX) {
+        bool rows = true;
+        for (const PairSource& q : pair.s) rows = rows && q.up_log[0] == 0 && q.first[0] == 0 && (q.wd == 0 || q.d == p.d);
+        if (rows) {
+            for (PairSource& q : pair.s) q.d *= p.n;
+            p.d *= p.n;
+            p.od *= p.n;
+            p.n = 1;
+        }
+    }
+    return launch_conv_matrix(p, &pair, s, rc);
+}
+
 int launch_conv3d(const ConvParams& p_in, hipStream_t s)
 {
     if (g_point && !p_in.digits && conv_point_applies(p_in)) {
@@ -935,7 +957,7 @@ int launch_conv3d(const ConvParams& p_in, hipStream_t s)
     // limit of that kernel sends the convolution here.
     if (!overridden()) {
         int rc = TERN_OK;
-        if (launch_conv_matrix(p, s, &rc)) return rc;
+        if (launch_conv_matrix(p, nullptr, s, &rc)) return rc;
     }
     const int lds_limit = lds_limit_for_current_device();
 

@@ -84,6 +84,18 @@ struct ConcatParams {
     uint32_t* out;
 };
 
+// A convolution input that lies in two tensors: the channels of source 0, upsampled, and behind them those
+// of source 1, cropped.  (ConvParams::in is unused then; its extents are those of the joined tensor.)
+struct PairSource {
+    const uint32_t* p;      // packed [N][d][h][w][2][wd]
+    int32_t d, h, w, wd;
+    int32_t up_log[3];      // log2 of the nearest-neighbour factor per axis
+    int32_t first[3];       // coordinate that lands on voxel 0 of the joined tensor
+};
+struct ConvPair {
+    PairSource s[2];
+};
+
 // tern_conv3d_real: ternary codes x float weights.
 struct RealConvParams {
     const uint32_t* in;     // packed [N][D][H][W][2][wd_in]
@@ -133,11 +145,13 @@ int launch_threshold_pack_i32(const int32_t* src, tern_dims dims, const int32_t*
 int launch_threshold_pack_f32(const float* src, tern_dims dims, const float* lo, const float* hi,
                               uint32_t* dst, hipStream_t s);
 int launch_conv3d(const ConvParams& p, hipStream_t s);
+// The same with the input in two tensors (packed output); false: not this way (nothing launched).
+bool launch_conv3d_pair(const ConvParams& p, const ConvPair& pair, hipStream_t s, int* rc);
 // 1x1x1 / stride 1 / no padding with up to 8 input words per plane: the pointwise kernel.
 bool conv_point_applies(const ConvParams& p);
 int launch_conv_point(const ConvParams& p, hipStream_t s);
 // Tiled convolution on the matrix cores; false: not for this convolution (nothing launched).
-bool launch_conv_matrix(const ConvParams& p, hipStream_t s, int* rc);
+bool launch_conv_matrix(const ConvParams& p, const ConvPair* pair, hipStream_t s, int* rc);
 // Records the plan of this thread's convolution launch for tern_last_launch.
 void note_launch(int kind, int v, int cb, int nks, int threads, unsigned gx, unsigned gy, size_t lds);
 // Matrix-core route: byte filter bank and the convolution that takes it as p.wgt.

@@ -412,3 +412,44 @@ def test_net_forward_one_channel_first_module(G):
                                     hi=L["hi"]) for L in f.layers])
     for li, ((t, c), code) in enumerate(zip(kept, want), start=1):
         np.testing.assert_array_equal(G.words(t), oracle.pack(code), err_msg=f"module {li}")
+
+
+@pytest.mark.parametrize("vol,ca,cs,k0,kj,up,stride,pad", [
+    ((1, 23, 30), 64, 64, (1, 3, 3), (1, 3, 3), (1, 2, 2), (1, 1, 1), (0, 0, 0)),      # a decoder step; planes of the batch as one stack
+    ((1, 40, 27), 128, 50, (1, 3, 3), (1, 3, 3), (1, 1, 4), (1, 1, 1), (0, 1, 1)),     # a last skip word part empty; padded
+    ((5, 12, 9), 64, 128, (3, 3, 3), (3, 3, 3), (2, 2, 2), (1, 1, 1), (1, 1, 1)),      # a volume, cropped along z
+    ((4, 9, 11), 192, 64, (3, 3, 3), (3, 3, 3), (1, 2, 1), (2, 2, 1), (1, 0, 1)),      # strided
+    ((3, 10, 10), 64, 64, (1, 3, 3), (1, 3, 3), (2, 2, 2), (1, 1, 1), (0, 0, 0)),      # no depth taps but upsampled along z
+    ((1, 15, 14), 64, 0, (1, 3, 3), (1, 3, 3), (1, 2, 2), (1, 1, 1), (0, 1, 1)),       # upsampled, no skip
+    ((1, 15, 14), 64, 64, (1, 3, 3), (1, 3, 3), (1, 3, 2), (1, 1, 1), (0, 0, 0)),      # a factor of three: joined in memory first
+    ((1, 15, 14), 32, 32, (1, 3, 3), (1, 3, 3), (1, 2, 2), (1, 1, 1), (0, 0, 0)),      # odd word counts: likewise
+    ((1, 15, 14), 64, 64, (1, 3, 3), (1, 1, 1), (1, 2, 2), (1, 1, 1), (0, 0, 0)),      # a single tap: likewise
+])
+def test_net_forward_reads_upsampled_and_skipped_input(G, vol, ca, cs, k0, kj, up, stride, pad):
+    """A module whose input is an upsampled tensor with the channels of a cropped one behind it, as the
+    convolution reads it from both, against the oracle on the joined tensor."""
+    import torch
+    from paper_1801_09449_amd import unet
+    n, seed = 3, 40 + ca + cs + vol[1]
+    half = np.array([0.5, 0.5], np.float32)
+    big = tuple(v * u + a for v, u, a in zip(vol, up, (0 if vol[0] == 1 else 1, 3, 2)))
+    # module 1 makes the skip, larger than the upsampled tensor; module 2 goes down to `vol`
+    xb = synth.gaussian((n, 2) + big, seed, synth.T_F32)
+    same = tuple(kk // 2 for kk in k0)
+    kshrink = tuple(b - (v - 1) * u for b, v, u in zip(big, vol, up))
+    spec = [(max(cs, 16), 2, k0, (1, 1, 1), same, dict(save="a")),
+            (ca, max(cs, 16), kshrink, up, (0, 0, 0), dict()),
+            (40, ca + cs, kj, stride, pad, dict(up=up, concat="a" if cs else None))]
+    layers = []
+    for li, (co, ci, k, st, pd, extra) in enumerate(spec, start=1):
+        w = synth.ternary((co, ci) + k, 0.5, seed, synth.T_WGT + 8 * li)
+        lo, hi = synth.bn_like_thresholds(co, int(np.prod(k)), ci, 0.5, 0.6, seed, synth.T_THR + 8 * li)
+        layers.append(dict(w=w, k=k, stride=st, pad=pd, lo=lo, hi=hi, pool=None, up=extra.get("up"),
+                           concat=extra.get("concat"), save=extra.get("save")))
+    plan = unet.UNetPlan(layers, None, None, -half, half)
+    _, kept = unet.unet_forward(plan, G.dev(xb), keep_layers=True)
+    torch.cuda.synchronize()
+    codes, _ = oracle.unet_forward(xb, -half, half, layers, None, None)
+    for li, ((t, c), want) in enumerate(zip(kept, codes), start=1):
+        np.testing.assert_array_equal(G.words(t), oracle.pack(want), err_msg=f"module {li}")
+    assert len(np.unique(codes[-1])) == 3
