@@ -524,10 +524,10 @@ static int fcn_run(const float* in, tern_dims in_dims, const float* in_lo, const
         pp.sh = g.stride[1]; pp.sw = g.stride[2];
         pp.pd = g.pad[0]; pp.ph = g.pad[1]; pp.pw = g.pad[2];
         pp.dh = g.dil[1]; pp.dw = g.dil[2];
-        // layer 0 runs behind the gathering in the same kernel (below) where that pays; the
-        // region reserved for the tap strings then stays unused
+        // one launch from the intensities to layer 0's codes (below) unless its taps lie too far apart for
+        // that kernel; the region reserved for the tap strings then stays unused
         first = pp;
-        fused = patch_conv_pays(pp, in_dims.n);
+        fused = first_conv_applies(pp, in_dims.n, layers[0].c_out);
         rc = fused ? TERN_OK : launch_patch_pack_f32(pp, in_dims.n, (hipStream_t)stream);
     } else {
         ws += (tern_packed_bytes(in_dims) + 255u) & ~(size_t)255u;
@@ -560,7 +560,7 @@ static int fcn_run(const float* in, tern_dims in_dims, const float* in_lo, const
             fc.out_packed = dst;
             fc.c_out = layers[0].c_out; fc.co_pad = (layers[0].c_out + 31) / 32 * 32;
             fc.wd_out = tern_words(layers[0].c_out);
-            rc = launch_patch_conv_f32(first, fc, in_dims.n, (hipStream_t)stream);
+            rc = launch_first_conv(first, fc, in_dims.n, (hipStream_t)stream);
         } else {
             rc = tern_conv3d(cur_buf, cur, layers[i].w_bank, layers[i].c_out, layers[i].g,
                              layers[i].thr_lo, layers[i].thr_hi, nullptr, dst, stream);
@@ -720,10 +720,10 @@ int net_walk(tern_dims in_dims, const tern_module* mods, int32_t n_mods, NetWalk
             pp.sh = g.stride[1]; pp.sw = g.stride[2];
             pp.pd = g.pad[0]; pp.ph = g.pad[1]; pp.pw = g.pad[2];
             pp.dh = g.dil[1]; pp.dw = g.dil[2];
-            // module 0 runs behind the gathering in the same kernel (below) where that pays; the
-            // region reserved for the tap strings then stays unused
+            // one launch from the intensities to module 0's codes (below) unless its taps lie too far apart
+            // for that kernel; the region reserved for the tap strings then stays unused
             first = pp;
-            fused = patch_conv_pays(pp, in_dims.n);
+            fused = first_conv_applies(pp, in_dims.n, mods[0].c_out);
             rc = fused ? TERN_OK : launch_patch_pack_f32(pp, in_dims.n, w->stream);
         } else {
             rc = tern_threshold_pack(w->in, TERN_SRC_F32, in_dims, w->in_lo, w->in_hi,
@@ -822,14 +822,13 @@ int net_walk(tern_dims in_dims, const tern_module* mods, int32_t n_mods, NetWalk
                                                (uint32_t*)(w->ws + ooff[(size_t)i])),
                                    w->stream);
             } else if (i == 0 && gathered) {
-                // gathering and single-tap convolution over the gathered words in one kernel
                 if (!aligned16(m.w_bank)) return TERN_EARG;
                 FirstConvParams fc;
                 fc.wgt = m.w_bank; fc.lo = m.thr_lo; fc.hi = m.thr_hi;
                 fc.out_packed = (uint32_t*)(w->ws + ooff[(size_t)i]);
                 fc.c_out = m.c_out; fc.co_pad = (m.c_out + 31) / 32 * 32;
                 fc.wd_out = tern_words(m.c_out);
-                rc = launch_patch_conv_f32(first, fc, in_dims.n, w->stream);
+                rc = launch_first_conv(first, fc, in_dims.n, w->stream);
             } else if (pooled) {
                 rc = tern_conv3d_digits((const uint32_t*)(w->ws + cur_off), cur, m.w_bank, m.c_out, m.g,
                                         m.thr_lo, m.thr_hi, nullptr, (uint32_t*)(w->ws + ooff[(size_t)i]),

@@ -121,8 +121,8 @@ struct PatchParams {
 // that route.
 bool patch_pack_applies(int32_t c_in, const tern_conv_geom& g, const tern_dims& out);
 int launch_patch_pack_f32(const PatchParams& p, int32_t n, hipStream_t s);
-// Layer 0 behind the gathering, in the same kernel (PatchParams::dst unused): single-tap filter
-// bank over the gathered words, integer cut points, packed output [N][od][oh][ow][2][wd_out].
+// Layer 0 from the intensities in one launch (tern_first_layer.hip; PatchParams::dst unused): tap-packed filter
+// bank, integer cut points, packed output [N][od][oh][ow][2][wd_out].
 struct FirstConvParams {
     const uint32_t* wgt;    // [words of the tap string][co_pad][2][1]
     const int32_t* lo;      // [c_out]
@@ -130,8 +130,8 @@ struct FirstConvParams {
     uint32_t* out_packed;
     int32_t c_out, co_pad, wd_out;
 };
-int launch_patch_conv_f32(const PatchParams& p, const FirstConvParams& c, int32_t n, hipStream_t s);
-bool patch_conv_pays(const PatchParams& p, int32_t n);
+int launch_first_conv(const PatchParams& p, const FirstConvParams& c, int32_t n, hipStream_t s);
+bool first_conv_applies(const PatchParams& p, int32_t n, int32_t c_out);
 
 // Largest dynamic LDS allocation the current device grants one workgroup, at most the 160 KB of a
 // gfx950 compute unit (queried once per device; 0 on error).

@@ -70,14 +70,15 @@ __device__ __forceinline__ void decide(uint32_t& pos, uint32_t& neg, float acc, 
     neg = __builtin_amdgcn_alignbit(neg, __float_as_uint(acc + width), 32 - BITS);
 }
 
-// The decisions of a 32 x 32 block, register v = filter 8 (v / 4) + 4 g + v % 4: widths come four at a
-// time from LDS (for the lane's own half g), highest filter first, so that filter 8 k + 4 g + j ends up at
-// bit 8 k + j.
-__device__ __forceinline__ void decide_block(uint32_t& pos, uint32_t& neg, const v16f& acc, const float* widths)
+// The decisions of a 32 x 32 block (K = 4) or of its first 8 K rows, register v = filter 8 (v / 4) + 4 g + v % 4:
+// widths come four at a time from LDS (for the lane's own half g), highest filter first, so that filter
+// 8 k + 4 g + j ends up at bit 8 k + j.
+template <int K>
+__device__ __forceinline__ void decide_rows(uint32_t& pos, uint32_t& neg, const v16f& acc, const float* widths)
 {
     pos = neg = 0u;
 #pragma unroll
-    for (int k = 3; k >= 0; --k) {
+    for (int k = K - 1; k >= 0; --k) {
         const float4 w = *reinterpret_cast<const float4*>(widths + 8 * k);
         decide<1>(pos, neg, acc[4 * k + 3], w.w);
         decide<1>(pos, neg, acc[4 * k + 2], w.z);
@@ -86,16 +87,23 @@ __device__ __forceinline__ void decide_block(uint32_t& pos, uint32_t& neg, const
         else decide<1>(pos, neg, acc[4 * k], w.x);
     }
 }
+__device__ __forceinline__ void decide_block(uint32_t& pos, uint32_t& neg, const v16f& acc, const float* widths)
+{
+    decide_rows<4>(pos, neg, acc, widths);
+}
 
 // pos / neg as decide_block leaves them to packed words, lane = voxel l % 32: lanes 0-31 get the voxels'
 // mask words, lanes 32-63 their sign words (+1 wins where both decisions hold).
-__device__ __forceinline__ uint32_t block_word(uint32_t pos, uint32_t neg)
+template <uint32_t MASK>
+__device__ __forceinline__ uint32_t word_of(uint32_t pos, uint32_t neg)
 {
-    const uint32_t m = __builtin_amdgcn_bitop3_b32(pos, neg, 0x0f0f0f0fu, 0x8a);   // (~pos | neg) & mask
-    const uint32_t s = __builtin_amdgcn_bitop3_b32(pos, neg, 0x0f0f0f0fu, 0x80);   // pos & neg & mask
+    const uint32_t m = __builtin_amdgcn_bitop3_b32(pos, neg, MASK, 0x8a);          // (~pos | neg) & mask
+    const uint32_t s = __builtin_amdgcn_bitop3_b32(pos, neg, MASK, 0x80);          // pos & neg & mask
     const auto sw = __builtin_amdgcn_permlane32_swap(m, s, false, false);
     return sw[0] | (sw[1] << 4);                                                   // both halves' filters
 }
+__device__ __forceinline__ uint32_t block_word(uint32_t pos, uint32_t neg) { return word_of<0x0f0f0f0fu>(pos, neg); }
+__device__ __forceinline__ uint32_t half_block_word(uint32_t pos, uint32_t neg) { return word_of<0x00000f0fu>(pos, neg); }
 
 }  // namespace
 }  // namespace tern
