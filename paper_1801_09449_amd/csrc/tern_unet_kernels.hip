@@ -6,6 +6,7 @@
 //   - real_conv_kernel: cross-correlation of ternary codes with float weights (+ bias).
 // Both are small HBM streams next to the convolutions; neither uses LDS.
 #include "tern_internal.h"
+#include "tern_matrix_choice.h"
 
 namespace tern {
 namespace {
@@ -329,6 +330,190 @@ __global__ __launch_bounds__(kBlock) void real_conv_lut_kernel(RealConvParams p,
     }
 }
 
+// The same convolution on the matrix cores: v_mfma_f32_16x16x32_bf16 over 16 voxels (columns) and 32 channels of a
+// tap.  A weight is the sum of three bf16 numbers (8 + 8 + 8 bits, cut off: exactly it), rows 4 f, 4 f + 1 and
+// 4 f + 2 of filter f's operand, and a code is the bf16 number +-2 or 0, so every product is exact; the three
+// sums of an output are floats of one lane and are added last, smallest first.  Sums differ from the kernels
+// above in their order alone (576 terms, normal weights: off by 4e-8 of the result's norm, table sums 2.7e-7).
+//
+// What bounds it: on one U-Net stack (20 thousand voxels) a round trip for the weights, one for the records and
+// the launch; on sixteen the widening of the codes, twelve vector instructions for each matrix instruction.
+// BYTES(one stack, sixteen): tables MEASURED_BEFORE, this MEASURED_NOW.
+//
+// Zero codes times an infinity would be NaN, which they are not in the table sums, and pieces of the smallest floats
+// would be lost: a workgroup that meets a weight that is not 0 and outside 2^-100 .. 2^100 adds one by one.
+typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef uint32_t v2w __attribute__((ext_vector_type(2)));
+typedef uint32_t v4w __attribute__((ext_vector_type(4)));
+
+struct RealMatrixPlan {
+    Divisor ow, oh, od;
+    Divisor taps, filter;        // taps of a (filter, channel); elements of a filter, padded channels included
+    int32_t words;               // channel words of a voxel
+};
+
+__device__ __forceinline__ int quot(int e, Divisor d) { return (int)(((uint64_t)(uint32_t)e * d.m) >> d.s); }
+
+// PAIR: two channel words of a voxel at a time (WD == 2: its whole record), else one.  NV: blocks of 16 voxels a wave.
+template <int WD, bool PADDED, int NV>
+__global__ __launch_bounds__(kBlock) void real_conv_matrix_kernel(RealConvParams p, RealMatrixPlan t)
+{
+    extern __shared__ __align__(16) uint8_t wl8[];
+    constexpr int UW = WD == 2 ? 2 : 1;                   // words of a unit of work
+    constexpr int BATCH = 9;                              // units whose records are under way together
+    const int tid = threadIdx.x, lane = tid & 63, col = lane & 15, q4 = lane >> 4;
+    const int T = p.kd * p.kh * p.kw;
+    const int units = T * (t.words / UW);
+    const uint32_t rec = 8u * (uint32_t)t.words;
+
+    // ---- this lane's voxels ----------------------------------------------------------------------------
+    int vox[NV], ix0[NV], iy0[NV], iz0[NV];
+    uint32_t off[NV];                                     // bytes of tap (0, 0, 0)'s record (unpadded: it exists)
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+        vox[v] = (int)min((int64_t)blockIdx.x * (4 * NV * 16) + ((tid >> 6) * NV + v) * 16 + col, p.total - 1);
+        const int r = quot(vox[v], t.ow), x = vox[v] - r * t.ow.d;
+        const int r2 = quot(r, t.oh), y = r - r2 * t.oh.d;
+        const int n = quot(r2, t.od), z = r2 - n * t.od.d;
+        ix0[v] = x * p.sw - p.pw; iy0[v] = y * p.sh - p.ph; iz0[v] = z * p.sd - p.pd;
+        off[v] = (uint32_t)(((n * p.d + iz0[v]) * p.h + iy0[v]) * p.w + ix0[v]) * rec;
+    }
+    struct Unit { int tap, a, b, c, word; };
+    auto next = [&](Unit& u) {                            // (the same for all lanes)
+        if ((u.word += UW) < t.words) return;
+        u.word = 0;
+        ++u.tap;
+        if (++u.c == p.kw) { u.c = 0; if (++u.b == p.kh) { u.b = 0; ++u.a; } }
+    };
+    uint32_t m[BATCH][NV][UW], s[BATCH][NV][UW];
+    auto fetch = [&](Unit& u, int count) {
+#pragma unroll
+        for (int k = 0; k < BATCH; ++k) {
+            if (k < count) {
+                const int64_t at = ((int64_t)(u.a * p.dd * p.h + u.b * p.dh) * p.w + u.c * p.dw) * rec + 4 * u.word;
+#pragma unroll
+                for (int v = 0; v < NV; ++v) {
+                    bool inb = true;
+                    if constexpr (PADDED)
+                        inb = (uint32_t)(iz0[v] + u.a * p.dd) < (uint32_t)p.d && (uint32_t)(iy0[v] + u.b * p.dh) < (uint32_t)p.h &&
+                              (uint32_t)(ix0[v] + u.c * p.dw) < (uint32_t)p.w;
+                    const uint8_t* from = reinterpret_cast<const uint8_t*>(p.in);
+                    if constexpr (PADDED) from += inb ? off[v] + (uint32_t)at : 0u;
+                    else from = from + at + off[v];
+                    if constexpr (WD == 2) {
+                        const v4w r = *reinterpret_cast<const v4w*>(from);
+                        m[k][v][0] = inb ? r.x : 0u; m[k][v][1] = inb ? r.y : 0u;
+                        s[k][v][0] = r.z; s[k][v][1] = r.w;
+                    } else {
+                        const uint32_t* w = reinterpret_cast<const uint32_t*>(from);
+                        m[k][v][0] = inb ? w[0] : 0u;
+                        s[k][v][0] = w[t.words];
+                    }
+                }
+                next(u);
+            }
+        }
+    };
+    // Codes of 32 channels -> this lane's eight of them as bf16 numbers +-2 or 0 (signs without a mask become -0):
+    // channels 4 q4 + {0, 16, 2, 18, 1, 17, 3, 19}.
+    const uint32_t m55 = 0x55555555u, mc0 = 0xc000c000u, sh = 14u - 4u * (uint32_t)q4;
+    auto widen = [&](uint32_t mw, uint32_t sw) {
+        const uint32_t even = __builtin_amdgcn_bitop3_b32(m55, mw, sw << 1, 0xca);   // mask at 2 k, sign at 2 k + 1
+        const uint32_t odd = __builtin_amdgcn_bitop3_b32(m55, mw >> 1, sw, 0xca);
+        v4w o;
+        o.x = (even << sh) & mc0;
+        o.y = (even << (sh - 2u)) & mc0;
+        o.z = (odd << sh) & mc0;
+        o.w = (odd << (sh - 2u)) & mc0;
+        return __builtin_bit_cast(v8bf, o);
+    };
+
+    for (int co0 = 0; co0 < p.c_out; co0 += 4) {
+        const int cg = min(4, p.c_out - co0);
+        Unit u = {0, 0, 0, 0, 0};
+        fetch(u, min(BATCH, units));
+        // ---- the filters' operands: [unit word][lane][8] bf16 -------------------------------------------
+        if (co0 > 0) __syncthreads();
+        bool odd_weight = false;
+        for (int i = tid; i < cg * t.filter.d; i += kBlock) {
+            const int f = quot(i, t.filter), e = i - f * t.filter.d;
+            const int c = quot(e, t.taps), tap = e - c * T;
+            const float w = c < p.c_in ? p.wgt[((size_t)(co0 + f) * p.c_in + c) * T + tap] : 0.0f;
+            const uint32_t bits = __float_as_uint(w), ex = (bits >> 23) & 255u;
+            odd_weight |= (bits << 1) != 0u && (ex < 27u || ex > 227u);
+            const float hi = __uint_as_float(bits & 0xffff0000u), rest = w - hi;
+            const float mid = __uint_as_float(__float_as_uint(rest) & 0xffff0000u), low = rest - mid;
+            const int cc = c & 31, j = 2 * ((cc & 1) * 2 + ((cc >> 1) & 1)) + (cc >> 4);
+            const int slot = (tap * t.words + (c >> 5)) * 64 + ((cc >> 2) & 3) * 16 + 4 * f;
+            uint16_t* at = reinterpret_cast<uint16_t*>(wl8) + slot * 8 + j;
+            at[0] = (uint16_t)(bits >> 16);
+            at[8] = (uint16_t)(__float_as_uint(mid) >> 16);
+            at[16] = (uint16_t)(__float_as_uint(low) >> 16);
+        }
+        const bool one_by_one = __syncthreads_or(odd_weight ? 1 : 0) != 0;
+        float sum[NV];
+        if (!one_by_one) {
+            // (rows of filters that do not exist and every fourth row hold anything: nobody reads their sums)
+            v4f acc[NV];
+#pragma unroll
+            for (int v = 0; v < NV; ++v) acc[v] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+            const uint8_t* a_at = wl8 + lane * 16;
+            int done = 0;
+            while (true) {
+                const int count = min(BATCH, units - done);
+#pragma unroll
+                for (int k = 0; k < BATCH; ++k)
+                    if (k < count)
+#pragma unroll
+                        for (int w = 0; w < UW; ++w) {
+                            const v8bf a = *reinterpret_cast<const v8bf*>(a_at);
+                            a_at += 1024;
+#pragma unroll
+                            for (int v = 0; v < NV; ++v)
+                                acc[v] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, widen(m[k][v][w], s[k][v][w]), acc[v], 0, 0, 0);
+                        }
+                done += count;
+                if (done >= units) break;
+                fetch(u, min(BATCH, units - done));
+            }
+#pragma unroll
+            for (int v = 0; v < NV; ++v) sum[v] = 0.5f * ((acc[v][2] + acc[v][1]) + acc[v][0]);
+        } else {
+#pragma unroll
+            for (int v = 0; v < NV; ++v) sum[v] = 0.0f;
+            const float* wf = p.wgt + (size_t)(co0 + min(q4, cg - 1)) * p.c_in * T;
+            Unit x = {0, 0, 0, 0, 0};
+            for (int i = 0; i < units; ++i) {
+                Unit at = x;
+                fetch(x, 1);
+#pragma unroll
+                for (int w = 0; w < UW; ++w) {
+                    const int live = min(32, p.c_in - 32 * (at.word + w));
+                    for (int j = 0; j < live; ++j) {
+                        const float wv = wf[(size_t)(32 * (at.word + w) + j) * T + at.tap];
+#pragma unroll
+                        for (int v = 0; v < NV; ++v)
+                            if ((m[0][v][w] >> j) & 1u) sum[v] += (s[0][v][w] >> j) & 1u ? -wv : wv;
+                    }
+                }
+            }
+        }
+        if (q4 < cg) {
+            const float b = p.bias ? p.bias[co0 + q4] : 0.0f;
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                const int64_t at = (int64_t)blockIdx.x * (4 * NV * 16) + ((tid >> 6) * NV + v) * 16 + col;
+                if (at < p.total) {
+                    const int n = quot(quot(quot(vox[v], t.ow), t.oh), t.od);
+                    const size_t ospatial = (size_t)p.od * p.oh * p.ow;
+                    p.out[((size_t)n * p.c_out + co0 + q4) * ospatial + (vox[v] - (size_t)n * ospatial)] = sum[v] + b;
+                }
+            }
+        }
+    }
+}
+
 // Per-channel code statistics of a packed tensor (the paper reports how sparse weights and
 // activations become, section 4).  A wave takes 64 voxels at a time; for every channel bit the
 // wave-wide vote of "this voxel's bit is set" is counted, lane j keeping the running nonzero
@@ -486,8 +671,37 @@ int launch_concat(const ConcatParams& p, hipStream_t s)
     return TERN_OK;
 }
 
+// The matrix kernel where its operands fit in 64 KB and 32 bits count the input's bytes and the output's voxels.
+static bool launch_real_matrix(const RealConvParams& p, hipStream_t s)
+{
+    const int64_t taps = (int64_t)p.kd * p.kh * p.kw, in_items = p.total / ((int64_t)p.od * p.oh * p.ow);
+    if (taps * p.wd_in > 64 || p.total > 0x7fffffff || in_items * p.d * p.h * p.w * p.wd_in * 8 > 0x7fffffff) return false;
+    RealMatrixPlan t;
+    t.ow = divisor(p.ow); t.oh = divisor(p.oh); t.od = divisor(p.od);
+    t.taps = divisor((int32_t)taps); t.filter = divisor((int32_t)(taps * 32 * p.wd_in));
+    t.words = p.wd_in;
+    const bool padded = p.pd || p.ph || p.pw;
+    const size_t lds = (size_t)(taps * p.wd_in) * 1024;
+    // Two blocks of voxels to a wave once every SIMD has two waves with them.
+    const bool two = p.total >= 2 * 2 * 16 * 1024;
+    const unsigned blocks = (unsigned)((p.total + (two ? 128 : 64) - 1) / (two ? 128 : 64));
+    const auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(blocks), dim3(kBlock), lds, s, p, t); };
+    if (p.wd_in == 2) {
+        if (padded) two ? go(real_conv_matrix_kernel<2, true, 2>) : go(real_conv_matrix_kernel<2, true, 1>);
+        else two ? go(real_conv_matrix_kernel<2, false, 2>) : go(real_conv_matrix_kernel<2, false, 1>);
+    } else {
+        if (padded) two ? go(real_conv_matrix_kernel<1, true, 2>) : go(real_conv_matrix_kernel<1, true, 1>);
+        else two ? go(real_conv_matrix_kernel<1, false, 2>) : go(real_conv_matrix_kernel<1, false, 1>);
+    }
+    return true;
+}
+
 int launch_real_conv(const RealConvParams& p, hipStream_t s)
 {
+    if (launch_real_matrix(p, s)) {
+        TERN_HIP_CHECK(hipGetLastError());
+        return TERN_OK;
+    }
     const int64_t blocks = (p.total + kBlock - 1) / kBlock;
     if (blocks > 0x7fffffff) return TERN_ESHAPE;
     const int cg = p.c_out <= 2 ? 2 : 4;

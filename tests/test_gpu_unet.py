@@ -176,6 +176,52 @@ def test_conv3d_real(G, ci, co, vol, k, stride, pad, dil):
     np.testing.assert_array_equal(goti, exact.astype(np.float32))
 
 
+@pytest.mark.parametrize("ci,co,vol,k,stride,pad,dil", [
+    (64, 2, (1, 260, 258), (1, 3, 3), 1, 0, 1),             # two blocks of voxels to a wave
+    (64, 9, (1, 259, 255), (1, 3, 3), 1, (0, 1, 1), 1),     # the same padded; three groups of filters, the last one filter
+    (32, 4, (3, 9, 10), (3, 3, 3), 1, 1, 1),
+    (96, 3, (2, 5, 6), (1, 3, 3), (1, 2, 1), (0, 2, 1), (1, 1, 2)),
+    (33, 1, (1, 1, 1), (1, 1, 1), 1, 0, 1),                 # one voxel
+    (20, 2, (4, 9, 9), (4, 4, 4), 1, 0, 1),                 # 64 operand blocks, the most that fit
+    (20, 2, (5, 13, 7), (5, 13, 1), 1, 0, 1),               # 65: table sums
+])
+def test_conv3d_real_matrix_blocks(G, ci, co, vol, k, stride, pad, dil):
+    """The prediction layer on the matrix cores, and weights over fifty orders of magnitude: each is three bf16
+    numbers exactly, so the bound of a 32-bit sum holds whatever the range."""
+    import paper_1801_09449_amd as T
+    t3 = lambda v: (v,) * 3 if isinstance(v, int) else tuple(v)
+    x = tern((2, ci) + vol, 29)
+    for spread in (0.0, 25.0):
+        w = synth.gaussian((co, ci) + k, 29, synth.T_F32)
+        w *= np.float32(10.0) ** (spread * np.tanh(synth.gaussian((co, ci) + k, 30, synth.T_F32))).astype(np.float32)
+        b = synth.gaussian((co,), 31, synth.T_F32)
+        want = oracle.conv3d_real(x, w, b, t3(stride), t3(pad), t3(dil))
+        got = T.tern_conv3d_real(gpu_pack(G, x), ci, G.dev(w), G.dev(b), stride, pad, dil).cpu().numpy()
+        bound = real_conv_bound(w, b)[None, :, None, None, None]
+        assert (np.abs(got.astype(np.float64) - want) <= bound).all()
+
+
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan, 3e38, 1e-40, 0.0])
+def test_conv3d_real_special_weights(G, value):
+    """A zero code takes no part, whatever its weight; the smallest floats are not lost."""
+    import paper_1801_09449_amd as T
+    x = tern((2, 40, 1, 12, 11), 33)
+    w = synth.gaussian((5, 40, 1, 3, 3), 33, synth.T_F32) * (1e-38 if value == 1e-40 else 1)
+    w[1, 7, 0, 1, 2] = w[4, 39, 0, 0, 0] = value
+    got = T.tern_conv3d_real(gpu_pack(G, x), 40, G.dev(w), None, 1, 0, 1).cpu().numpy().astype(np.float64)
+    finite = np.where(np.isfinite(w), w, np.float32(0.0))
+    want = oracle.conv3d_real(x, finite, None, (1,) * 3, (0,) * 3, (1,) * 3).astype(np.float64)
+    odd = np.zeros_like(want)                                       # what the two odd weights add
+    if not np.isfinite(value):
+        for o, c, (b, a) in ((1, 7, (1, 2)), (4, 39, (0, 0))):
+            code = x[:, c, :, b:b + want.shape[3], a:a + want.shape[4]]
+            odd[:, o] = np.where(code == 0, 0.0, code * np.float64(value))
+    bound = real_conv_bound(finite, np.zeros(5, np.float32))[None, :, None, None, None]
+    plain = odd == 0
+    assert (np.abs(got - want)[plain] <= np.broadcast_to(bound, want.shape)[plain]).all()
+    np.testing.assert_array_equal(got[~plain], odd[~plain])
+
+
 # ---- code statistics ---------------------------------------------------------------------------------
 @pytest.mark.parametrize("n,c,vol", [(1, 1, (1, 1, 1)), (2, 5, (3, 5, 7)), (1, 33, (4, 9, 11)), (3, 64, (2, 8, 8)),
                                      (1, 100, (5, 13, 6)), (2, 256, (3, 4, 5)), (1, 16, (40, 64, 70))])
