@@ -5,6 +5,8 @@
 //     upsampling and cropping map onto it, and lays the sources' channel bits side by side;
 //   - real_conv_kernel: cross-correlation of ternary codes with float weights (+ bias).
 // Both are small HBM streams next to the convolutions; neither uses LDS.
+#include <type_traits>
+
 #include "tern_internal.h"
 #include "tern_matrix_choice.h"
 
@@ -337,8 +339,8 @@ __global__ __launch_bounds__(kBlock) void real_conv_lut_kernel(RealConvParams p,
 // above in their order alone (576 terms, normal weights: off by 4e-8 of the result's norm, table sums 2.7e-7).
 //
 // What bounds it: on one U-Net stack (20 thousand voxels) a round trip for the weights, one for the records and
-// the launch; on sixteen the widening of the codes, twelve vector instructions for each matrix instruction.
-// BYTES(one stack, sixteen): tables MEASURED_BEFORE, this MEASURED_NOW.
+// the launch; on sixteen the vector instructions around the matrix ones (addresses, twelve to widen the codes).
+// Measured, 64 -> 2 channels, 3 x 3: 20 thousand voxels 17.6 us with tables, 6.0 here; 323 thousand 25.5 and 20.2.
 //
 // Zero codes times an infinity would be NaN, which they are not in the table sums, and pieces of the smallest floats
 // would be lost: a workgroup that meets a weight that is not 0 and outside 2^-100 .. 2^100 adds one by one.
@@ -350,76 +352,88 @@ typedef uint32_t v4w __attribute__((ext_vector_type(4)));
 struct RealMatrixPlan {
     Divisor ow, oh, od;
     Divisor taps, filter;        // taps of a (filter, channel); elements of a filter, padded channels included
-    int32_t words;               // channel words of a voxel
+    Reciprocal kw, kh, words;    // divisions of unit numbers
+    int32_t tiles;
+    uint32_t bytes;              // of the input
 };
 
 __device__ __forceinline__ int quot(int e, Divisor d) { return (int)(((uint64_t)(uint32_t)e * d.m) >> d.s); }
+__device__ __forceinline__ int quot(int e, Reciprocal r) { return (int)(__umul24((uint32_t)e, r.m) >> r.s); }
 
-// PAIR: two channel words of a voxel at a time (WD == 2: its whole record), else one.  NV: blocks of 16 voxels a wave.
-template <int WD, bool PADDED, int NV>
+// A unit of work: a tap's whole record (WD == 2) or one channel word of it, of 16 voxels.  BATCH units' records are
+// under way together, and every batch is a whole one: units past the last read zeros.
+// NV: blocks of 16 voxels to a wave.
+template <int WD, bool PADDED, int BATCH, int NV>
 __global__ __launch_bounds__(kBlock) void real_conv_matrix_kernel(RealConvParams p, RealMatrixPlan t)
 {
     extern __shared__ __align__(16) uint8_t wl8[];
-    constexpr int UW = WD == 2 ? 2 : 1;                   // words of a unit of work
-    constexpr int BATCH = 9;                              // units whose records are under way together
+    constexpr int UW = WD == 2 ? 2 : 1;                   // words of a unit
+    constexpr int TILE = 4 * NV * 16;
+    constexpr uint32_t NOTHING = 0x80000000u;             // past the input's end: reads as zeros
     const int tid = threadIdx.x, lane = tid & 63, col = lane & 15, q4 = lane >> 4;
     const int T = p.kd * p.kh * p.kw;
-    const int units = T * (t.words / UW);
-    const uint32_t rec = 8u * (uint32_t)t.words;
+    const int units = T * p.wd_in / UW;                   // at most 64
+    const uint32_t rec = 8u * (uint32_t)p.wd_in;
 
-    // ---- this lane's voxels ----------------------------------------------------------------------------
-    int vox[NV], ix0[NV], iy0[NV], iz0[NV];
-    uint32_t off[NV];                                     // bytes of tap (0, 0, 0)'s record (unpadded: it exists)
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-        vox[v] = (int)min((int64_t)blockIdx.x * (4 * NV * 16) + ((tid >> 6) * NV + v) * 16 + col, p.total - 1);
-        const int r = quot(vox[v], t.ow), x = vox[v] - r * t.ow.d;
-        const int r2 = quot(r, t.oh), y = r - r2 * t.oh.d;
-        const int n = quot(r2, t.od), z = r2 - n * t.od.d;
-        ix0[v] = x * p.sw - p.pw; iy0[v] = y * p.sh - p.ph; iz0[v] = z * p.sd - p.pd;
-        off[v] = (uint32_t)(((n * p.d + iz0[v]) * p.h + iy0[v]) * p.w + ix0[v]) * rec;
+    // lane u holds where unit u's record starts, from tap (0, 0, 0)'s, and its tap's steps in z, y and x
+    uint32_t unit_off = NOTHING;
+    int unit_z, unit_y, unit_x;
+    {
+        const int u = min(lane, units - 1);
+        const int tap = UW == 2 ? u : quot(u, t.words), word = UW == 2 ? 0 : u - tap * p.wd_in;
+        const int r = quot(tap, t.kw), a = quot(r, t.kh);
+        unit_z = a * p.dd; unit_y = (r - a * p.kh) * p.dh; unit_x = (tap - r * p.kw) * p.dw;
+        if (lane < units) unit_off = (uint32_t)((unit_z * p.h + unit_y) * p.w + unit_x) * rec + 4u * (uint32_t)word;
     }
-    struct Unit { int tap, a, b, c, word; };
-    auto next = [&](Unit& u) {                            // (the same for all lanes)
-        if ((u.word += UW) < t.words) return;
-        u.word = 0;
-        ++u.tap;
-        if (++u.c == p.kw) { u.c = 0; if (++u.b == p.kh) { u.b = 0; ++u.a; } }
+
+    int vox[NV], ix0[NV], iy0[NV], iz0[NV];
+    uint32_t off[NV];                                     // bytes of tap (0, 0, 0)'s record, modulo 2^32
+    auto enter = [&](int tile) {
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            vox[v] = (int)min((int64_t)tile * TILE + ((tid >> 6) * NV + v) * 16 + col, p.total - 1);
+            const int r = quot(vox[v], t.ow), x = vox[v] - r * t.ow.d;
+            const int r2 = quot(r, t.oh), y = r - r2 * t.oh.d;
+            const int n = quot(r2, t.od), z = r2 - n * t.od.d;
+            ix0[v] = x * p.sw - p.pw; iy0[v] = y * p.sh - p.ph; iz0[v] = z * p.sd - p.pd;
+            off[v] = (uint32_t)(((n * p.d + iz0[v]) * p.h + iy0[v]) * p.w + ix0[v]) * rec;
+        }
+    };
+    const __amdgpu_buffer_rsrc_t src = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(p.in), 0, t.bytes, 0x00020000);
+    auto address = [&](int u, int v) {                    // (u: the same for all lanes)
+        uint32_t o = off[v] + (u < 64 ? (uint32_t)__builtin_amdgcn_readlane((int)unit_off, u & 63) : NOTHING);
+        if constexpr (PADDED) {
+            const bool inb = (uint32_t)(iz0[v] + __builtin_amdgcn_readlane(unit_z, u & 63)) < (uint32_t)p.d &&
+                             (uint32_t)(iy0[v] + __builtin_amdgcn_readlane(unit_y, u & 63)) < (uint32_t)p.h &&
+                             (uint32_t)(ix0[v] + __builtin_amdgcn_readlane(unit_x, u & 63)) < (uint32_t)p.w;
+            o = inb && u < units ? o : NOTHING;
+        }
+        return o;
     };
     uint32_t m[BATCH][NV][UW], s[BATCH][NV][UW];
-    auto fetch = [&](Unit& u, int count) {
+    auto fetch = [&](int first) {
 #pragma unroll
-        for (int k = 0; k < BATCH; ++k) {
-            if (k < count) {
-                const int64_t at = ((int64_t)(u.a * p.dd * p.h + u.b * p.dh) * p.w + u.c * p.dw) * rec + 4 * u.word;
+        for (int k = 0; k < BATCH; ++k)
 #pragma unroll
-                for (int v = 0; v < NV; ++v) {
-                    bool inb = true;
-                    if constexpr (PADDED)
-                        inb = (uint32_t)(iz0[v] + u.a * p.dd) < (uint32_t)p.d && (uint32_t)(iy0[v] + u.b * p.dh) < (uint32_t)p.h &&
-                              (uint32_t)(ix0[v] + u.c * p.dw) < (uint32_t)p.w;
-                    const uint8_t* from = reinterpret_cast<const uint8_t*>(p.in);
-                    if constexpr (PADDED) from += inb ? off[v] + (uint32_t)at : 0u;
-                    else from = from + at + off[v];
-                    if constexpr (WD == 2) {
-                        const v4w r = *reinterpret_cast<const v4w*>(from);
-                        m[k][v][0] = inb ? r.x : 0u; m[k][v][1] = inb ? r.y : 0u;
-                        s[k][v][0] = r.z; s[k][v][1] = r.w;
-                    } else {
-                        const uint32_t* w = reinterpret_cast<const uint32_t*>(from);
-                        m[k][v][0] = inb ? w[0] : 0u;
-                        s[k][v][0] = w[t.words];
-                    }
+            for (int v = 0; v < NV; ++v) {
+                const uint32_t o = address(first + k, v);
+                if constexpr (WD == 2) {
+                    const v4w r = __builtin_amdgcn_raw_buffer_load_b128(src, o, 0, 0);
+                    m[k][v][0] = r.x; m[k][v][1] = r.y;
+                    s[k][v][0] = r.z; s[k][v][1] = r.w;
+                } else {
+                    m[k][v][0] = __builtin_amdgcn_raw_buffer_load_b32(src, o, 0, 0);
+                    s[k][v][0] = __builtin_amdgcn_raw_buffer_load_b32(src, o, (int)(rec >> 1), 0);
                 }
-                next(u);
             }
-        }
     };
     // Codes of 32 channels -> this lane's eight of them as bf16 numbers +-2 or 0 (signs without a mask become -0):
     // channels 4 q4 + {0, 16, 2, 18, 1, 17, 3, 19}.
-    const uint32_t m55 = 0x55555555u, mc0 = 0xc000c000u, sh = 14u - 4u * (uint32_t)q4;
+    uint32_t m55 = 0x55555555u, mc0 = 0xc000c000u;        // (in vector registers: scalar operands take an instruction twice as long)
+    asm volatile("" : "+v"(m55), "+v"(mc0));
+    const uint32_t sh = 14u - 4u * (uint32_t)q4;
     auto widen = [&](uint32_t mw, uint32_t sw) {
-        const uint32_t even = __builtin_amdgcn_bitop3_b32(m55, mw, sw << 1, 0xca);   // mask at 2 k, sign at 2 k + 1
+        const uint32_t even = __builtin_amdgcn_bitop3_b32(m55, mw, sw + sw, 0xca);   // mask at 2 k, sign at 2 k + 1
         const uint32_t odd = __builtin_amdgcn_bitop3_b32(m55, mw >> 1, sw, 0xca);
         v4w o;
         o.x = (even << sh) & mc0;
@@ -428,88 +442,105 @@ __global__ __launch_bounds__(kBlock) void real_conv_matrix_kernel(RealConvParams
         o.w = (odd << (sh - 2u)) & mc0;
         return __builtin_bit_cast(v8bf, o);
     };
+    auto write = [&](int tile, int co, const float (&sum)[NV]) {
+        const float b = p.bias ? p.bias[co] : 0.0f;
+#pragma unroll
+        for (int v = 0; v < NV; ++v)
+            if ((int64_t)tile * TILE + ((tid >> 6) * NV + v) * 16 + col < p.total) {
+                const int n = quot(quot(quot(vox[v], t.ow), t.oh), t.od);
+                const size_t ospatial = (size_t)p.od * p.oh * p.ow;
+                p.out[((size_t)n * p.c_out + co) * ospatial + (vox[v] - (size_t)n * ospatial)] = sum[v] + b;
+            }
+    };
 
     for (int co0 = 0; co0 < p.c_out; co0 += 4) {
         const int cg = min(4, p.c_out - co0);
-        Unit u = {0, 0, 0, 0, 0};
-        fetch(u, min(BATCH, units));
-        // ---- the filters' operands: [unit word][lane][8] bf16 -------------------------------------------
+        enter(blockIdx.x);
+        fetch(0);
+        // ---- the filters' operands, once per workgroup: [unit word][lane][8] bf16 ----------------------
         if (co0 > 0) __syncthreads();
         bool odd_weight = false;
-        for (int i = tid; i < cg * t.filter.d; i += kBlock) {
-            const int f = quot(i, t.filter), e = i - f * t.filter.d;
-            const int c = quot(e, t.taps), tap = e - c * T;
-            const float w = c < p.c_in ? p.wgt[((size_t)(co0 + f) * p.c_in + c) * T + tap] : 0.0f;
-            const uint32_t bits = __float_as_uint(w), ex = (bits >> 23) & 255u;
-            odd_weight |= (bits << 1) != 0u && (ex < 27u || ex > 227u);
-            const float hi = __uint_as_float(bits & 0xffff0000u), rest = w - hi;
-            const float mid = __uint_as_float(__float_as_uint(rest) & 0xffff0000u), low = rest - mid;
-            const int cc = c & 31, j = 2 * ((cc & 1) * 2 + ((cc >> 1) & 1)) + (cc >> 4);
-            const int slot = (tap * t.words + (c >> 5)) * 64 + ((cc >> 2) & 3) * 16 + 4 * f;
-            uint16_t* at = reinterpret_cast<uint16_t*>(wl8) + slot * 8 + j;
-            at[0] = (uint16_t)(bits >> 16);
-            at[8] = (uint16_t)(__float_as_uint(mid) >> 16);
-            at[16] = (uint16_t)(__float_as_uint(low) >> 16);
+        const int elements = cg * t.filter.d;
+        constexpr int ROUND = 5;                          // weights that a thread has under way
+        for (int base = tid; base < elements; base += ROUND * kBlock) {
+            float ww[ROUND];
+            int slot[ROUND];
+#pragma unroll
+            for (int k = 0; k < ROUND; ++k) {
+                const int i = min(base + k * kBlock, elements - 1);
+                const int f = quot(i, t.filter), e = i - f * t.filter.d;
+                const int c = quot(e, t.taps), tap = e - c * T;
+                const float w = p.wgt[((size_t)(co0 + f) * p.c_in + min(c, p.c_in - 1)) * T + tap];
+                ww[k] = c < p.c_in ? w : 0.0f;
+                const int cc = c & 31, j = 2 * ((cc & 1) * 2 + ((cc >> 1) & 1)) + (cc >> 4);
+                slot[k] = ((tap * p.wd_in + (c >> 5)) * 64 + ((cc >> 2) & 3) * 16 + 4 * f) * 8 + j;
+            }
+#pragma unroll
+            for (int k = 0; k < ROUND; ++k) {             // (past the end: the last one again)
+                const uint32_t bits = __float_as_uint(ww[k]), ex = (bits >> 23) & 255u;
+                odd_weight |= (bits << 1) != 0u && (ex < 27u || ex > 227u);
+                const float hi = __uint_as_float(bits & 0xffff0000u), rest = ww[k] - hi;
+                const float mid = __uint_as_float(__float_as_uint(rest) & 0xffff0000u), low = rest - mid;
+                uint16_t* at = reinterpret_cast<uint16_t*>(wl8) + slot[k];
+                at[0] = (uint16_t)(bits >> 16);
+                at[8] = (uint16_t)(__float_as_uint(mid) >> 16);
+                at[16] = (uint16_t)(__float_as_uint(low) >> 16);
+            }
         }
-        const bool one_by_one = __syncthreads_or(odd_weight ? 1 : 0) != 0;
-        float sum[NV];
-        if (!one_by_one) {
+        if (__syncthreads_or(odd_weight ? 1 : 0) != 0) {
+            for (int tile = blockIdx.x; tile < t.tiles; tile += gridDim.x) {
+                enter(tile);
+                float sum[NV];
+                const float* wf = p.wgt + (size_t)(co0 + min(q4, cg - 1)) * p.c_in * T;
+#pragma unroll
+                for (int v = 0; v < NV; ++v) {
+                    sum[v] = 0.0f;
+                    for (int u = 0; u < units; ++u) {
+                        const uint32_t o = address(u, v);
+                        const int tap = UW == 2 ? u : quot(u, t.words);
+                        for (int w = 0; w < UW; ++w) {
+                            const int word = UW == 2 ? w : u - tap * p.wd_in, live = min(32, p.c_in - 32 * word);
+                            const uint32_t mw = __builtin_amdgcn_raw_buffer_load_b32(src, o, 4 * w, 0);
+                            const uint32_t sw = __builtin_amdgcn_raw_buffer_load_b32(src, o, 4 * w + (int)(rec >> 1), 0);
+                            for (int j = 0; j < live; ++j) {
+                                const float wv = wf[(size_t)(32 * word + j) * T + tap];
+                                if ((mw >> j) & 1u) sum[v] += (sw >> j) & 1u ? -wv : wv;
+                            }
+                        }
+                    }
+                }
+                if (q4 < cg) write(tile, co0 + q4, sum);
+            }
+            continue;
+        }
+        for (int tile = blockIdx.x;;) {
             // (rows of filters that do not exist and every fourth row hold anything: nobody reads their sums)
             v4f acc[NV];
 #pragma unroll
             for (int v = 0; v < NV; ++v) acc[v] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
-            const uint8_t* a_at = wl8 + lane * 16;
-            int done = 0;
-            while (true) {
-                const int count = min(BATCH, units - done);
+            for (int first = 0;;) {
 #pragma unroll
                 for (int k = 0; k < BATCH; ++k)
-                    if (k < count)
 #pragma unroll
-                        for (int w = 0; w < UW; ++w) {
-                            const v8bf a = *reinterpret_cast<const v8bf*>(a_at);
-                            a_at += 1024;
-#pragma unroll
-                            for (int v = 0; v < NV; ++v)
-                                acc[v] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, widen(m[k][v][w], s[k][v][w]), acc[v], 0, 0, 0);
-                        }
-                done += count;
-                if (done >= units) break;
-                fetch(u, min(BATCH, units - done));
-            }
-#pragma unroll
-            for (int v = 0; v < NV; ++v) sum[v] = 0.5f * ((acc[v][2] + acc[v][1]) + acc[v][0]);
-        } else {
-#pragma unroll
-            for (int v = 0; v < NV; ++v) sum[v] = 0.0f;
-            const float* wf = p.wgt + (size_t)(co0 + min(q4, cg - 1)) * p.c_in * T;
-            Unit x = {0, 0, 0, 0, 0};
-            for (int i = 0; i < units; ++i) {
-                Unit at = x;
-                fetch(x, 1);
-#pragma unroll
-                for (int w = 0; w < UW; ++w) {
-                    const int live = min(32, p.c_in - 32 * (at.word + w));
-                    for (int j = 0; j < live; ++j) {
-                        const float wv = wf[(size_t)(32 * (at.word + w) + j) * T + at.tap];
+                    for (int w = 0; w < UW; ++w) {
+                        // (a unit past the last: zeros times any filter)
+                        const v8bf a = *reinterpret_cast<const v8bf*>(wl8 + (min(first + k, units - 1) * UW + w) * 1024 + lane * 16);
 #pragma unroll
                         for (int v = 0; v < NV; ++v)
-                            if ((m[0][v][w] >> j) & 1u) sum[v] += (s[0][v][w] >> j) & 1u ? -wv : wv;
+                            acc[v] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, widen(m[k][v][w], s[k][v][w]), acc[v], 0, 0, 0);
                     }
-                }
+                first += BATCH;
+                if (first >= units) break;
+                fetch(first);
             }
-        }
-        if (q4 < cg) {
-            const float b = p.bias ? p.bias[co0 + q4] : 0.0f;
+            float sum[NV];
 #pragma unroll
-            for (int v = 0; v < NV; ++v) {
-                const int64_t at = (int64_t)blockIdx.x * (4 * NV * 16) + ((tid >> 6) * NV + v) * 16 + col;
-                if (at < p.total) {
-                    const int n = quot(quot(quot(vox[v], t.ow), t.oh), t.od);
-                    const size_t ospatial = (size_t)p.od * p.oh * p.ow;
-                    p.out[((size_t)n * p.c_out + co0 + q4) * ospatial + (vox[v] - (size_t)n * ospatial)] = sum[v] + b;
-                }
-            }
+            for (int v = 0; v < NV; ++v) sum[v] = 0.5f * ((acc[v][2] + acc[v][1]) + acc[v][0]);
+            if (q4 < cg) write(tile, co0 + q4, sum);
+            tile += gridDim.x;
+            if (tile >= t.tiles) break;
+            enter(tile);
+            fetch(0);
         }
     }
 }
@@ -671,28 +702,44 @@ int launch_concat(const ConcatParams& p, hipStream_t s)
     return TERN_OK;
 }
 
+// Workgroups of a launch, each with its own copy of the filters' operands.
+constexpr int kRealGroups = 1024;
+
+template <int WD, bool PADDED, int BATCH>
+static void go_real_matrix(const RealConvParams& p, RealMatrixPlan& t, hipStream_t s)
+{
+    constexpr int NV = 1;
+    t.tiles = (int32_t)((p.total + 64 * NV - 1) / (64 * NV));
+    const unsigned blocks = (unsigned)(t.tiles < kRealGroups ? t.tiles : kRealGroups);
+    const size_t lds = (size_t)(p.kd * p.kh * p.kw * p.wd_in) * 1024;
+    hipLaunchKernelGGL((real_conv_matrix_kernel<WD, PADDED, BATCH, NV>), dim3(blocks), dim3(kBlock), lds, s, p, t);
+}
+
 // The matrix kernel where its operands fit in 64 KB and 32 bits count the input's bytes and the output's voxels.
 static bool launch_real_matrix(const RealConvParams& p, hipStream_t s)
 {
     const int64_t taps = (int64_t)p.kd * p.kh * p.kw, in_items = p.total / ((int64_t)p.od * p.oh * p.ow);
-    if (taps * p.wd_in > 64 || p.total > 0x7fffffff || in_items * p.d * p.h * p.w * p.wd_in * 8 > 0x7fffffff) return false;
+    const int64_t bytes = in_items * p.d * p.h * p.w * p.wd_in * 8;
+    if (taps * p.wd_in > 64 || p.total > 0x7fffffff || bytes > 0x7fffffff) return false;
+    // Many voxels with few products each are faster through the tables, whose work goes by channels and not by
+    // words of them: 262 thousand voxels, 64 -> 2 channels, single tap 7.2 us and 9.6 here; 313 thousand, 3 x 3:
+    // 8 channels 14.1 and 18.0, 24 channels 17.9 and 18.1; 116 thousand, 3 x 3 x 3: 8 channels 20.3 and 20.9, 14
+    // channels 24.8 and 20.9.  Eight thousand voxels: 14.8 to 47 with tables, 6.8 to 9.6 here.
+    if (p.total >= 32768 && taps * p.c_in < 224) return false;
     RealMatrixPlan t;
     t.ow = divisor(p.ow); t.oh = divisor(p.oh); t.od = divisor(p.od);
     t.taps = divisor((int32_t)taps); t.filter = divisor((int32_t)(taps * 32 * p.wd_in));
-    t.words = p.wd_in;
-    const bool padded = p.pd || p.ph || p.pw;
-    const size_t lds = (size_t)(taps * p.wd_in) * 1024;
-    // Two blocks of voxels to a wave once every SIMD has two waves with them.
-    const bool two = p.total >= 2 * 2 * 16 * 1024;
-    const unsigned blocks = (unsigned)((p.total + (two ? 128 : 64) - 1) / (two ? 128 : 64));
-    const auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(blocks), dim3(kBlock), lds, s, p, t); };
-    if (p.wd_in == 2) {
-        if (padded) two ? go(real_conv_matrix_kernel<2, true, 2>) : go(real_conv_matrix_kernel<2, true, 1>);
-        else two ? go(real_conv_matrix_kernel<2, false, 2>) : go(real_conv_matrix_kernel<2, false, 1>);
-    } else {
-        if (padded) two ? go(real_conv_matrix_kernel<1, true, 2>) : go(real_conv_matrix_kernel<1, true, 1>);
-        else two ? go(real_conv_matrix_kernel<1, false, 2>) : go(real_conv_matrix_kernel<1, false, 1>);
-    }
+    t.kw = reciprocal((uint32_t)p.kw, 64); t.kh = reciprocal((uint32_t)p.kh, 64); t.words = reciprocal((uint32_t)p.wd_in, 64);
+    t.bytes = (uint32_t)bytes;
+    const bool padded = p.pd || p.ph || p.pw, few = taps * (p.wd_in == 2 ? 1 : p.wd_in) <= 3;
+    const auto go = [&](auto wd, auto pad) {
+        if (few) go_real_matrix<decltype(wd)::value, decltype(pad)::value, 3>(p, t, s);
+        else go_real_matrix<decltype(wd)::value, decltype(pad)::value, 9>(p, t, s);
+    };
+    const std::integral_constant<int, 1> one;
+    const std::integral_constant<int, 2> two;
+    if (p.wd_in == 2) padded ? go(two, std::true_type{}) : go(two, std::false_type{});
+    else padded ? go(one, std::true_type{}) : go(one, std::false_type{});
     return true;
 }
 
