@@ -153,7 +153,11 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
     const bool half_last = ODD && ks == nks - 1 && (((p.kd * p.kh * p.kw * t.nch) & 1) != 0);
     const int step_words = ROWS ? 2 * row_words : row_words;   // (tap-packed: per row)
     const uint32_t* bank = p.wgt + (size_t)(active ? cb : 0) * FW;
-    uint32_t lane_f = (uint32_t)(i32 * FW);
+    // Which way the sums are decided: through the 6-bit floats where the instructions count, shifted in one by one in
+    // the small waves of short launches, where only a wave's own time does (a U-Net's fifteen launches on one stack
+    // 86.3 us, through the 6-bit floats 87.6).
+    constexpr bool SIX = PACKED && VB == 4;
+    uint32_t lane_f = (uint32_t)((SIX ? row_filter(i32) : i32) * FW);
     if constexpr (ROWS) lane_f += (uint32_t)(g * row_words);
     else if constexpr (KIND != kTapPacked) lane_f += (uint32_t)(KIND == kBinary ? g : 2 * g);
     v2u f0[NB], f1[NB];
@@ -282,8 +286,9 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
     if constexpr (PACKED) {
         if (tid < wg_filters) {
             const Cut cut = cut_of(cut_lo, cut_hi, (int)blockIdx.y * wg_filters + tid < p.c_out);
-            cuts[tid] = cut.start;
-            cuts[wg_filters + tid] = cut.width;
+            const int at = SIX ? (tid & ~31) + filter_row(tid & 31) : tid;
+            cuts[at] = cut.start;
+            cuts[wg_filters + at] = cut.width;
         }
     }
     __syncthreads();
@@ -465,15 +470,26 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
     if constexpr (PACKED) {
         uint32_t* out = p.out_packed + vox0 * 2u * p.wd_out + g * p.wd_out + (cb >> 5);
         const bool pair = NB == 2 && (p.wd_out & 1) == 0 && !SPLIT;   // (cb >> 5 is even then)
+        Decider d;
+        v8bf widths[NB];
+        if constexpr (SIX) {
+            d = decider();
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) widths[nb] = width_operand(cuts[wg_filters + (wc * NB + nb) * 32 + i32], g == 0);
+        }
 #pragma unroll
         for (int vb = 0; vb < VB; ++vb) {
             uint32_t word[NB];
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) {
                 if (!finishes(vb * NB + nb)) continue;
-                uint32_t pos, neg;
-                decide_block(pos, neg, acc[vb][nb], cuts + wg_filters + (wc * NB + nb) * 32 + 4 * g);
-                word[nb] = block_word(pos, neg);
+                if constexpr (SIX) {
+                    word[nb] = decided_word(acc[vb][nb], widths[nb], d);
+                } else {
+                    uint32_t pos, neg;
+                    decide_block(pos, neg, acc[vb][nb], cuts + wg_filters + (wc * NB + nb) * 32 + 4 * g);
+                    word[nb] = block_word(pos, neg);
+                }
             }
             int dx, dy, dz;
             if (offset_of(vb, dx, dy, dz)) {

@@ -9,9 +9,10 @@
 // words of a voxel's word pair, lanes 32-63 the sign words, and one half-wave swap sorts them), four
 // blocks ahead of their use (two blocks ahead, cut points in registers instead of LDS and accumulators that
 // the compiler put into accumulation registers: 21 us where this takes 12).  Bound by memory where the
-// output is int32, by the epilogue's three vector instructions per output where it is packed.  Measured
-// against one lane per voxel with bit counts: 64 -> 64 channels on 96^3 24.5 -> 12.0 us packed (28 MB,
-// 2.4 TB/s) and 39.0 -> 36.9 us int32 (6.5 TB/s), 128 -> 128 on 64^3 22.0 -> 8.9, 256 -> 256 on 609
+// output is int32, by the decisions on the sums where it is packed (through 6-bit floats: with three vector
+// instructions to a sum 64 -> 64 channels on 96^3 took 11.1 us, now 9.8).  Measured
+// against one lane per voxel with bit counts: 64 -> 64 channels on 96^3 24.5 -> 9.8 us packed (28 MB,
+// 2.9 TB/s) and 39.0 -> 36.9 us int32 (6.5 TB/s), 128 -> 128 on 64^3 22.0 -> 8.9, 256 -> 256 on 609
 // voxels 9.2 -> 2.9, 32 -> 32 on 64^3 4.7 -> 3.9.
 #include <type_traits>
 
@@ -37,8 +38,9 @@ struct PointParams {
 
 // S: steps of 64 channels (word pairs); ODD: an odd number of words per voxel (the last pair is half
 // empty, bank and records are read word by word); BIN: sign-only filters.
+// Three waves to a SIMD, two where the filters and the decisions' registers leave no room for a third.
 template <int S, int NB, bool PACKED, bool BIN, bool ODD>
-__global__ __launch_bounds__(kPointThreads) __attribute__((amdgpu_waves_per_eu(3))) void conv_point_kernel(PointParams p)
+__global__ __launch_bounds__(kPointThreads) __attribute__((amdgpu_waves_per_eu(S >= 3 && NB == 2 && PACKED ? 2 : 3))) void conv_point_kernel(PointParams p)
 {
     constexpr int WD = ODD ? 2 * S - 1 : 2 * S;
     constexpr int REC = 2 * WD;                          // words of a voxel record
@@ -54,8 +56,9 @@ __global__ __launch_bounds__(kPointThreads) __attribute__((amdgpu_waves_per_eu(3
             const int co = c0 + (int)threadIdx.x;
             const bool live = co < p.c_out;
             const Cut c = cut_of(live ? p.lo[co] : 0, live ? p.hi[co] : 0, live);
-            cuts[threadIdx.x] = c.start;
-            cuts[32 * NB + threadIdx.x] = c.width;
+            const int at = ((int)threadIdx.x & ~31) + filter_row((int)threadIdx.x & 31);
+            cuts[at] = c.start;
+            cuts[32 * NB + at] = c.width;
         }
     }
     const int64_t first64 = ((int64_t)blockIdx.x * (kPointThreads / 64) + wave) * p.blocks_per_wave;
@@ -101,7 +104,7 @@ __global__ __launch_bounds__(kPointThreads) __attribute__((amdgpu_waves_per_eu(3
     v4i F[NB][S];
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
-        const int co = c0 + nb * 32 + i32;               // below co_pad: whole blocks of 32 exist
+        const int co = c0 + nb * 32 + (PACKED ? row_filter(i32) : i32);   // below co_pad: whole blocks of 32 exist
 #pragma unroll
         for (int s = 0; s < S; ++s) {
             v2u w;
@@ -135,6 +138,14 @@ __global__ __launch_bounds__(kPointThreads) __attribute__((amdgpu_waves_per_eu(3
             start[nb][4 * k] = h.x; start[nb][4 * k + 1] = h.y; start[nb][4 * k + 2] = h.z; start[nb][4 * k + 3] = h.w;
         }
 
+    Decider d;
+    v8bf widths[NB];
+    if constexpr (PACKED) {
+        d = decider();
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) widths[nb] = width_operand(cuts[32 * NB + nb * 32 + i32], g == 0);
+    }
+
     // ---- blocks of 32 voxels -------------------------------------------------------------------
     auto block = [&](v2u (&x)[S], int b) {
         v4i V[S];
@@ -159,11 +170,7 @@ __global__ __launch_bounds__(kPointThreads) __attribute__((amdgpu_waves_per_eu(3
         if constexpr (PACKED) {
             uint32_t word[NB];
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb) {
-                uint32_t pos, neg;
-                decide_block(pos, neg, acc[nb], cuts + 32 * NB + nb * 32 + 4 * g);
-                word[nb] = block_word(pos, neg);
-            }
+            for (int nb = 0; nb < NB; ++nb) word[nb] = decided_word(acc[nb], widths[nb], d);
             if (vox < p.voxels) {
                 uint32_t* o = p.out_packed + ((size_t)(b * 32) * 2u + (uint32_t)(i32 * 2)) * p.wd_out + g * p.wd_out + (c0 >> 5);
                 if (NB == 2 && (p.wd_out & 1) == 0) {
