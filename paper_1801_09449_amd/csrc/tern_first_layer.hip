@@ -70,7 +70,7 @@ __global__ __launch_bounds__(kFirstThreads) void first_conv_kernel(PatchParams p
     // ---- intensities -> codes ---------------------------------------------------------------------------
     const size_t plane = (size_t)p.h * p.w;
     const float* src_n = p.src + (size_t)n * p.d * plane;
-    constexpr int U = STACK ? 1 : 2;                       // columns that a thread has in flight
+    constexpr int U = 2;                                   // columns that a thread has in flight (a stack's one: 6.4 us for 6.2)
     auto fill = [&](int base) {
         float v[U][PLANES];
         bool in_plane[U];
