@@ -207,8 +207,8 @@ size_t tern_fcn_workspace_bytes(tern_dims in_dims, const tern_layer* layers /* h
  *               depth stride and dilation, the input region instead holds, per
  *               output voxel of layer 0, that voxel's kernel taps gathered into a bit string:
  *               Eq. 6 and the gathering run as one pass over the intensities and layer 0
- *               becomes a single-tap convolution, which usually runs in that same pass on the
- *               strings in registers; the region is then reserved but not written.  Results
+ *               becomes a single-tap convolution.  Usually one launch goes from the intensities
+ *               to layer 0's codes; the region is then reserved but not written.  Results
  *               are identical either way.)
  *               When layer_out (host array of n_layers pointers, may be NULL) is given,
  *               layer_out[i] receives the device address of layer i's packed output (inside
@@ -326,8 +326,8 @@ int tern_conv3d_digits(const uint32_t* in_packed, tern_dims in_dims, const uint3
  * tern_net_forward -- a network of ternary modules with skip connections (the baseline U-Net of
  * section 3 / Table 1, or any encoder-decoder of that kind), run as one call: Eq. 6 on the float
  * input, then for every module, in order, [nearest upsampling of the incoming tensor and
- * appending of an earlier module's centre-cropped output, via the tern_concat kernel] and a
- * fused tern_conv3d; optionally a float-weight prediction layer (tern_conv3d_real) on the last
+ * appending of an earlier module's centre-cropped output: the convolution reads both tensors
+ * where it can, else tern_concat's kernel joins them first] and a fused tern_conv3d; optionally a float-weight prediction layer (tern_conv3d_real) on the last
  * module's output.  Average pooling in front of a module is expressed either through the
  * module's filters and stride (tern_fold_avgpool; pool left at 1) or through pool[]: the
  * incoming tensor (after upsampling and concatenation, if any) is sum-pooled over windows of
@@ -347,7 +347,8 @@ int tern_conv3d_digits(const uint32_t* in_packed, tern_dims in_dims, const uint3
  *                holds the packed input (or, as in tern_fcn_forward, the gathered taps of a
  *                one-channel input's first module), every module's output and every
  *                concatenated or pooled tensor, each in a region of its own (nothing is
- *                overwritten within a call).
+ *                overwritten within a call; a concatenated one's is reserved but not written where
+ *                the convolution reads its parts).
  *   module_out / module_dims : optional host arrays of n_mods entries that receive the device
  *                address (inside workspace) and logical extents of every module's packed output.
  * Errors as for the calls it is made of; TERN_EARG for an invalid skip_from or crop,

@@ -3,8 +3,8 @@
 // column, the Prediction row):
 //   - concat_kernel: every output voxel gathers, per source, the voxel that nearest-neighbour
 //     upsampling and cropping map onto it, and lays the sources' channel bits side by side;
-//   - real_conv_kernel: cross-correlation of ternary codes with float weights (+ bias).
-// Both are small HBM streams next to the convolutions; neither uses LDS.
+//   - real_conv_*_kernel: cross-correlation of ternary codes with float weights (+ bias), on the matrix cores, by
+//     tables of partial sums or term by term.
 #include <type_traits>
 
 #include "tern_internal.h"

@@ -215,7 +215,7 @@ def test_conv3d_real_special_weights(G, value):
     if not np.isfinite(value):
         for o, c, (b, a) in ((1, 7, (1, 2)), (4, 39, (0, 0))):
             code = x[:, c, :, b:b + want.shape[3], a:a + want.shape[4]]
-            odd[:, o] = np.where(code == 0, 0.0, code * np.float64(value))
+            odd[:, o] = np.where(code == 0, 0.0, np.where(code == 0, 1, code) * np.float64(value))
     bound = real_conv_bound(finite, np.zeros(5, np.float32))[None, :, None, None, None]
     plain = odd == 0
     assert (np.abs(got - want)[plain] <= np.broadcast_to(bound, want.shape)[plain]).all()
