@@ -251,8 +251,14 @@ int launch_conv_point(const ConvParams& c, hipStream_t s)
     const int nb = fb % 2 == 0 && c.wd_in <= 4 && blocks * gz * (fb / 2) >= 1024 ? 2 : 1;
     const int groups = fb / nb;
     if (groups > 65535) return TERN_ESHAPE;
-    const int64_t waves_wanted = !packed && groups > 1 && c.wd_in <= 3 ? 8192 : 4096;
-    int64_t per = (blocks * gz * groups + waves_wanted - 1) / waves_wanted;
+    // Three, and no workgroups left for a second round, for packed output from three words, whose registers leave room
+    // for three: 96 -> 128 channels on 270 000 voxels 12.8 us with 4096 waves, 9.1 with 3072; -> 64 on 885 thousand
+    // 15.2 and 12.5; -> 256 on 64 000 8.7 and 8.2.  Not where 4096 come out even over several groups (262 144 voxels,
+    // -> 128 9.6 and 10.8, -> 256 18.5 and 19.9), and not from four words (128 -> 128 on 262 144 8.4 and 9.7).
+    const int64_t work = blocks * gz * groups;
+    const bool three = packed && nb == 2 && c.wd_in == 3 && (groups == 1 || work % 4096 != 0);
+    const int64_t waves_wanted = !packed && groups > 1 && c.wd_in <= 3 ? 8192 : three ? 3072 : 4096;
+    int64_t per = (work + waves_wanted - 1) / waves_wanted;
     if (per > 64) per = 64;
     p.blocks_per_wave = (int32_t)per;
     const int64_t waves = (blocks + per - 1) / per;
