@@ -27,10 +27,10 @@
 // are divided by multiplication (ten integer divisions were 250 instructions before the first load), cut points
 // and halo items are fetched at once, and halo voxels go through a buffer descriptor that returns zeros outside the
 // volume.  Together: 32 -> 32 on 24^3 5.46 -> 4.99 us, 96 -> 70 stride 2 on 2 x 45 x 53 x 37 13.9 -> 12.5, 64 -> 64
-// on 96^3 with dilation 2 53.8 -> 51.5, a U-Net's fifteen launches 125.6 -> 113.3.
-// Measured, fused output, bit-count kernels before: 64 -> 64 channels on 64^3: 88 -> 15.4 us, on 96^3 with
-// dilation 2: 276 -> 54 us; 256 -> 256 on 2 x 32^3: 321 -> 43 us (5 400 TFLOP/s: loop 38, fill 3, epilogue 3 us);
-// 64 -> 64 3 x 3 on 16 planes of 232 x 168: 83 -> 23 us.
+// on 96^3 with dilation 2 53.8 -> 51.5, a U-Net's eighteen launches 125.6 -> 113.3.
+// Measured, fused output, bit-count kernels before: 64 -> 64 channels on 64^3: 88 -> 13.8 us, on 96^3 with
+// dilation 2: 276 -> 48 us; 256 -> 256 on 2 x 32^3: 321 -> 42 us (5 500 TFLOP/s: loop 38, fill 3, epilogue 1 us);
+// 64 -> 64 3 x 3 on 16 planes of 232 x 168: 83 -> 22 us.
 #include <type_traits>
 
 #include "tern_internal.h"
