@@ -9,8 +9,8 @@
 // words of a voxel's word pair, lanes 32-63 the sign words, and one half-wave swap sorts them), four
 // blocks ahead of their use (two blocks ahead, cut points in registers instead of LDS and accumulators that
 // the compiler put into accumulation registers: 21 us where this takes 12).  Bound by memory where the
-// output is int32, by the decisions on the sums where it is packed (through 6-bit floats: with three vector
-// instructions to a sum 64 -> 64 channels on 96^3 took 11.1 us, now 9.8).  Measured
+// output is int32, by the decisions on the sums where it is packed (through 6-bit floats in large launches: with three
+// vector instructions to a sum 64 -> 64 channels on 96^3 took 11.1 us, now 9.8).  Measured
 // against one lane per voxel with bit counts: 64 -> 64 channels on 96^3 24.5 -> 9.8 us packed (28 MB,
 // 2.9 TB/s) and 39.0 -> 36.9 us int32 (6.5 TB/s), 128 -> 128 on 64^3 22.0 -> 8.9, 256 -> 256 on 609
 // voxels 9.2 -> 2.9, 32 -> 32 on 64^3 4.7 -> 3.9.
@@ -18,11 +18,12 @@
 
 #include "tern_internal.h"
 #include "tern_matrix_common.h"
+#include "tern_point_choice.h"
 
 namespace tern {
 namespace {
 
-constexpr int kPointThreads = 256;
+constexpr int kPointThreads = 64 * kPointWaves;
 
 struct PointParams {
     const uint32_t* in;      // packed [voxels][2][wd] (batch items folded for packed output)
@@ -37,11 +38,13 @@ struct PointParams {
 };
 
 // S: steps of 64 channels (word pairs); ODD: an odd number of words per voxel (the last pair is half
-// empty, bank and records are read word by word); BIN: sign-only filters.
-// Three waves to a SIMD, two where the filters and the decisions' registers leave no room for a third.
-template <int S, int NB, bool PACKED, bool BIN, bool ODD>
-__global__ __launch_bounds__(kPointThreads) __attribute__((amdgpu_waves_per_eu(S >= 3 && NB == 2 && PACKED ? 2 : 3))) void conv_point_kernel(PointParams p)
+// empty, bank and records are read word by word); BIN: sign-only filters; OUT: int32 sums, packed codes shifted
+// in one by one, or packed codes through 6-bit floats.
+enum { kSums = 0, kShifted = 1, kSix = 2 };
+template <int S, int NB, int OUT, bool BIN, bool ODD>
+__global__ __launch_bounds__(kPointThreads) __attribute__((amdgpu_waves_per_eu(3))) void conv_point_kernel(PointParams p)
 {
+    constexpr bool PACKED = OUT != kSums, SIX = OUT == kSix;
     constexpr int WD = ODD ? 2 * S - 1 : 2 * S;
     constexpr int REC = 2 * WD;                          // words of a voxel record
     const int lane = threadIdx.x & 63, i32 = lane & 31, g = lane >> 5;
@@ -56,7 +59,7 @@ __global__ __launch_bounds__(kPointThreads) __attribute__((amdgpu_waves_per_eu(S
             const int co = c0 + (int)threadIdx.x;
             const bool live = co < p.c_out;
             const Cut c = cut_of(live ? p.lo[co] : 0, live ? p.hi[co] : 0, live);
-            const int at = ((int)threadIdx.x & ~31) + filter_row((int)threadIdx.x & 31);
+            const int at = SIX ? ((int)threadIdx.x & ~31) + filter_row((int)threadIdx.x & 31) : (int)threadIdx.x;
             cuts[at] = c.start;
             cuts[32 * NB + at] = c.width;
         }
@@ -104,7 +107,7 @@ __global__ __launch_bounds__(kPointThreads) __attribute__((amdgpu_waves_per_eu(S
     v4i F[NB][S];
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
-        const int co = c0 + nb * 32 + (PACKED ? row_filter(i32) : i32);   // below co_pad: whole blocks of 32 exist
+        const int co = c0 + nb * 32 + (SIX ? row_filter(i32) : i32);   // below co_pad: whole blocks of 32 exist
 #pragma unroll
         for (int s = 0; s < S; ++s) {
             v2u w;
@@ -140,7 +143,7 @@ __global__ __launch_bounds__(kPointThreads) __attribute__((amdgpu_waves_per_eu(S
 
     Decider d;
     v8bf widths[NB];
-    if constexpr (PACKED) {
+    if constexpr (SIX) {
         d = decider();
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) widths[nb] = width_operand(cuts[32 * NB + nb * 32 + i32], g == 0);
@@ -170,7 +173,15 @@ __global__ __launch_bounds__(kPointThreads) __attribute__((amdgpu_waves_per_eu(S
         if constexpr (PACKED) {
             uint32_t word[NB];
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb) word[nb] = decided_word(acc[nb], widths[nb], d);
+            for (int nb = 0; nb < NB; ++nb) {
+                if constexpr (SIX) {
+                    word[nb] = decided_word(acc[nb], widths[nb], d);
+                } else {
+                    uint32_t pos, neg;
+                    decide_block(pos, neg, acc[nb], cuts + 32 * NB + nb * 32 + 4 * g);
+                    word[nb] = block_word(pos, neg);
+                }
+            }
             if (vox < p.voxels) {
                 uint32_t* o = p.out_packed + ((size_t)(b * 32) * 2u + (uint32_t)(i32 * 2)) * p.wd_out + g * p.wd_out + (c0 >> 5);
                 if (NB == 2 && (p.wd_out & 1) == 0) {
@@ -203,18 +214,24 @@ __global__ __launch_bounds__(kPointThreads) __attribute__((amdgpu_waves_per_eu(S
     }
 }
 
-template <int S, bool ODD>
-void launch_steps(const PointParams& p, bool packed, bool binary, int nb, dim3 grid, hipStream_t s)
+template <int S, int NB, bool ODD>
+void launch_blocks(const PointParams& p, int out, bool binary, dim3 grid, hipStream_t s)
 {
-    const dim3 block(kPointThreads);
-#define TERN_POINT(NB_, BIN_)                                                                              \
-    do {                                                                                                   \
-        if (packed) hipLaunchKernelGGL((conv_point_kernel<S, NB_, true, BIN_, ODD>), grid, block, 0, s, p);  \
-        else hipLaunchKernelGGL((conv_point_kernel<S, NB_, false, BIN_, ODD>), grid, block, 0, s, p);        \
-    } while (0)
-    if (nb == 2) { if (binary) TERN_POINT(2, true); else TERN_POINT(2, false); }
-    else { if (binary) TERN_POINT(1, true); else TERN_POINT(1, false); }
-#undef TERN_POINT
+    const auto go = [&](auto o, auto bin) {
+        hipLaunchKernelGGL((conv_point_kernel<S, NB, decltype(o)::value, decltype(bin)::value, ODD>), grid, dim3(kPointThreads), 0, s, p);
+    };
+    const auto with = [&](auto o) { binary ? go(o, std::true_type{}) : go(o, std::false_type{}); };
+    if (out == kSums) return with(std::integral_constant<int, kSums>{});
+    if (out == kSix) return with(std::integral_constant<int, kSix>{});
+    with(std::integral_constant<int, kShifted>{});
+}
+
+template <int S, bool ODD>
+void launch_steps(const PointParams& p, int out, bool binary, int nb, dim3 grid, hipStream_t s)
+{
+    if constexpr (S <= 2)                                // (two filter blocks to a wave: up to four words)
+        if (nb == 2) return launch_blocks<S, 2, ODD>(p, out, binary, grid, s);
+    launch_blocks<S, 1, ODD>(p, out, binary, grid, s);
 }
 
 }  // namespace
@@ -241,37 +258,20 @@ int launch_conv_point(const ConvParams& c, hipStream_t s)
     const int gz = packed ? 1 : c.n;
     p.voxels = (int32_t)voxels;                          // at most 2^31 - 1 per tensor
     p.c_out = c.c_out; p.wd_out = c.wd_out; p.co_pad = c.co_pad;
-    const int fb = (c.c_out + 31) / 32;
-    const int64_t blocks = (voxels + 31) / 32;
-    // Two filter blocks per wave where they come in pairs, fit the registers (up to four words) and the
-    // launch still has a wave per SIMD; then as many blocks per wave as leave four waves per SIMD: setting a
-    // wave up (filters, cut points) costs as much as two blocks.  Eight where several groups write int32 from up
-    // to three words: a block's stores take longer than that (32 -> 256 channels on 2 x 26 675 voxels 16.4 us
-    // with four, 12.4; one group of few filters 3.9 and 4.3, eight words -> 128 channels 19.7 and 22.0).
-    const int nb = fb % 2 == 0 && c.wd_in <= 4 && blocks * gz * (fb / 2) >= 1024 ? 2 : 1;
-    const int groups = fb / nb;
-    if (groups > 65535) return TERN_ESHAPE;
-    // Three, and no workgroups left for a second round, for packed output from three words, whose registers leave room
-    // for three: 96 -> 128 channels on 270 000 voxels 12.8 us with 4096 waves, 9.1 with 3072; -> 64 on 885 thousand
-    // 15.2 and 12.5; -> 256 on 64 000 8.7 and 8.2.  Not where 4096 come out even over several groups (262 144 voxels,
-    // -> 128 9.6 and 10.8, -> 256 18.5 and 19.9), and not from four words (128 -> 128 on 262 144 8.4 and 9.7).
-    const int64_t work = blocks * gz * groups;
-    const bool three = packed && nb == 2 && c.wd_in == 3 && (groups == 1 || work % 4096 != 0);
-    const int64_t waves_wanted = !packed && groups > 1 && c.wd_in <= 3 ? 8192 : three ? 3072 : 4096;
-    int64_t per = (work + waves_wanted - 1) / waves_wanted;
-    if (per > 64) per = 64;
-    p.blocks_per_wave = (int32_t)per;
-    const int64_t waves = (blocks + per - 1) / per;
-    const dim3 grid((unsigned)((waves + kPointThreads / 64 - 1) / (kPointThreads / 64)), (unsigned)groups, (unsigned)gz);
+    const PointLaunch l = point_launch(voxels, gz, c.c_out, c.wd_in, packed);
+    if (l.groups > 65535) return TERN_ESHAPE;
+    p.blocks_per_wave = l.blocks_per_wave;
+    const dim3 grid((unsigned)l.gx, (unsigned)l.groups, (unsigned)gz);
+    const int out = !packed ? kSums : l.six ? kSix : kShifted;
     switch (c.wd_in) {
-        case 1: launch_steps<1, true>(p, packed, c.binary != 0, nb, grid, s); break;
-        case 2: launch_steps<1, false>(p, packed, c.binary != 0, nb, grid, s); break;
-        case 3: launch_steps<2, true>(p, packed, c.binary != 0, nb, grid, s); break;
-        case 4: launch_steps<2, false>(p, packed, c.binary != 0, nb, grid, s); break;
-        case 5: launch_steps<3, true>(p, packed, c.binary != 0, nb, grid, s); break;
-        case 6: launch_steps<3, false>(p, packed, c.binary != 0, nb, grid, s); break;
-        case 7: launch_steps<4, true>(p, packed, c.binary != 0, nb, grid, s); break;
-        default: launch_steps<4, false>(p, packed, c.binary != 0, nb, grid, s); break;
+        case 1: launch_steps<1, true>(p, out, c.binary != 0, l.nb, grid, s); break;
+        case 2: launch_steps<1, false>(p, out, c.binary != 0, l.nb, grid, s); break;
+        case 3: launch_steps<2, true>(p, out, c.binary != 0, l.nb, grid, s); break;
+        case 4: launch_steps<2, false>(p, out, c.binary != 0, l.nb, grid, s); break;
+        case 5: launch_steps<3, true>(p, out, c.binary != 0, l.nb, grid, s); break;
+        case 6: launch_steps<3, false>(p, out, c.binary != 0, l.nb, grid, s); break;
+        case 7: launch_steps<4, true>(p, out, c.binary != 0, l.nb, grid, s); break;
+        default: launch_steps<4, false>(p, out, c.binary != 0, l.nb, grid, s); break;
     }
     TERN_HIP_CHECK(hipGetLastError());
     return TERN_OK;

@@ -282,6 +282,30 @@ def test_pointwise_runs_shorter_and_longer_than_the_fetch_is_ahead(G, ci, co, vo
     check(G, synth.conv_case("px_runs", 2, ci, co, vol, k=1, pad=0, seed=832 + ci, p0_a=0.4))
 
 
+@pytest.mark.parametrize("ci,co,vox", [
+    (32, 32, 270001), (64, 64, 100001), (40, 96, 60001), (96, 128, 50001), (96, 40, 262113), (128, 64, 98305),    # through 6-bit floats
+    (100, 200, 20011), (128, 70, 33333), (160, 64, 270001), (256, 300, 60001), (224, 8, 530001),
+    (64, 100, 4099), (128, 256, 9001), (256, 256, 33001)])                                                        # shifted in
+def test_pointwise_packed_large_and_filled_up(G, ci, co, vox):
+    """Packed codes at the edges of the launch's rules: 6-bit floats and shifts, one and two filter blocks to a wave,
+    groups whose workgroups are filled up to a multiple of eight; a part block at the end."""
+    import torch
+    import paper_1801_09449_amd as T
+    g = torch.Generator(device="cuda").manual_seed(ci + co)
+    act = torch.randint(-1, 2, (1, ci, 1, 1, vox), generator=g, device="cuda", dtype=torch.int8)
+    w = torch.randint(-1, 2, (co, ci, 1, 1, 1), generator=g, device="cuda", dtype=torch.int8)
+    lo = torch.randint(-9, 3, (co,), generator=g, device="cuda", dtype=torch.int32)
+    hi = lo + torch.randint(-2, 12, (co,), generator=g, device="cuda", dtype=torch.int32)
+    a = T.tern_pack(act)
+    for binary in (False, True):
+        wb = torch.where(w < 0, w, torch.ones_like(w)) if binary else w
+        acc = reference(act, wb, (0, 0, 0))
+        want = T.tern_threshold_pack(acc, lo, hi)
+        fn, pack = (T.tern_conv3d_binary, T.tern_pack_filters_binary) if binary else (T.tern_conv3d, T.tern_pack_filters)
+        assert torch.equal(fn(a, ci, pack(wb), co, 1, 1, 0, 1, thr_lo=lo, thr_hi=hi), want)
+        assert T.tern_last_launch()["kernel"] == T.KERNEL_POINTWISE
+
+
 @pytest.mark.parametrize("ci", [32, 192])
 def test_pointwise_batches_beyond_the_grid(G, ci):
     """More batch items than a grid has layers, int32 and packed output, binary and ternary filters."""
