@@ -204,12 +204,9 @@ size_t tern_fcn_workspace_bytes(tern_dims in_dims, const tern_layer* layers /* h
  *   workspace : device scratch of at least tern_fcn_workspace_bytes() bytes, 16-byte aligned;
  *               holds the packed activations of the input and of every layer but the last.
  *               (With a one-channel input and a 3x3x3, 1x3x3 or 15x3x3 first kernel of unit
- *               depth stride and dilation, the input region instead holds, per
- *               output voxel of layer 0, that voxel's kernel taps gathered into a bit string:
- *               Eq. 6 and the gathering run as one pass over the intensities and layer 0
- *               becomes a single-tap convolution.  Usually one launch goes from the intensities
- *               to layer 0's codes; the region is then reserved but not written.  Results
- *               are identical either way.)
+ *               depth stride and dilation, one launch goes from the intensities to layer 0's codes.
+ *               The input region then has room for layer 0's kernel taps as bit strings, one per
+ *               output voxel, and is not written.)
  *               When layer_out (host array of n_layers pointers, may be NULL) is given,
  *               layer_out[i] receives the device address of layer i's packed output (inside
  *               workspace, or out_packed for the last layer) so that callers can inspect every
@@ -344,7 +341,7 @@ int tern_conv3d_digits(const uint32_t* in_packed, tern_dims in_dims, const uint3
  *                head_b, head_out are ignored); head_b may be NULL; head_out receives
  *                [N][head_c_out][Do][Ho][Wo] floats, head_dims (host, optional) its extents.
  *   workspace  : device scratch of at least tern_net_workspace_bytes() bytes, 16-byte aligned;
- *                holds the packed input (or, as in tern_fcn_forward, the gathered taps of a
+ *                holds the packed input (or, as in tern_fcn_forward, room for the taps of a
  *                one-channel input's first module), every module's output and every
  *                concatenated or pooled tensor, each in a region of its own (nothing is
  *                overwritten within a call; a concatenated one's is reserved but not written where

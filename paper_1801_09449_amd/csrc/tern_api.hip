@@ -110,6 +110,26 @@ static ConvParams conv_params(const uint32_t* in_packed, const tern_dims& in_dim
     return p;
 }
 
+// The same of a first layer on a scalar volume.
+static FirstConvParams first_params(const float* in, const float* in_lo, const float* in_hi, const tern_dims& in_dims,
+                                    const uint32_t* w_bank, int32_t c_out, const tern_conv_geom& g, const tern_dims& o,
+                                    const int32_t* thr_lo, const int32_t* thr_hi, uint32_t* out_packed)
+{
+    FirstConvParams p;
+    p.src = in; p.in_lo = in_lo; p.in_hi = in_hi;
+    p.wgt = w_bank; p.lo = thr_lo; p.hi = thr_hi;
+    p.out_packed = out_packed;
+    p.n = in_dims.n; p.d = in_dims.d; p.h = in_dims.h; p.w = in_dims.w;
+    p.od = o.d; p.oh = o.h; p.ow = o.w;
+    p.kd = g.k[0];
+    p.sh = g.stride[1]; p.sw = g.stride[2];
+    p.pd = g.pad[0]; p.ph = g.pad[1]; p.pw = g.pad[2];
+    p.dh = g.dil[1]; p.dw = g.dil[2];
+    p.c_out = c_out; p.co_pad = (c_out + 31) / 32 * 32;
+    p.wd_out = tern_words(c_out);
+    return p;
+}
+
 static bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
 }  // namespace tern
@@ -472,11 +492,11 @@ static int fcn_plan(tern_dims in_dims, const tern_layer* layers, int32_t n_layer
         tern_dims o;
         int rc = geom_check(cur, layers[i].c_out, layers[i].g, &o);
         if (rc != TERN_OK) return rc;
-        if (i == 0 && patch_pack_applies(in_dims.c, layers[0].g, o)) {
-            // the first region then holds the gathered taps (one word pair per output voxel of
-            // layer 0) instead of the packed input
-            const tern_dims patches = {o.n, layers[0].g.k[0] * layers[0].g.k[1] * layers[0].g.k[2], o.d, o.h, o.w};
-            total = (tern_packed_bytes(patches) + 255u) & ~(size_t)255u;
+        if (i == 0 && first_conv_applies(in_dims.c, layers[0].g, o)) {
+            // the first region then has room for the taps of every output voxel of layer 0 as bit strings, instead of
+            // the packed input; nothing is written there
+            const tern_dims taps = {o.n, layers[0].g.k[0] * layers[0].g.k[1] * layers[0].g.k[2], o.d, o.h, o.w};
+            total = (tern_packed_bytes(taps) + 255u) & ~(size_t)255u;
         }
         if (i + 1 < n_layers) total += (tern_packed_bytes(o) + 255u) & ~(size_t)255u;
         cur = o;
@@ -505,30 +525,12 @@ static int fcn_run(const float* in, tern_dims in_dims, const float* in_lo, const
     tern_dims o0;
     int rc = geom_check(in_dims, layers[0].c_out, layers[0].g, &o0);
     if (rc != TERN_OK) return rc;
-    // A one-channel input with a 3x3x3, 1x3x3 or 15x3x3 first kernel: Eq. 6 and the gathering of
-    // every output voxel's taps into a bit string happen in one pass over the intensities, and
-    // layer 0 becomes a single-tap convolution over those strings (its tap-packed filter bank is already in the
-    // matching layout).  Otherwise: Eq. 6 on the raw intensities, packed, then layer 0 as is.
-    const bool gathered = patch_pack_applies(in_dims.c, layers[0].g, o0);
-    PatchParams first = {};
-    bool fused = false;
-    if (gathered) {
-        const tern_dims patches = {o0.n, layers[0].g.k[0] * layers[0].g.k[1] * layers[0].g.k[2], o0.d, o0.h, o0.w};
-        ws += (tern_packed_bytes(patches) + 255u) & ~(size_t)255u;
-        const tern_conv_geom& g = layers[0].g;
-        PatchParams pp;
-        pp.src = in; pp.lo = in_lo; pp.hi = in_hi; pp.dst = cur_buf;
-        pp.d = in_dims.d; pp.h = in_dims.h; pp.w = in_dims.w;
-        pp.od = o0.d; pp.oh = o0.h; pp.ow = o0.w;
-        pp.kd = g.k[0]; pp.kh = g.k[1]; pp.kw = g.k[2];
-        pp.sh = g.stride[1]; pp.sw = g.stride[2];
-        pp.pd = g.pad[0]; pp.ph = g.pad[1]; pp.pw = g.pad[2];
-        pp.dh = g.dil[1]; pp.dw = g.dil[2];
-        // one launch from the intensities to layer 0's codes (below) unless its taps lie too far apart for
-        // that kernel; the region reserved for the tap strings then stays unused
-        first = pp;
-        fused = first_conv_applies(pp, in_dims.n, layers[0].c_out);
-        rc = fused ? TERN_OK : launch_patch_pack_f32(pp, in_dims.n, (hipStream_t)stream);
+    // A one-channel input with a 3x3x3, 1x3x3 or 15x3x3 first kernel: one launch from the intensities to layer 0's
+    // codes.  Otherwise: Eq. 6 on the raw intensities, packed, then layer 0 as is.
+    const bool direct = first_conv_applies(in_dims.c, layers[0].g, o0);
+    if (direct) {
+        const tern_dims taps = {o0.n, layers[0].g.k[0] * layers[0].g.k[1] * layers[0].g.k[2], o0.d, o0.h, o0.w};
+        ws += (tern_packed_bytes(taps) + 255u) & ~(size_t)255u;
     } else {
         ws += (tern_packed_bytes(in_dims) + 255u) & ~(size_t)255u;
         rc = tern_threshold_pack(in, TERN_SRC_F32, in_dims, in_lo, in_hi, cur_buf, stream);
@@ -545,22 +547,11 @@ static int fcn_run(const float* in, tern_dims in_dims, const float* in_lo, const
         } else {
             dst = out_packed;
         }
-        if (i == 0 && gathered && !fused) {
-            const int32_t taps = layers[0].g.k[0] * layers[0].g.k[1] * layers[0].g.k[2];
-            const tern_dims pin = {o.n, taps, o.d, o.h, o.w};
-            const tern_conv_geom unit = {{1, 1, 1}, {1, 1, 1}, {0, 0, 0}, {1, 1, 1}};
+        if (i == 0 && direct) {
             if (!aligned16(layers[0].w_bank) || !aligned16(dst)) return TERN_EARG;
-            rc = launch_conv3d(conv_params(cur_buf, pin, layers[0].w_bank, layers[0].c_out, unit, o,
-                                           layers[0].thr_lo, layers[0].thr_hi, nullptr, dst),
-                               (hipStream_t)stream);
-        } else if (i == 0 && gathered) {
-            if (!aligned16(layers[0].w_bank) || !aligned16(dst)) return TERN_EARG;
-            FirstConvParams fc;
-            fc.wgt = layers[0].w_bank; fc.lo = layers[0].thr_lo; fc.hi = layers[0].thr_hi;
-            fc.out_packed = dst;
-            fc.c_out = layers[0].c_out; fc.co_pad = (layers[0].c_out + 31) / 32 * 32;
-            fc.wd_out = tern_words(layers[0].c_out);
-            rc = launch_first_conv(first, fc, in_dims.n, (hipStream_t)stream);
+            rc = launch_first_conv(first_params(in, in_lo, in_hi, in_dims, layers[0].w_bank, layers[0].c_out, layers[0].g, o,
+                                                layers[0].thr_lo, layers[0].thr_hi, dst),
+                                   (hipStream_t)stream);
         } else {
             rc = tern_conv3d(cur_buf, cur, layers[i].w_bank, layers[i].c_out, layers[i].g,
                              layers[i].thr_lo, layers[i].thr_hi, nullptr, dst, stream);
@@ -689,46 +680,25 @@ int net_walk(tern_dims in_dims, const tern_module* mods, int32_t n_mods, NetWalk
     std::vector<size_t> ooff((size_t)n_mods);
     size_t off = 0;
     const size_t in_off = off;
-    // Module 0 on a one-channel input with a 3x3x3 / 1x3x3 kernel: the input region holds the
-    // gathered taps of every output voxel instead of the packed input (see tern_fcn_forward).
-    bool gathered = false;
+    // Module 0 on a one-channel input with a 3x3x3, 1x3x3 or 15x3x3 kernel: one launch from the intensities to its codes,
+    // and the input region has room for the taps of every output voxel instead of the packed input (see tern_fcn_forward).
+    bool direct = false;
     tern_dims o0 = in_dims;
     {
         const tern_module& m0 = mods[0];
         const bool plain = m0.skip_from == -1 && m0.up[0] == 1 && m0.up[1] == 1 && m0.up[2] == 1 &&
                            m0.pool[0] <= 1 && m0.pool[1] <= 1 && m0.pool[2] <= 1;
         if (plain && geom_check(in_dims, m0.c_out, m0.g, &o0) == TERN_OK)
-            gathered = patch_pack_applies(in_dims.c, m0.g, o0);
+            direct = first_conv_applies(in_dims.c, m0.g, o0);
     }
-    if (gathered) {
-        const tern_dims patches = {o0.n, mods[0].g.k[0] * mods[0].g.k[1] * mods[0].g.k[2], o0.d, o0.h, o0.w};
-        off += region(patches);
+    if (direct) {
+        const tern_dims taps = {o0.n, mods[0].g.k[0] * mods[0].g.k[1] * mods[0].g.k[2], o0.d, o0.h, o0.w};
+        off += region(taps);
     } else {
         off += region(in_dims);
     }
-    PatchParams first = {};
-    bool fused = false;
-    if (w && w->run) {
-        int rc;
-        if (gathered) {
-            const tern_conv_geom& g = mods[0].g;
-            PatchParams pp;
-            pp.src = w->in; pp.lo = w->in_lo; pp.hi = w->in_hi; pp.dst = (uint32_t*)(w->ws + in_off);
-            pp.d = in_dims.d; pp.h = in_dims.h; pp.w = in_dims.w;
-            pp.od = o0.d; pp.oh = o0.h; pp.ow = o0.w;
-            pp.kd = g.k[0]; pp.kh = g.k[1]; pp.kw = g.k[2];
-            pp.sh = g.stride[1]; pp.sw = g.stride[2];
-            pp.pd = g.pad[0]; pp.ph = g.pad[1]; pp.pw = g.pad[2];
-            pp.dh = g.dil[1]; pp.dw = g.dil[2];
-            // one launch from the intensities to module 0's codes (below) unless its taps lie too far apart
-            // for that kernel; the region reserved for the tap strings then stays unused
-            first = pp;
-            fused = first_conv_applies(pp, in_dims.n, mods[0].c_out);
-            rc = fused ? TERN_OK : launch_patch_pack_f32(pp, in_dims.n, w->stream);
-        } else {
-            rc = tern_threshold_pack(w->in, TERN_SRC_F32, in_dims, w->in_lo, w->in_hi,
-                                     (uint32_t*)(w->ws + in_off), w->stream);
-        }
+    if (w && w->run && !direct) {
+        const int rc = tern_threshold_pack(w->in, TERN_SRC_F32, in_dims, w->in_lo, w->in_hi, (uint32_t*)(w->ws + in_off), w->stream);
         if (rc != TERN_OK) return rc;
     }
     tern_dims cur = in_dims;
@@ -811,24 +781,11 @@ int net_walk(tern_dims in_dims, const tern_module* mods, int32_t n_mods, NetWalk
             if (!m.w_bank || !m.thr_lo || !m.thr_hi) return TERN_ENULL;
             if (joined) {
                 // (launched above)
-            } else if (i == 0 && gathered && !fused) {
-                // single-tap convolution over the gathered words
-                const int32_t taps = m.g.k[0] * m.g.k[1] * m.g.k[2];
-                const tern_dims pin = {o.n, taps, o.d, o.h, o.w};
-                const tern_conv_geom unit = {{1, 1, 1}, {1, 1, 1}, {0, 0, 0}, {1, 1, 1}};
+            } else if (i == 0 && direct) {
                 if (!aligned16(m.w_bank)) return TERN_EARG;
-                rc = launch_conv3d(conv_params((const uint32_t*)(w->ws + cur_off), pin, m.w_bank, m.c_out, unit,
-                                               o, m.thr_lo, m.thr_hi, nullptr,
-                                               (uint32_t*)(w->ws + ooff[(size_t)i])),
-                                   w->stream);
-            } else if (i == 0 && gathered) {
-                if (!aligned16(m.w_bank)) return TERN_EARG;
-                FirstConvParams fc;
-                fc.wgt = m.w_bank; fc.lo = m.thr_lo; fc.hi = m.thr_hi;
-                fc.out_packed = (uint32_t*)(w->ws + ooff[(size_t)i]);
-                fc.c_out = m.c_out; fc.co_pad = (m.c_out + 31) / 32 * 32;
-                fc.wd_out = tern_words(m.c_out);
-                rc = launch_first_conv(first, fc, in_dims.n, w->stream);
+                rc = launch_first_conv(first_params(w->in, w->in_lo, w->in_hi, in_dims, m.w_bank, m.c_out, m.g, o, m.thr_lo, m.thr_hi,
+                                                    (uint32_t*)(w->ws + ooff[(size_t)i])),
+                                       w->stream);
             } else if (pooled) {
                 rc = tern_conv3d_digits((const uint32_t*)(w->ws + cur_off), cur, m.w_bank, m.c_out, m.g,
                                         m.thr_lo, m.thr_hi, nullptr, (uint32_t*)(w->ws + ooff[(size_t)i]),

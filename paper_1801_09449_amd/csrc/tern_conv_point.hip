@@ -1,6 +1,5 @@
 // Pointwise ternary convolution for gfx950: a 1x1x1 kernel with unit stride and no padding
-// (paper section 2, Eq. 9; the 1x1 rows of Table 1; also the second half of a one-channel first
-// layer whose taps were gathered into a bit string per voxel).
+// (paper section 2, Eq. 9; the 1x1 rows of Table 1).
 //
 // An output voxel depends on one input voxel only, so there is no halo, no LDS and no barrier: the volume
 // is a flat list of voxels.  A wave holds the filters of 32 NB channels in registers, widened to 4-bit

@@ -7,12 +7,17 @@
 // output needs and zeros at the others.  Shallow kernels (KD = 1, 3): seven planes to a 32-bit record, nine tap
 // columns in 63 of a step's 64 products, 8 - KD output planes from the same voxel operand with as many filter
 // operands.  Stacks (KD = 15): sixteen planes to a record, four tap columns to a step, three steps.
-// In-plane strides, dilations and paddings only move the columns that a lane reads.
+// In-plane strides, dilations and paddings only move the columns that a lane reads.  Where taps lie so far apart that
+// the box between them holds more columns than they read, each of three taps has a band of its own in LDS (FAR).
 //
 // What bounds it: intensities in, words out, and the decisions (three vector instructions per sum); gathering
 // the taps bit by bit, as the vector units needed them, took most of the time of the kernels before.  Measured
 // against those: 3x3x3 to 16 channels on 128 x 128 x 64 16.3 -> 9.9 us, 15x3x3 to 32 channels on one stack of
-// 15 x 236 x 172 10.1 -> 6.4, on sixteen (gathered to memory, then convolved) 28.1 -> 16.
+// 15 x 236 x 172 10.1 -> 6.4, on sixteen (gathered to memory, then convolved) 28.1 -> 16.  Far taps, in a box or
+// gathered before: 3x3x3 to 64 channels with dilation 19 on 79 x 170 x 278 140 -> 53, 15x3x3 to 16 with dilation 19 on two
+// stacks of 18 x 243 x 55 21.5 -> 8.7 (the kernel that gathered and convolved in one launch: 96 and 9.1).
+#include <type_traits>
+
 #include "tern_internal.h"
 #include "tern_matrix_choice.h"
 #include "tern_matrix_common.h"
@@ -28,13 +33,18 @@ struct FirstPlan {
     int32_t rows;                        // output rows of a wave
     Divisor tiles_x, tiles_y, tiles_z, hx_div;
     int32_t weights, cuts;               // LDS byte offsets: operands' parts and cut points
+    // (FAR) an axis of the columns: extent of a tap's band (of all taps in one: more than there are), voxels between
+    // neighbours in it, columns between neighbouring outputs and between neighbouring taps
+    struct Axis {
+        int32_t band, step, lane, tap;
+    } x, y;
 };
 
 __device__ __forceinline__ int quot(int e, Divisor d) { return (int)(((uint64_t)(uint32_t)e * d.m) >> d.s); }
 
 // FEW: at most 16 filters, the lower half of a block's rows.
-template <int KD, bool FEW>
-__global__ __launch_bounds__(kFirstThreads) void first_conv_kernel(PatchParams p, FirstConvParams c, FirstPlan t)
+template <int KD, bool FEW, bool FAR>
+__global__ __launch_bounds__(kFirstThreads) void first_conv_kernel(FirstConvParams p, FirstPlan t)
 {
     extern __shared__ __align__(16) uint8_t lds8[];
     constexpr bool STACK = KD > 7;
@@ -56,16 +66,21 @@ __global__ __launch_bounds__(kFirstThreads) void first_conv_kernel(PatchParams p
     const int gx0 = ox0 * p.sw - p.pw, gy0 = oy0 * p.sh - p.ph, gz0 = oz0 - p.pd;
 
     // ---- this thread's share of the filters: tap column `col` of filter f, nibble a = tap plane a -------
-    const int fb = blockIdx.y, f = tid & 31;
+    const int f = tid & 31;
+    int fb = blockIdx.y;
     uint32_t wm[WORDS], ws[WORDS];
+    int cut_lo, cut_hi;
+    auto fetch_filters = [&]() {
 #pragma unroll
-    for (int q = 0; q < WORDS; ++q) {
-        const v2u w = *reinterpret_cast<const v2u*>(c.wgt + ((size_t)q * c.co_pad + fb * 32 + f) * 2);
-        wm[q] = w.x; ws[q] = w.y;
-    }
-    const int co = min(fb * 32 + f, c.c_out - 1);
-    const int cut_lo = c.lo[co], cut_hi = c.hi[co];
-    const float lo = p.lo[0], hi = p.hi[0];
+        for (int q = 0; q < WORDS; ++q) {
+            const v2u w = *reinterpret_cast<const v2u*>(p.wgt + ((size_t)q * p.co_pad + fb * 32 + f) * 2);
+            wm[q] = w.x; ws[q] = w.y;
+        }
+        const int co = min(fb * 32 + f, p.c_out - 1);
+        cut_lo = p.lo[co]; cut_hi = p.hi[co];
+    };
+    fetch_filters();
+    const float lo = p.in_lo[0], hi = p.in_hi[0];
 
     // ---- intensities -> codes ---------------------------------------------------------------------------
     const size_t plane = (size_t)p.h * p.w;
@@ -78,7 +93,12 @@ __global__ __launch_bounds__(kFirstThreads) void first_conv_kernel(PatchParams p
         for (int u = 0; u < U; ++u) {
             const int e = min(base + u * kFirstThreads + tid, t.cols - 1);
             const int cy = quot(e, t.hx_div), cx = e - cy * t.hx;
-            const int iy = gy0 + cy, ix = gx0 + cx;
+            int iy = gy0 + cy, ix = gx0 + cx;
+            if constexpr (FAR) {
+                const int by = (cy >= t.y.band) + (cy >= 2 * t.y.band), bx = (cx >= t.x.band) + (cx >= 2 * t.x.band);
+                iy = gy0 + by * p.dh + (cy - by * t.y.band) * t.y.step;
+                ix = gx0 + bx * p.dw + (cx - bx * t.x.band) * t.x.step;
+            }
             in_plane[u] = (uint32_t)iy < (uint32_t)p.h && (uint32_t)ix < (uint32_t)p.w;
             const int off = in_plane[u] ? iy * p.w + ix : 0;
 #pragma unroll
@@ -109,163 +129,203 @@ __global__ __launch_bounds__(kFirstThreads) void first_conv_kernel(PatchParams p
     fill(0);
 
     // ---- filters and cut points -> LDS --------------------------------------------------------------------
-    // Column records: shallow [9][32] of 32 bits, stacks [12][32] of 64 bits (columns 9 .. 11 are zero).
-    for (int col = tid >> 5; col < (STACK ? 12 : 9); col += kFirstThreads / 32) {
-        uint32_t r[2] = {0u, 0u};
-        if (col < 9) {
-#pragma unroll
-            for (int a = 0; a < KD; ++a) {
-                constexpr int kBits = 9;
-                const int q = (a * kBits) >> 5, sh = (a * kBits) & 31;
-                const uint32_t m = __builtin_amdgcn_alignbit(q + 1 < WORDS ? wm[q + 1 < WORDS ? q + 1 : q] : 0u, wm[q], sh) >> col;
-                const uint32_t s = __builtin_amdgcn_alignbit(q + 1 < WORDS ? ws[q + 1 < WORDS ? q + 1 : q] : 0u, ws[q], sh) >> col;
-                r[a >> 3] |= ((m & 1u) << 1 | (s & m & 1u) << 3) << (4 * (a & 7));
-            }
-        }
-        if constexpr (STACK) *reinterpret_cast<v2u*>(lds8 + t.weights + (col * 32 + f) * 8) = v2u{r[0], r[1]};
-        else *reinterpret_cast<uint32_t*>(lds8 + t.weights + (col * 32 + f) * 4) = r[0];
-    }
     float* cuts = reinterpret_cast<float*>(lds8 + t.cuts);
-    if (tid < 32) {
-        const Cut cut = cut_of(cut_lo, cut_hi, fb * 32 + tid < c.c_out);
-        cuts[tid] = cut.start;
-        cuts[32 + tid] = cut.width;
-    }
+    auto stage_filters = [&]() {
+        // Column records: shallow [9][32] of 32 bits, stacks [12][32] of 64 bits (columns 9 .. 11 are zero).
+        for (int col = tid >> 5; col < (STACK ? 12 : 9); col += kFirstThreads / 32) {
+            uint32_t r[2] = {0u, 0u};
+            if (col < 9) {
+#pragma unroll
+                for (int a = 0; a < KD; ++a) {
+                    constexpr int kBits = 9;
+                    const int q = (a * kBits) >> 5, sh = (a * kBits) & 31;
+                    const uint32_t m = __builtin_amdgcn_alignbit(q + 1 < WORDS ? wm[q + 1 < WORDS ? q + 1 : q] : 0u, wm[q], sh) >> col;
+                    const uint32_t s = __builtin_amdgcn_alignbit(q + 1 < WORDS ? ws[q + 1 < WORDS ? q + 1 : q] : 0u, ws[q], sh) >> col;
+                    r[a >> 3] |= ((m & 1u) << 1 | (s & m & 1u) << 3) << (4 * (a & 7));
+                }
+            }
+            if constexpr (STACK) *reinterpret_cast<v2u*>(lds8 + t.weights + (col * 32 + f) * 8) = v2u{r[0], r[1]};
+            else *reinterpret_cast<uint32_t*>(lds8 + t.weights + (col * 32 + f) * 4) = r[0];
+        }
+        if (tid < 32) {
+            const Cut cut = cut_of(cut_lo, cut_hi, fb * 32 + tid < p.c_out);
+            cuts[tid] = cut.start;
+            cuts[32 + tid] = cut.width;
+        }
+    };
+    stage_filters();
     for (int base = U * kFirstThreads; base < t.cols; base += U * kFirstThreads) fill(base);
     __syncthreads();
 
-    // ---- operands of the filters, start values ---------------------------------------------------------------
-    const int ox = ox0 + 32 * (wave & 1) + i32;
-    if (ox0 + 32 * (wave & 1) >= p.ow) return;
-    constexpr int STEPS = STACK ? 3 : 1;
-    v4i A[STACK ? STEPS : TZ];
-    if constexpr (STACK) {
-#pragma unroll
-        for (int q = 0; q < STEPS; ++q) {
-            const v2u a = *reinterpret_cast<const v2u*>(lds8 + t.weights + ((4 * q + 2 * g) * 32 + i32) * 8);
-            const v2u b = *reinterpret_cast<const v2u*>(lds8 + t.weights + ((4 * q + 2 * g + 1) * 32 + i32) * 8);
-            A[q] = v4i{(int)a.x, (int)a.y, (int)b.x, (int)b.y};
-        }
-    } else {
-        // lanes 0-31: tap columns 0 .. 3 and, above their seven planes, planes 0 .. 3 of column 4; lanes 32-63:
-        // columns 5 .. 8 and planes 4 .. 6 of column 4
-        const uint32_t* w = reinterpret_cast<const uint32_t*>(lds8 + t.weights) + i32;
-        const uint32_t w4 = w[4 * 32];
-        uint32_t wc[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) wc[j] = w[(5 * g + j) * 32];
-#pragma unroll
-        for (int z = 0; z < TZ; ++z)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) A[z][j] = (int)((wc[j] << (4 * z)) | (((w4 << (4 * z)) >> (4 * j + 16 * g)) << 28));
-    }
-    v16f start;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const float4 h = *reinterpret_cast<const float4*>(cuts + 8 * k + 4 * g);
-        start[4 * k] = h.x; start[4 * k + 1] = h.y; start[4 * k + 2] = h.z; start[4 * k + 3] = h.w;
-    }
-    const float* widths = cuts + 32 + 4 * g;
-
-    const size_t slab = (size_t)p.oh * p.ow * 2u * c.wd_out;
-    auto store = [&](const v16f& acc, int oy, int oz) {
-        uint32_t pos, neg;
-        decide_rows<FEW ? 2 : 4>(pos, neg, acc, widths);
-        const uint32_t word = FEW ? half_block_word(pos, neg) : block_word(pos, neg);
-        if (ox < p.ow) c.out_packed[((size_t)n * p.od + oz) * slab + ((size_t)oy * p.ow + ox) * 2u * c.wd_out + g * c.wd_out + fb] = word;
-    };
-    // columns of this lane's taps, LDS bytes from that of tap (0, 0)
-    constexpr int REC = STACK ? 8 : 4;
-    auto tap_col = [&](int col) { return ((col / 3) * p.dh * t.hx + (col % 3) * p.dw) * REC; };
-    for (int r = 0; r < t.rows; ++r) {
-        const int y = (wave >> 1) * t.rows + r, oy = oy0 + y;
-        if (oy >= p.oh) break;
-        const uint8_t* at = lds8 + (y * p.sh * t.hx + (32 * (wave & 1) + i32) * p.sw) * REC;
+    const bool active = ox0 + 32 * (wave & 1) < p.ow;
+    const int x = 32 * (wave & 1) + i32, ox = ox0 + x;
+    const int col_x = FAR ? min(x, p.ow - 1 - ox0) : x;    // (a narrow volume has no more columns)
+    const int lane_x = FAR ? t.x.lane : p.sw, lane_y = FAR ? t.y.lane : p.sh, tap_x = FAR ? t.x.tap : p.dw, tap_y = FAR ? t.y.tap : p.dh;
+    auto contract = [&]() {
+        // ---- operands of the filters, start values ---------------------------------------------------------------
+        constexpr int STEPS = STACK ? 3 : 1;
+        v4i A[STACK ? STEPS : TZ];
         if constexpr (STACK) {
-            v16f acc = start;
 #pragma unroll
             for (int q = 0; q < STEPS; ++q) {
-                // (columns past the ninth have zero weights: any codes do)
-                const int c0 = g ? min(4 * q + 2, 8) : 4 * q, c1 = g ? min(4 * q + 3, 8) : min(4 * q + 1, 8);
-                const v2u a = *reinterpret_cast<const v2u*>(at + tap_col(c0)), b = *reinterpret_cast<const v2u*>(at + tap_col(c1));
-                acc = multiply(A[q], v4i{(int)a.x, (int)a.y, (int)b.x, (int)b.y}, acc);
+                const v2u a = *reinterpret_cast<const v2u*>(lds8 + t.weights + ((4 * q + 2 * g) * 32 + i32) * 8);
+                const v2u b = *reinterpret_cast<const v2u*>(lds8 + t.weights + ((4 * q + 2 * g + 1) * 32 + i32) * 8);
+                A[q] = v4i{(int)a.x, (int)a.y, (int)b.x, (int)b.y};
             }
-            store(acc, oy, oz0);
         } else {
-            const uint32_t mid = *reinterpret_cast<const uint32_t*>(at + tap_col(4));
-            v4i B;
+            // lanes 0-31: tap columns 0 .. 3 and, above their seven planes, planes 0 .. 3 of column 4; lanes 32-63:
+            // columns 5 .. 8 and planes 4 .. 6 of column 4
+            const uint32_t* w = reinterpret_cast<const uint32_t*>(lds8 + t.weights) + i32;
+            const uint32_t w4 = w[4 * 32];
+            uint32_t wc[4];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const uint32_t col = *reinterpret_cast<const uint32_t*>(at + (g ? tap_col(5 + j) : tap_col(j)));
-                B[j] = (int)(col | ((mid >> (4 * j + 16 * g)) << 28));
-            }
+            for (int j = 0; j < 4; ++j) wc[j] = w[(5 * g + j) * 32];
 #pragma unroll
             for (int z = 0; z < TZ; ++z)
-                if (oz0 + z < p.od) store(multiply(A[z], B, start), oy, oz0 + z);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) A[z][j] = (int)((wc[j] << (4 * z)) | (((w4 << (4 * z)) >> (4 * j + 16 * g)) << 28));
         }
+        v16f start;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const float4 h = *reinterpret_cast<const float4*>(cuts + 8 * k + 4 * g);
+            start[4 * k] = h.x; start[4 * k + 1] = h.y; start[4 * k + 2] = h.z; start[4 * k + 3] = h.w;
+        }
+        const float* widths = cuts + 32 + 4 * g;
+
+        const size_t slab = (size_t)p.oh * p.ow * 2u * p.wd_out;
+        auto store = [&](const v16f& acc, int oy, int oz) {
+            uint32_t pos, neg;
+            decide_rows<FEW ? 2 : 4>(pos, neg, acc, widths);
+            const uint32_t word = FEW ? half_block_word(pos, neg) : block_word(pos, neg);
+            if (ox < p.ow) p.out_packed[((size_t)n * p.od + oz) * slab + ((size_t)oy * p.ow + ox) * 2u * p.wd_out + g * p.wd_out + fb] = word;
+        };
+        // columns of this lane's taps, LDS bytes from that of tap (0, 0)
+        constexpr int REC = STACK ? 8 : 4;
+        auto tap_col = [&](int col) { return ((col / 3) * tap_y * t.hx + (col % 3) * tap_x) * REC; };
+        for (int r = 0; r < t.rows; ++r) {
+            const int y = (wave >> 1) * t.rows + r, oy = oy0 + y;
+            if (oy >= p.oh) break;
+            const uint8_t* at = lds8 + (y * lane_y * t.hx + col_x * lane_x) * REC;
+            if constexpr (STACK) {
+                v16f acc = start;
+#pragma unroll
+                for (int q = 0; q < STEPS; ++q) {
+                    // (columns past the ninth have zero weights: any codes do)
+                    const int c0 = g ? min(4 * q + 2, 8) : 4 * q, c1 = g ? min(4 * q + 3, 8) : min(4 * q + 1, 8);
+                    const v2u a = *reinterpret_cast<const v2u*>(at + tap_col(c0)), b = *reinterpret_cast<const v2u*>(at + tap_col(c1));
+                    acc = multiply(A[q], v4i{(int)a.x, (int)a.y, (int)b.x, (int)b.y}, acc);
+                }
+                store(acc, oy, oz0);
+            } else {
+                const uint32_t mid = *reinterpret_cast<const uint32_t*>(at + tap_col(4));
+                v4i B;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const uint32_t col = *reinterpret_cast<const uint32_t*>(at + (g ? tap_col(5 + j) : tap_col(j)));
+                    B[j] = (int)(col | ((mid >> (4 * j + 16 * g)) << 28));
+                }
+#pragma unroll
+                for (int z = 0; z < TZ; ++z)
+                    if (oz0 + z < p.od) store(multiply(A[z], B, start), oy, oz0 + z);
+            }
+        }
+    };
+    if constexpr (FAR && !FEW) {
+        // all filters on the columns that are there, where the launch has tiles enough
+        for (;;) {
+            if (active) contract();
+            fb += gridDim.y;
+            if (fb * 32 >= p.c_out) break;
+            fetch_filters();
+            __syncthreads();
+            stage_filters();
+            __syncthreads();
+        }
+    } else {
+        if (active) contract();
     }
 }
 
+// Columns of one axis: all between the first tap of the first output and the last of the last, or (far) three bands of
+// one column to an output.
+inline int64_t box_of(int outputs, int stride, int dil) { return (int64_t)(outputs - 1) * stride + 2 * (int64_t)dil + 1; }
+inline int64_t axis_of(int outputs, int stride, int dil, bool far, FirstPlan::Axis& a)
+{
+    a.band = far ? outputs : 1 << 20;
+    a.step = far ? stride : 1;
+    a.lane = far ? 1 : stride;
+    a.tap = far ? outputs : dil;
+    return far ? 3 * outputs : box_of(outputs, stride, dil);
+}
+
 template <int KD>
-bool plan_first(const PatchParams& p, int32_t n, int32_t c_out, FirstPlan& t, dim3& grid, size_t& lds)
+void plan_first(const FirstConvParams& p, FirstPlan& t, bool& far, dim3& grid, size_t& lds)
 {
     constexpr bool STACK = KD > 7;
     constexpr int TZ = STACK ? 1 : 8 - KD, REC = STACK ? 8 : 4;
     const int64_t tx = cdiv(p.ow, kTileX), tz = cdiv(p.od, TZ);
+    // Bands where they are fewer by a quarter: a box's lines come whole, and bands read them up to three times (a stack
+    // with steps of three and dilation 3: 196 columns in a box, 192 in bands, 17 and 21 us).  At most 256 columns in a row and
+    // eight rows to a row of outputs, so that four outputs' records, or two's, are within 16 KB (stacks: 32).
+    const int wide = p.ow < kTileX ? p.ow : kTileX;
+    const bool far_x = box_of(wide, p.sw, p.dw) > 4 * wide;
+    int64_t hx, hy, tiles;
     for (t.rows = 4;; t.rows >>= 1) {
-        // extents of the columns: beyond 16 K a workgroup would fill more than it reads
-        const int64_t hx = (int64_t)(kTileX - 1) * p.sw + 2 * (int64_t)p.dw + 1;
-        const int64_t hy = (int64_t)(2 * t.rows - 1) * p.sh + 2 * (int64_t)p.dh + 1;
-        const int64_t ty = cdiv(p.oh, 2 * t.rows), tiles = tx * ty * tz * n;
-        const bool last = t.rows == 1;
-        if (hx > 4096 || hy > 4096 || hx * hy > 4096) {
-            if (last) return false;
-            continue;
-        }
-        if (!last && tiles < 512) continue;                // two workgroups per compute unit
-        if (tiles > 0x7fffffff || cdiv(c_out, 32) > 65535) return false;
-        t.hx = (int32_t)hx;
-        t.cols = (int32_t)(hx * hy);
-        t.hx_div = divisor(t.hx);
-        t.tiles_x = divisor((int32_t)tx); t.tiles_y = divisor((int32_t)ty); t.tiles_z = divisor((int32_t)tz);
-        t.weights = (t.cols * REC + 15) & ~15;
-        t.cuts = t.weights + (STACK ? 12 * 32 * 8 : 9 * 32 * 4);
-        lds = (size_t)t.cuts + 64 * sizeof(float);
-        grid = dim3((unsigned)tiles, (unsigned)cdiv(c_out, 32));
-        return true;
+        const bool far_y = box_of(2 * t.rows, p.sh, p.dh) > 8 * t.rows;
+        far = box_of(kTileX, p.sw, p.dw) > 4 * kTileX || far_y;
+        hx = axis_of(far ? wide : kTileX, p.sw, p.dw, far && far_x, t.x);
+        hy = axis_of(2 * t.rows, p.sh, p.dh, far_y, t.y);
+        tiles = tx * cdiv(p.oh, 2 * t.rows) * tz * p.n;    // at most the voxels
+        // two workgroups per compute unit
+        if (t.rows == 1 || (hx * hy <= 4096 && tiles >= 512)) break;
     }
+    t.hx = (int32_t)hx;
+    t.cols = (int32_t)(hx * hy);
+    t.hx_div = divisor(t.hx);
+    t.tiles_x = divisor((int32_t)tx);
+    t.tiles_y = divisor(cdiv(p.oh, 2 * t.rows));
+    t.tiles_z = divisor((int32_t)tz);
+    t.weights = (t.cols * REC + 15) & ~15;
+    t.cuts = t.weights + (STACK ? 12 * 32 * 8 : 9 * 32 * 4);
+    lds = (size_t)t.cuts + 64 * sizeof(float);
+    grid = dim3((unsigned)tiles, far && tiles >= 512 ? 1u : (unsigned)cdiv(p.c_out, 32));
 }
 
 template <int KD>
-bool launch_first(const PatchParams& p, const FirstConvParams& c, int32_t n, hipStream_t s)
+void launch_first(const FirstConvParams& p, hipStream_t s)
 {
     FirstPlan t;
+    bool far;
     dim3 grid;
     size_t lds;
-    if (!plan_first<KD>(p, n, c.c_out, t, grid, lds)) return false;
-    if (c.c_out <= 16) hipLaunchKernelGGL((first_conv_kernel<KD, true>), grid, dim3(kFirstThreads), lds, s, p, c, t);
-    else hipLaunchKernelGGL((first_conv_kernel<KD, false>), grid, dim3(kFirstThreads), lds, s, p, c, t);
-    return true;
+    plan_first<KD>(p, t, far, grid, lds);
+    const auto go = [&](auto few, auto apart) {
+        hipLaunchKernelGGL((first_conv_kernel<KD, decltype(few)::value, decltype(apart)::value>), grid, dim3(kFirstThreads), lds, s, p, t);
+    };
+    const std::true_type yes;
+    const std::false_type no;
+    if (p.c_out <= 16) far ? go(yes, yes) : go(yes, no);
+    else far ? go(no, yes) : go(no, no);
 }
 
 }  // namespace
 
-bool first_conv_applies(const PatchParams& p, int32_t n, int32_t c_out)
+// One-channel input, 3 x 3 in the plane by 1, 3 or 15 planes, unit depth stride and dilation.  (The further limits
+// decide between workspace layouts of tern_fcn_forward and tern_net_forward.)
+bool first_conv_applies(int32_t c_in, const tern_conv_geom& g, const tern_dims& out)
 {
-    FirstPlan t;
-    dim3 grid;
-    size_t lds;
-    if (p.kh != 3 || p.kw != 3) return false;
-    if (p.kd == 1) return plan_first<1>(p, n, c_out, t, grid, lds);
-    if (p.kd == 3) return plan_first<3>(p, n, c_out, t, grid, lds);
-    if (p.kd == 15) return plan_first<15>(p, n, c_out, t, grid, lds);
-    return false;
+    if (c_in != 1 || g.k[1] != 3 || g.k[2] != 3 || g.stride[0] != 1 || g.dil[0] != 1) return false;
+    if (g.k[0] != 1 && g.k[0] != 3 && g.k[0] != 15) return false;
+    const int planes = g.k[0] == 15 ? 1 : 8;
+    return (int64_t)cdiv(out.d, planes) * out.n <= 65535 && cdiv(out.h, 4) <= 65535;
 }
 
-int launch_first_conv(const PatchParams& p, const FirstConvParams& c, int32_t n, hipStream_t s)
+int launch_first_conv(const FirstConvParams& p, hipStream_t s)
 {
-    const bool done = p.kd == 1 ? launch_first<1>(p, c, n, s) : p.kd == 3 ? launch_first<3>(p, c, n, s) : p.kd == 15 && launch_first<15>(p, c, n, s);
-    if (!done) return TERN_EARG;
+    if (p.kd == 1) launch_first<1>(p, s);
+    else if (p.kd == 3) launch_first<3>(p, s);
+    else launch_first<15>(p, s);
     TERN_HIP_CHECK(hipGetLastError());
     return TERN_OK;
 }

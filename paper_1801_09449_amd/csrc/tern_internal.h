@@ -108,30 +108,23 @@ struct RealConvParams {
     int64_t total;          // output voxels
 };
 
-// Gathering of the taps of a one-channel first layer (see patch_pack_f32_kernel).
-struct PatchParams {
-    const float* src;       // [N][1][d][h][w]
-    const float* lo;        // [1] cut points of the input activation
-    const float* hi;
-    uint32_t* dst;          // [N][od][oh][ow][2][1]
-    int32_t d, h, w, od, oh, ow;
-    int32_t kd, kh, kw, sh, sw, pd, ph, pw, dh, dw;
-};
-// True when a first layer with c_in input channels, geometry g and output extents `out` can take
-// that route.
-bool patch_pack_applies(int32_t c_in, const tern_conv_geom& g, const tern_dims& out);
-int launch_patch_pack_f32(const PatchParams& p, int32_t n, hipStream_t s);
-// Layer 0 from the intensities in one launch (tern_first_layer.hip; PatchParams::dst unused): tap-packed filter
-// bank, integer cut points, packed output [N][od][oh][ow][2][wd_out].
+// Layer 0 on a scalar volume, from the intensities to packed codes in one launch (tern_first_layer.hip): cut points of
+// the intensities, tap-packed filter bank, integer cut points, packed output [N][od][oh][ow][2][wd_out].
 struct FirstConvParams {
-    const uint32_t* wgt;    // [words of the tap string][co_pad][2][1]
+    const float* src;       // [n][1][d][h][w]
+    const float* in_lo;     // [1]
+    const float* in_hi;
+    const uint32_t* wgt;    // [words of a filter's taps][co_pad][2][1]
     const int32_t* lo;      // [c_out]
     const int32_t* hi;
     uint32_t* out_packed;
+    int32_t n, d, h, w, od, oh, ow;
+    int32_t kd, sh, sw, pd, ph, pw, dh, dw;
     int32_t c_out, co_pad, wd_out;
 };
-int launch_first_conv(const PatchParams& p, const FirstConvParams& c, int32_t n, hipStream_t s);
-bool first_conv_applies(const PatchParams& p, int32_t n, int32_t c_out);
+// True when a first layer with c_in input channels, geometry g and output extents `out` takes that route.
+bool first_conv_applies(int32_t c_in, const tern_conv_geom& g, const tern_dims& out);
+int launch_first_conv(const FirstConvParams& p, hipStream_t s);
 
 // Largest dynamic LDS allocation the current device grants one workgroup, at most the 160 KB of a
 // gfx950 compute unit (queried once per device; 0 on error).

@@ -314,165 +314,6 @@ int launch_threshold_pack_f32(const float* src, tern_dims dims, const float* lo,
     return launch_pack_any<float, 1>(src, dims, lo, hi, dst, s);
 }
 
-// ---- first layer of a network on a scalar volume: gather the kernel taps into one word ----------
-// With one input channel a packed voxel carries a single live bit per plane, and a convolution
-// would have to collect its T <= 32 taps bit by bit for every output voxel and channel slice.
-// This kernel does that collecting once, straight from the float intensities (applying the
-// activation cut points on the way): output voxel o gets a mask string and a sign string whose
-// bit t is the code of tap t = (a*kh + b)*kw + c of o's receptive field (0 outside the volume).
-// The convolution then is a single-tap one over T "channels", and the tap-packed filter bank
-// (bit t of its one word per channel = tap t) is exactly that convolution's plain bank.
-// A thread owns one (ox, oy) column and kPatchZ consecutive output planes; with unit depth stride
-// and dilation these share input planes, so kPatchZ + KD - 1 plane parts serve kPatchZ outputs.
-// Only where tern_first_layer.hip does not reach (taps too far apart in the plane for its tiles).
-// Instantiated for the usual first kernels, 3x3x3 and 1x3x3, and for the 15x3x3 stack kernel of
-// Table 1, whose 135 taps make a five-word string (any in-plane stride, dilation, pad).
-namespace {
-
-// PZ = output planes per thread, WDP = words per plane of the gathered tap string.
-// Tap strings of output voxels (ox, oy, oz0 .. oz0+PZ-1) of batch item n: wm[t][q], ws[t][q].
-template <int KD, int KH, int KW, int PZ>
-__device__ __forceinline__ void gather_taps(const PatchParams& p, int n, int ox, int oy, int oz0,
-                                            uint32_t (&wm)[PZ][(KD * KH * KW + 31) / 32],
-                                            uint32_t (&ws)[PZ][(KD * KH * KW + 31) / 32])
-{
-    constexpr int NB = KH * KW;   // taps per input plane
-    constexpr int WDP = (KD * NB + 31) / 32;
-    const float lo = p.lo[0], hi = p.hi[0];
-    const float* src_n = p.src + (size_t)n * p.d * p.h * p.w;
-    const size_t plane = (size_t)p.h * p.w;
-
-    // In-plane offsets of this column's taps, fixed for the whole walk; taps outside the plane
-    // read element 0 and are masked out afterwards, so every load is unconditional.
-    int off[NB];
-    uint32_t valid = 0u;
-#pragma unroll
-    for (int b = 0; b < KH; ++b)
-#pragma unroll
-        for (int c = 0; c < KW; ++c) {
-            const int iy = oy * p.sh - p.ph + b * p.dh;
-            const int ix = ox * p.sw - p.pw + c * p.dw;
-            const bool ok = iy >= 0 && iy < p.h && ix >= 0 && ix < p.w;
-            off[b * KW + c] = ok ? iy * p.w + ix : 0;
-            valid |= (ok ? 1u : 0u) << (b * KW + c);
-        }
-
-    // All input planes this thread needs, fetched before any of them is used: one memory round
-    // trip for the whole walk.  Planes outside the volume read plane 0 and are masked out.
-    constexpr int NP = PZ + KD - 1;
-    float v[NP][NB];
-#pragma unroll
-    for (int j = 0; j < NP; ++j) {
-        const int iz = oz0 - p.pd + j;
-        const float* pl = src_n + (size_t)((iz >= 0 && iz < p.d) ? iz : 0) * plane;
-#pragma unroll
-        for (int i = 0; i < NB; ++i) v[j][i] = pl[off[i]];
-    }
-    // codes of the in-plane taps of every fetched plane, tap (b, c) at bit b*KW + c
-    uint32_t m[NP], s[NP];
-#pragma unroll
-    for (int j = 0; j < NP; ++j) {
-        const int iz = oz0 - p.pd + j;
-        uint32_t P = 0u, N = 0u;
-#pragma unroll
-        for (int i = NB - 1; i >= 0; --i) {
-            // P = 2P + (hi < v), N = 2N + (v < lo): the comparison result travels through the
-            // carry flag into the low bit (ordered comparisons: false for NaN, like the C ones)
-            asm("v_cmp_lt_f32 vcc, %2, %1\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc"
-                : "+v"(P) : "v"(v[j][i]), "s"(hi) : "vcc");
-            asm("v_cmp_gt_f32 vcc, %2, %1\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc"
-                : "+v"(N) : "v"(v[j][i]), "s"(lo) : "vcc");
-        }
-        const uint32_t vm = (iz >= 0 && iz < p.d) ? valid : 0u;
-        P &= vm;
-        N &= vm & ~P;          // +1 wins should the cut points be crossed (lo > hi)
-        m[j] = P | N;
-        s[j] = N;
-    }
-#pragma unroll
-    for (int t = 0; t < PZ; ++t) {
-        // plane a of the kernel occupies bits [a*NB, a*NB + NB) of the tap string
-#pragma unroll
-        for (int q = 0; q < WDP; ++q) wm[t][q] = ws[t][q] = 0u;
-#pragma unroll
-        for (int a = 0; a < KD; ++a) {
-            constexpr int kNB = NB;
-            const int word = (a * kNB) / 32, sh = (a * kNB) % 32;
-            wm[t][word] |= m[t + a] << sh;
-            ws[t][word] |= s[t + a] << sh;
-            if (sh + kNB > 32) {
-                wm[t][word + 1] |= m[t + a] >> (32 - sh);
-                ws[t][word + 1] |= s[t + a] >> (32 - sh);
-            }
-        }
-    }
-}
-
-template <int KD, int KH, int KW, int PZ>
-__global__ __launch_bounds__(256) void patch_pack_f32_kernel(PatchParams p)
-{
-    constexpr int WDP = (KD * KH * KW + 31) / 32;
-    const int ox = blockIdx.x * 64 + threadIdx.x;
-    const int oy = blockIdx.y * 4 + threadIdx.y;
-    const int nseg = (p.od + PZ - 1) / PZ;
-    const int seg = blockIdx.z % nseg;
-    const int n = blockIdx.z / nseg;
-    if (ox >= p.ow || oy >= p.oh) return;
-    const int oz0 = seg * PZ;
-    uint32_t wm[PZ][WDP], ws[PZ][WDP];
-    gather_taps<KD, KH, KW, PZ>(p, n, ox, oy, oz0, wm, ws);
-    uint32_t* out = p.dst + ((((size_t)n * p.od + oz0) * p.oh + oy) * p.ow + ox) * 2u * WDP;
-    const size_t ostep = (size_t)p.oh * p.ow * 2u * WDP;
-#pragma unroll
-    for (int t = 0; t < PZ; ++t) {
-        if (oz0 + t >= p.od) break;
-        uint32_t* o = out + (size_t)t * ostep;
-        if constexpr (WDP == 1) {
-            *reinterpret_cast<uint2*>(o) = make_uint2(wm[t][0], ws[t][0]);
-        } else {
-#pragma unroll
-            for (int q = 0; q < WDP; ++q) { o[q] = wm[t][q]; o[WDP + q] = ws[t][q]; }
-        }
-    }
-}
-
-// Kernel extents the gathering kernel is instantiated for -> output planes per thread (0: none).
-// 15x3x3 is the stack-of-slices first layer of Table 1 (its output has a single plane).
-inline int patch_planes_per_thread(int kd, int kh, int kw)
-{
-    if (kh != 3 || kw != 3) return 0;
-    if (kd == 3 || kd == 1) return 8;
-    if (kd == 15) return 1;
-    return 0;
-}
-
-}  // namespace
-
-bool patch_pack_applies(int32_t c_in, const tern_conv_geom& g, const tern_dims& out)
-{
-    const int pz = patch_planes_per_thread(g.k[0], g.k[1], g.k[2]);
-    if (!(c_in == 1 && pz > 0 && g.stride[0] == 1 && g.dil[0] == 1)) return false;
-    // launch grid limits of the gathering kernel
-    const int64_t nseg = (out.d + pz - 1) / pz;
-    return nseg * out.n <= 65535 && (out.h + 3) / 4 <= 65535;
-}
-
-int launch_patch_pack_f32(const PatchParams& p, int32_t n, hipStream_t s)
-{
-    const int pz = patch_planes_per_thread(p.kd, p.kh, p.kw);
-    if (pz == 0) return TERN_EARG;
-    const int nseg = (p.od + pz - 1) / pz;
-    const dim3 grid((unsigned)((p.ow + 63) / 64), (unsigned)((p.oh + 3) / 4), (unsigned)(nseg * n)), block(64, 4);
-    if (p.kd == 3)
-        hipLaunchKernelGGL((patch_pack_f32_kernel<3, 3, 3, 8>), grid, block, 0, s, p);
-    else if (p.kd == 1)
-        hipLaunchKernelGGL((patch_pack_f32_kernel<1, 3, 3, 8>), grid, block, 0, s, p);
-    else
-        hipLaunchKernelGGL((patch_pack_f32_kernel<15, 3, 3, 1>), grid, block, 0, s, p);
-    TERN_HIP_CHECK(hipGetLastError());
-    return TERN_OK;
-}
-
 // ---- filter bank ------------------------------------------------------------------------------
 // Layout consumed by the convolution kernels (documented in include/tern.h).
 // Plain: uint32 [T * nchunk][co_pad][2][wc]; step s = tap * nchunk + chunk holds, for every

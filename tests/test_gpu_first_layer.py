@@ -40,6 +40,13 @@ def run(G, x, in_lo, in_hi, w, lo, hi, stride, pad, dil):
     ((3, 3, 3), 2, (7, 30, 80), 16, (1, 1, 3), (2, 5, 4), (1, 3, 2)),         # planes and columns of padding alone
     ((3, 3, 3), 1, (5, 40, 620), 8, (1, 1, 70), (1, 1, 1), (1, 1, 1)),        # columns too far apart for a tile
     ((3, 3, 3), 1, (5, 260, 130), 8, (1, 1, 1), (1, 60, 40), (1, 120, 60)),
+    ((3, 3, 3), 1, (6, 196, 25), 16, (1, 1, 70), (1, 0, 0), (1, 2, 1)),       # one output along x, whose taps lie together
+    ((3, 3, 3), 1, (5, 60, 141), 17, (1, 3, 4), (1, 5, 60), (1, 5, 60)),      # a narrow output, taps far apart along x
+    ((3, 3, 3), 2, (40, 131, 130), 70, (1, 1, 1), (1, 20, 66), (1, 20, 66)),  # far apart along both; all blocks of filters in a workgroup
+    ((3, 3, 3), 1, (9, 70, 40), 40, (1, 1, 1), (1, 3, 1), (1, 4, 1)),         # along y alone; a workgroup to a block of filters
+    ((1, 3, 3), 1, (7, 40, 200), 33, (1, 1, 1), (0, 9, 70), (1, 9, 70)),
+    ((15, 3, 3), 8, (15, 130, 140), 64, (1, 1, 1), (0, 0, 0), (1, 16, 16)),
+    ((15, 3, 3), 2, (16, 60, 330), 40, (1, 1, 2), (1, 0, 90), (1, 24, 130)),
     ((1, 3, 3), 1, (7, 8, 64), 16, (1, 1, 1), (0, 1, 1), (1, 1, 1)),
     ((1, 3, 3), 2, (15, 33, 97), 33, (1, 2, 1), (0, 0, 2), (1, 1, 2)),
     ((15, 3, 3), 1, (15, 20, 34), 16, (1, 1, 1), (0, 0, 0), (1, 1, 1)),
