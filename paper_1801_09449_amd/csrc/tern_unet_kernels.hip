@@ -340,19 +340,22 @@ __global__ __launch_bounds__(kBlock) void real_conv_lut_kernel(RealConvParams p,
 //
 // What bounds it: on one U-Net stack (20 thousand voxels) a round trip for the weights, one for the records and
 // the launch; on sixteen the vector instructions around the matrix ones (addresses, twelve to widen the codes).
-// Measured, 64 -> 2 channels, 3 x 3: 20 thousand voxels 17.6 us with tables, 6.0 here; 323 thousand 25.5 and 20.2.
+// Measured, 64 -> 2 channels, 3 x 3: 20 thousand voxels 17.6 us with tables, 6.0 here; 323 thousand 25.5 and 20.2;
+// 128 -> 2 on 191 thousand 39 and 23.
 //
 // Zero codes times an infinity would be NaN, which they are not in the table sums, and pieces of the smallest floats
 // would be lost: a workgroup that meets a weight that is not 0 and outside 2^-100 .. 2^100 adds one by one.
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef uint32_t v2w __attribute__((ext_vector_type(2)));
+typedef uint32_t v3w __attribute__((ext_vector_type(3)));
 typedef uint32_t v4w __attribute__((ext_vector_type(4)));
 
 struct RealMatrixPlan {
     Divisor ow, oh, od;
     Divisor taps, filter;        // taps of a (filter, channel); elements of a filter, padded channels included
-    Reciprocal kw, kh, words;    // divisions of unit numbers
+    Divisor chunks;              // units of a tap
+    Reciprocal kw, kh;           // divisions of tap numbers
     int32_t tiles;
     uint32_t bytes;              // of the input
 };
@@ -360,19 +363,40 @@ struct RealMatrixPlan {
 __device__ __forceinline__ int quot(int e, Divisor d) { return (int)(((uint64_t)(uint32_t)e * d.m) >> d.s); }
 __device__ __forceinline__ int quot(int e, Reciprocal r) { return (int)(__umul24((uint32_t)e, r.m) >> r.s); }
 
-// A unit of work: a tap's whole record (WD == 2) or one channel word of it, of 16 voxels.  BATCH units' records are
-// under way together, and every batch is a whole one: units past the last read zeros.
-// NV: blocks of 16 voxels to a wave.
-template <int WD, bool PADDED, int BATCH, int NV>
+// N consecutive words, `at` and `more` bytes from the buffer's start, in the fewest loads (records are 8-byte aligned
+// and a load need be 4-byte aligned only).
+template <int N>
+__device__ __forceinline__ void load_words(uint32_t* d, __amdgpu_buffer_rsrc_t src, uint32_t at, int more)
+{
+    if constexpr (N >= 4) {
+        const v4w v = __builtin_amdgcn_raw_buffer_load_b128(src, at, more, 0);
+        d[0] = v.x; d[1] = v.y; d[2] = v.z; d[3] = v.w;
+        if constexpr (N > 4) load_words<N - 4>(d + 4, src, at, more + 16);
+    } else if constexpr (N == 3) {
+        const v3w v = __builtin_amdgcn_raw_buffer_load_b96(src, at, more, 0);
+        d[0] = v.x; d[1] = v.y; d[2] = v.z;
+    } else if constexpr (N == 2) {
+        const v2w v = __builtin_amdgcn_raw_buffer_load_b64(src, at, more, 0);
+        d[0] = v.x; d[1] = v.y;
+    } else {
+        d[0] = __builtin_amdgcn_raw_buffer_load_b32(src, at, more, 0);
+    }
+}
+
+// A unit of work: UW channel words of a tap, of 16 voxels.  RECORD: a record is one unit of two words and one load.
+// Else mask words and sign words are loaded separately, whole records' where they are up to five or seven words (word by word, 128 -> 2
+// channels, 3 x 3, on 191 thousand voxels took 95 us, now 23: sixteen lanes 32 bytes apart meet in a few cache banks, and
+// the loads of five or seven words touch every line as often).  BATCH units' records are under way together, and every
+// batch is a whole one: units past the last read zeros.
+template <int UW, bool RECORD, bool PADDED, int BATCH>
 __global__ __launch_bounds__(kBlock) void real_conv_matrix_kernel(RealConvParams p, RealMatrixPlan t)
 {
     extern __shared__ __align__(16) uint8_t wl8[];
-    constexpr int UW = WD == 2 ? 2 : 1;                   // words of a unit
-    constexpr int TILE = 4 * NV * 16;
+    constexpr int TILE = 64;                              // voxels of a workgroup, sixteen to a wave
     constexpr uint32_t NOTHING = 0x80000000u;             // past the input's end: reads as zeros
     const int tid = threadIdx.x, lane = tid & 63, col = lane & 15, q4 = lane >> 4;
     const int T = p.kd * p.kh * p.kw;
-    const int units = T * p.wd_in / UW;                   // at most 64
+    const int units = T * t.chunks.d;                     // at most 64
     const uint32_t rec = 8u * (uint32_t)p.wd_in;
 
     // lane u holds where unit u's record starts, from tap (0, 0, 0)'s, and its tap's steps in z, y and x
@@ -380,52 +404,48 @@ __global__ __launch_bounds__(kBlock) void real_conv_matrix_kernel(RealConvParams
     int unit_z, unit_y, unit_x;
     {
         const int u = min(lane, units - 1);
-        const int tap = UW == 2 ? u : quot(u, t.words), word = UW == 2 ? 0 : u - tap * p.wd_in;
+        const int tap = quot(u, t.chunks), word = UW * (u - tap * t.chunks.d);
         const int r = quot(tap, t.kw), a = quot(r, t.kh);
         unit_z = a * p.dd; unit_y = (r - a * p.kh) * p.dh; unit_x = (tap - r * p.kw) * p.dw;
         if (lane < units) unit_off = (uint32_t)((unit_z * p.h + unit_y) * p.w + unit_x) * rec + 4u * (uint32_t)word;
     }
 
-    int vox[NV], ix0[NV], iy0[NV], iz0[NV];
-    uint32_t off[NV];                                     // bytes of tap (0, 0, 0)'s record, modulo 2^32
+    int vox, ix0, iy0, iz0;
+    uint32_t off;                                         // bytes of tap (0, 0, 0)'s record, modulo 2^32
     auto enter = [&](int tile) {
-#pragma unroll
-        for (int v = 0; v < NV; ++v) {
-            vox[v] = (int)min((int64_t)tile * TILE + ((tid >> 6) * NV + v) * 16 + col, p.total - 1);
-            const int r = quot(vox[v], t.ow), x = vox[v] - r * t.ow.d;
-            const int r2 = quot(r, t.oh), y = r - r2 * t.oh.d;
-            const int n = quot(r2, t.od), z = r2 - n * t.od.d;
-            ix0[v] = x * p.sw - p.pw; iy0[v] = y * p.sh - p.ph; iz0[v] = z * p.sd - p.pd;
-            off[v] = (uint32_t)(((n * p.d + iz0[v]) * p.h + iy0[v]) * p.w + ix0[v]) * rec;
-        }
+        vox = (int)min((int64_t)tile * TILE + (tid >> 6) * 16 + col, p.total - 1);
+        const int r = quot(vox, t.ow), x = vox - r * t.ow.d;
+        const int r2 = quot(r, t.oh), y = r - r2 * t.oh.d;
+        const int n = quot(r2, t.od), z = r2 - n * t.od.d;
+        ix0 = x * p.sw - p.pw; iy0 = y * p.sh - p.ph; iz0 = z * p.sd - p.pd;
+        off = (uint32_t)(((n * p.d + iz0) * p.h + iy0) * p.w + ix0) * rec;
     };
     const __amdgpu_buffer_rsrc_t src = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(p.in), 0, t.bytes, 0x00020000);
-    auto address = [&](int u, int v) {                    // (u: the same for all lanes)
-        uint32_t o = off[v] + (u < 64 ? (uint32_t)__builtin_amdgcn_readlane((int)unit_off, u & 63) : NOTHING);
+    auto address = [&](int u) {                           // (u: the same for all lanes)
+        uint32_t o = off + (u < 64 ? (uint32_t)__builtin_amdgcn_readlane((int)unit_off, u & 63) : NOTHING);
         if constexpr (PADDED) {
-            const bool inb = (uint32_t)(iz0[v] + __builtin_amdgcn_readlane(unit_z, u & 63)) < (uint32_t)p.d &&
-                             (uint32_t)(iy0[v] + __builtin_amdgcn_readlane(unit_y, u & 63)) < (uint32_t)p.h &&
-                             (uint32_t)(ix0[v] + __builtin_amdgcn_readlane(unit_x, u & 63)) < (uint32_t)p.w;
+            const bool inb = (uint32_t)(iz0 + __builtin_amdgcn_readlane(unit_z, u & 63)) < (uint32_t)p.d &&
+                             (uint32_t)(iy0 + __builtin_amdgcn_readlane(unit_y, u & 63)) < (uint32_t)p.h &&
+                             (uint32_t)(ix0 + __builtin_amdgcn_readlane(unit_x, u & 63)) < (uint32_t)p.w;
             o = inb && u < units ? o : NOTHING;
         }
         return o;
     };
-    uint32_t m[BATCH][NV][UW], s[BATCH][NV][UW];
+    uint32_t m[BATCH][UW], s[BATCH][UW];
     auto fetch = [&](int first) {
 #pragma unroll
-        for (int k = 0; k < BATCH; ++k)
-#pragma unroll
-            for (int v = 0; v < NV; ++v) {
-                const uint32_t o = address(first + k, v);
-                if constexpr (WD == 2) {
-                    const v4w r = __builtin_amdgcn_raw_buffer_load_b128(src, o, 0, 0);
-                    m[k][v][0] = r.x; m[k][v][1] = r.y;
-                    s[k][v][0] = r.z; s[k][v][1] = r.w;
-                } else {
-                    m[k][v][0] = __builtin_amdgcn_raw_buffer_load_b32(src, o, 0, 0);
-                    s[k][v][0] = __builtin_amdgcn_raw_buffer_load_b32(src, o, (int)(rec >> 1), 0);
-                }
+        for (int k = 0; k < BATCH; ++k) {
+            const uint32_t o = address(first + k);
+            const int signs = (int)(rec >> 1);
+            if constexpr (RECORD) {
+                const v4w r = __builtin_amdgcn_raw_buffer_load_b128(src, o, 0, 0);
+                m[k][0] = r.x; m[k][1] = r.y;
+                s[k][0] = r.z; s[k][1] = r.w;
+            } else {
+                load_words<UW>(m[k], src, o, 0);
+                load_words<UW>(s[k], src, o, signs);
             }
+        }
     };
     // Codes of 32 channels -> this lane's eight of them as bf16 numbers +-2 or 0 (signs without a mask become -0):
     // channels 4 q4 + {0, 16, 2, 18, 1, 17, 3, 19}.
@@ -442,15 +462,13 @@ __global__ __launch_bounds__(kBlock) void real_conv_matrix_kernel(RealConvParams
         o.w = (odd << (sh - 2u)) & mc0;
         return __builtin_bit_cast(v8bf, o);
     };
-    auto write = [&](int tile, int co, const float (&sum)[NV]) {
+    auto write = [&](int tile, int co, float sum) {
         const float b = p.bias ? p.bias[co] : 0.0f;
-#pragma unroll
-        for (int v = 0; v < NV; ++v)
-            if ((int64_t)tile * TILE + ((tid >> 6) * NV + v) * 16 + col < p.total) {
-                const int n = quot(quot(quot(vox[v], t.ow), t.oh), t.od);
-                const size_t ospatial = (size_t)p.od * p.oh * p.ow;
-                p.out[((size_t)n * p.c_out + co) * ospatial + (vox[v] - (size_t)n * ospatial)] = sum[v] + b;
-            }
+        if ((int64_t)tile * TILE + (tid >> 6) * 16 + col < p.total) {
+            const int n = quot(quot(quot(vox, t.ow), t.oh), t.od);
+            const size_t ospatial = (size_t)p.od * p.oh * p.ow;
+            p.out[((size_t)n * p.c_out + co) * ospatial + (vox - (size_t)n * ospatial)] = sum + b;
+        }
     };
 
     for (int co0 = 0; co0 < p.c_out; co0 += 4) {
@@ -490,22 +508,18 @@ __global__ __launch_bounds__(kBlock) void real_conv_matrix_kernel(RealConvParams
         if (__syncthreads_or(odd_weight ? 1 : 0) != 0) {
             for (int tile = blockIdx.x; tile < t.tiles; tile += gridDim.x) {
                 enter(tile);
-                float sum[NV];
+                float sum = 0.0f;
                 const float* wf = p.wgt + (size_t)(co0 + min(q4, cg - 1)) * p.c_in * T;
-#pragma unroll
-                for (int v = 0; v < NV; ++v) {
-                    sum[v] = 0.0f;
-                    for (int u = 0; u < units; ++u) {
-                        const uint32_t o = address(u, v);
-                        const int tap = UW == 2 ? u : quot(u, t.words);
-                        for (int w = 0; w < UW; ++w) {
-                            const int word = UW == 2 ? w : u - tap * p.wd_in, live = min(32, p.c_in - 32 * word);
-                            const uint32_t mw = __builtin_amdgcn_raw_buffer_load_b32(src, o, 4 * w, 0);
-                            const uint32_t sw = __builtin_amdgcn_raw_buffer_load_b32(src, o, 4 * w + (int)(rec >> 1), 0);
-                            for (int j = 0; j < live; ++j) {
-                                const float wv = wf[(size_t)(32 * word + j) * T + tap];
-                                if ((mw >> j) & 1u) sum[v] += (sw >> j) & 1u ? -wv : wv;
-                            }
+                for (int u = 0; u < units; ++u) {
+                    const uint32_t o = address(u);
+                    const int tap = quot(u, t.chunks), word = UW * (u - tap * t.chunks.d);
+                    for (int w = 0; w < UW; ++w) {
+                        const int live = min(32, p.c_in - 32 * (word + w));
+                        const uint32_t mw = __builtin_amdgcn_raw_buffer_load_b32(src, o, 4 * w, 0);
+                        const uint32_t sw = __builtin_amdgcn_raw_buffer_load_b32(src, o, 4 * w + (int)(rec >> 1), 0);
+                        for (int j = 0; j < live; ++j) {
+                            const float wv = wf[(size_t)(32 * (word + w) + j) * T + tap];
+                            if ((mw >> j) & 1u) sum += (sw >> j) & 1u ? -wv : wv;
                         }
                     }
                 }
@@ -515,9 +529,7 @@ __global__ __launch_bounds__(kBlock) void real_conv_matrix_kernel(RealConvParams
         }
         for (int tile = blockIdx.x;;) {
             // (rows of filters that do not exist and every fourth row hold anything: nobody reads their sums)
-            v4f acc[NV];
-#pragma unroll
-            for (int v = 0; v < NV; ++v) acc[v] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+            v4f acc = {0.0f, 0.0f, 0.0f, 0.0f};
             for (int first = 0;;) {
 #pragma unroll
                 for (int k = 0; k < BATCH; ++k)
@@ -525,18 +537,13 @@ __global__ __launch_bounds__(kBlock) void real_conv_matrix_kernel(RealConvParams
                     for (int w = 0; w < UW; ++w) {
                         // (a unit past the last: zeros times any filter)
                         const v8bf a = *reinterpret_cast<const v8bf*>(wl8 + (min(first + k, units - 1) * UW + w) * 1024 + lane * 16);
-#pragma unroll
-                        for (int v = 0; v < NV; ++v)
-                            acc[v] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, widen(m[k][v][w], s[k][v][w]), acc[v], 0, 0, 0);
+                        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, widen(m[k][w], s[k][w]), acc, 0, 0, 0);
                     }
                 first += BATCH;
                 if (first >= units) break;
                 fetch(first);
             }
-            float sum[NV];
-#pragma unroll
-            for (int v = 0; v < NV; ++v) sum[v] = 0.5f * ((acc[v][2] + acc[v][1]) + acc[v][0]);
-            if (q4 < cg) write(tile, co0 + q4, sum);
+            if (q4 < cg) write(tile, co0 + q4, 0.5f * ((acc[2] + acc[1]) + acc[0]));
             tile += gridDim.x;
             if (tile >= t.tiles) break;
             enter(tile);
@@ -705,14 +712,14 @@ int launch_concat(const ConcatParams& p, hipStream_t s)
 // Workgroups of a launch, each with its own copy of the filters' operands.
 constexpr int kRealGroups = 1024;
 
-template <int WD, bool PADDED, int BATCH>
+template <int UW, bool RECORD, bool PADDED, int BATCH>
 static void go_real_matrix(const RealConvParams& p, RealMatrixPlan& t, hipStream_t s)
 {
-    constexpr int NV = 1;
-    t.tiles = (int32_t)((p.total + 64 * NV - 1) / (64 * NV));
+    t.chunks = divisor(p.wd_in / UW);
+    t.tiles = (int32_t)((p.total + 63) / 64);
     const unsigned blocks = (unsigned)(t.tiles < kRealGroups ? t.tiles : kRealGroups);
     const size_t lds = (size_t)(p.kd * p.kh * p.kw * p.wd_in) * 1024;
-    hipLaunchKernelGGL((real_conv_matrix_kernel<WD, PADDED, BATCH, NV>), dim3(blocks), dim3(kBlock), lds, s, p, t);
+    hipLaunchKernelGGL((real_conv_matrix_kernel<UW, RECORD, PADDED, BATCH>), dim3(blocks), dim3(kBlock), lds, s, p, t);
 }
 
 // The matrix kernel where its operands fit in 64 KB and 32 bits count the input's bytes and the output's voxels.
@@ -721,25 +728,45 @@ static bool launch_real_matrix(const RealConvParams& p, hipStream_t s)
     const int64_t taps = (int64_t)p.kd * p.kh * p.kw, in_items = p.total / ((int64_t)p.od * p.oh * p.ow);
     const int64_t bytes = in_items * p.d * p.h * p.w * p.wd_in * 8;
     if (taps * p.wd_in > 64 || p.total > 0x7fffffff || bytes > 0x7fffffff) return false;
-    // Many voxels with few products each are faster through the tables, whose work goes by channels and not by
-    // words of them: 262 thousand voxels, 64 -> 2 channels, single tap 7.2 us and 9.6 here; 313 thousand, 3 x 3:
-    // 8 channels 14.1 and 18.0, 24 channels 17.9 and 18.1; 116 thousand, 3 x 3 x 3: 8 channels 20.3 and 20.9, 14
-    // channels 24.8 and 20.9.  Eight thousand voxels: 14.8 to 47 with tables, 6.8 to 9.6 here.
-    if (p.total >= 32768 && taps * p.c_in < 224) return false;
+    // Many voxels with few products each are faster through the tables, whose work goes by channels and not by words of
+    // them, has no addresses to compute per word where there is padding, and halves with at most two outputs; building
+    // them is what costs on fewer voxels.  Tables and here, us:
+    //   64 -> 2, single tap, 262 thousand voxels 7.2 and 9.6; 8 -> 2, 3 x 3, 313 thousand 14.1 and 18.0; eight thousand
+    //   voxels 14.8 to 47 and 6.8 to 9.6;
+    //   words part empty, padded: 44 -> 2, 12 taps, 373 thousand 27 and 43; 10 -> 3, 25 taps, 327 thousand 34 and 49; full
+    //   ones: 64 -> 2, 3 x 3, 323 thousand 25.5 and 20.2; 29 -> 2, 3 x 3, unpadded, 213 thousand 16.0 and 11.6;
+    //   at most two outputs, padded: 64 -> 2, 3 x 3, 9.8 million 491 and 555, unpadded 14 million 706 and 635;
+    //   140 -> 2, 4 taps, padded, 4.1 million 238 and 299.
+    // Over 2 064 random layers the rule takes 2 % longer than the better of the two, 9 % at the most.
+    const bool padded = p.pd || p.ph || p.pw, pair = p.c_out <= 2, many = p.total >= 131072;
+    const int64_t products = taps * p.c_in;
+    if (p.total >= 32768 && products < (!pair || !many ? 224 : padded ? 288 : 225)) return false;
+    const int full = padded ? (pair ? 28 : 18) : (pair ? 16 : 0);    // channels to a word that pay
+    if (many && products <= 850 && (p.c_in < full * p.wd_in || (padded && pair && p.total >= 524288))) return false;
     RealMatrixPlan t;
     t.ow = divisor(p.ow); t.oh = divisor(p.oh); t.od = divisor(p.od);
     t.taps = divisor((int32_t)taps); t.filter = divisor((int32_t)(taps * 32 * p.wd_in));
-    t.kw = reciprocal((uint32_t)p.kw, 64); t.kh = reciprocal((uint32_t)p.kh, 64); t.words = reciprocal((uint32_t)p.wd_in, 64);
+    t.kw = reciprocal((uint32_t)p.kw, 64); t.kh = reciprocal((uint32_t)p.kh, 64);
     t.bytes = (uint32_t)bytes;
-    const bool padded = p.pd || p.ph || p.pw, few = taps * (p.wd_in == 2 ? 1 : p.wd_in) <= 3;
-    const auto go = [&](auto wd, auto pad) {
-        if (few) go_real_matrix<decltype(wd)::value, decltype(pad)::value, 3>(p, t, s);
-        else go_real_matrix<decltype(wd)::value, decltype(pad)::value, 9>(p, t, s);
+    // Units of whole records up to eight words, else of a divisor of their number.
+    const auto go = [&](auto uw, auto record, auto pad) {
+        constexpr int UW = decltype(uw)::value, B = UW <= 2 ? 9 : UW <= 4 ? 5 : 3;
+        if (taps * (p.wd_in / UW) <= 3) go_real_matrix<UW, decltype(record)::value, decltype(pad)::value, 3>(p, t, s);
+        else go_real_matrix<UW, decltype(record)::value, decltype(pad)::value, B>(p, t, s);
     };
-    const std::integral_constant<int, 1> one;
-    const std::integral_constant<int, 2> two;
-    if (p.wd_in == 2) padded ? go(two, std::true_type{}) : go(two, std::false_type{});
-    else padded ? go(one, std::true_type{}) : go(one, std::false_type{});
+    const auto words = [&](auto pad) {
+        const std::false_type no;
+        const int w = p.wd_in;
+        if (w == 2) go(std::integral_constant<int, 2>{}, std::true_type{}, pad);
+        else if (w == 5) go(std::integral_constant<int, 5>{}, no, pad);
+        else if (w == 7) go(std::integral_constant<int, 7>{}, no, pad);
+        else if (w % 4 == 0) go(std::integral_constant<int, 4>{}, no, pad);
+        else if (w % 3 == 0) go(std::integral_constant<int, 3>{}, no, pad);
+        else if (w % 2 == 0) go(std::integral_constant<int, 2>{}, no, pad);
+        else go(std::integral_constant<int, 1>{}, no, pad);
+    };
+    if (padded) words(std::true_type{});
+    else words(std::false_type{});
     return true;
 }
 

@@ -177,8 +177,18 @@ def test_conv3d_real(G, ci, co, vol, k, stride, pad, dil):
 
 
 @pytest.mark.parametrize("ci,co,vol,k,stride,pad,dil", [
-    (64, 2, (1, 260, 258), (1, 3, 3), 1, 0, 1),             # two blocks of voxels to a wave
+    (64, 2, (1, 260, 258), (1, 3, 3), 1, 0, 1),             # a workgroup has more than one tile
     (64, 9, (1, 259, 255), (1, 3, 3), 1, (0, 1, 1), 1),     # the same padded; three groups of filters, the last one filter
+    (128, 2, (1, 61, 67), (1, 3, 3), 1, (0, 1, 1), 1),      # records of four words, padded, more taps than fetched at a time
+    (99, 5, (1, 40, 43), (1, 2, 2), 2, 0, 1),               # four words, the last one part empty; strided
+    (96, 3, (1, 190, 180), (1, 3, 3), 1, 0, 1),             # three words, more than one tile
+    (150, 2, (1, 21, 35), (1, 3, 3), 1, (0, 2, 1), 2),      # five, dilated
+    (192, 4, (3, 9, 11), (1, 3, 3), 1, 0, 1),               # six, two units to a tap
+    (200, 1, (1, 13, 17), (1, 3, 3), 1, (0, 1, 0), 1),      # seven
+    (224, 6, (2, 9, 9), (1, 1, 1), 1, 0, 1),                # seven, one unit in all
+    (256, 2, (1, 20, 19), (2, 2, 2), 1, 1, 1),              # eight, two units to a tap; 64 operand blocks
+    (320, 3, (1, 11, 12), (1, 2, 3), 1, 0, 1),              # ten, five units of two words
+    (352, 2, (1, 9, 40), (1, 1, 5), 1, 0, 1),               # eleven, word by word
     (32, 4, (3, 9, 10), (3, 3, 3), 1, 1, 1),
     (96, 3, (2, 5, 6), (1, 3, 3), (1, 2, 1), (0, 2, 1), (1, 1, 2)),
     (33, 1, (1, 1, 1), (1, 1, 1), 1, 0, 1),                 # one voxel
@@ -219,6 +229,36 @@ def test_conv3d_real_special_weights(G, value):
     bound = real_conv_bound(finite, np.zeros(5, np.float32))[None, :, None, None, None]
     plain = odd == 0
     assert (np.abs(got - want)[plain] <= np.broadcast_to(bound, want.shape)[plain]).all()
+    np.testing.assert_array_equal(got[~plain], odd[~plain])
+
+
+@pytest.mark.parametrize("value", [np.inf, 1e-40])
+@pytest.mark.parametrize("ci,co,n,vol,k,pad", [
+    (20, 2, 1, (1, 30, 31), (1, 3, 3), (0, 1, 1)),          # one word
+    (96, 6, 2, (3, 9, 10), (1, 3, 3), (0, 0, 0)),           # three, a second group of filters
+    (160, 2, 1, (1, 12, 13), (1, 3, 3), (0, 1, 0)),         # five, padded
+    (256, 1, 1, (1, 12, 13), (1, 2, 2), (0, 1, 1)),         # eight
+    (64, 2, 3, (1, 170, 160), (1, 3, 3), (0, 1, 1)),        # two; a workgroup has more than one tile
+])
+def test_conv3d_real_added_one_by_one(G, ci, co, n, vol, k, pad, value):
+    """Weights that are not three bf16 numbers send a workgroup the plain way: every word count's addresses there,
+    padding, and several tiles.  An infinite weight shows where its channel's code is not zero, with its sign."""
+    import paper_1801_09449_amd as T
+    x = tern((n, ci) + vol, 37)
+    w = synth.gaussian((co, ci) + k, 37, synth.T_F32)
+    at = (co - 1, ci - 1, 0, k[1] - 1, 0)
+    w[at] = value
+    got = T.tern_conv3d_real(gpu_pack(G, x), ci, G.dev(w), None, 1, pad, 1).cpu().numpy().astype(np.float64)
+    finite = np.where(np.isfinite(w), w, np.float32(0.0))
+    want = oracle.conv3d_real(x, finite, None, (1,) * 3, pad, (1,) * 3).astype(np.float64)
+    bound = np.broadcast_to(real_conv_bound(finite, np.zeros(co, np.float32))[None, :, None, None, None], want.shape)
+    odd = np.zeros_like(want)
+    if not np.isfinite(value):
+        xp = np.pad(x, ((0, 0), (0, 0)) + tuple((a, a) for a in pad))
+        code = xp[:, ci - 1, :, at[3]:at[3] + want.shape[3], :want.shape[4]]
+        odd[:, co - 1] = np.where(code == 0, 0.0, np.where(code == 0, 1, code) * np.inf)
+    plain = odd == 0
+    assert (np.abs(got - want)[plain] <= bound[plain]).all()
     np.testing.assert_array_equal(got[~plain], odd[~plain])
 
 
