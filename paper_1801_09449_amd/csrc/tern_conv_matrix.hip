@@ -58,7 +58,7 @@ struct MatrixPlan {
     int32_t lks;                     // waves that share a tile's steps and add up their sums in LDS (log2)
     int32_t hx, hy, hz;              // halo extents in voxels
     Divisor tiles_x, tiles_y, tiles_z;
-    uint32_t reach;                  // bytes of input from a tile's first plane to its last
+    uint32_t reach;                  // bytes of input from a tile's first plane to its last (FAR: its rows of a plane)
     int32_t nch;                     // words (or word pairs) per voxel
     int32_t pl;                      // LDS bytes of one word plane
     int32_t zero_off;                // LDS byte offset of a zero record (odd word counts)
@@ -108,7 +108,8 @@ __device__ __forceinline__ void advance(Walk& w, int nch, int inc_ch, int& tab, 
     }
 }
 
-template <int VB, int NB, bool PACKED, int KIND, bool ODD, bool SPLIT>
+// FAR: a tile's planes together span more than 4 GB, so a buffer descriptor takes the tile's rows of one plane at a time.
+template <int VB, int NB, bool PACKED, int KIND, bool ODD, bool SPLIT, bool FAR>
 __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPlan t)
 {
     extern __shared__ __align__(16) uint8_t lds8[];
@@ -205,15 +206,15 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
         const int zb = max(gz0, 0);
         const uint32_t rec = 8u * (uint32_t)wd, line = (uint32_t)p.w * rec, slice = (uint32_t)p.h * line;
         const uint32_t* from = KIND == kPair ? t.pair.base : p.in + ((size_t)n * p.d + zb) * ((size_t)p.h * p.w * 2u * wd);
-        const __amdgpu_buffer_rsrc_t src = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(from), 0, t.reach, 0x00020000);
+        __amdgpu_buffer_rsrc_t src = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(from), 0, t.reach, 0x00020000);
         uint32_t pair0 = 0, pair1 = 0;                      // the batch item's first bytes; word pair c of source 1 is pair c - nch0 there
         if constexpr (KIND == kPair) {
             pair0 = t.pair.start[0] + (uint32_t)n * t.pair.item[0];
             pair1 = t.pair.start[1] + (uint32_t)n * t.pair.item[1] - 8u * (uint32_t)t.pair.nch0;
         }
-        const uint32_t origin = (uint32_t)(gz0 - zb) * slice + (uint32_t)gy0 * line + (uint32_t)gx0 * rec;
+        uint32_t origin = (uint32_t)(gz0 - zb) * slice + (uint32_t)gy0 * line + (uint32_t)gx0 * rec;
         constexpr uint32_t OUTSIDE = 0xfffffff0u;
-        const int items = nvox * t.nch;
+        int items = nvox * t.nch;
         constexpr bool PAIRS = !ODD || KIND == kDigits;     // two words per plane and item
         // Items a thread keeps in flight (single words: more would cost a wave per SIMD).  Eight where the registers are
         // there anyway: 64 channels on 8 x 8 x 8 with dilation 2 are 6.75 items to a thread, and the second round trip
@@ -280,8 +281,21 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
             }
         };
         // The first round by itself: in front of a loop the compiler waits for every load that is under way.
-        round(0);
-        for (int base = FILL * nthreads; base < items; base += FILL * nthreads) round(base);
+        if constexpr (!FAR) {
+            round(0);
+            for (int base = FILL * nthreads; base < items; base += FILL * nthreads) round(base);
+        } else {
+            const int yb = max(gy0, 0);
+            for (int hz = 0, base = 0; hz < t.hz; ++hz) {
+                const int z = min(max(gz0 + hz, 0), p.d - 1);   // (a plane outside the volume reads nothing)
+                from = p.in + (((size_t)n * p.d + z) * p.h + yb) * ((size_t)p.w * 2u * wd);
+                src = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(from), 0, t.reach, 0x00020000);
+                origin = (uint32_t)(gy0 - yb) * line + (uint32_t)gx0 * rec - (uint32_t)hz * slice;
+                items = (hz + 1) * plane * t.nch;
+                for (; base < items; base += FILL * nthreads) round(base);
+                base = items;
+            }
+        }
         if (ODD && tid < 4) reinterpret_cast<uint32_t*>(lds8 + t.zero_off)[tid] = 0u;
     }
     // Cut points in LDS: start values, then widths.
@@ -528,10 +542,10 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
     }
 }
 
-template <int VB, int NB, bool PACKED, int KIND, bool ODD, bool SPLIT>
+template <int VB, int NB, bool PACKED, int KIND, bool ODD, bool SPLIT, bool FAR>
 int launch_variant(const ConvParams& p, const MatrixPlan& t, size_t lds_bytes, dim3 grid, int threads, hipStream_t s)
 {
-    auto kern = conv_matrix_kernel<VB, NB, PACKED, KIND, ODD, SPLIT>;
+    auto kern = conv_matrix_kernel<VB, NB, PACKED, KIND, ODD, SPLIT, FAR>;
     if (lds_bytes > 64 * 1024) {
         static thread_local int raised_on_device = -1;
         int dev = 0;
@@ -548,20 +562,20 @@ int launch_variant(const ConvParams& p, const MatrixPlan& t, size_t lds_bytes, d
     return TERN_OK;
 }
 
-template <int VB, int NB, bool PACKED, bool SPLIT>
+template <int VB, int NB, bool PACKED, bool SPLIT, bool FAR>
 int launch_kind(const ConvParams& p, const MatrixPlan& t, bool odd, size_t lds, dim3 grid, int threads, hipStream_t s)
 {
-    if constexpr (PACKED)
-        if (t.pair.base) return launch_variant<VB, NB, PACKED, kPair, false, SPLIT>(p, t, lds, grid, threads, s);
-    if (p.tp_slots) return launch_variant<VB, NB, PACKED, kTapPacked, true, SPLIT>(p, t, lds, grid, threads, s);
+    if constexpr (PACKED && !FAR)
+        if (t.pair.base) return launch_variant<VB, NB, PACKED, kPair, false, SPLIT, FAR>(p, t, lds, grid, threads, s);
+    if (p.tp_slots) return launch_variant<VB, NB, PACKED, kTapPacked, true, SPLIT, FAR>(p, t, lds, grid, threads, s);
     if (p.digits)
-        return odd ? launch_variant<VB, NB, PACKED, kDigits, true, SPLIT>(p, t, lds, grid, threads, s)
-                   : launch_variant<VB, NB, PACKED, kDigits, false, SPLIT>(p, t, lds, grid, threads, s);
+        return odd ? launch_variant<VB, NB, PACKED, kDigits, true, SPLIT, FAR>(p, t, lds, grid, threads, s)
+                   : launch_variant<VB, NB, PACKED, kDigits, false, SPLIT, FAR>(p, t, lds, grid, threads, s);
     if (p.binary)
-        return odd ? launch_variant<VB, NB, PACKED, kBinary, true, SPLIT>(p, t, lds, grid, threads, s)
-                   : launch_variant<VB, NB, PACKED, kBinary, false, SPLIT>(p, t, lds, grid, threads, s);
-    return odd ? launch_variant<VB, NB, PACKED, kTernary, true, SPLIT>(p, t, lds, grid, threads, s)
-               : launch_variant<VB, NB, PACKED, kTernary, false, SPLIT>(p, t, lds, grid, threads, s);
+        return odd ? launch_variant<VB, NB, PACKED, kBinary, true, SPLIT, FAR>(p, t, lds, grid, threads, s)
+                   : launch_variant<VB, NB, PACKED, kBinary, false, SPLIT, FAR>(p, t, lds, grid, threads, s);
+    return odd ? launch_variant<VB, NB, PACKED, kTernary, true, SPLIT, FAR>(p, t, lds, grid, threads, s)
+               : launch_variant<VB, NB, PACKED, kTernary, false, SPLIT, FAR>(p, t, lds, grid, threads, s);
 }
 
 }  // namespace
@@ -595,7 +609,8 @@ static bool pair_plan(const ConvPair& pair, int32_t n, PairPlan& u)
 
 // Every convolution goes this way except those that one of the limits below sends to the bit-count
 // kernels: more than 128 taps (the tap offsets of a wave sit in two registers), sums that could pass
-// 2^21 (the epilogue works with halves; LDS runs out first, so far), and halo tiles that do not fit in LDS.
+// 2^21 (the epilogue works with halves; LDS runs out first, so far), halo tiles that do not fit in LDS, and tiles
+// whose rows of a plane span more than 4 GB.
 // A tile holds all words of its voxels: 3 x 3 x 3 kernels fit up to 47 words (1504 channels) at stride 1, 19 with
 // dilation 2, 10 with 3, 14 at stride 2, 7 and 4 with dilation 2 and 3; from the next word on they take three
 // to eight times as long as their neighbours.
@@ -621,14 +636,28 @@ bool launch_conv_matrix(const ConvParams& p, const ConvPair* pair, hipStream_t s
     Choice c;
     Tile q;
     if (!choose_cached(shape, c) || !tile_of(shape, c, q)) return false;
+    // A tile's planes within 4 GB (a volume's may be more), or else its rows of each: then with waves of 128 voxels on 32
+    // filters, as there is one form of that kernel (64 -> 64 channels, 3 x 3, on a plane of 16 400 x 16 400
+    // 6.9 ms; half of it, which one descriptor reaches, 3.4, with bit counts 17.6).
+    const int64_t line_bytes = 8 * (int64_t)p.wd_in * p.w, plane_bytes = line_bytes * p.h;
+    int64_t reach = pair ? t.pair.reach : plane_bytes * (q.hz < p.d ? q.hz : p.d);
+    const bool far = reach > 0xffff0000ll;
+    if (far) {
+        const bool flat = p.od == 1, deep = p.od > 1 && p.kd > 1;
+        const int8_t* sh = kWaveShape[1][flat][0];
+        c = {4, 1, sh[0], sh[1], 1, 1, 1, 1};
+        while (c.nwc < 4 && 2 * c.nwc <= cdiv(p.c_out, 32)) c.nwc *= 2;
+        (deep ? c.nwz : c.nwy) = 4 / c.nwc;
+        if (!tile_of(shape, c, q)) {
+            c.nwy = c.nwz = 1;
+            if (!tile_of(shape, c, q)) return false;
+        }
+        reach = line_bytes * (q.hy < p.h ? q.hy : p.h);
+        if (reach > 0xffff0000ll) return false;
+    }
     const int X = 1 << c.lxb, Y = 1 << c.lyb, Z = (32 * c.vb) >> (c.lxb + c.lyb);
     const int64_t gy = q.wgs / q.tiles;
     if (q.tiles > 0x7fffffff || gy > 65535) return false;
-    // A tile's planes within 4 GB (a volume's may be more).
-    const int64_t plane_bytes = 8 * (int64_t)p.wd_in * p.h * p.w;
-    if (!pair && plane_bytes > 0xffff0000ll) return false;
-    const int64_t reach = pair ? t.pair.reach : plane_bytes * (q.hz < p.d ? q.hz : p.d);
-    if (reach > 0xffff0000ll) return false;
     t.lxb = c.lxb; t.lyb = c.lyb; t.lwy = log2_up(c.nwy); t.lwz = log2_up(c.nwz); t.nwc = c.nwc;
     t.hx = (int32_t)q.hx; t.hy = (int32_t)q.hy; t.hz = (int32_t)q.hz;
     t.tiles_x = divisor(cdiv(p.ow, X)); t.tiles_y = divisor(cdiv(p.oh, Y * c.nwy)); t.tiles_z = divisor(cdiv(p.od, Z * c.nwz));
@@ -654,11 +683,16 @@ bool launch_conv_matrix(const ConvParams& p, const ConvPair* pair, hipStream_t s
     const int threads = 64 * c.nwy * c.nwz * c.nwc * c.nks;
     const size_t lds = (size_t)q.lds;
     note_launch(TERN_KERNEL_TILED, c.vb / 2, 32 * c.nb, c.nks, threads, grid.x, grid.y, lds);
+    if (far) {
+        *rc = packed ? launch_kind<4, 1, true, false, true>(p, t, odd, lds, grid, threads, s)
+                     : launch_kind<4, 1, false, false, true>(p, t, odd, lds, grid, threads, s);
+        return true;
+    }
     const auto kind = [&](auto vb, auto nb, auto split) {
         constexpr int VB = decltype(vb)::value, NB = decltype(nb)::value;
         constexpr bool SPLIT = decltype(split)::value;
-        return packed ? launch_kind<VB, NB, true, SPLIT>(p, t, odd, lds, grid, threads, s)
-                      : launch_kind<VB, NB, false, SPLIT>(p, t, odd, lds, grid, threads, s);
+        return packed ? launch_kind<VB, NB, true, SPLIT, false>(p, t, odd, lds, grid, threads, s)
+                      : launch_kind<VB, NB, false, SPLIT, false>(p, t, odd, lds, grid, threads, s);
     };
     const std::integral_constant<int, 1> one;
     const std::integral_constant<int, 2> two;

@@ -317,3 +317,42 @@ def test_pointwise_batches_beyond_the_grid(G, ci):
     got = T.tern_conv3d_binary(T.tern_pack(G.dev(c.act)), ci, T.tern_pack_filters_binary(G.dev(w)), 3, 1, 1, 0, 1)
     torch.cuda.synchronize()
     np.testing.assert_array_equal(got.cpu().numpy(), oracle.conv3d(c.act, w, ConvGeom(c.k, c.stride, c.pad, c.dil)))
+
+
+@pytest.mark.parametrize("ci,co,vol,k,stride,binary", [
+    (64, 64, (1, 16400, 16400), (1, 3, 3), 1, False),       # one plane of 4.3 GB
+    (40, 70, (4, 9000, 8500), (3, 3, 3), 1, False),         # 1.2 GB each, four to a tile; a last word part empty
+    (96, 20, (4, 9400, 9800), (2, 3, 3), 2, True),          # odd word count, strided, binary filters
+])
+def test_planes_of_a_tile_beyond_four_gigabytes(G, ci, co, vol, k, stride, binary):
+    """Tiles whose planes together span more than 4 GB stay on the matrix cores.  Against the same convolution of boxes
+    cut out of the volume: its corners and its middle."""
+    import torch
+    import paper_1801_09449_amd as T
+    d, h, w = vol
+    g = torch.Generator(device="cuda").manual_seed(ci)
+    act = torch.randint(-2**31, 2**31 - 1, (1, d, h, w, 2, T.tern_words(ci)), generator=g, device="cuda", dtype=torch.int32)
+    if ci % 32:
+        act[..., -1] &= (1 << ci % 32) - 1
+    act[:, :, :, :, 1] &= act[:, :, :, :, 0]
+    wgt = torch.randint(-1, 2, (co, ci) + k, generator=g, device="cuda", dtype=torch.int8)
+    bank = T.tern_pack_filters_binary(torch.where(wgt < 0, wgt, torch.ones_like(wgt))) if binary else T.tern_pack_filters(wgt)
+    lo, hi = (torch.full((co,), v, device="cuda", dtype=torch.int32) for v in (-8, 9))
+    pad = tuple(min(1, a - 1) for a in k)
+    st = (1 if d == 1 else stride, stride, stride)
+    conv = lambda a, p: T.tern_conv3d(a, ci, bank, co, k, st, p, 1, thr_lo=lo, thr_hi=hi, binary=binary)
+    got = conv(act, pad)
+    plan = T.tern_last_launch()
+    assert plan["kernel"] == T.KERNEL_TILED and (plan["voxels_per_lane"], plan["channels_per_pass"]) == (2, 32)
+    for cy, cx in ((0, 0), (0, w - 300), (h - 300, 0), (h - 300, w - 300), (h // 2, w // 2)):
+        y0, x0 = cy // stride * stride, cx // stride * stride
+        box = act[:, :, y0:y0 + 300, x0:x0 + 300].contiguous()
+        want = conv(box, pad)
+        oy, ox = y0 // stride, x0 // stride
+        n, m = want.shape[2], want.shape[3]
+        # outputs whose taps are all in the box, or beyond the volume's own edge
+        ys, ye = (0 if y0 == 0 else 2), (n if y0 + 300 >= h else n - 2)
+        xs, xe = (0 if x0 == 0 else 2), (m if x0 + 300 >= w else m - 2)
+        assert torch.equal(got[:, :, oy + ys:oy + ye, ox + xs:ox + xe], want[:, :, ys:ye, xs:xe]), (cy, cx)
+    del act, got
+    torch.cuda.empty_cache()
