@@ -266,10 +266,14 @@ int tern_fcn_forward_static(const float* in, tern_dims in_dims, const float* in_
  *
  * tern_conv3d_real -- the full-precision output layer: cross-correlation of packed ternary codes
  * with float weights w [c_out][C_in][kd][kh][kw] plus bias [c_out] (NULL = none), zero padding,
- * float output [N][c_out][Do][Ho][Wo].  Each term is +-w exactly; they are added in fp32 in the
- * order taps (d, h, w), then ascending input channel, starting from the bias, so the result
- * differs from exact arithmetic by at most (terms) * 2^-24 * (|bias| + sum |w| over the filter).
- * Meant for a handful of output channels (Table 1: 2); one thread per output voxel.
+ * float output [N][c_out][Do][Ho][Wo].  Each term is +-w exactly and the sum is one of floats.  The
+ * order of its terms and of the bias is not specified: it may depend on the extents and on the
+ * weights, and a weight may enter in up to three parts that add up to it exactly.  The result
+ * differs from exact arithmetic by at most (terms + 1) * 2^-24 * (|bias| + sum |w| over the filter).
+ * Equal calls give equal results.  A weight that is infinite or NaN makes the outputs infinite or NaN
+ * where its code is not zero; where it is zero it usually adds nothing, but layers of more than 64
+ * (tap, word of C_in) pairs or of more than 2^31 - 1 bytes of input may give NaN there.
+ * Meant for a handful of output channels (Table 1: 2).
  *
  * tern_pool_digits / tern_digits_weights / tern_conv3d_digits -- average pooling in front of a
  * ternary convolution (Table 1: AvgPool 2x2 before modules 4, 6 and 8) at twice, not four times,
