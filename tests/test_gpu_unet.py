@@ -422,10 +422,9 @@ def test_unet_reduced(G):
     check_unet(G, synth.unet_table1(seed=6, n=1, width_div=3, size=(92, 100), slices=15))
 
 
-def test_unet_many_stacks_take_the_two_kernel_first_module(G):
-    """Four full-size stacks, narrow channels: module #1 has more output voxels than the fused
-    gather-and-convolve kernel is used for, so its taps are gathered to memory and convolved by the
-    pointwise kernel over five words (one stack takes the fused kernel, see the full-size test)."""
+def test_unet_several_stacks_of_narrow_channels(G):
+    """Four full-size stacks, narrow channels: a part of a word in every module, and inputs that are joined in
+    memory (odd word counts)."""
     check_unet(G, synth.unet_table1(seed=7, n=4, width_div=8))
 
 
@@ -483,7 +482,7 @@ def test_net_forward_generic_wiring(G):
 
 
 def test_net_forward_one_channel_first_module(G):
-    """A plain chain through tern_net_forward whose first module qualifies for the gathered-tap
+    """A plain chain through tern_net_forward whose first module qualifies for the one-launch
     route (one input channel, 3x3x3): same codes as the oracle's chain, module by module."""
     import torch
     from paper_1801_09449_amd import unet
@@ -500,20 +499,21 @@ def test_net_forward_one_channel_first_module(G):
         np.testing.assert_array_equal(G.words(t), oracle.pack(code), err_msg=f"module {li}")
 
 
-@pytest.mark.parametrize("vol,ca,cs,k0,kj,up,stride,pad", [
-    ((1, 23, 30), 64, 64, (1, 3, 3), (1, 3, 3), (1, 2, 2), (1, 1, 1), (0, 0, 0)),      # a decoder step; planes of the batch as one stack
-    ((1, 40, 27), 128, 50, (1, 3, 3), (1, 3, 3), (1, 1, 4), (1, 1, 1), (0, 1, 1)),     # a last skip word part empty; padded
-    ((5, 12, 9), 64, 128, (3, 3, 3), (3, 3, 3), (2, 2, 2), (1, 1, 1), (1, 1, 1)),      # a volume, cropped along z
-    ((4, 9, 11), 192, 64, (3, 3, 3), (3, 3, 3), (1, 2, 1), (2, 2, 1), (1, 0, 1)),      # strided
-    ((3, 10, 10), 64, 64, (1, 3, 3), (1, 3, 3), (2, 2, 2), (1, 1, 1), (0, 0, 0)),      # no depth taps but upsampled along z
-    ((1, 15, 14), 64, 0, (1, 3, 3), (1, 3, 3), (1, 2, 2), (1, 1, 1), (0, 1, 1)),       # upsampled, no skip
-    ((1, 15, 14), 64, 64, (1, 3, 3), (1, 3, 3), (1, 3, 2), (1, 1, 1), (0, 0, 0)),      # a factor of three: joined in memory first
-    ((1, 15, 14), 32, 32, (1, 3, 3), (1, 3, 3), (1, 2, 2), (1, 1, 1), (0, 0, 0)),      # odd word counts: likewise
-    ((1, 15, 14), 64, 64, (1, 3, 3), (1, 1, 1), (1, 2, 2), (1, 1, 1), (0, 0, 0)),      # a single tap: likewise
+@pytest.mark.parametrize("vol,ca,cs,k0,kj,up,stride,pad,read", [
+    ((1, 23, 30), 64, 64, (1, 3, 3), (1, 3, 3), (1, 2, 2), (1, 1, 1), (0, 0, 0), True),      # a decoder step; planes of the batch as one stack
+    ((1, 40, 27), 128, 50, (1, 3, 3), (1, 3, 3), (1, 1, 4), (1, 1, 1), (0, 1, 1), True),     # a last skip word part empty; padded
+    ((5, 12, 9), 64, 128, (3, 3, 3), (3, 3, 3), (2, 2, 2), (1, 1, 1), (1, 1, 1), True),      # a volume, cropped along z
+    ((4, 9, 11), 192, 64, (3, 3, 3), (3, 3, 3), (1, 2, 1), (2, 2, 1), (1, 0, 1), True),      # strided
+    ((3, 10, 10), 64, 64, (1, 3, 3), (1, 3, 3), (2, 2, 2), (1, 1, 1), (0, 0, 0), True),      # no depth taps but upsampled along z
+    ((1, 15, 14), 64, 0, (1, 3, 3), (1, 3, 3), (1, 2, 2), (1, 1, 1), (0, 1, 1), True),       # upsampled, no skip
+    ((1, 15, 14), 64, 64, (1, 3, 3), (1, 3, 3), (1, 3, 2), (1, 1, 1), (0, 0, 0), False),      # a factor of three: joined in memory first
+    ((1, 15, 14), 32, 32, (1, 3, 3), (1, 3, 3), (1, 2, 2), (1, 1, 1), (0, 0, 0), False),      # odd word counts: likewise
+    ((1, 15, 14), 64, 64, (1, 3, 3), (1, 1, 1), (1, 2, 2), (1, 1, 1), (0, 0, 0), False),      # a single tap: likewise
 ])
-def test_net_forward_reads_upsampled_and_skipped_input(G, vol, ca, cs, k0, kj, up, stride, pad):
+def test_net_forward_reads_upsampled_and_skipped_input(G, vol, ca, cs, k0, kj, up, stride, pad, read):
     """A module whose input is an upsampled tensor with the channels of a cropped one behind it, as the
-    convolution reads it from both, against the oracle on the joined tensor."""
+    convolution reads it from both, against the oracle on the joined tensor.  Where it does, the region of the
+    workspace for the joined tensor is not written."""
     import torch
     from paper_1801_09449_amd import unet
     n, seed = 3, 40 + ca + cs + vol[1]
@@ -533,9 +533,66 @@ def test_net_forward_reads_upsampled_and_skipped_input(G, vol, ca, cs, k0, kj, u
         layers.append(dict(w=w, k=k, stride=st, pad=pd, lo=lo, hi=hi, pool=None, up=extra.get("up"),
                            concat=extra.get("concat"), save=extra.get("save")))
     plan = unet.UNetPlan(layers, None, None, -half, half)
-    _, kept = unet.unet_forward(plan, G.dev(xb), keep_layers=True)
+    xd = G.dev(xb)
+    ws = plan.workspace(xd).fill_(0xa5)
+    _, kept = unet.unet_forward(plan, xd, keep_layers=True)
     torch.cuda.synchronize()
+    start, end = (kept[i][0].data_ptr() - ws.data_ptr() for i in (1, 2))
+    joined = ws[(start + kept[1][0].numel() * 4 + 255) // 256 * 256:end]
+    assert joined.numel() >= n * (ca + cs) // 4 and bool((joined == 0xa5).all()) == read
     codes, _ = oracle.unet_forward(xb, -half, half, layers, None, None)
     for li, ((t, c), want) in enumerate(zip(kept, codes), start=1):
         np.testing.assert_array_equal(G.words(t), oracle.pack(want), err_msg=f"module {li}")
     assert len(np.unique(codes[-1])) == 3
+
+
+@pytest.mark.parametrize("n,ca,cs,co,hw,blocks", [
+    (12, 64, 64, 64, 96, 1),
+    (6, 64, 64, 256, 96, 2),
+    (12, 128, 50, 128, 94, 2),         # six words, the last one part empty
+    (13, 64, 0, 64, 97, 1),            # no skip
+])
+def test_net_forward_joined_input_in_large_waves(G, n, ca, cs, co, hw, blocks):
+    """The same in launches that give waves 128 voxels and 32 or 64 filters, as a U-Net's decoder has on a batch, against
+    a float32 convolution of the decoded tensors (sums below 2^24: exact)."""
+    import torch
+    import paper_1801_09449_amd as T
+    g = torch.Generator(device="cuda").manual_seed(ca + cs + co)
+    half = hw // 2
+    x = torch.randn((n, 1, 1, 2 * half + 3, 2 * half + 6), generator=g, device="cuda")
+    cut = torch.full((1,), 0.5, device="cuda")
+    mods, weights = [], []
+    for c_out, c_in, k, st, pd, extra in (
+            (cs or 16, 1, (1, 3, 3), (1, 1, 1), (0, 1, 1), {}),
+            (ca, cs or 16, (1, 5, 8), (1, 2, 2), (0, 0, 0), {}),
+            (co, ca + cs, (1, 3, 3), (1, 1, 1), (0, 0, 1), dict(up=(1, 2, 2), skip_from=0 if cs else -1))):
+        w = torch.randint(-1, 2, (c_out, c_in) + k, generator=g, device="cuda", dtype=torch.int8)
+        s = max(1, int(0.3 * (c_in * k[1] * k[2]) ** 0.5))
+        lo, hi = (torch.randint(a, a + 3, (c_out,), generator=g, device="cuda", dtype=torch.int32) for a in (-s, s - 2))
+        mods.append(T.NetModule(c_out, T.tern_pack_filters(w), lo, hi, k, st, pd, (1, 1, 1), **extra))
+        weights.append((w, lo, hi))
+    _, views = T.tern_net_forward(x, -cut, cut, mods, return_modules=True)
+    plan = T.tern_last_launch()
+    assert (plan["voxels_per_lane"], plan["channels_per_pass"]) == (2, 32 * blocks)
+
+    def codes(v):
+        t, dm = v
+        bits = (t[..., None] >> torch.arange(32, device="cuda", dtype=torch.int32)) & 1      # [n, d, h, w, 2, words, 32]
+        bits = bits.flatten(-2)[..., :dm[1]].float()
+        return (bits[..., 0, :] * (1 - 2 * bits[..., 1, :])).permute(0, 4, 1, 2, 3)[:, :, 0]
+    up = codes(views[1]).repeat_interleave(2, 2).repeat_interleave(2, 3)
+    if cs:
+        skip = codes(views[0])
+        y0, x0 = (skip.shape[2] - up.shape[2]) // 2, (skip.shape[3] - up.shape[3]) // 2
+        up = torch.cat([up, skip[:, :, y0:y0 + up.shape[2], x0:x0 + up.shape[3]]], 1)
+    w, lo, hi = weights[2]
+    up = torch.nn.functional.pad(up, (1, 1))
+    oh, ow = up.shape[2] - 2, up.shape[3] - 2
+    acc = torch.zeros((n, co, oh * ow), device="cuda")
+    for b in range(3):
+        for a in range(3):
+            tap = w[:, :, 0, b, a].float().contiguous()
+            for i in range(n):
+                acc[i] += tap @ up[i, :, b:b + oh, a:a + ow].reshape(ca + cs, -1)
+    want = T.tern_threshold_pack(acc.view(n, co, 1, oh, ow).int(), lo, hi)
+    assert torch.equal(views[2][0], want)

@@ -30,7 +30,7 @@ def test_static_scratch_chain_matches_workspace_chain_twice_in_a_row():
     from tests.gpu_util import dev, words
     T.lib()
     assert torch.cuda.is_available()
-    # first a chain with a one-channel input (gathered first layer, strides, 5 layers), then a
+    # first a chain with a one-channel input (one launch from the intensities, strides, 5 layers), then a
     # smaller one with a three-channel input (plain Eq. 6 + pack in front): the second call finds
     # the first call's activations in the array and must not be disturbed by them
     first = synth.config2(seed=11, vol=(40, 48, 24), channels=(16, 32, 32, 64, 64), strides=(1, 2, 1, 2, 1))
@@ -58,7 +58,7 @@ def test_static_scratch_chain_refuses_what_does_not_fit():
     from tests.gpu_util import dev
     f = synth.config2(seed=13, vol=(8, 8, 8), channels=(16, 16), strides=(1, 1))
     layers = layers_of(T, dev, f)
-    # 1 x 1 x 160 x 160 x 160 floats: the gathered taps and the first layer's output need 2 x 32.8 MB
+    # 1 x 1 x 160 x 160 x 160 floats: room for the first layer's taps and its output need 2 x 32.8 MB
     x = torch.zeros((1, 1, 160, 160, 160), dtype=torch.float32, device="cuda")
     assert T.tern_fcn_workspace_bytes(x.shape, layers) > T.tern_static_scratch_bytes()
     with pytest.raises(T.TernError) as e:
