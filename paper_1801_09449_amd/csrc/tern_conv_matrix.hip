@@ -74,8 +74,6 @@ struct MatrixPlan {
 // them in memory first took a launch of 4 us at 15 to 90 thousand voxels and 12 to 13 us at sixteen times as many).
 enum { kTernary = 0, kBinary = 1, kDigits = 2, kTapPacked = 3, kPair = 4 };
 
-__device__ __forceinline__ uint32_t quotient(uint32_t e, Reciprocal r) { return __umul24(e, r.m) >> r.s; }
-__device__ __forceinline__ int quotient(int e, Divisor d) { return (int)(((uint64_t)(uint32_t)e * d.m) >> d.s); }
 
 // Two balanced-ternary digits per value (low + 3 high, -4 .. 4) to the E2M1 code of the value
 // (magnitudes 1, 2, 3, 4 = 0010, 0100, 0101, 0110), channels in the order of expand().

@@ -40,8 +40,6 @@ struct FirstPlan {
     } x, y;
 };
 
-__device__ __forceinline__ int quot(int e, Divisor d) { return (int)(((uint64_t)(uint32_t)e * d.m) >> d.s); }
-
 // FEW: at most 16 filters, the lower half of a block's rows.
 template <int KD, bool FEW, bool FAR>
 __global__ __launch_bounds__(kFirstThreads) void first_conv_kernel(FirstConvParams p, FirstPlan t)
@@ -59,9 +57,9 @@ __global__ __launch_bounds__(kFirstThreads) void first_conv_kernel(FirstConvPara
         const int per_xcd = gridDim.x >> 3;
         if (bid < (per_xcd << 3)) bid = (bid & 7) * per_xcd + (bid >> 3);
     }
-    const int row = quot(bid, t.tiles_x), tix = bid - row * t.tiles_x.d;
-    const int layer = quot(row, t.tiles_y), tiy = row - layer * t.tiles_y.d;
-    const int n = quot(layer, t.tiles_z), tiz = layer - n * t.tiles_z.d;
+    const int row = quotient(bid, t.tiles_x), tix = bid - row * t.tiles_x.d;
+    const int layer = quotient(row, t.tiles_y), tiy = row - layer * t.tiles_y.d;
+    const int n = quotient(layer, t.tiles_z), tiz = layer - n * t.tiles_z.d;
     const int ox0 = tix * kTileX, oy0 = tiy * (2 * t.rows), oz0 = tiz * TZ;
     const int gx0 = ox0 * p.sw - p.pw, gy0 = oy0 * p.sh - p.ph, gz0 = oz0 - p.pd;
 
@@ -92,7 +90,7 @@ __global__ __launch_bounds__(kFirstThreads) void first_conv_kernel(FirstConvPara
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int e = min(base + u * kFirstThreads + tid, t.cols - 1);
-            const int cy = quot(e, t.hx_div), cx = e - cy * t.hx;
+            const int cy = quotient(e, t.hx_div), cx = e - cy * t.hx;
             int iy = gy0 + cy, ix = gx0 + cx;
             if constexpr (FAR) {
                 const int by = (cy >= t.y.band) + (cy >= 2 * t.y.band), bx = (cx >= t.x.band) + (cx >= 2 * t.x.band);

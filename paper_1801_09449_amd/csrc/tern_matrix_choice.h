@@ -12,6 +12,8 @@
 #include <memory>
 #include <new>
 
+#include "tern_division.h"
+
 namespace tern {
 namespace {
 
@@ -39,38 +41,6 @@ struct Tile {
 
 inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 inline int32_t cdiv(int32_t a, int32_t b) { return (a + b - 1) / b; }
-
-// Divisions of the kernel by what its launch knows.  Small numbers: e / d = (e * m) >> s for 0 <= e < emax <= 2^15
-// (below 2^16 for d a power of two): with emax * d <= 2^s the error of m = ceil(2^s / d) stays below 1 / d, and
-// e * m < 2^32.
-struct Reciprocal {
-    uint32_t m, s;
-};
-inline Reciprocal reciprocal(uint32_t d, uint32_t emax)
-{
-    uint32_t s = 0;
-    while (((uint64_t)1 << s) < (uint64_t)emax * d) ++s;
-    const Reciprocal r = {(uint32_t)((((uint64_t)1 << s) + d - 1) / d), s};
-    return r;
-}
-// Block numbers, e below 2^31: the product takes 64 bits.  m = ceil(2^s / d) with s = 31 + ceil(log2 d) is below
-// 2^32, and m * d exceeds 2^s by less than d <= 2^(s - 31).
-struct Divisor {
-    uint32_t m, s;
-    int32_t d;
-};
-inline int32_t log2_up(int32_t x)
-{
-    int32_t l = 0;
-    while (((int64_t)1 << l) < x) ++l;
-    return l;
-}
-inline Divisor divisor(int32_t d)
-{
-    const uint32_t s = 31 + (uint32_t)log2_up(d);
-    const Divisor r = {(uint32_t)((((uint64_t)1 << s) + (uint32_t)d - 1) / (uint32_t)d), s, d};
-    return r;
-}
 
 constexpr int64_t kMaxHalo = 20480, kMaxItems = 32768;   // voxels of a halo tile, units of its fill
 

@@ -140,7 +140,7 @@ __device__ __forceinline__ Decider decider()
     d.ones = __builtin_bit_cast(v8bf, one);
     return d;
 }
-// A row's width as three bf16 numbers (at most 22 bits: exactly), the rows' operand of the additions.
+// A row's width as three bf16 numbers (at most 23 bits: exactly), the rows' operand of the additions.
 __device__ __forceinline__ v8bf width_operand(float w, bool lower_half)
 {
     const uint32_t hi = __float_as_uint(w) & 0xffff0000u;

@@ -8,7 +8,7 @@
 #include <type_traits>
 
 #include "tern_internal.h"
-#include "tern_matrix_choice.h"
+#include "tern_division.h"
 
 namespace tern {
 namespace {
@@ -360,9 +360,6 @@ struct RealMatrixPlan {
     uint32_t bytes;              // of the input
 };
 
-__device__ __forceinline__ int quot(int e, Divisor d) { return (int)(((uint64_t)(uint32_t)e * d.m) >> d.s); }
-__device__ __forceinline__ int quot(int e, Reciprocal r) { return (int)(__umul24((uint32_t)e, r.m) >> r.s); }
-
 // N consecutive words, `at` and `more` bytes from the buffer's start, in the fewest loads (records are 8-byte aligned
 // and a load need be 4-byte aligned only).
 template <int N>
@@ -404,8 +401,8 @@ __global__ __launch_bounds__(kBlock) void real_conv_matrix_kernel(RealConvParams
     int unit_z, unit_y, unit_x;
     {
         const int u = min(lane, units - 1);
-        const int tap = quot(u, t.chunks), word = UW * (u - tap * t.chunks.d);
-        const int r = quot(tap, t.kw), a = quot(r, t.kh);
+        const int tap = quotient(u, t.chunks), word = UW * (u - tap * t.chunks.d);
+        const int r = (int)quotient((uint32_t)tap, t.kw), a = (int)quotient((uint32_t)r, t.kh);
         unit_z = a * p.dd; unit_y = (r - a * p.kh) * p.dh; unit_x = (tap - r * p.kw) * p.dw;
         if (lane < units) unit_off = (uint32_t)((unit_z * p.h + unit_y) * p.w + unit_x) * rec + 4u * (uint32_t)word;
     }
@@ -414,9 +411,9 @@ __global__ __launch_bounds__(kBlock) void real_conv_matrix_kernel(RealConvParams
     uint32_t off;                                         // bytes of tap (0, 0, 0)'s record, modulo 2^32
     auto enter = [&](int tile) {
         vox = (int)min((int64_t)tile * TILE + (tid >> 6) * 16 + col, p.total - 1);
-        const int r = quot(vox, t.ow), x = vox - r * t.ow.d;
-        const int r2 = quot(r, t.oh), y = r - r2 * t.oh.d;
-        const int n = quot(r2, t.od), z = r2 - n * t.od.d;
+        const int r = quotient(vox, t.ow), x = vox - r * t.ow.d;
+        const int r2 = quotient(r, t.oh), y = r - r2 * t.oh.d;
+        const int n = quotient(r2, t.od), z = r2 - n * t.od.d;
         ix0 = x * p.sw - p.pw; iy0 = y * p.sh - p.ph; iz0 = z * p.sd - p.pd;
         off = (uint32_t)(((n * p.d + iz0) * p.h + iy0) * p.w + ix0) * rec;
     };
@@ -465,7 +462,7 @@ __global__ __launch_bounds__(kBlock) void real_conv_matrix_kernel(RealConvParams
     auto write = [&](int tile, int co, float sum) {
         const float b = p.bias ? p.bias[co] : 0.0f;
         if ((int64_t)tile * TILE + (tid >> 6) * 16 + col < p.total) {
-            const int n = quot(quot(quot(vox, t.ow), t.oh), t.od);
+            const int n = quotient(quotient(quotient(vox, t.ow), t.oh), t.od);
             const size_t ospatial = (size_t)p.od * p.oh * p.ow;
             p.out[((size_t)n * p.c_out + co) * ospatial + (vox - (size_t)n * ospatial)] = sum + b;
         }
@@ -486,8 +483,8 @@ __global__ __launch_bounds__(kBlock) void real_conv_matrix_kernel(RealConvParams
 #pragma unroll
             for (int k = 0; k < ROUND; ++k) {
                 const int i = min(base + k * kBlock, elements - 1);
-                const int f = quot(i, t.filter), e = i - f * t.filter.d;
-                const int c = quot(e, t.taps), tap = e - c * T;
+                const int f = quotient(i, t.filter), e = i - f * t.filter.d;
+                const int c = quotient(e, t.taps), tap = e - c * T;
                 const float w = p.wgt[((size_t)(co0 + f) * p.c_in + min(c, p.c_in - 1)) * T + tap];
                 ww[k] = c < p.c_in ? w : 0.0f;
                 const int cc = c & 31, j = 2 * ((cc & 1) * 2 + ((cc >> 1) & 1)) + (cc >> 4);
@@ -512,7 +509,7 @@ __global__ __launch_bounds__(kBlock) void real_conv_matrix_kernel(RealConvParams
                 const float* wf = p.wgt + (size_t)(co0 + min(q4, cg - 1)) * p.c_in * T;
                 for (int u = 0; u < units; ++u) {
                     const uint32_t o = address(u);
-                    const int tap = quot(u, t.chunks), word = UW * (u - tap * t.chunks.d);
+                    const int tap = quotient(u, t.chunks), word = UW * (u - tap * t.chunks.d);
                     for (int w = 0; w < UW; ++w) {
                         const int live = min(32, p.c_in - 32 * (word + w));
                         const uint32_t mw = __builtin_amdgcn_raw_buffer_load_b32(src, o, 4 * w, 0);
@@ -741,8 +738,9 @@ static bool launch_real_matrix(const RealConvParams& p, hipStream_t s)
     const bool padded = p.pd || p.ph || p.pw, pair = p.c_out <= 2, many = p.total >= 131072;
     const int64_t products = taps * p.c_in;
     if (p.total >= 32768 && products < (!pair || !many ? 224 : padded ? 288 : 225)) return false;
+    const bool fit = 5 * taps * ((p.c_in + 3) / 4 * 4) * (pair ? 2 : 4) * 4 <= 64 * 1024;   // (tables, as below)
     const int full = padded ? (pair ? 28 : 18) : (pair ? 16 : 0);    // channels to a word that pay
-    if (many && products <= 850 && (p.c_in < full * p.wd_in || (padded && pair && p.total >= 524288))) return false;
+    if (many && fit && products <= 850 && (p.c_in < full * p.wd_in || (padded && pair && p.total >= 524288))) return false;
     RealMatrixPlan t;
     t.ow = divisor(p.ow); t.oh = divisor(p.oh); t.od = divisor(p.od);
     t.taps = divisor((int32_t)taps); t.filter = divisor((int32_t)(taps * 32 * p.wd_in));
