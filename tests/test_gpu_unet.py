@@ -153,7 +153,13 @@ def real_conv_bound(w, b):
                                                         (37, 5, (4, 6, 7), (3, 3, 3), (1, 2, 1), (1, 0, 2), (1, 1, 2)),
                                                         (8, 1, (3, 3, 3), (1, 1, 1), 1, 0, 1),
                                                         (300, 2, (3, 4, 5), (3, 3, 3), 1, 1, 1),     # filters too large for LDS
-                                                        (130, 7, (2, 9, 70), (1, 3, 3), 1, (0, 1, 1), 1)])
+                                                        (130, 7, (2, 9, 70), (1, 3, 3), 1, (0, 1, 1), 1),
+                                                        (64, 2, (1, 200, 170), (1, 1, 1), 1, 0, 1),         # tables: two words, two outputs
+                                                        (40, 4, (1, 190, 180), (1, 1, 3), 1, (0, 0, 1), 1),  # the same, four, padded
+                                                        (8, 3, (1, 190, 180), (1, 3, 3), 1, (0, 1, 1), 1),   # one word, padded
+                                                        (130, 2, (1, 12, 13), (1, 3, 5), 1, (0, 1, 2), 1),   # filters in LDS, two outputs
+                                                        (130, 7, (1, 9, 20), (1, 3, 5), (1, 2, 1), 0, 1),    # the same, four at a time
+                                                        (300, 5, (3, 4, 5), (3, 3, 3), 1, 1, 1)])            # filters too large for LDS
 def test_conv3d_real(G, ci, co, vol, k, stride, pad, dil):
     import paper_1801_09449_amd as T
     t3 = lambda v: (v,) * 3 if isinstance(v, int) else tuple(v)
