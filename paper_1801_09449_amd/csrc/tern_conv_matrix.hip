@@ -23,14 +23,19 @@
 // over two to eight waves that add their sums in LDS (exact, so in any order): 512 -> 256 channels 3 x 3 on
 // 52 x 36 13.0 -> 8.7 us, 256 -> 256 on 16^3 17.7 -> 10.1, 32 -> 32 on 24^3 7.2 -> 5.9.  Under full load the
 // clock falls to 1.9 GHz, where 32 cycles are 8 000 TFLOP/s for the chip.
+// A step is to be its loads, its widening and its matrix instructions and nothing else: tap offsets lie ready in a
+// register's lanes, bank rows come through a descriptor whose end stands for the last row's absent partner, and no branch
+// stands around a load.  With a scalar walk over taps and words, its branches, clamped row numbers and bank words two steps
+// ahead a small wave's step took 470 cycles, now 230 (32 -> 32 on 24^3: 5.0 -> 4.3 us; 96 -> 70 stride 2 on 2 x 45 x 53 x 37
+// 12.6 -> 11.1; a six-layer encoder 39.1 -> 35.6).
 // What stands in front of the first matrix instruction counts for a launch of 5 to 9 us: workgroup and wave numbers
 // are divided by multiplication (ten integer divisions were 250 instructions before the first load), cut points
 // and halo items are fetched at once, and halo voxels go through a buffer descriptor that returns zeros outside the
 // volume.  Together: 32 -> 32 on 24^3 5.46 -> 4.99 us, 96 -> 70 stride 2 on 2 x 45 x 53 x 37 13.9 -> 12.5, 64 -> 64
 // on 96^3 with dilation 2 53.8 -> 51.5, a U-Net's eighteen launches 125.6 -> 113.3.
-// Measured, fused output, bit-count kernels before: 64 -> 64 channels on 64^3: 88 -> 13.8 us, on 96^3 with
-// dilation 2: 276 -> 48 us; 256 -> 256 on 2 x 32^3: 321 -> 42 us (5 500 TFLOP/s: loop 38, fill 3, epilogue 1 us);
-// 64 -> 64 3 x 3 on 16 planes of 232 x 168: 83 -> 22 us.
+// Measured, fused output, bit-count kernels before: 64 -> 64 channels on 64^3: 88 -> 13.5 us, on 96^3 with
+// dilation 2: 276 -> 44.5 us; 256 -> 256 on 2 x 32^3: 321 -> 42 us (5 500 TFLOP/s: loop 38, fill 3, epilogue 1 us);
+// 64 -> 64 3 x 3 on 16 planes of 232 x 168: 83 -> 17.8 us.
 #include <type_traits>
 
 #include "tern_internal.h"
@@ -60,6 +65,7 @@ struct MatrixPlan {
     Divisor tiles_x, tiles_y, tiles_z;
     uint32_t reach;                  // bytes of input from a tile's first plane to its last (FAR: its rows of a plane)
     int32_t nch;                     // words (or word pairs) per voxel
+    int32_t rows;                    // of the filter bank
     int32_t pl;                      // LDS bytes of one word plane
     int32_t zero_off;                // LDS byte offset of a zero record (odd word counts)
     int32_t tp_log;                  // tap-packed bank: log2 of the taps per row
@@ -91,24 +97,9 @@ __device__ __forceinline__ v4i expand_digits(uint32_t lm, uint32_t hm, uint32_t 
     return o;
 }
 
-// Scalar walk over (kernel tap, channel word or pair of words) in bank order.  The LDS offsets of the
-// taps sit in the lanes of two registers (tap t in lane t % 64 of the (t / 64)-th).
-struct Walk {
-    int tap, ch, off;
-};
-__device__ __forceinline__ void advance(Walk& w, int nch, int inc_ch, int& tab, int tab1)
-{
-    w.off += inc_ch;
-    if (++w.ch == nch) {
-        w.ch = 0;
-        if (++w.tap == 64) tab = tab1;
-        w.off = __builtin_amdgcn_readlane(tab, w.tap & 63);
-    }
-}
-
 // FAR: a tile's planes together span more than 4 GB, so a buffer descriptor takes the tile's rows of one plane at a time.
 template <int VB, int NB, bool PACKED, int KIND, bool ODD, bool SPLIT, bool FAR>
-__global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPlan t)
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void conv_matrix_kernel(ConvParams p, MatrixPlan t)
 {
     extern __shared__ __align__(16) uint8_t lds8[];
     const int tid = threadIdx.x;
@@ -143,44 +134,70 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
 
     // ---- filter words ------------------------------------------------------------------------
     constexpr int FW = KIND == kDigits ? 4 : KIND == kBinary ? (ODD ? 1 : 2) : (ODD ? 2 : 4);  // words per filter and row
-    const int row_words = p.co_pad * FW;
-    const int all_steps = ODD ? (p.kd * p.kh * p.kw * t.nch + 1) >> 1
-                              : p.kd * p.kh * p.kw * (KIND == kDigits ? t.nch >> 1 : t.nch);
+    const int row_bytes = p.co_pad * FW * 4;
+    const int entries = p.kd * p.kh * p.kw * (KIND == kDigits && !ODD ? t.nch >> 1 : t.nch);     // (tap, word or pair of words)
+    const int all_steps = ODD ? (entries + 1) >> 1 : entries;
     // this wave's steps: first .. first + steps - 1
     const int first = (all_steps * ks) >> lks;
     const int steps = ((all_steps * (ks + 1)) >> lks) - first;
-    const bool half_last = ODD && ks == nks - 1 && (((p.kd * p.kh * p.kw * t.nch) & 1) != 0);
-    const int step_words = ROWS ? 2 * row_words : row_words;   // (tap-packed: per row)
-    const uint32_t* bank = p.wgt + (size_t)(active ? cb : 0) * FW;
+    // (odd numbers of entries) a last entry without a partner, under one's filters unless those can be zeros
+    const bool half_last = ODD && (KIND == kBinary || FAR) && ks == nks - 1 && (entries & 1) != 0;
     // Which way the sums are decided: through the 6-bit floats where the instructions count, shifted in one by one in
     // the small waves of short launches, where only a wave's own time does (a U-Net's fifteen launches on one stack
     // 86.3 us, through the 6-bit floats 87.6).
     constexpr bool SIX = PACKED && VB == 4;
-    uint32_t lane_f = (uint32_t)((SIX ? row_filter(i32) : i32) * FW);
-    if constexpr (ROWS) lane_f += (uint32_t)(g * row_words);
-    else if constexpr (KIND != kTapPacked) lane_f += (uint32_t)(KIND == kBinary ? g : 2 * g);
-    v2u f0[NB], f1[NB];
-    auto fetch_f = [&](v2u (&f)[NB], int step) {
-        const int s = first + min(step, steps - 1);
-        const uint32_t* b = bank + (size_t)(KIND == kTapPacked ? (2 * s) >> t.tp_log : s) * (size_t)step_words;
-        uint32_t o = lane_f;
-        if constexpr (ROWS && ODD) {
-            if (half_last && s == all_steps - 1 && g) o -= (uint32_t)row_words;   // any row: its activations are zero
-        }
+    uint32_t lane_f = (uint32_t)((SIX ? row_filter(i32) : i32) * FW * 4);
+    if constexpr (ROWS) lane_f += (uint32_t)(g * row_bytes);
+    else if constexpr (KIND != kTapPacked) lane_f += (uint32_t)(KIND == kBinary ? 4 * g : 8 * g);
+    // Steps whose words are under way at once: about as many as a small wave has.
+    constexpr int AHEAD = VB == 4 ? 2 : NB == 1 ? 8 : 4;
+    v2u f[AHEAD][NB];
+    // The words of a step's bank rows, in turn, through a buffer descriptor that ends with the wave's last row and reads as
+    // zeros from there on.  FAR, where the bank may be of any size: a step's, or the last step's again.
+    constexpr int AT_ONCE = ROWS ? 2 : 1;
+    const int last_row = min(t.rows, KIND == kTapPacked ? t.rows : AT_ONCE * (first + steps));
+    const __amdgpu_buffer_rsrc_t bank_src =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(p.wgt), 0, (int)((uint32_t)last_row * (uint32_t)row_bytes), 0x00020000);
+    const uint32_t* bank = p.wgt + (size_t)(active ? cb : 0) * FW;
+    uint32_t next = lane_f + (uint32_t)((active ? cb : 0) * FW * 4) + (uint32_t)(KIND == kTapPacked ? 0 : AT_ONCE * first) * (uint32_t)row_bytes;
+    auto fetch_f = [&](v2u (&to)[NB], int step) {
+        if constexpr (!FAR) {
+            const uint32_t o = KIND == kTapPacked ? next + (uint32_t)((2 * (first + step)) >> t.tp_log) * (uint32_t)row_bytes : next;
+            if constexpr (KIND != kTapPacked) next += (uint32_t)(AT_ONCE * row_bytes);
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) {
-            if constexpr (KIND == kBinary) {
-                f[nb].x = b[o + nb * 32 * FW];
-            } else if constexpr (KIND == kDigits) {
-                f[nb].x = b[o + nb * 32 * FW];
-                f[nb].y = b[o + nb * 32 * FW + 2];
-            } else {
-                f[nb] = *reinterpret_cast<const v2u*>(b + o + nb * 32 * FW);
+            for (int nb = 0; nb < NB; ++nb) {
+                if constexpr (KIND == kBinary) {
+                    to[nb].x = __builtin_amdgcn_raw_buffer_load_b32(bank_src, o + nb * 32 * FW * 4, 0, 0);
+                } else if constexpr (KIND == kDigits) {
+                    to[nb].x = __builtin_amdgcn_raw_buffer_load_b32(bank_src, o + nb * 32 * FW * 4, 0, 0);
+                    to[nb].y = __builtin_amdgcn_raw_buffer_load_b32(bank_src, o + nb * 32 * FW * 4 + 8, 0, 0);
+                } else {
+                    to[nb] = __builtin_bit_cast(v2u, __builtin_amdgcn_raw_buffer_load_b64(bank_src, o + nb * 32 * FW * 4, 0, 0));
+                }
+            }
+        } else {
+            const int s = first + min(step, steps - 1), row = KIND == kTapPacked ? (2 * s) >> t.tp_log : AT_ONCE * s;
+            const uint8_t* b = reinterpret_cast<const uint8_t*>(bank) + (size_t)row * (size_t)row_bytes;
+            uint32_t o = lane_f;
+            if constexpr (ROWS && ODD) {
+                if (half_last && s == all_steps - 1 && g) o -= (uint32_t)row_bytes;   // any row: its activations are zero
+            }
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) {
+                const uint32_t* w = reinterpret_cast<const uint32_t*>(b + o) + nb * 32 * FW;
+                if constexpr (KIND == kBinary) to[nb].x = w[0];
+                else if constexpr (KIND == kDigits) to[nb].x = w[0], to[nb].y = w[2];
+                else to[nb] = *reinterpret_cast<const v2u*>(w);
             }
         }
     };
-    fetch_f(f0, 0);
-    fetch_f(f1, 1);
+    // Two steps' words in front of the halo tile's loads, the others behind them.
+    fetch_f(f[0], 0);
+    fetch_f(f[1], 1);
+    auto fetch_others = [&]() {
+#pragma unroll
+        for (int k = 2; k < AHEAD; ++k) fetch_f(f[k], k);
+    };
 
     // Cut points of the workgroup's filters, thread j those of filter j (a workgroup has at least as many
     // threads).  Fetched here, with the first loads, and staged behind the halo tile: fetched there they cost
@@ -218,7 +235,7 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
         // there anyway: 64 channels on 8 x 8 x 8 with dilation 2 are 6.75 items to a thread, and the second round trip
         // for the rest was 2.5 % of the launch (96^3: 49.4 -> 48.2 us).
         constexpr int FILL = PAIRS ? (VB == 4 ? 8 : 6) : 3;
-        auto round = [&](int base) {
+        auto round = [&](int base, auto first_one) {
             uint32_t r[FILL][4];
             int dst[FILL];
 #pragma unroll
@@ -262,6 +279,7 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
                     r[k][2] = __builtin_amdgcn_raw_buffer_load_b32(src, o, 4 * wd, 0);
                 }
             }
+            if constexpr (decltype(first_one)::value) fetch_others();
 #pragma unroll
             for (int k = 0; k < FILL; ++k) {
                 if (!ODD && k > 0 && base + k * nthreads >= items) break;
@@ -280,8 +298,8 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
         };
         // The first round by itself: in front of a loop the compiler waits for every load that is under way.
         if constexpr (!FAR) {
-            round(0);
-            for (int base = FILL * nthreads; base < items; base += FILL * nthreads) round(base);
+            round(0, std::true_type{});
+            for (int base = FILL * nthreads; base < items; base += FILL * nthreads) round(base, std::false_type{});
         } else {
             const int yb = max(gy0, 0);
             for (int hz = 0, base = 0; hz < t.hz; ++hz) {
@@ -290,11 +308,11 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
                 src = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(from), 0, t.reach, 0x00020000);
                 origin = (uint32_t)(gy0 - yb) * line + (uint32_t)gx0 * rec - (uint32_t)hz * slice;
                 items = (hz + 1) * plane * t.nch;
-                for (; base < items; base += FILL * nthreads) round(base);
+                for (; base < items; base += FILL * nthreads) round(base, std::false_type{});
                 base = items;
             }
         }
-        if (ODD && tid < 4) reinterpret_cast<uint32_t*>(lds8 + t.zero_off)[tid] = 0u;
+        if (ODD && (KIND == kBinary || FAR) && tid < 4) reinterpret_cast<uint32_t*>(lds8 + t.zero_off)[tid] = 0u;
     }
     // Cut points in LDS: start values, then widths.
     float* cuts = reinterpret_cast<float*>(lds8 + t.cut_off);
@@ -322,26 +340,28 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
         const int r = (int)quotient((uint32_t)tap, t.r_kw), a = (int)quotient((uint32_t)r, t.r_kh);
         return (((a * p.dd * t.hy) + (r - a * p.kh) * p.dh) * t.hx + (tap - r * p.kw) * p.dw) * REC;
     };
-    int tab0 = tap_off(lane);
-    int tab1 = tab0;
-    if (p.kd * p.kh * p.kw > 64) tab1 = tap_off(64 + lane);
     const int nch = KIND == kDigits && !ODD ? t.nch >> 1 : t.nch;
     const int inc_ch = ODD ? t.pl : 2 * t.pl;
-    Walk w = {0, 0, 0};
-    if constexpr (SPLIT) {
-        const int e = ODD ? 2 * first : first;                 // first entry of this wave
-        w.tap = (int)quotient((uint32_t)e, t.r_nch);
-        w.ch = e - w.tap * nch;
-        if (w.tap >= 64) tab0 = tab1;
-        w.off = __builtin_amdgcn_readlane(tab0, w.tap & 63) + w.ch * inc_ch;
-    }
-
+    // The entries' LDS offsets lie in the lanes of a register, so that a step is a readlane: lanes 48 and up those of the
+    // first two steps, lanes 0 to 47 those of the next, in turn.
+    int table, entry = 48, entry0 = (ODD ? 2 : 1) * first;
+    auto tabulate = [&]() {
+        const int e = min(entry0 + (lane < 48 ? lane + (ODD ? 4 : 2) : lane - 48), entries - 1);   // (the last again past the end)
+        const int tap = (int)quotient((uint32_t)e, t.r_nch);
+        table = tap_off(tap) + (e - tap * nch) * inc_ch;
+    };
+    tabulate();
+    auto next_entry = [&]() { return __builtin_amdgcn_readlane(table, entry++); };
+    auto next_table = [&]() {                                  // (after a whole number of rounds of either loop)
+        if (__builtin_expect(entry == 48, 0)) {
+            entry = 0;
+            entry0 += 48;
+            tabulate();
+        }
+    };
     auto fetch_v = [&](v4i (&x)[VB], int step) {
         if constexpr (ODD) {
-            const int o0 = w.off;
-            advance(w, nch, inc_ch, tab0, tab1);
-            const int o1 = w.off;
-            advance(w, nch, inc_ch, tab0, tab1);
+            const int o0 = next_entry(), o1 = next_entry();
             const int o = g ? o1 : o0;
             const bool dead = half_last && step == steps - 1;
 #pragma unroll
@@ -351,9 +371,9 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
                 x[vb] = *reinterpret_cast<const v4i*>(lds8 + a);
             }
         } else {
+            const int o = next_entry();
 #pragma unroll
-            for (int vb = 0; vb < VB; ++vb) x[vb] = *reinterpret_cast<const v4i*>(lds8 + lane_v[vb] + w.off);
-            advance(w, nch, inc_ch, tab0, tab1);
+            for (int vb = 0; vb < VB; ++vb) x[vb] = *reinterpret_cast<const v4i*>(lds8 + lane_v[vb] + o);
         }
     };
     v16f acc[VB][NB], start[NB];
@@ -374,25 +394,26 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
         }
     }
 
+    auto widen_block = [&](v4i (&F)[NB], const v2u (&f)[NB], int step, int nb) {
+        if constexpr (KIND == kBinary) {
+            v2u u;
+            u.x = (f[nb].x << 2) | m33;
+            u.y = f[nb].x | m33;
+            F[nb] = expand(u, maa);
+        } else if constexpr (KIND == kTapPacked) {
+            const uint32_t sh = (uint32_t)(((2 * (first + step) + g) & ((1 << t.tp_log) - 1)) * p.tp_shift);
+            F[nb] = expand(interleave(f[nb].x >> sh, f[nb].y >> sh, m33), maa);
+        } else if constexpr (!ROWS) {
+            // lanes 0-31 hold both mask words, lanes 32-63 both sign words of a filter
+            const auto sw = __builtin_amdgcn_permlane32_swap(f[nb].x, f[nb].y, false, false);
+            F[nb] = expand(interleave(sw[0], sw[1], m33), maa);
+        } else {
+            F[nb] = expand(interleave(f[nb].x, f[nb].y, m33), maa);
+        }
+    };
     auto widen = [&](v4i (&F)[NB], const v2u (&f)[NB], int step) {
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) {
-            if constexpr (KIND == kBinary) {
-                v2u u;
-                u.x = (f[nb].x << 2) | m33;
-                u.y = f[nb].x | m33;
-                F[nb] = expand(u, maa);
-            } else if constexpr (KIND == kTapPacked) {
-                const uint32_t sh = (uint32_t)(((2 * (first + step) + g) & ((1 << t.tp_log) - 1)) * p.tp_shift);
-                F[nb] = expand(interleave(f[nb].x >> sh, f[nb].y >> sh, m33), maa);
-            } else if constexpr (!ROWS) {
-                // lanes 0-31 hold both mask words, lanes 32-63 both sign words of a filter
-                const auto sw = __builtin_amdgcn_permlane32_swap(f[nb].x, f[nb].y, false, false);
-                F[nb] = expand(interleave(sw[0], sw[1], m33), maa);
-            } else {
-                F[nb] = expand(interleave(f[nb].x, f[nb].y, m33), maa);
-            }
-        }
+        for (int nb = 0; nb < NB; ++nb) widen_block(F, f, step, nb);
     };
     auto contract = [&](const v4i (&F)[NB], const v4i (&x)[VB], auto first) {
 #pragma unroll
@@ -402,72 +423,88 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
                 acc[vb][nb] = multiply(F[nb], x[vb], decltype(first)::value ? start[nb] : acc[vb][nb]);
     };
 
-    // Operands of step i + 1 are fetched and widened in front of step i's matrix instructions, filter words
-    // two steps further ahead.  (The barriers keep the compiler from moving those loads above the use of
-    // the registers they replace, which made it copy them and wait for loads it had just issued.)
     v4i x0[VB], x1[VB];
     v4i F0[NB], F1[NB];
     fetch_v(x0, 0);
-    widen(F0, f0, 0);
-    fetch_f(f0, 2);
-    if (steps > 1) {
-        fetch_v(x1, 1);
-        widen(F1, f1, 1);
-        fetch_f(f1, 3);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    contract(F0, x0, std::true_type{});
-    int i = 1;
-    for (; i + 2 <= steps; i += 2) {
-        fetch_v(x0, i + 1);
-        widen(F0, f0, i + 1);
-        __builtin_amdgcn_sched_barrier(0);
-        fetch_f(f0, i + 3);
-        __builtin_amdgcn_sched_barrier(0);
-        contract(F1, x1, std::false_type{});
-        __builtin_amdgcn_sched_barrier(0);
-        if (i + 2 < steps) fetch_v(x1, i + 2);
-        widen(F1, f1, i + 2);
-        __builtin_amdgcn_sched_barrier(0);
-        fetch_f(f1, i + 4);
-        __builtin_amdgcn_sched_barrier(0);
-        contract(F0, x0, std::false_type{});
-        __builtin_amdgcn_sched_barrier(0);
-    }
-    if (i < steps) contract(F1, x1, std::false_type{});
-
-    // ---- partial sums: block b of a tile is finished by wave b % nks of its nks (a power of two) ------
-    constexpr int BLOCKS = VB * NB;
-    auto finishes = [&](int b) { return !SPLIT || (b & (nks - 1)) == ks; };
-    if constexpr (SPLIT) {
-        __syncthreads();                                       // everyone is done with the halo tile
-        float* mine = reinterpret_cast<float*>(lds8) + (size_t)wave * (BLOCKS * 1024) + lane * 4;
+    fetch_v(x1, 1);
+    entry = 0;
+    if constexpr (VB == 4) {
+        // Operands of step i + 1 are fetched and widened between step i's matrix instructions, filter words two steps further
+        // ahead.  In front of all of them, both waves of a SIMD did that at the same time, with the matrix cores idle: 64 -> 64
+        // channels on 96^3 with dilation 2 46.1 -> 44.5 us, 256 -> 256 on 2 x 32^3 45.6 -> 42.1 (with a wave priority for that
+        // part 41.3 and 47.2).  (The barriers hold the order; a load moved above the last use of its registers has the compiler
+        // copy them and wait.)
+        auto column = [&](const v4i (&F)[NB], const v4i (&x)[VB], int vb) {
 #pragma unroll
-        for (int b = 0; b < BLOCKS; ++b)
-            if (!finishes(b)) {
+            for (int nb = 0; nb < NB; ++nb) acc[vb][nb] = multiply(F[nb], x[vb], acc[vb][nb]);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        auto step_of = [&](const v4i (&F)[NB], const v4i (&x)[VB], v4i (&F_next)[NB], v2u (&words)[NB], v4i (&x_next)[VB], int next) {
+            column(F, x, 0);
+            fetch_v(x_next, next);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const v16f& a = acc[b / NB][b % NB];
-                    *reinterpret_cast<float4*>(mine + b * 1024 + k * 256) = make_float4(a[4 * k], a[4 * k + 1], a[4 * k + 2], a[4 * k + 3]);
+            for (int vb = 1; vb < VB; ++vb) {
+                column(F, x, vb);
+                if (vb <= NB) widen_block(F_next, words, next, vb - 1);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            fetch_f(words, next + 2);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        widen(F0, f[0], 0);
+        fetch_f(f[0], 2);
+        widen(F1, f[1], 1);
+        fetch_f(f[1], 3);
+        __builtin_amdgcn_sched_barrier(0);
+        contract(F0, x0, std::true_type{});
+        int i = 1;
+        for (; i + 2 <= steps; i += 2) {
+            next_table();
+            step_of(F1, x1, F0, f[0], x0, i + 1);
+            step_of(F0, x0, F1, f[1], x1, i + 2);
+        }
+        if (i < steps) contract(F1, x1, std::false_type{});
+    } else {
+        // Voxels of the next two steps and filter words of the next AHEAD are under way, with no branch around their
+        // loads: behind one the compiler waits for all that may be.
+#pragma unroll
+        for (int vb = 0; vb < VB; ++vb)
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) acc[vb][nb] = start[nb];
+        [&]() __attribute__((always_inline)) {
+            for (int done = 0;; done += AHEAD) {
+                next_table();
+#pragma unroll
+                for (int k = 0; k < AHEAD; ++k) {
+                    v4i (&x)[VB] = k & 1 ? x1 : x0;
+                    widen(F0, f[k], done + k);
+                    fetch_f(f[k], done + k + AHEAD);
+                    contract(F0, x, std::false_type{});
+                    if (done + k + 1 >= steps) return;
+                    fetch_v(x, done + k + 2);
+                    __builtin_amdgcn_sched_barrier(0);
                 }
             }
+        }();
+    }
+
+    // ---- partial sums ------------------------------------------------------------------------------
+    // A tile's sums go through LDS in quads, four registers of a wave (a byte of 32 voxels' words), and each of its waves
+    // adds up and finishes as many: quads ks * Q .. ks * Q + Q - 1.  (Whole blocks left four or six of eight waves without
+    // any and the others with seven round trips to LDS: 1.0 to 2.6 us of a launch, now 0.8 to 1.7.)
+    constexpr int QUADS = VB * NB * 4;
+    if constexpr (SPLIT) {
+        __syncthreads();                                       // everyone is done with the halo tile
+        float* mine = reinterpret_cast<float*>(lds8) + (size_t)wave * (QUADS * 256) + lane * 4;
+#pragma unroll
+        for (int u = 0; u < QUADS; ++u) {
+            const v16f& a = acc[u / 4 / NB][u / 4 % NB];
+            const int k = 4 * (u & 3);
+            *reinterpret_cast<float4*>(mine + u * 256) = make_float4(a[k], a[k + 1], a[k + 2], a[k + 3]);
+        }
         __syncthreads();
-        if (!active || ks >= BLOCKS) return;
-#pragma unroll
-        for (int b = 0; b < BLOCKS; ++b)
-            if (finishes(b)) {
-                v16f a = acc[b / NB][b % NB];
-                for (int o = 0; o < nks; ++o)
-                    if (o != ks) {
-                        const float* theirs = reinterpret_cast<float*>(lds8) + (size_t)(wtile * nks + o) * (BLOCKS * 1024) + b * 1024 + lane * 4;
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) {
-                            const float4 x = *reinterpret_cast<const float4*>(theirs + k * 256);
-                            a[4 * k] += x.x; a[4 * k + 1] += x.y; a[4 * k + 2] += x.z; a[4 * k + 3] += x.w;
-                        }
-                    }
-                acc[b / NB][b % NB] = a;
-            }
+        if (!active) return;
     }
 
     // ---- epilogue: lane = voxel l % 32 of a block, register v = filter 8 (v / 4) + 4 g + v % 4 -----
@@ -482,9 +519,70 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
     };
     const size_t line = (size_t)p.ow, slab = (size_t)p.oh * p.ow;
     const size_t vox0 = (((size_t)n * p.od + bz + lz) * p.oh + by + ly) * p.ow + bx + lx;
+    if constexpr (SPLIT) {
+        auto finish = [&](auto log2_waves) {
+            constexpr int LKS = decltype(log2_waves)::value, Q = QUADS >> LKS, QB = Q < 4 ? Q : 4;   // (quads of one block)
+            const float* theirs = reinterpret_cast<const float*>(lds8) + ((size_t)(wtile << LKS) * QUADS + ks * Q) * 256 + lane * 4;
+            float4 sum[Q];
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                float4 part[1 << LKS];
+#pragma unroll
+                for (int o = 0; o < 1 << LKS; ++o) part[o] = *reinterpret_cast<const float4*>(theirs + (o * QUADS + q) * 256);
+                sum[q] = part[0];
+#pragma unroll
+                for (int o = 1; o < 1 << LKS; ++o) {
+                    sum[q].x += part[o].x; sum[q].y += part[o].y; sum[q].z += part[o].z; sum[q].w += part[o].w;
+                }
+            }
+#pragma unroll
+            for (int q0 = 0; q0 < Q; q0 += QB) {
+                const int u = ks * Q + q0, vb = u / 4 / NB, nb = u / 4 % NB, k0 = u & 3;
+                int dx, dy, dz;
+                const bool live = offset_of(vb, dx, dy, dz);
+                if constexpr (PACKED) {
+                    const float* widths = cuts + wg_filters + (wc * NB + nb) * 32 + 8 * k0 + 4 * g;
+                    uint32_t pos = 0u, neg = 0u;
+#pragma unroll
+                    for (int q = QB - 1; q >= 0; --q) {
+                        const float4 w = *reinterpret_cast<const float4*>(widths + 8 * q);
+                        const float4 a = sum[q0 + q];
+                        decide<1>(pos, neg, a.w, w.w);
+                        decide<1>(pos, neg, a.z, w.z);
+                        decide<1>(pos, neg, a.y, w.y);
+                        if (q > 0) decide<5>(pos, neg, a.x, w.x);
+                        else decide<1>(pos, neg, a.x, w.x);
+                    }
+                    const uint32_t word = block_word(pos, neg);
+                    if (live && cb + nb * 32 < p.c_out) {
+                        uint32_t* o = p.out_packed + (vox0 + dz * slab + dy * line + dx) * 2u * p.wd_out + g * p.wd_out + (cb >> 5) + nb;
+                        if constexpr (QB == 4) *o = word;
+                        else if constexpr (QB == 2) reinterpret_cast<uint16_t*>(o)[k0 >> 1] = (uint16_t)word;
+                        else reinterpret_cast<uint8_t*>(o)[k0] = (uint8_t)word;
+                    }
+                } else if (live) {
+                    const size_t cs = (size_t)p.od * slab;
+                    const int c0 = cb + nb * 32 + 8 * k0 + 4 * g;
+                    int32_t* o = p.out_acc + ((size_t)n * p.c_out + c0) * cs + (vox0 - (size_t)n * cs) + dz * slab + dy * line + dx;
+#pragma unroll
+                    for (int q = 0; q < QB; ++q) {
+                        const float4 a = sum[q0 + q];
+                        if (c0 + 8 * q < p.c_out) o[(8 * q) * cs] = (int32_t)a.x;
+                        if (c0 + 8 * q + 1 < p.c_out) o[(8 * q + 1) * cs] = (int32_t)a.y;
+                        if (c0 + 8 * q + 2 < p.c_out) o[(8 * q + 2) * cs] = (int32_t)a.z;
+                        if (c0 + 8 * q + 3 < p.c_out) o[(8 * q + 3) * cs] = (int32_t)a.w;
+                    }
+                }
+            }
+        };
+        if (lks == 1) finish(std::integral_constant<int, 1>{});
+        else if (lks == 2) finish(std::integral_constant<int, 2>{});
+        else finish(std::integral_constant<int, 3>{});
+        return;
+    }
     if constexpr (PACKED) {
         uint32_t* out = p.out_packed + vox0 * 2u * p.wd_out + g * p.wd_out + (cb >> 5);
-        const bool pair = NB == 2 && (p.wd_out & 1) == 0 && !SPLIT;   // (cb >> 5 is even then)
+        const bool pair = NB == 2 && (p.wd_out & 1) == 0;   // (cb >> 5 is even then)
         Decider d;
         v8bf widths[NB];
         if constexpr (SIX) {
@@ -497,7 +595,6 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
             uint32_t word[NB];
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) {
-                if (!finishes(vb * NB + nb)) continue;
                 if constexpr (SIX) {
                     word[nb] = decided_word(acc[vb][nb], widths[nb], d);
                 } else {
@@ -514,7 +611,7 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
                 } else {
 #pragma unroll
                     for (int nb = 0; nb < NB; ++nb)
-                        if (finishes(vb * NB + nb) && cb + nb * 32 < p.c_out) o[nb] = word[nb];
+                        if (cb + nb * 32 < p.c_out) o[nb] = word[nb];
                 }
             }
         }
@@ -527,7 +624,7 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
 #pragma unroll
             for (int vb = 0; vb < VB; ++vb) {
                 int dx, dy, dz;
-                if (finishes(vb * NB + nb) && offset_of(vb, dx, dy, dz)) {
+                if (offset_of(vb, dx, dy, dz)) {
                     int32_t* o = p.out_acc + ((size_t)n * p.c_out + c0) * cs + in_item + dz * slab + dy * line + dx;
 #pragma unroll
                     for (int v = 0; v < 16; ++v) {
@@ -639,7 +736,11 @@ bool launch_conv_matrix(const ConvParams& p, const ConvPair* pair, hipStream_t s
     // 6.9 ms; half of it, which one descriptor reaches, 3.4, with bit counts 17.6).
     const int64_t line_bytes = 8 * (int64_t)p.wd_in * p.w, plane_bytes = line_bytes * p.h;
     int64_t reach = pair ? t.pair.reach : plane_bytes * (q.hz < p.d ? q.hz : p.d);
-    const bool far = reach > 0xffff0000ll;
+    // (the bank is read through one, too)
+    const int64_t bank_rows = p.tp_slots ? cdiv(taps, (int64_t)p.tp_slots) : taps * (p.wd_in / p.wc);
+    const int64_t bank_bytes = bank_rows * p.co_pad * p.wc * (p.binary ? 4 : 8);
+    const bool far = reach > 0xffff0000ll || bank_bytes > 0xf0000000ll;
+    if (far && pair) return false;
     if (far) {
         const bool flat = p.od == 1, deep = p.od > 1 && p.kd > 1;
         const int8_t* sh = kWaveShape[1][flat][0];
@@ -661,6 +762,7 @@ bool launch_conv_matrix(const ConvParams& p, const ConvPair* pair, hipStream_t s
     t.tiles_x = divisor(cdiv(p.ow, X)); t.tiles_y = divisor(cdiv(p.oh, Y * c.nwy)); t.tiles_z = divisor(cdiv(p.od, Z * c.nwz));
     t.reach = (uint32_t)reach;
     t.nch = p.digits || odd ? words : words / 2;
+    t.rows = (int32_t)bank_rows;
     t.pl = (int32_t)(q.hx * q.hy * q.hz * 16);
     t.zero_off = words * t.pl;
     t.cut_off = (int32_t)q.cuts;

@@ -80,6 +80,16 @@ def test_largest_sums_and_cut_points_around_them(G, sign):
     check(G, c)
 
 
+@pytest.mark.parametrize("ci,co,vol,k", [
+    # entries of a wave around the 48 and 96 whose offsets it holds at a time, in twos and fours
+    (64, 40, (1, 5, 60), (1, 1, 49)), (64, 8, (1, 9, 30), (1, 5, 10)), (64, 96, (2, 9, 30), (1, 3, 17)),
+    (64, 64, (1, 12, 30), (1, 7, 14)), (32, 33, (1, 5, 60), (1, 1, 51)), (96, 32, (1, 9, 30), (1, 1, 17)),
+    (32, 64, (1, 9, 30), (1, 4, 13)), (32, 24, (3, 9, 20), (1, 9, 11)), (12, 32, (1, 9, 40), (1, 3, 17)),
+    (64, 64, (20, 40, 44), (3, 5, 7)), (32, 64, (20, 40, 44), (3, 5, 7)), (160, 128, (16, 40, 44), 3)])
+def test_entries_of_a_wave_and_its_tables(G, ci, co, vol, k):
+    check(G, synth.conv_case("mx_tables", 1, ci, co, vol, k, 1, 1, 1, p0_w=0.5, p0_a=0.4, seed=817))
+
+
 @pytest.mark.parametrize("ci,co,vol,k", [(256, 256, (4, 8, 9), 3), (512, 32, (1, 9, 17), (1, 3, 3)), (96, 70, (6, 7, 8), 3),
                                          (32, 32, (9, 8, 8), 3), (16, 40, (8, 9, 8), 3), (160, 64, (5, 6, 7), (3, 3, 2)),
                                          (64, 128, (8, 8, 8), 5)])
