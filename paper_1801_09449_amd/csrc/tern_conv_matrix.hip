@@ -32,7 +32,12 @@
 // are divided by multiplication (ten integer divisions were 250 instructions before the first load), cut points
 // and halo items are fetched at once, and halo voxels go through a buffer descriptor that returns zeros outside the
 // volume.  Together: 32 -> 32 on 24^3 5.46 -> 4.99 us, 96 -> 70 stride 2 on 2 x 45 x 53 x 37 13.9 -> 12.5, 64 -> 64
-// on 96^3 with dilation 2 53.8 -> 51.5, a U-Net's eighteen launches 125.6 -> 113.3.
+// on 96^3 with dilation 2 53.8 -> 51.5, a U-Net's eighteen launches 125.6 -> 113.3.  A wave by itself issues an instruction,
+// scalar or vector, every 2.4 ns, and the halo voxels arrive 0.1 to 0.4 us after the last of their loads, which 250
+// instructions stood in front of: strides and counts come ready from the host, and bank rows, cut points and operands' places
+// are fetched and computed behind those loads.  64 -> 64 3 x 3 on 232 x 168 4.71 -> 4.49 us, on sixteen planes
+// 17.3 -> 16.5, a U-Net on one stack 81.0 -> 78.9.  (Coordinates stepped with carries instead of divisions, records of up to
+// four words to a load: shorter per voxel, longer in front of the first, 32 -> 32 on 24^3 4.23 -> 4.69 us.)
 // Measured, fused output, bit-count kernels before: 64 -> 64 channels on 64^3: 88 -> 13.5 us, on 96^3 with
 // dilation 2: 276 -> 44.5 us; 256 -> 256 on 2 x 32^3: 321 -> 42 us (5 500 TFLOP/s: loop 38, fill 3, epilogue 1 us);
 // 64 -> 64 3 x 3 on 16 planes of 232 x 168: 83 -> 17.8 us.
@@ -63,9 +68,13 @@ struct MatrixPlan {
     int32_t lks;                     // waves that share a tile's steps and add up their sums in LDS (log2)
     int32_t hx, hy, hz;              // halo extents in voxels
     Divisor tiles_x, tiles_y, tiles_z;
-    uint32_t reach;                  // bytes of input from a tile's first plane to its last (FAR: its rows of a plane)
+    int32_t threads, tiles;          // of a workgroup, of the launch
+    uint32_t reach;                  // bytes of input, or of its part from a tile's first plane to its last (FAR: its rows of a plane)
+    int32_t whole;                   // all of the input
+    uint32_t rec, line, slice, item; // input bytes of a voxel, a row, a plane, a batch item (item: if whole)
     int32_t nch;                     // words (or word pairs) per voxel
-    int32_t rows;                    // of the filter bank
+    int32_t rows, row_bytes;         // of the filter bank
+    int32_t plane, items;            // voxels of a plane of the halo tile, units of its fill
     int32_t pl;                      // LDS bytes of one word plane
     int32_t zero_off;                // LDS byte offset of a zero record (odd word counts)
     int32_t tp_log;                  // tap-packed bank: log2 of the taps per row
@@ -103,13 +112,13 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void c
 {
     extern __shared__ __align__(16) uint8_t lds8[];
     const int tid = threadIdx.x;
-    const int nthreads = blockDim.x;
+    const int nthreads = t.threads;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
     int bid = blockIdx.x;
     {   // contiguous runs of tiles per XCD (workgroups go to the 8 XCDs round-robin)
-        const int per_xcd = gridDim.x >> 3;
+        const int per_xcd = t.tiles >> 3;
         if (bid < (per_xcd << 3)) bid = (bid & 7) * per_xcd + (bid >> 3);
     }
     const int row = quotient(bid, t.tiles_x), tix = bid - row * t.tiles_x.d;
@@ -128,13 +137,11 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void c
     constexpr int REC = 16;                                 // LDS bytes per word and voxel: 32 four-bit floats
     static_assert(KIND != kTapPacked || ODD, "one word per voxel");
     constexpr bool ROWS = (ODD || KIND == kDigits) && KIND != kTapPacked;           // the lane groups read different bank rows
-    const int plane = t.hx * t.hy;
-    const int nvox = plane * t.hz;
-    const int wd = p.wd_in;
+    const int plane = t.plane;
 
     // ---- filter words ------------------------------------------------------------------------
     constexpr int FW = KIND == kDigits ? 4 : KIND == kBinary ? (ODD ? 1 : 2) : (ODD ? 2 : 4);  // words per filter and row
-    const int row_bytes = p.co_pad * FW * 4;
+    const int row_bytes = t.row_bytes;
     const int entries = p.kd * p.kh * p.kw * (KIND == kDigits && !ODD ? t.nch >> 1 : t.nch);     // (tap, word or pair of words)
     const int all_steps = ODD ? (entries + 1) >> 1 : entries;
     // this wave's steps: first .. first + steps - 1
@@ -191,24 +198,46 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void c
             }
         }
     };
-    // Two steps' words in front of the halo tile's loads, the others behind them.
-    fetch_f(f[0], 0);
-    fetch_f(f[1], 1);
-    auto fetch_others = [&]() {
-#pragma unroll
-        for (int k = 2; k < AHEAD; ++k) fetch_f(f[k], k);
-    };
-
     // Cut points of the workgroup's filters, thread j those of filter j (a workgroup has at least as many
-    // threads).  Fetched here, with the first loads, and staged behind the halo tile: fetched there they cost
-    // another round trip in front of the barrier (0.4 to 0.9 us of a launch of 5 to 9).
+    // threads).  Staged behind the halo tile: fetched there they cost another round trip in front of the barrier
+    // (0.4 to 0.9 us of a launch of 5 to 9).
     const int wg_filters = t.nwc * 32 * NB;
     int cut_lo = 0, cut_hi = 0;
-    if constexpr (PACKED) {
-        const int co = min((int)blockIdx.y * wg_filters + min(tid, wg_filters - 1), p.c_out - 1);
-        cut_lo = p.lo[co];
-        cut_hi = p.hi[co];
-    }
+
+    // ---- operands' places in LDS -------------------------------------------------------------------
+    int lane_v[VB];
+    auto tap_off = [&](int tap) {
+        const int r = (int)quotient((uint32_t)tap, t.r_kw), a = (int)quotient((uint32_t)r, t.r_kh);
+        return (((a * p.dd * t.hy) + (r - a * p.kh) * p.dh) * t.hx + (tap - r * p.kw) * p.dw) * REC;
+    };
+    const int nch = KIND == kDigits && !ODD ? t.nch >> 1 : t.nch;
+    const int inc_ch = ODD ? t.pl : 2 * t.pl;
+    // The entries' LDS offsets lie in the lanes of a register, so that a step is a readlane: lanes 48 and up those of the
+    // first two steps, lanes 0 to 47 those of the next, in turn.
+    int table, entry = 48, entry0 = (ODD ? 2 : 1) * first;
+    auto tabulate = [&]() {
+        const int e = min(entry0 + (lane < 48 ? lane + (ODD ? 4 : 2) : lane - 48), entries - 1);   // (the last again past the end)
+        const int tap = (int)quotient((uint32_t)e, t.r_nch);
+        table = tap_off(tap) + (e - tap * nch) * inc_ch;
+    };
+    // All that has time until the halo tile's first words arrive.
+    auto meanwhile = [&]() {
+#pragma unroll
+        for (int k = 0; k < AHEAD; ++k) fetch_f(f[k], k);
+        if constexpr (PACKED) {
+            const int co = min((int)blockIdx.y * wg_filters + min(tid, wg_filters - 1), p.c_out - 1);
+            cut_lo = p.lo[co];
+            cut_hi = p.hi[co];
+        }
+#pragma unroll
+        for (int vb = 0; vb < VB; ++vb) {
+            const int vi = vb * 32 + i32;
+            const int x = vi & (X - 1), y = (vi >> t.lxb) & (Y - 1), z = vi >> (t.lxb + t.lyb);
+            const int v = ((wz * Z + z) * p.sd * t.hy + (wy * Y + y) * p.sh) * t.hx + x * p.sw;
+            lane_v[vb] = v * REC + (ODD ? 0 : g * t.pl);
+        }
+        tabulate();
+    };
 
     uint32_t m33 = 0x33333333u, maa = 0xaaaaaaaau;
     asm volatile("" : "+v"(m33), "+v"(maa));
@@ -216,20 +245,26 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void c
     // ---- halo tile -> LDS ----------------------------------------------------------------------
     const int gx0 = ox0 * p.sw - p.pw, gy0 = oy0 * p.sh - p.ph, gz0 = oz0 * p.sd - p.pd;
     {
-        // Offsets from the tile's first plane within the volume, in bytes and modulo 2^32; voxels outside the
-        // volume get one past the end, which reads as zeros.
-        const int zb = max(gz0, 0);
-        const uint32_t rec = 8u * (uint32_t)wd, line = (uint32_t)p.w * rec, slice = (uint32_t)p.h * line;
-        const uint32_t* from = KIND == kPair ? t.pair.base : p.in + ((size_t)n * p.d + zb) * ((size_t)p.h * p.w * 2u * wd);
+        // Offsets are in bytes and modulo 2^32; voxels outside the volume get one past the end, which reads as zeros.
+        const uint32_t* from = KIND == kPair ? t.pair.base : p.in;
+        uint32_t origin = (uint32_t)gz0 * t.slice + (uint32_t)gy0 * t.line + (uint32_t)gx0 * t.rec;
+        if constexpr (KIND != kPair && !FAR) {
+            if (t.whole) {
+                origin += (uint32_t)n * t.item;
+            } else {
+                const int zb = max(gz0, 0);
+                from += ((size_t)n * p.d + zb) * (size_t)(t.slice >> 2);
+                origin -= (uint32_t)zb * t.slice;
+            }
+        }
         __amdgpu_buffer_rsrc_t src = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(from), 0, t.reach, 0x00020000);
         uint32_t pair0 = 0, pair1 = 0;                      // the batch item's first bytes; word pair c of source 1 is pair c - nch0 there
         if constexpr (KIND == kPair) {
             pair0 = t.pair.start[0] + (uint32_t)n * t.pair.item[0];
             pair1 = t.pair.start[1] + (uint32_t)n * t.pair.item[1] - 8u * (uint32_t)t.pair.nch0;
         }
-        uint32_t origin = (uint32_t)(gz0 - zb) * slice + (uint32_t)gy0 * line + (uint32_t)gx0 * rec;
         constexpr uint32_t OUTSIDE = 0xfffffff0u;
-        int items = nvox * t.nch;
+        int items = t.items;
         constexpr bool PAIRS = !ODD || KIND == kDigits;     // two words per plane and item
         // Items a thread keeps in flight (single words: more would cost a wave per SIMD).  Eight where the registers are
         // there anyway: 64 channels on 8 x 8 x 8 with dilation 2 are 6.75 items to a thread, and the second round trip
@@ -240,7 +275,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void c
             int dst[FILL];
 #pragma unroll
             for (int k = 0; k < FILL; ++k) {
-                if (!ODD && k > 0 && base + k * nthreads >= items) break;   // (the same for every thread)
+                if (k > 0 && base + k * nthreads >= items) break;   // (the same for every thread)
                 const uint32_t e = (uint32_t)(base + k * nthreads + tid);
                 const uint32_t v = quotient(e, t.r_ch);
                 const uint32_t c = e - __umul24(v, (uint32_t)t.nch);
@@ -268,21 +303,21 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void c
                     r[k][0] = m.x; r[k][1] = m.y; r[k][2] = sg.x; r[k][3] = sg.y;
                     continue;
                 }
-                uint32_t o = origin + hz * slice + hy * line + __umul24(hx, rec) + (PAIRS ? 8u : 4u) * c;
+                uint32_t o = origin + hz * t.slice + hy * t.line + __umul24(hx, t.rec) + (PAIRS ? 8u : 4u) * c;
                 o = inside ? o : OUTSIDE;
                 if constexpr (PAIRS) {
                     const v2u a = __builtin_amdgcn_raw_buffer_load_b64(src, o, 0, 0);
-                    const v2u b = __builtin_amdgcn_raw_buffer_load_b64(src, o, 4 * wd, 0);
+                    const v2u b = __builtin_amdgcn_raw_buffer_load_b64(src, o, t.rec >> 1, 0);
                     r[k][0] = a.x; r[k][1] = a.y; r[k][2] = b.x; r[k][3] = b.y;
                 } else {
                     r[k][0] = __builtin_amdgcn_raw_buffer_load_b32(src, o, 0, 0);
-                    r[k][2] = __builtin_amdgcn_raw_buffer_load_b32(src, o, 4 * wd, 0);
+                    r[k][2] = __builtin_amdgcn_raw_buffer_load_b32(src, o, t.rec >> 1, 0);
                 }
             }
-            if constexpr (decltype(first_one)::value) fetch_others();
+            if constexpr (decltype(first_one)::value) meanwhile();
 #pragma unroll
             for (int k = 0; k < FILL; ++k) {
-                if (!ODD && k > 0 && base + k * nthreads >= items) break;
+                if (k > 0 && base + k * nthreads >= items) break;
                 if (dst[k] >= 0) {
                     uint8_t* d = lds8 + dst[k];
                     if constexpr (KIND == kDigits) {
@@ -301,12 +336,13 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void c
             round(0, std::true_type{});
             for (int base = FILL * nthreads; base < items; base += FILL * nthreads) round(base, std::false_type{});
         } else {
+            meanwhile();
             const int yb = max(gy0, 0);
             for (int hz = 0, base = 0; hz < t.hz; ++hz) {
                 const int z = min(max(gz0 + hz, 0), p.d - 1);   // (a plane outside the volume reads nothing)
-                from = p.in + (((size_t)n * p.d + z) * p.h + yb) * ((size_t)p.w * 2u * wd);
+                from = p.in + (((size_t)n * p.d + z) * p.h + yb) * (size_t)(t.line >> 2);
                 src = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(from), 0, t.reach, 0x00020000);
-                origin = (uint32_t)(gy0 - yb) * line + (uint32_t)gx0 * rec - (uint32_t)hz * slice;
+                origin = (uint32_t)(gy0 - yb) * t.line + (uint32_t)gx0 * t.rec - (uint32_t)hz * t.slice;
                 items = (hz + 1) * plane * t.nch;
                 for (; base < items; base += FILL * nthreads) round(base, std::false_type{});
                 base = items;
@@ -328,29 +364,6 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void c
     if (!SPLIT && !active) return;
 
     // ---- contraction ---------------------------------------------------------------------------
-    int lane_v[VB];
-#pragma unroll
-    for (int vb = 0; vb < VB; ++vb) {
-        const int vi = vb * 32 + i32;
-        const int x = vi & (X - 1), y = (vi >> t.lxb) & (Y - 1), z = vi >> (t.lxb + t.lyb);
-        const int v = ((wz * Z + z) * p.sd * t.hy + (wy * Y + y) * p.sh) * t.hx + x * p.sw;
-        lane_v[vb] = v * REC + (ODD ? 0 : g * t.pl);
-    }
-    auto tap_off = [&](int tap) {
-        const int r = (int)quotient((uint32_t)tap, t.r_kw), a = (int)quotient((uint32_t)r, t.r_kh);
-        return (((a * p.dd * t.hy) + (r - a * p.kh) * p.dh) * t.hx + (tap - r * p.kw) * p.dw) * REC;
-    };
-    const int nch = KIND == kDigits && !ODD ? t.nch >> 1 : t.nch;
-    const int inc_ch = ODD ? t.pl : 2 * t.pl;
-    // The entries' LDS offsets lie in the lanes of a register, so that a step is a readlane: lanes 48 and up those of the
-    // first two steps, lanes 0 to 47 those of the next, in turn.
-    int table, entry = 48, entry0 = (ODD ? 2 : 1) * first;
-    auto tabulate = [&]() {
-        const int e = min(entry0 + (lane < 48 ? lane + (ODD ? 4 : 2) : lane - 48), entries - 1);   // (the last again past the end)
-        const int tap = (int)quotient((uint32_t)e, t.r_nch);
-        table = tap_off(tap) + (e - tap * nch) * inc_ch;
-    };
-    tabulate();
     auto next_entry = [&]() { return __builtin_amdgcn_readlane(table, entry++); };
     auto next_table = [&]() {                                  // (after a whole number of rounds of either loop)
         if (__builtin_expect(entry == 48, 0)) {
@@ -735,7 +748,8 @@ bool launch_conv_matrix(const ConvParams& p, const ConvPair* pair, hipStream_t s
     // filters, as there is one form of that kernel (64 -> 64 channels, 3 x 3, on a plane of 16 400 x 16 400
     // 6.9 ms; half of it, which one descriptor reaches, 3.4, with bit counts 17.6).
     const int64_t line_bytes = 8 * (int64_t)p.wd_in * p.w, plane_bytes = line_bytes * p.h;
-    int64_t reach = pair ? t.pair.reach : plane_bytes * (q.hz < p.d ? q.hz : p.d);
+    const bool whole = plane_bytes * p.d * p.n <= 0xffff0000ll;
+    int64_t reach = pair ? t.pair.reach : whole ? plane_bytes * p.d * p.n : plane_bytes * (q.hz < p.d ? q.hz : p.d);
     // (the bank is read through one, too)
     const int64_t bank_rows = p.tp_slots ? cdiv(taps, (int64_t)p.tp_slots) : taps * (p.wd_in / p.wc);
     const int64_t bank_bytes = bank_rows * p.co_pad * p.wc * (p.binary ? 4 : 8);
@@ -761,12 +775,20 @@ bool launch_conv_matrix(const ConvParams& p, const ConvPair* pair, hipStream_t s
     t.hx = (int32_t)q.hx; t.hy = (int32_t)q.hy; t.hz = (int32_t)q.hz;
     t.tiles_x = divisor(cdiv(p.ow, X)); t.tiles_y = divisor(cdiv(p.oh, Y * c.nwy)); t.tiles_z = divisor(cdiv(p.od, Z * c.nwz));
     t.reach = (uint32_t)reach;
+    t.whole = whole;
+    t.rec = 8u * (uint32_t)p.wd_in; t.line = (uint32_t)line_bytes; t.slice = (uint32_t)plane_bytes;
+    t.item = (uint32_t)(plane_bytes * p.d);
     t.nch = p.digits || odd ? words : words / 2;
     t.rows = (int32_t)bank_rows;
+    t.row_bytes = p.co_pad * p.wc * (p.binary ? 4 : 8);
+    t.plane = t.hx * t.hy;
+    t.items = (int32_t)q.items;
     t.pl = (int32_t)(q.hx * q.hy * q.hz * 16);
     t.zero_off = words * t.pl;
     t.cut_off = (int32_t)q.cuts;
     t.lks = log2_up(c.nks);
+    const int threads = 64 * c.nwy * c.nwz * c.nwc * c.nks;
+    t.threads = threads; t.tiles = (int32_t)q.tiles;
     t.r_nwc = reciprocal((uint32_t)c.nwc, 8);
     const uint32_t emax = (uint32_t)q.items;
     t.r_hx = reciprocal((uint32_t)t.hx, emax);
@@ -780,7 +802,6 @@ bool launch_conv_matrix(const ConvParams& p, const ConvPair* pair, hipStream_t s
     if (p.tp_slots)
         while ((p.tp_shift << t.tp_log) < 32) ++t.tp_log;
     const dim3 grid((unsigned)q.tiles, (unsigned)gy);
-    const int threads = 64 * c.nwy * c.nwz * c.nwc * c.nks;
     const size_t lds = (size_t)q.lds;
     note_launch(TERN_KERNEL_TILED, c.vb / 2, 32 * c.nb, c.nks, threads, grid.x, grid.y, lds);
     if (far) {
