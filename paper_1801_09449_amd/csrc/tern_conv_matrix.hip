@@ -741,9 +741,11 @@ bool launch_conv_matrix(const ConvParams& p, const ConvPair* pair, hipStream_t s
     const bool odd = (words & 1) != 0, packed = p.out_packed != nullptr;
     const MatrixShape shape = {p.n, p.c_out, p.od, p.oh, p.ow, p.kd, p.kh, p.kw, p.sd, p.sh, p.sw, p.dd, p.dh, p.dw,
                                words, p.digits, packed ? 1 : 0, (int32_t)lds_limit};
-    Choice c;
+    Choice c, settled;
     Tile q;
-    if (!choose_cached(shape, c) || !tile_of(shape, c, q)) return false;
+    if (!choose_cached(shape, c, &settled)) return false;
+    if (!p.tp_slots) c = settled;
+    if (!tile_of(shape, c, q)) return false;
     // A tile's planes within 4 GB (a volume's may be more), or else its rows of each: then with waves of 128 voxels on 32
     // filters, as there is one form of that kernel (64 -> 64 channels, 3 x 3, on a plane of 16 400 x 16 400
     // 6.9 ms; half of it, which one descriptor reaches, 3.4, with bit counts 17.6).

@@ -236,21 +236,84 @@ inline bool choose(const MatrixShape& s, Choice& best)
     return cost < 1e300;
 }
 
+// A second look at launches of the small waves, which a wave's own time decides: how its waves are shared out between
+// space, filters and steps, in tiles of the same shape.  The estimate above takes up to six halo items a lane for one round
+// trip; they are instructions, a wave by itself issues one every 2.4 ns, and waves that share a halo tile fill it together.
+// Its time here, in ns: a wave's own as long as launches come in whole rounds, and what the waves of a SIMD take together, the
+// norm of both.  The weights are a fit to launches on 252 shapes of up to 20 GMAC, planes and volumes; another launch is
+// taken where it is 4 % shorter, on 40 of them, by 6 % in the geometric mean (2 % longer to 20 % shorter): 128 -> 128 channels
+// 3 x 3 on 113 x 81 5.2 -> 4.5 us, 512 -> 256 on 52 x 36 6.9 -> 6.3, 64 -> 64 on 232 x 168 4.5 -> 4.1.  Not from 6 us on, where
+// rates decide (216 -> 32, 3 x 3, on sixteen of 43 x 197 13.6 and 14.7); and the caller leaves tap-packed filters out, whose
+// shifts make a step longer than it is here (5 -> 26 on 2 x 30 x 56 x 14 4.9 and 5.4).
+inline double small_cost(const MatrixShape& s, const Choice& c, const Tile& t, int lks)
+{
+    const int waves = waves_of(c), groups = cdiv(s.c_out, 32) / c.nb, active = c.nwc > groups ? waves / c.nwc * groups : waves;
+    const double rounds64 = rounds64_of(waves, t.items), steps = steps_of(s, lks);
+    const double blocks = c.nb, two = c.nb - 1, split = c.nks > 1 ? 1.0 : 0.0;
+    const int64_t per_cu = (t.wgs + 255) >> 8;
+    const double wave = 560.0 + 83.0 * rounds64 + (20.0 + 35.0 * two) * steps + blocks * ((s.packed ? 270.0 : 400.0) * kShare[c.nks] + 380.0 * split);
+    const double busy = (double)per_cu * 0.25 * (active * wave + (waves - active) * (500.0 + 83.0 * rounds64));
+    int fit = (c.nb == 2 ? 16 : 20) / waves;                       // (by registers)
+    const int by_lds = (int)(163840.0f / (float)(int32_t)t.lds);
+    if (by_lds < fit) fit = by_lds < 1 ? 1 : by_lds;
+    const double alone = 840.0 + 147.0 * rounds64 + (98.0 + 75.0 * two) * steps + blocks * (s.packed ? 150.0 : 1600.0) * kShare[c.nks] +
+                         split * (420.0 + 330.0 * two);
+    const double latency = (double)((per_cu + fit - 1) / fit) * alone;
+    return std::sqrt(busy * busy + latency * latency);
+}
+inline void settle(const MatrixShape& s, Choice& c)
+{
+    if (c.vb != 2) return;
+    const Choice from = c;
+    Tile t;
+    if (!tile_of(s, from, t)) return;
+    const int fb = cdiv(s.c_out, 32);
+    const bool deep = s.od > 1 && s.kd > 1;
+    const int64_t all_steps = ((int64_t)s.kd * s.kh * s.kw * s.words + 1) / 2;
+    double least = small_cost(s, from, t, log2_up(from.nks));
+    if (least > 6000.0) return;
+    least *= 0.96;
+    for (int nws = 1; nws <= 8; nws *= 2) {
+        const int nwy = deep ? 1 : nws, nwz = deep ? nws : 1;
+        Tile halo;
+        if (!halo_of(s, 2, from.lxb, from.lyb, nwy, nwz, halo)) break;
+        for (int nb = 1; nb <= from.nb; ++nb)                      // (two blocks of filters only where they were allowed)
+            for (int nwc = 1; nwc * nws <= 8 && nwc <= fb / nb; ++nwc) {
+                if ((nwc & (nwc - 1)) && nwc != fb / nb) continue;
+                // (a split leaves each wave at least four steps)
+                for (int lks = 0; lks < 4 && nwc * nws << lks <= 8 && (lks == 0 || all_steps >= 4 << lks); ++lks) {
+                    const Choice x = {2, nb, from.lxb, from.lyb, nwy, nwz, nwc, 1 << lks};
+                    if (!tile_of(s, x, t)) continue;
+                    const double cost = small_cost(s, x, t, lks);
+                    if (cost < least) { least = cost; c = x; }
+                }
+            }
+    }
+}
+
 // Each thread keeps the choices of the geometries it met last, by hash, two to a place (a found one takes
 // 13 ns).  A network has about a dozen: of 64 kept in the order of their making, those of six image sizes
-// pushed each other out.
-inline bool choose_cached(const MatrixShape& s, Choice& c)
+// pushed each other out.  `settled`: the same after the second look.
+inline bool choose_cached(const MatrixShape& s, Choice& c, Choice* settled = nullptr)
 {
     struct Entry {
         MatrixShape shape;
-        Choice c;
+        Choice c, settled;
         int32_t ok;
     };
+    const auto make = [](const MatrixShape& shape, Choice& a, Choice& b) {
+        const bool ok = choose(shape, a);
+        b = a;
+        if (ok) settle(shape, b);
+        return ok;
+    };
+    Choice other;
+    Choice& b = settled ? *settled : other;
     constexpr int kPlaces = 256;
     static thread_local std::unique_ptr<Entry[]> table;
     if (!table) {
         table.reset(new (std::nothrow) Entry[2 * kPlaces]);
-        if (!table) return choose(s, c);
+        if (!table) return make(s, c, b);
         memset(static_cast<void*>(table.get()), 0, sizeof(Entry) * 2 * kPlaces);   // (no shape has zero words)
     }
     uint64_t h = 0;
@@ -259,11 +322,12 @@ inline bool choose_cached(const MatrixShape& s, Choice& c)
     for (int32_t x : v) h = (h ^ (uint32_t)x) * 0x9e3779b97f4a7c15u, h ^= h >> 29;
     Entry* e = &table[2 * (h >> 32) % (2 * kPlaces)];
     for (int i = 0; i < 2; ++i)
-        if (memcmp(&e[i].shape, &s, sizeof s) == 0) { c = e[i].c; return e[i].ok != 0; }
+        if (memcmp(&e[i].shape, &s, sizeof s) == 0) { c = e[i].c; b = e[i].settled; return e[i].ok != 0; }
     e[1] = e[0];
     e[0].shape = s;
-    e[0].ok = choose(s, e[0].c);
+    e[0].ok = make(s, e[0].c, e[0].settled);
     c = e[0].c;
+    b = e[0].settled;
     return e[0].ok != 0;
 }
 

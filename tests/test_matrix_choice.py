@@ -127,6 +127,41 @@ int main()
 """
 
 
+SETTLED = r"""
+#include "tern_matrix_choice.h"
+#include <cstdio>
+#include <random>
+using namespace tern;
+int main()
+{
+    std::mt19937_64 r(3);
+    auto pick = [&](std::initializer_list<int> l) { return *(l.begin() + r() % l.size()); };
+    long changed = 0, wrong = 0;
+    for (int i = 0; i < 6000; ++i) {
+        const bool flat = r() % 2;
+        MatrixShape s = {pick({1, 1, 2, 4}), pick({8, 32, 64, 70, 128, 256, 512}), flat ? 1 : 2 + (int)(r() % 40), 2 + (int)(r() % 200), 2 + (int)(r() % 200),
+                         flat ? 1 : pick({2, 3}), pick({1, 2, 3, 5}), pick({1, 2, 3, 5}), 1, pick({1, 2}), pick({1, 2}), 1, pick({1, 3}), pick({1, 3}),
+                         pick({1, 2, 3, 4, 7, 8, 16}), pick({0, 0, 1}), pick({0, 1}), pick({65536, 163840})};
+        Choice a, b, c;
+        Tile ta, tb;
+        if (!choose_cached(s, a, &b)) continue;
+        if (!tile_of(s, a, ta) || !tile_of(s, b, tb)) { ++wrong; continue; }
+        const int steps = (s.kd * s.kh * s.kw * s.words + 1) / 2, groups = (s.c_out + 31) / 32;
+        if (memcmp(&a, &b, sizeof a) == 0) continue;
+        ++changed;
+        // same tile of a wave, small waves only; within a workgroup, its LDS and the steps; an even number of filter blocks for pairs
+        if (a.vb != 2 || b.vb != 2 || a.lxb != b.lxb || a.lyb != b.lyb || b.nb > a.nb || (b.nb == 2 && groups % 2)) ++wrong;
+        if (b.nwy * b.nwz * b.nwc * b.nks > 8 || tb.lds > s.lds_limit || tb.items > kMaxItems || b.nwc > groups / b.nb) ++wrong;
+        if (b.nks > 1 && steps < 4 * b.nks) ++wrong;
+        if (small_cost(s, b, tb, log2_up(b.nks)) > 0.96 * small_cost(s, a, ta, log2_up(a.nks)) || small_cost(s, a, ta, log2_up(a.nks)) > 6000.0) ++wrong;
+        Choice again;
+        if (!choose_cached(s, c, &again) || memcmp(&again, &b, sizeof b) || memcmp(&c, &a, sizeof a)) ++wrong;
+    }
+    printf("%ld %ld\n", changed, wrong);
+}
+"""
+
+
 DIVISIONS = r"""
 #include "tern_matrix_choice.h"
 #include <cstdio>
@@ -185,3 +220,11 @@ def test_cheap_choice_is_the_choice_of_a_plain_search(tmp_path):
 def test_divisions_by_multiplication(tmp_path):
     """The launch's reciprocals give the quotients of the integers, at multiples and beside them up to 2^31."""
     assert build_and_run(tmp_path, DIVISIONS).strip() == "0"
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_second_look_keeps_to_what_a_launch_may_be(tmp_path):
+    """The launches that the second look puts in place of small waves' first choice: same tiles, within the limits of a
+    workgroup, shorter by its estimate, and found again with the first choice."""
+    changed, wrong = map(int, build_and_run(tmp_path, SETTLED).split())
+    assert changed > 100 and wrong == 0
