@@ -38,9 +38,9 @@
 // are fetched and computed behind those loads.  64 -> 64 3 x 3 on 232 x 168 4.71 -> 4.49 us, on sixteen planes
 // 17.3 -> 16.5, a U-Net on one stack 81.0 -> 78.9.  (Coordinates stepped with carries instead of divisions, records of up to
 // four words to a load: shorter per voxel, longer in front of the first, 32 -> 32 on 24^3 4.23 -> 4.69 us.)
-// Measured, fused output, bit-count kernels before: 64 -> 64 channels on 64^3: 88 -> 13.5 us, on 96^3 with
-// dilation 2: 276 -> 44.5 us; 256 -> 256 on 2 x 32^3: 321 -> 42 us (5 500 TFLOP/s: loop 38, fill 3, epilogue 1 us);
-// 64 -> 64 3 x 3 on 16 planes of 232 x 168: 83 -> 17.8 us.
+// Measured, fused output, bit-count kernels before: 64 -> 64 channels on 64^3: 88 -> 13.2 us, on 96^3 with
+// dilation 2: 276 -> 43 us; 256 -> 256 on 2 x 32^3: 321 -> 42 us (5 500 TFLOP/s: loop 38, fill 3, epilogue 1 us);
+// 64 -> 64 3 x 3 on 16 planes of 232 x 168: 83 -> 15.7 us.
 #include <type_traits>
 
 #include "tern_internal.h"
@@ -521,17 +521,29 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void c
     }
 
     // ---- epilogue: lane = voxel l % 32 of a block, register v = filter 8 (v / 4) + 4 g + v % 4 -----
-    // A block's voxels differ from block 0's by the same box offset in every lane.
+    // A block's voxels differ from block 0's by the same box offset in every lane.  Voxel numbers are below 2^31: in 64 bits
+    // the steps from block to block took 19 scalar instructions each (64 -> 64 3 x 3 on sixteen planes of 232 x 168 16.5 -> 15.7
+    // us, 64 -> 64 on 64^3 13.5 -> 13.2; as arguments from the host, which come through a load of their own, 16.5 and 13.6).
     const int lx = i32 & (X - 1), ly = (i32 >> t.lxb) & (Y - 1), lz = i32 >> (t.lxb + t.lyb);
     const int bx = ox0, by = oy0 + wy * Y, bz = oz0 + wz * Z;
-    auto offset_of = [&](int vb, int& dx, int& dy, int& dz) {
-        dx = (vb * 32) & (X - 1);
-        dy = ((vb * 32) >> t.lxb) & (Y - 1);
-        dz = (vb * 32) >> (t.lxb + t.lyb);
+    auto inside = [&](int vb, uint32_t& step) {                // step: voxels from block 0
+        const int dx = (vb * 32) & (X - 1), dy = ((vb * 32) >> t.lxb) & (Y - 1), dz = (vb * 32) >> (t.lxb + t.lyb);
+        step = (uint32_t)((dz * p.oh + dy) * p.ow + dx);
         return lx < p.ow - bx - dx && ly < p.oh - by - dy && lz < p.od - bz - dz;
     };
-    const size_t line = (size_t)p.ow, slab = (size_t)p.oh * p.ow;
-    const size_t vox0 = (((size_t)n * p.od + bz + lz) * p.oh + by + ly) * p.ow + bx + lx;
+    const uint32_t vox0 = (((uint32_t)n * p.od + bz) * p.oh + by) * p.ow + bx + ((uint32_t)(lz * p.oh) + ly) * p.ow + lx;
+    // int32 sums of rows 8 k + j, j < 4, of quads k from a block's filter c0 on (c0 with the lane's 4 g)
+    const size_t cs = (size_t)p.od * p.oh * p.ow;
+    auto sums_at = [&](int c0, uint32_t step) { return p.out_acc + ((size_t)n * p.c_out + c0) * cs + (vox0 + step - (uint32_t)n * (uint32_t)cs); };
+    auto store_quads = [&](int32_t* o, int c0, auto quads, auto&& value) {
+        constexpr int N = decltype(quads)::value;
+        const bool all = (c0 & ~7) + 8 * N <= p.c_out;      // (the same for every lane)
+#pragma unroll
+        for (int v = 0; v < 4 * N; ++v) {
+            if (all || c0 + (v >> 2) * 8 + (v & 3) < p.c_out) *o = (int32_t)value(v);
+            o += (v & 3) == 3 ? 5 * cs : cs;
+        }
+    };
     if constexpr (SPLIT) {
         auto finish = [&](auto log2_waves) {
             constexpr int LKS = decltype(log2_waves)::value, Q = QUADS >> LKS, QB = Q < 4 ? Q : 4;   // (quads of one block)
@@ -551,8 +563,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void c
 #pragma unroll
             for (int q0 = 0; q0 < Q; q0 += QB) {
                 const int u = ks * Q + q0, vb = u / 4 / NB, nb = u / 4 % NB, k0 = u & 3;
-                int dx, dy, dz;
-                const bool live = offset_of(vb, dx, dy, dz);
+                uint32_t step;
+                if (!inside(vb, step)) continue;
                 if constexpr (PACKED) {
                     const float* widths = cuts + wg_filters + (wc * NB + nb) * 32 + 8 * k0 + 4 * g;
                     uint32_t pos = 0u, neg = 0u;
@@ -567,24 +579,16 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void c
                         else decide<1>(pos, neg, a.x, w.x);
                     }
                     const uint32_t word = block_word(pos, neg);
-                    if (live && cb + nb * 32 < p.c_out) {
-                        uint32_t* o = p.out_packed + (vox0 + dz * slab + dy * line + dx) * 2u * p.wd_out + g * p.wd_out + (cb >> 5) + nb;
-                        if constexpr (QB == 4) *o = word;
-                        else if constexpr (QB == 2) reinterpret_cast<uint16_t*>(o)[k0 >> 1] = (uint16_t)word;
-                        else reinterpret_cast<uint8_t*>(o)[k0] = (uint8_t)word;
-                    }
-                } else if (live) {
-                    const size_t cs = (size_t)p.od * slab;
+                    uint32_t* o = p.out_packed + (size_t)(vox0 + step) * (2u * p.wd_out) + g * p.wd_out + (cb >> 5) + nb;
+                    if constexpr (QB == 4) *o = word;
+                    else if constexpr (QB == 2) reinterpret_cast<uint16_t*>(o)[k0 >> 1] = (uint16_t)word;
+                    else reinterpret_cast<uint8_t*>(o)[k0] = (uint8_t)word;
+                } else {
                     const int c0 = cb + nb * 32 + 8 * k0 + 4 * g;
-                    int32_t* o = p.out_acc + ((size_t)n * p.c_out + c0) * cs + (vox0 - (size_t)n * cs) + dz * slab + dy * line + dx;
-#pragma unroll
-                    for (int q = 0; q < QB; ++q) {
-                        const float4 a = sum[q0 + q];
-                        if (c0 + 8 * q < p.c_out) o[(8 * q) * cs] = (int32_t)a.x;
-                        if (c0 + 8 * q + 1 < p.c_out) o[(8 * q + 1) * cs] = (int32_t)a.y;
-                        if (c0 + 8 * q + 2 < p.c_out) o[(8 * q + 2) * cs] = (int32_t)a.z;
-                        if (c0 + 8 * q + 3 < p.c_out) o[(8 * q + 3) * cs] = (int32_t)a.w;
-                    }
+                    store_quads(sums_at(c0, step), c0, std::integral_constant<int, QB>{}, [&](int v) {
+                        const float4& a = sum[q0 + (v >> 2)];
+                        return (v & 3) == 0 ? a.x : (v & 3) == 1 ? a.y : (v & 3) == 2 ? a.z : a.w;
+                    });
                 }
             }
         };
@@ -594,8 +598,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void c
         return;
     }
     if constexpr (PACKED) {
-        uint32_t* out = p.out_packed + vox0 * 2u * p.wd_out + g * p.wd_out + (cb >> 5);
-        const bool pair = NB == 2 && (p.wd_out & 1) == 0;   // (cb >> 5 is even then)
+        uint32_t* out = p.out_packed + (size_t)vox0 * (2u * p.wd_out) + g * p.wd_out + (cb >> 5);
         Decider d;
         v8bf widths[NB];
         if constexpr (SIX) {
@@ -616,35 +619,22 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void c
                     word[nb] = block_word(pos, neg);
                 }
             }
-            int dx, dy, dz;
-            if (offset_of(vb, dx, dy, dz)) {
-                uint32_t* o = out + (dz * slab + dy * line + dx) * 2u * p.wd_out;
-                if (pair) {
-                    *reinterpret_cast<v2u*>(o) = v2u{word[0], word[NB - 1]};
-                } else {
-#pragma unroll
-                    for (int nb = 0; nb < NB; ++nb)
-                        if (cb + nb * 32 < p.c_out) o[nb] = word[nb];
-                }
+            uint32_t step;
+            if (inside(vb, step)) {
+                uint32_t* o = out + (size_t)step * (2u * p.wd_out);
+                // (two blocks of filters come where there is an even number of blocks: all words exist)
+                if constexpr (NB == 2) *reinterpret_cast<v2u*>(o) = v2u{word[0], word[1]};
+                else *o = word[0];
             }
         }
     } else {
-        const size_t cs = (size_t)p.od * slab;
-        const size_t in_item = vox0 - (size_t)n * cs;
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
             const int c0 = cb + nb * 32 + 4 * g;
 #pragma unroll
             for (int vb = 0; vb < VB; ++vb) {
-                int dx, dy, dz;
-                if (offset_of(vb, dx, dy, dz)) {
-                    int32_t* o = p.out_acc + ((size_t)n * p.c_out + c0) * cs + in_item + dz * slab + dy * line + dx;
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) {
-                        const int dc = (v >> 2) * 8 + (v & 3);
-                        if (c0 + dc < p.c_out) o[dc * cs] = (int32_t)acc[vb][nb][v];
-                    }
-                }
+                uint32_t step;
+                if (inside(vb, step)) store_quads(sums_at(c0, step), c0, std::integral_constant<int, 4>{}, [&](int v) { return acc[vb][nb][v]; });
             }
         }
     }
