@@ -742,9 +742,9 @@ bool launch_conv_matrix(const ConvParams& p, const ConvPair* pair, hipStream_t s
     const int64_t line_bytes = 8 * (int64_t)p.wd_in * p.w, plane_bytes = line_bytes * p.h;
     const bool whole = plane_bytes * p.d * p.n <= 0xffff0000ll;
     int64_t reach = pair ? t.pair.reach : whole ? plane_bytes * p.d * p.n : plane_bytes * (q.hz < p.d ? q.hz : p.d);
-    // (the bank is read through one, too)
+    // (the bank is read through one, too, and a row past its end, which has to read as zeros, has to lie within 4 GB)
     const int64_t bank_rows = p.tp_slots ? cdiv(taps, (int64_t)p.tp_slots) : taps * (p.wd_in / p.wc);
-    const int64_t bank_bytes = bank_rows * p.co_pad * p.wc * (p.binary ? 4 : 8);
+    const int64_t bank_bytes = (bank_rows + 1) * p.co_pad * p.wc * (p.binary ? 4 : 8);
     const bool far = reach > 0xffff0000ll || bank_bytes > 0xf0000000ll;
     if (far && pair) return false;
     if (far) {
