@@ -191,17 +191,19 @@ __global__ __launch_bounds__(kFirstThreads) void first_conv_kernel(FirstConvPara
         }
         const float* widths = cuts + 32 + 4 * g;
 
-        const size_t slab = (size_t)p.oh * p.ow * 2u * p.wd_out;
+        // (a row of output can be more than 2^32 words)
+        const size_t line = (size_t)p.ow * (2u * p.wd_out), slab = p.oh * line;
         auto decided = [&](const v16f& acc) {
             uint32_t pos, neg;
             decide_rows<FEW ? 2 : 4>(pos, neg, acc, widths);
             return FEW ? half_block_word(pos, neg) : block_word(pos, neg);
         };
-        uint32_t* out = p.out_packed + ((size_t)n * p.od + oz0) * slab + (size_t)(ox * 2) * p.wd_out + g * p.wd_out + fb;
+        uint32_t* out = p.out_packed + ((size_t)n * p.od + oz0) * slab + (size_t)(oy0 + (wave >> 1) * t.rows) * line +
+                        (size_t)ox * (2u * p.wd_out) + g * p.wd_out + fb;
         // columns of this lane's taps, LDS bytes from that of tap (0, 0)
         constexpr int REC = STACK ? 8 : 4;
         auto tap_col = [&](int col) { return ((col / 3) * tap_y * t.hx + (col % 3) * tap_x) * REC; };
-        for (int r = 0; r < t.rows; ++r) {
+        for (int r = 0; r < t.rows; ++r, out += line) {
             const int y = (wave >> 1) * t.rows + r, oy = oy0 + y;
             if (oy >= p.oh) break;
             const uint8_t* at = lds8 + (y * lane_y * t.hx + col_x * lane_x) * REC;
@@ -215,7 +217,7 @@ __global__ __launch_bounds__(kFirstThreads) void first_conv_kernel(FirstConvPara
                     acc = multiply(A[q], v4i{(int)a.x, (int)a.y, (int)b.x, (int)b.y}, acc);
                 }
                 const uint32_t word = decided(acc);
-                if (ox < p.ow) out[(size_t)oy * (2u * p.ow * p.wd_out)] = word;
+                if (ox < p.ow) *out = word;
             } else {
                 const uint32_t mid = *reinterpret_cast<const uint32_t*>(at + tap_col(4));
                 v4i B;
@@ -224,7 +226,7 @@ __global__ __launch_bounds__(kFirstThreads) void first_conv_kernel(FirstConvPara
                     const uint32_t col = *reinterpret_cast<const uint32_t*>(at + (g ? tap_col(5 + j) : tap_col(j)));
                     B[j] = (int)(col | ((mid >> (4 * j + 16 * g)) << 28));
                 }
-                uint32_t* o = out + (size_t)oy * (2u * p.ow * p.wd_out);
+                uint32_t* o = out;
                 // All of a tile's planes without a branch between them, so that one's products run under another's decisions
                 // (145 layers 0.975 of their time with a branch in front of each plane; far taps with more than 16 filters, which
                 // have the registers of a wave less, up to 1.15).

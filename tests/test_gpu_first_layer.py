@@ -75,3 +75,35 @@ def test_first_layer_special_intensities(G, k):
     lo, hi = synth.bn_like_thresholds(16, int(np.prod(k)), 1, 0.5, 0.6, 6, synth.T_THR)
     half = np.array([0.5], np.float32)
     run(G, x, -half, half, w, lo, hi, (1, 1, 1), (1, 1, 1), (1, 1, 1))
+
+
+@pytest.mark.parametrize("vol,c_out", [
+    ((1, 2, 131072), 524288),          # a row of output is 2^32 words
+])
+def test_first_layer_offsets_beyond_32_bits(G, vol, c_out):
+    """Against the same layer with some of the filters, and on the two ends of the volume."""
+    import torch
+    import paper_1801_09449_amd as T
+    gen = torch.Generator("cuda").manual_seed(c_out)
+    k, pad, half = (1, 3, 3), (0, 1, 1), torch.full((1,), 0.5, device="cuda")
+    x = torch.randn((1, 1) + vol, generator=gen, device="cuda")
+    w = torch.randint(-1, 2, (c_out, 1) + k, generator=gen, device="cuda", dtype=torch.int8)
+    lo, hi = torch.full((c_out,), -2, device="cuda", dtype=torch.int32), torch.arange(c_out, device="cuda", dtype=torch.int32) % 4
+
+    def run_on(x, a, b):
+        L = T.FcnLayer(1, b - a, T.tern_pack_filters(w[a:b].contiguous()), lo[a:b].contiguous(), hi[a:b].contiguous(), k, (1, 1, 1), pad, (1, 1, 1))
+        return T.tern_fcn_forward(x, -half, half, [L])
+
+    got = run_on(x, 0, c_out)
+    part = min(c_out, 4096)
+    end = min(vol[2], 131072)
+    for a in sorted({0, c_out // 2, c_out - part}):
+        words = slice(a // 32, (a + part + 31) // 32)
+        if a + part > c_out:
+            continue
+        left, right = (run_on(x[..., s].contiguous(), a, a + part) for s in (slice(0, end), slice(vol[2] - end, vol[2])))
+        cut = end if end == vol[2] else end - 1            # (a slice's inner edge has padding beside it)
+        assert torch.equal(got[:, :, :, :cut, :, words], left[:, :, :, :cut])
+        assert torch.equal(got[:, :, :, vol[2] - cut:, :, words], right[:, :, :, end - cut:])
+    del got, x, left, right
+    torch.cuda.empty_cache()
