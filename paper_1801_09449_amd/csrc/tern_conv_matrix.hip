@@ -156,8 +156,13 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void c
     uint32_t lane_f = (uint32_t)((SIX ? row_filter(i32) : i32) * FW * 4);
     if constexpr (ROWS) lane_f += (uint32_t)(g * row_bytes);
     else if constexpr (KIND != kTapPacked) lane_f += (uint32_t)(KIND == kBinary ? 4 * g : 8 * g);
-    // Steps whose words are under way at once: about as many as a small wave has.
-    constexpr int AHEAD = VB == 4 ? 2 : NB == 1 ? 8 : 4;
+    // Steps whose words are under way at once.  Their loads stand between those of the halo tile and its words, and take
+    // registers: six steps of one filter block leave a small wave 80, six waves to a SIMD (two-tensor inputs: 82, five).  With
+    // eight there were five of most forms, and launches that need the sixth took up to 1.16 times as long: 256 -> 96 on
+    // 12 x 62 x 62 24.4 -> 20.6 us, 128 -> 96 stride 2 on 4 x 80 x 16 x 70 16.0 -> 13.4; with four, int32 sums of few steps up to
+    // 1.07.  Two-digit rows take two loads to a step, and those of six steps were 4 to 13 % of small launches: 128 -> 128, 2 x 2,
+    // on sixteen planes of 37 x 44 4.7 -> 3.9 us, 256 -> 257 on 49 x 7 x 32 14.3 -> 13.3.
+    constexpr int AHEAD = VB == 4 || KIND == kDigits ? 2 : NB == 1 ? 6 : 4;
     v2u f[AHEAD][NB];
     // The words of a step's bank rows, in turn, through a buffer descriptor that ends with the wave's last row and reads as
     // zeros from there on.  FAR, where the bank may be of any size: a step's, or the last step's again.

@@ -1,8 +1,10 @@
 """The launch chooser of the tiled matrix kernel (csrc/tern_matrix_choice.h, host code): against a plain search
 over every launch with the estimate written out in ordinary divisions, over random geometries."""
 import os
+import re
 import shutil
 import subprocess
+import tempfile
 
 import pytest
 
@@ -228,3 +230,47 @@ def test_second_look_keeps_to_what_a_launch_may_be(tmp_path):
     workgroup, shorter by its estimate, and found again with the first choice."""
     changed, wrong = map(int, build_and_run(tmp_path, SETTLED).split())
     assert changed > 100 and wrong == 0
+
+
+READELF = "/opt/rocm/llvm/bin/llvm-readelf"
+
+
+def kernels_of(lib):
+    """name -> (vector registers, bytes of scratch) of the library's kernels, from the notes of its code objects."""
+    with open(lib, "rb") as f:
+        data = f.read()
+    out = {}
+    for part in data.split(b"__CLANG_OFFLOAD_BUNDLE__")[1:]:
+        at = part.find(b"\x7fELF")
+        if at < 0:
+            continue
+        with tempfile.NamedTemporaryFile(suffix=".elf") as t:
+            t.write(part[at:])
+            t.flush()
+            notes = subprocess.run([READELF, "--notes", t.name], stdout=subprocess.PIPE, stderr=subprocess.DEVNULL, text=True).stdout
+        for k in notes.split("  - .agpr_count:")[1:]:
+            value = lambda key: re.search(r"\.%s:\s+(\S+)" % key, k).group(1)
+            out[value("name")] = int(value("vgpr_count")), int(value("private_segment_fixed_size"))
+    return out
+
+
+@pytest.mark.skipif(not os.path.exists(READELF), reason="needs llvm-readelf")
+def test_resident_waves_of_the_matrix_kernels():
+    """The launch choice counts 24, 16 and 8 waves of a compute unit resident; a kernel's registers, in eights of a SIMD's
+    512, have to leave room for them."""
+    from paper_1801_09449_amd import build
+    if not os.path.exists(build.LIB):
+        pytest.skip("needs the built library")
+    found = 0
+    for name, (registers, scratch) in kernels_of(build.LIB).items():
+        m = re.search(r"conv_matrix_kernelILi(\d)ELi(\d)ELb[01]ELi(\d)E", name)
+        if not m:
+            continue
+        found += 1
+        vb, nb, kind = map(int, m.groups())
+        waves = 4 * (512 // (-(-registers // 8) * 8))
+        least = 8 if vb * nb == 8 else 16 if vb * nb == 4 else 24
+        if (vb, nb, kind) == (2, 1, 4):        # input in two tensors
+            least = 20
+        assert waves >= least and scratch == 0, (name, registers, scratch)
+    assert found == 104
