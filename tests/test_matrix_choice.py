@@ -164,6 +164,31 @@ int main()
 """
 
 
+RESIDENT = r"""
+#include "tern_matrix_choice.h"
+#include <cstdio>
+using namespace tern;
+int main()
+{
+    // (n, c_out, output, kernel, stride, dilation, words, digits, packed, LDS limit); workgroups of eight waves
+    const MatrixShape s = {1, 64, 1, 64, 64, 1, 3, 3, 1, 1, 1, 1, 1, 1, 2, 0, 1, 163840};
+    for (int nb = 1; nb <= 2; ++nb) {
+        const Choice c = {2, nb, 3, 3, 8, 1, 1, 1};
+        auto square = [&](int per_cu) {
+            const Tile t = {0, 0, 0, 0, 256 * per_cu, 8192, 512, 0};
+            const double x = small_cost(s, c, t, 0);
+            return x * x;
+        };
+        // per_cu^2 of the waves' common time and rounds^2 of one workgroup's, which two leave at one round
+        const double common = (square(2) - square(1)) / 3.0, alone = square(1) - common;
+        int fit = 2;
+        while (square(fit + 1) - (fit + 1) * (fit + 1) * common < 1.5 * alone) ++fit;
+        printf("%d ", fit);
+    }
+}
+"""
+
+
 DIVISIONS = r"""
 #include "tern_matrix_choice.h"
 #include <cstdio>
@@ -274,3 +299,9 @@ def test_resident_waves_of_the_matrix_kernels():
             least = 20
         assert waves >= least and scratch == 0, (name, registers, scratch)
     assert found == 104
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_second_look_counts_the_same_resident_waves(tmp_path):
+    """24 and 16 waves of a compute unit, three and two workgroups of eight, in the second look as in the first."""
+    assert build_and_run(tmp_path, RESIDENT).split() == ["3", "2"]
