@@ -739,7 +739,7 @@ bool launch_conv_matrix(const ConvParams& p, const ConvPair* pair, hipStream_t s
     Choice c, settled;
     Tile q;
     if (!choose_cached(shape, c, &settled)) return false;
-    if (!p.tp_slots) c = settled;
+    if (!p.tp_slots || c.vb == 4) c = settled;
     if (!tile_of(shape, c, q)) return false;
     // A tile's planes within 4 GB (a volume's may be more), or else its rows of each: then with waves of 128 voxels on 32
     // filters, as there is one form of that kernel (64 -> 64 channels, 3 x 3, on a plane of 16 400 x 16 400

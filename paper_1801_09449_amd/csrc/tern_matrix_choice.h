@@ -264,9 +264,26 @@ inline double small_cost(const MatrixShape& s, const Choice& c, const Tile& t, i
     const double latency = (double)((per_cu + fit - 1) / fit) * alone;
     return std::sqrt(busy * busy + latency * latency);
 }
+// int32 sums of the large waves: a store writes a row of the wave's voxels, and rows of 4 or 8 are an eighth or a quarter of a
+// 128-byte line, whose parts reach memory one by one once the waves of a chip hold more of them than its caches.  Waves of 16
+// voxels along x instead, where the stores count beside the products and few more tiles are needed: 24 -> 128 channels on
+// 4 x 26 x 87 x 76 171 -> 95 us, 32 -> 128 on 76 x 72 x 43 61 -> 36, 64 -> 160, 3 x 3, on eight planes of 200 x 167 44 -> 35.  The lines
+// are drawn on 499 launches: with more entries, or more tiles than that, up to 1.7 times as long.
+inline void lengthen_rows(const MatrixShape& s, Choice& c)
+{
+    if (c.vb != 4 || s.packed || c.lxb >= 4) return;
+    const int64_t entries = (int64_t)s.kd * s.kh * s.kw * s.words;
+    const bool much = 4.0 * s.n * s.c_out * ((double)s.od * s.oh * s.ow) >= 80e6;
+    const int sixteenths = entries <= 32 ? (much ? 20 : 17) : entries <= 54 && much ? 17 : 0;
+    Choice x = c;
+    x.lxb = 4;
+    x.lyb = s.od == 1 ? 3 : 2;
+    Tile from, to;
+    if (tile_of(s, c, from) && tile_of(s, x, to) && to.tiles * 16 <= from.tiles * sixteenths) c = x;
+}
 inline void settle(const MatrixShape& s, Choice& c)
 {
-    if (c.vb != 2) return;
+    if (c.vb != 2) return lengthen_rows(s, c);
     const Choice from = c;
     Tile t;
     if (!tile_of(s, from, t)) return;

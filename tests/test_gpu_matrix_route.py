@@ -192,6 +192,26 @@ def test_bit_count_plans_where_the_matrix_kernel_does_not_go(G, n, ci, co, vol, 
     assert torch.equal(packed, T.tern_pack(codes))
 
 
+@pytest.mark.parametrize("n,ci,co,vol,k", [
+    (1, 24, 64, (60, 80, 70), (3, 3, 3)), (2, 32, 70, (41, 53, 75), (3, 3, 3)), (1, 64, 33, (75, 81, 113), (3, 3, 3)), (16, 8, 40, (1, 181, 203), (1, 3, 3)),
+    (8, 16, 64, (1, 150, 171), (1, 3, 3)), (3, 96, 160, (1, 190, 171), (1, 3, 3))])
+def test_int32_sums_in_rows_of_16_voxels(G, n, ci, co, vol, k):
+    """Large int32 results, whose waves are turned along x, with remainders along every axis and in the filters."""
+    import torch
+    import paper_1801_09449_amd as T
+    gen = torch.Generator("cuda").manual_seed(870 + ci)
+    act = torch.randint(-1, 2, (n, ci) + vol, generator=gen, device="cuda", dtype=torch.int8)
+    w = torch.randint(-1, 2, (co, ci) + k, generator=gen, device="cuda", dtype=torch.int8)
+    pad = tuple(x // 2 for x in k)
+    want = reference(act, w, pad)
+    got = T.tern_conv3d(T.tern_pack(act), ci, T.tern_pack_filters(w), co, k=k, pad=pad, out=torch.full_like(want, 12345))
+    assert T.tern_last_launch()["voxels_per_lane"] == 2
+    assert torch.equal(got, want)
+    wb = torch.where(w < 0, w, torch.ones_like(w))
+    got = T.tern_conv3d_binary(T.tern_pack(act), ci, T.tern_pack_filters_binary(wb), co, k, 1, pad, 1)
+    assert torch.equal(got, reference(act, wb, pad))
+
+
 @pytest.mark.parametrize("n,ci,co,vol,k,s,p,d,digits", [
     (5, 96, 8, (2, 3, 2), (3, 1, 1), 2, (3, 0, 0), 3, False), (2, 96, 19, (1, 4, 1), (3, 1, 1), 2, (3, 0, 0), 3, False),
     (2, 288, 2, (96, 2, 3), 1, 2, 0, 1, True), (1, 160, 32, (67, 2, 83), 1, (1, 2, 2), 0, 1, True),

@@ -151,6 +151,12 @@ int main()
         const int steps = (s.kd * s.kh * s.kw * s.words + 1) / 2, groups = (s.c_out + 31) / 32;
         if (memcmp(&a, &b, sizeof a) == 0) continue;
         ++changed;
+        if (a.vb == 4) {
+            // int32 sums in rows of 16, in workgroups and with steps as before, and up to a quarter more tiles
+            if (s.packed || a.lxb > 3 || b.lxb != 4 || b.vb != 4 || a.nb != b.nb || a.nwy != b.nwy || a.nwz != b.nwz || a.nwc != b.nwc || b.nks != 1) ++wrong;
+            if (tb.tiles * 16 > ta.tiles * 20 || tb.lds > s.lds_limit || tb.items > kMaxItems || s.kd * s.kh * s.kw * s.words > 54) ++wrong;
+            continue;
+        }
         // same tile of a wave, small waves only; within a workgroup, its LDS and the steps; an even number of filter blocks for pairs
         if (a.vb != 2 || b.vb != 2 || a.lxb != b.lxb || a.lyb != b.lyb || b.nb > a.nb || (b.nb == 2 && groups % 2)) ++wrong;
         if (b.nwy * b.nwz * b.nwc * b.nks > 8 || tb.lds > s.lds_limit || tb.items > kMaxItems || b.nwc > groups / b.nb) ++wrong;
@@ -185,6 +191,33 @@ int main()
         while (square(fit + 1) - (fit + 1) * (fit + 1) * common < 1.5 * alone) ++fit;
         printf("%d ", fit);
     }
+}
+"""
+
+
+ROWS = r"""
+#include "tern_matrix_choice.h"
+#include <cstdio>
+using namespace tern;
+int main()
+{
+    // (n, c_out, output, kernel, stride, dilation, words, digits, packed, LDS limit)
+    const MatrixShape volume = {1, 128, 76, 72, 43, 3, 3, 3, 1, 1, 1, 1, 1, 1, 1, 0, 0, 163840}, planes = {8, 160, 1, 198, 165, 1, 3, 3, 1, 1, 1, 1, 1, 1, 2, 0, 0, 163840};
+    auto row = [](MatrixShape s, int lxb, int lyb) {
+        Choice c = {4, 1, lxb, lyb, 1, 1, 1, 1};
+        settle(s, c);
+        printf("%d%d ", c.lxb, c.lyb);
+    };
+    row(volume, 3, 2); row(volume, 2, 2); row(volume, 4, 3); row(planes, 3, 4); row(planes, 2, 5); row(planes, 5, 2);
+    MatrixShape s = volume;
+    s.packed = 1; row(s, 3, 2);                              // packed words
+    s = volume; s.words = 2; row(s, 3, 2);                   // 54 entries, as many tiles
+    s.ow = 35; row(s, 3, 2);                                 // a fifth more
+    s = volume; s.words = 3; row(s, 3, 2);                   // 81 entries
+    s = volume; s.c_out = 80; row(s, 3, 2);                  // 75 MB, as many tiles
+    s.ow = 35; row(s, 3, 2);                                 // a fifth more
+    s = volume; s.ow = 35; row(s, 3, 2);                     // 98 MB, a fifth more
+    s.ow = 18; s.c_out = 256; row(s, 3, 2);                  // a third more
 }
 """
 
@@ -305,3 +338,9 @@ def test_resident_waves_of_the_matrix_kernels():
 def test_second_look_counts_the_same_resident_waves(tmp_path):
     """24 and 16 waves of a compute unit, three and two workgroups of eight, in the second look as in the first."""
     assert build_and_run(tmp_path, RESIDENT).split() == ["3", "2"]
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_rows_of_int32_sums(tmp_path):
+    """Which launches of the large waves get rows of 16 voxels (log2 extents along x and y)."""
+    assert build_and_run(tmp_path, ROWS).split() == ["42", "42", "43", "43", "43", "52", "32", "42", "32", "32", "42", "32", "42", "32"]
