@@ -80,16 +80,6 @@ def test_largest_sums_and_cut_points_around_them(G, sign):
     check(G, c)
 
 
-@pytest.mark.parametrize("ci,co,vol,k", [
-    # entries of a wave around the 48 and 96 whose offsets it holds at a time, in twos and fours
-    (64, 40, (1, 5, 60), (1, 1, 49)), (64, 8, (1, 9, 30), (1, 5, 10)), (64, 96, (2, 9, 30), (1, 3, 17)),
-    (64, 64, (1, 12, 30), (1, 7, 14)), (32, 33, (1, 5, 60), (1, 1, 51)), (96, 32, (1, 9, 30), (1, 1, 17)),
-    (32, 64, (1, 9, 30), (1, 4, 13)), (32, 24, (3, 9, 20), (1, 9, 11)), (12, 32, (1, 9, 40), (1, 3, 17)),
-    (64, 64, (20, 40, 44), (3, 5, 7)), (32, 64, (20, 40, 44), (3, 5, 7)), (160, 128, (16, 40, 44), 3)])
-def test_entries_of_a_wave_and_its_tables(G, ci, co, vol, k):
-    check(G, synth.conv_case("mx_tables", 1, ci, co, vol, k, 1, 1, 1, p0_w=0.5, p0_a=0.4, seed=817))
-
-
 @pytest.mark.parametrize("ci,co,vol,k", [(256, 256, (4, 8, 9), 3), (512, 32, (1, 9, 17), (1, 3, 3)), (96, 70, (6, 7, 8), 3),
                                          (32, 32, (9, 8, 8), 3), (16, 40, (8, 9, 8), 3), (160, 64, (5, 6, 7), (3, 3, 2)),
                                          (64, 128, (8, 8, 8), 5)])
@@ -161,6 +151,61 @@ def reference(act, w, pad):
                 for i in range(act.shape[0]):
                     out[i] += tap @ x[i, :, z:z + o[0], y:y + o[1], v:v + o[2]].reshape(w.shape[1], -1)
     return out.view(act.shape[0], w.shape[0], *o).int()
+
+
+TABLES = [
+    # A wave holds the offsets of its first two steps (one entry each, or two where words are odd in number) and of the next 48
+    # entries: entries on both sides of the first and second renewal.  (small or large waves, filters of a wave, waves that
+    # share the steps, renewals): n, c_in, c_out, output, kernel
+    ((1, 32, 1, 0), 4, 32, 32, (1, 160, 197), (1, 4, 13)), ((1, 32, 1, 1), 4, 32, 32, (1, 160, 197), (1, 1, 53)),
+    ((1, 32, 1, 2), 4, 32, 32, (1, 300, 337), (1, 1, 101)), ((1, 32, 1, 0), 1, 64, 32, (1, 400, 437), (1, 1, 49)),
+    ((1, 32, 1, 1), 1, 64, 32, (1, 400, 437), (1, 3, 17)), ((1, 32, 1, 1), 1, 64, 32, (1, 400, 437), (1, 7, 14)),
+    ((1, 32, 1, 2), 1, 64, 32, (1, 400, 437), (1, 9, 11)), ((1, 32, 4, 2), 1, 480, 32, (20, 40, 43), (3, 3, 3)),
+    ((1, 32, 2, 1), 1, 512, 64, (20, 40, 43), (2, 3, 3)), ((1, 64, 1, 1), 1, 224, 256, (20, 40, 43), (1, 3, 3)),
+    ((1, 64, 1, 2), 1, 768, 256, (20, 40, 43), (1, 3, 3)), ((1, 64, 2, 2), 2, 480, 256, (12, 24, 27), (2, 3, 3)),
+    ((1, 32, 1, 0), 4, 16, 32, (1, 160, 197), (1, 4, 13)), ((1, 32, 1, 1), 4, 16, 32, (1, 160, 197), (1, 1, 53)),
+    ((1, 32, 1, 2), 4, 16, 32, (1, 300, 337), (1, 1, 101)),
+    ((2, 32, 1, 0), 4, 32, 32, (1, 240, 277), (1, 4, 13)), ((2, 32, 1, 1), 4, 32, 32, (1, 240, 277), (1, 1, 53)),
+    ((2, 32, 1, 1), 4, 32, 32, (1, 240, 277), (1, 10, 10)), ((2, 32, 1, 2), 4, 32, 32, (1, 240, 277), (1, 1, 101)),
+    ((2, 64, 1, 1), 4, 32, 64, (1, 300, 337), (1, 1, 53)), ((2, 64, 1, 2), 4, 32, 64, (1, 300, 337), (1, 8, 13)),
+    ((2, 32, 1, 0), 4, 64, 32, (1, 240, 277), (1, 5, 10)), ((2, 32, 1, 1), 4, 64, 32, (1, 240, 277), (1, 3, 17)),
+    ((2, 32, 1, 2), 4, 64, 32, (1, 240, 277), (1, 9, 11)), ((2, 64, 1, 1), 4, 64, 64, (1, 300, 337), (1, 7, 14)),
+    ((2, 64, 1, 2), 4, 64, 64, (1, 300, 337), (1, 1, 101)), ((2, 32, 1, 1), 4, 16, 32, (1, 240, 277), (1, 1, 53)),
+    ((2, 32, 1, 2), 4, 16, 32, (1, 240, 277), (1, 1, 101)),
+    ("digits", (1, 32, 1, 2), 1, 480, 256, (20, 40, 43), (1, 3, 3)), ("digits", (1, 32, 1, 2), 1, 256, 256, (20, 40, 43), (3, 3, 3)),
+    ("digits", (2, 64, 1, 2), 1, 256, 256, (30, 60, 63), (3, 3, 3))]
+
+
+@pytest.mark.parametrize("case", TABLES, ids=lambda c: "-".join(map(str, c)).replace(" ", ""))
+def test_entries_of_a_wave_and_its_tables(G, case):
+    import torch
+    import paper_1801_09449_amd as T
+    digits = case[0] == "digits"
+    form, n, ci, co, out, k = case[-6:]
+    gen = torch.Generator("cuda").manual_seed(817)
+    vol = tuple(o + a - 1 for o, a in zip(out, k))
+    act = torch.randint(-1, 2, (n, ci) + vol, generator=gen, device="cuda", dtype=torch.int8)
+    w = torch.randint(-1, 2, (co, ci) + k, generator=gen, device="cuda", dtype=torch.int8)
+    words = T.tern_words(ci)
+    entries = k[0] * k[1] * k[2] * words // (1 if words % 2 else 2)
+    lo, hi = torch.full((co,), -9, dtype=torch.int32, device="cuda"), torch.arange(co, device="cuda", dtype=torch.int32) % 21
+    for binary in (False,) if digits else (False, True):
+        wt = torch.where(w < 0, w, torch.ones_like(w)) if binary else w
+        a, c2 = T.tern_pack(act), ci
+        if digits:
+            a, c2 = T.tern_pool_digits(a, ci, (1, 1, 1))
+            bank = T.tern_pack_filters(G.dev(T.tern_digits_weights(wt.cpu().numpy())))
+        else:
+            bank = T.tern_pack_filters_binary(wt) if binary else T.tern_pack_filters(wt)
+        want = reference(act, wt, (0, 0, 0))
+        for kw in ({}, dict(thr_lo=lo, thr_hi=hi)):
+            got = T.tern_conv3d(a, c2, bank, co, k=k, pad=0, binary=binary, digits=digits, **kw)
+            plan = T.tern_last_launch()
+            renewals = (entries // plan["tap_split"] - (5 if words % 2 else 3)) // 48
+            if not kw and not binary:
+                assert (plan["voxels_per_lane"], plan["channels_per_pass"], plan["tap_split"], renewals) == form
+            assert bool(renewals) == bool(form[3])
+            assert torch.equal(got, T.tern_threshold_pack(want, lo, hi) if kw else want), (binary, bool(kw))
 
 
 @pytest.mark.parametrize("binary", [False, True])
