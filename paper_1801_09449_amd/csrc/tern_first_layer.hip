@@ -41,7 +41,8 @@ struct FirstPlan {
 };
 
 // FEW: at most 16 filters, the lower half of a block's rows.
-template <int KD, bool FEW, bool FAR>
+// TOGETHER: all of a tile's planes without a branch between them, so that one's products run under another's decisions.
+template <int KD, bool FEW, bool FAR, bool TOGETHER>
 __global__ __launch_bounds__(kFirstThreads) void first_conv_kernel(FirstConvParams p, FirstPlan t)
 {
     extern __shared__ __align__(16) uint8_t lds8[];
@@ -227,10 +228,7 @@ __global__ __launch_bounds__(kFirstThreads) void first_conv_kernel(FirstConvPara
                     B[j] = (int)(col | ((mid >> (4 * j + 16 * g)) << 28));
                 }
                 uint32_t* o = out;
-                // All of a tile's planes without a branch between them, so that one's products run under another's decisions
-                // (145 layers 0.975 of their time with a branch in front of each plane; far taps with more than 16 filters, which
-                // have the registers of a wave less, up to 1.15).
-                if ((FEW || !FAR) && oz0 + TZ <= p.od) {
+                if (TOGETHER && oz0 + TZ <= p.od) {
                     uint32_t word[TZ];
 #pragma unroll
                     for (int z = 0; z < TZ; ++z) word[z] = decided(multiply(A[z], B, start));
@@ -318,13 +316,28 @@ void launch_first(const FirstConvParams& p, hipStream_t s)
     dim3 grid;
     size_t lds;
     plan_first<KD>(p, t, far, grid, lds);
-    const auto go = [&](auto few, auto apart) {
-        hipLaunchKernelGGL((first_conv_kernel<KD, decltype(few)::value, decltype(apart)::value>), grid, dim3(kFirstThreads), lds, s, p, t);
+    const auto go = [&](auto few, auto apart, auto together) {
+        hipLaunchKernelGGL((first_conv_kernel<KD, decltype(few)::value, decltype(apart)::value, decltype(together)::value>), grid, dim3(kFirstThreads), lds, s, p, t);
     };
     const std::true_type yes;
     const std::false_type no;
-    if (p.c_out <= 16) far ? go(yes, yes) : go(yes, no);
-    else far ? go(no, yes) : go(no, no);
+    const auto apart = [&](auto few, auto together) { far ? go(few, yes, together) : go(few, no, together); };
+    if constexpr (KD == 15) {
+        p.c_out <= 16 ? apart(yes, no) : apart(no, no);
+    } else {
+        // A tile's planes together take the registers of a fifth wave of a SIMD (3x3x3: 104 to 112 of them, 92 to 96 without; single
+        // planes have four waves either way; far taps with more than 16 filters up to 1.15 times as long together).  So they are
+        // where the launch takes no more rounds of four workgroups per compute unit than of five, and, beyond one
+        // round, with up to three words of filters, whose stores come that close together: 3x3x3 to 256 channels on
+        // 4 x 30 x 55 x 16 19.2 us by planes and 20.8 together, to 128 on 2 x 40 x 57 x 67 19.9 and 21.8; to 64 on 56 x 155 x 165 25.1
+        // and 22.7, to 32 on 2 x 33 x 29 x 22 6.4 and 6.1.
+        const int64_t wgs = (int64_t)grid.x * grid.y;
+        const bool together = KD == 1 || wgs <= 1024 || (p.wd_out <= 3 && (wgs + 1023) / 1024 == (wgs + 1279) / 1280);
+        const std::bool_constant<KD == 1> by_planes;           // (no such form of single planes)
+        if (p.c_out <= 16) together ? apart(yes, yes) : apart(yes, by_planes);
+        else if (far) go(no, yes, no);
+        else together ? go(no, no, yes) : go(no, no, by_planes);
+    }
 }
 
 }  // namespace

@@ -37,6 +37,9 @@ def run(G, x, in_lo, in_hi, w, lo, hi, stride, pad, dil):
     ((3, 3, 3), 2, (40, 131, 70), 16, (1, 1, 1), (1, 1, 1), (1, 1, 1)),       # four rows to a wave
     ((3, 3, 3), 1, (23, 131, 70), 40, (1, 1, 1), (1, 0, 1), (1, 1, 1)),       # two rows; a second block of filters
     ((3, 3, 3), 1, (9, 40, 150), 24, (1, 2, 2), (1, 1, 1), (1, 1, 1)),
+    ((3, 3, 3), 1, (11, 40, 130), 256, (1, 1, 1), (1, 1, 1), (1, 1, 1)),      # more workgroups than are resident: plane by plane
+    ((3, 3, 3), 1, (23, 60, 130), 96, (1, 1, 1), (1, 1, 1), (1, 1, 1)),       # two rounds with four or five waves: planes together
+    ((3, 3, 3), 2, (83, 131, 70), 16, (1, 1, 1), (1, 1, 1), (1, 1, 1)),       # plane by plane with half a block of filters
     ((3, 3, 3), 2, (7, 30, 80), 16, (1, 1, 3), (2, 5, 4), (1, 3, 2)),         # planes and columns of padding alone
     ((3, 3, 3), 1, (5, 40, 620), 8, (1, 1, 70), (1, 1, 1), (1, 1, 1)),        # columns too far apart for a tile
     ((3, 3, 3), 1, (5, 260, 130), 8, (1, 1, 1), (1, 60, 40), (1, 120, 60)),

@@ -334,6 +334,25 @@ def test_resident_waves_of_the_matrix_kernels():
     assert found == 104
 
 
+@pytest.mark.skipif(not os.path.exists(READELF), reason="needs llvm-readelf")
+def test_resident_waves_of_the_first_layer_kernels():
+    """Of a volume's kernels the ones that take a tile's planes one by one leave room for five waves of a SIMD, the ones that
+    take them together for four, which the launch counts on; the far ones of more than 16 filters have four."""
+    from paper_1801_09449_amd import build
+    if not os.path.exists(build.LIB):
+        pytest.skip("needs the built library")
+    found = 0
+    for name, (registers, scratch) in kernels_of(build.LIB).items():
+        m = re.search(r"first_conv_kernelILi3ELb([01])ELb([01])ELb([01])E", name)
+        if not m:
+            continue
+        found += 1
+        few, far, together = (x == "1" for x in m.groups())
+        waves = 512 // (-(-registers // 8) * 8)
+        assert waves >= (4 if together or (far and not few) else 5) and scratch == 0, (name, registers, scratch)
+    assert found == 7
+
+
 @pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
 def test_second_look_counts_the_same_resident_waves(tmp_path):
     """24 and 16 waves of a compute unit, three and two workgroups of eight, in the second look as in the first."""
