@@ -247,11 +247,13 @@ inline bool choose(const MatrixShape& s, Choice& best)
 // taken where it is 4 % shorter, on 40 of them, by 6 % in the geometric mean (2 % longer to 20 % shorter): 128 -> 128 channels
 // 3 x 3 on 113 x 81 5.2 -> 4.5 us, 512 -> 256 on 52 x 36 6.9 -> 6.3, 64 -> 64 on 232 x 168 4.5 -> 4.1.  Not from 6 us on, where
 // rates decide (216 -> 32, 3 x 3, on sixteen of 43 x 197 13.6 and 14.7); and the caller leaves tap-packed filters out, whose
-// shifts make a step longer than it is here (5 -> 26 on 2 x 30 x 56 x 14 4.9 and 5.4).
+// shifts make a step longer than it is here (5 -> 26 on 2 x 30 x 56 x 14 4.9 and 5.4).  The fit is to one-digit input; an item
+// of two digits takes longer to widen and counts half as much again (counted like the others, 64 -> 37,
+// 2 x 2 x 2 with stride 2, on 4 x 78 x 6 x 66 went to half the waves, 5.5 -> 6.7 us, and 128 -> 64, 2 x 2 x 2, on 2 x 6 x 78 x 20 5.8 -> 6.5).
 inline double small_cost(const MatrixShape& s, const Choice& c, const Tile& t, int lks)
 {
     const int waves = waves_of(c), groups = cdiv(s.c_out, 32) / c.nb, active = c.nwc > groups ? waves / c.nwc * groups : waves;
-    const double rounds64 = rounds64_of(waves, t.items), steps = steps_of(s, lks);
+    const double rounds64 = (s.digits ? 1.5 : 1.0) * rounds64_of(waves, t.items), steps = steps_of(s, lks);
     const double blocks = c.nb, two = c.nb - 1, split = c.nks > 1 ? 1.0 : 0.0;
     const int64_t per_cu = (t.wgs + 255) >> 8;
     const double wave = 560.0 + 83.0 * rounds64 + (20.0 + 35.0 * two) * steps + blocks * ((s.packed ? 270.0 : 400.0) * kShare[c.nks] + 380.0 * split);

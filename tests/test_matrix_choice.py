@@ -195,6 +195,25 @@ int main()
 """
 
 
+DIGITS = r"""
+#include "tern_matrix_choice.h"
+#include <cstdio>
+using namespace tern;
+int main()
+{
+    // (n, c_out, output, kernel, stride, dilation, words, digits, packed, LDS limit): two-digit input, a tile's fill against its steps
+    const MatrixShape s[] = {{4, 37, 40, 4, 34, 2, 2, 2, 2, 2, 2, 1, 1, 1, 2, 1, 1, 163840}, {16, 64, 1, 24, 64, 1, 3, 3, 1, 2, 2, 1, 1, 1, 3, 1, 1, 163840},
+                             {2, 64, 7, 79, 21, 2, 2, 2, 1, 1, 1, 1, 1, 1, 4, 1, 1, 163840}, {4, 32, 1, 107, 97, 1, 2, 2, 1, 1, 1, 1, 1, 1, 4, 1, 1, 163840}};
+    for (const MatrixShape& x : s) {
+        Choice a, b;
+        Tile ta, tb;
+        if (!choose_cached(x, a, &b) || !tile_of(x, a, ta) || !tile_of(x, b, tb)) return 1;
+        printf("%d ", rounds64_of(waves_of(b), tb.items) <= rounds64_of(waves_of(a), ta.items));
+    }
+}
+"""
+
+
 ROWS = r"""
 #include "tern_matrix_choice.h"
 #include <cstdio>
@@ -363,3 +382,9 @@ def test_second_look_counts_the_same_resident_waves(tmp_path):
 def test_rows_of_int32_sums(tmp_path):
     """Which launches of the large waves get rows of 16 voxels (log2 extents along x and y)."""
     assert build_and_run(tmp_path, ROWS).split() == ["42", "42", "43", "43", "43", "52", "32", "42", "32", "32", "42", "32", "42", "32"]
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_second_look_counts_the_fill_of_two_digit_input(tmp_path):
+    """Launches that took 1.06 to 1.22 times as long with their steps split over fewer waves, which fill the tile alone."""
+    assert build_and_run(tmp_path, DIGITS).split() == ["1"] * 4
