@@ -712,8 +712,8 @@ static bool pair_plan(const ConvPair& pair, int32_t n, PairPlan& u)
 
 // Every convolution goes this way except those that one of the limits below sends to the bit-count
 // kernels: more than 128 taps (the tap offsets of a wave sit in two registers), sums that could pass
-// 2^21 (the epilogue works with halves; LDS runs out first, so far), halo tiles that do not fit in LDS, and tiles
-// whose rows of a plane span more than 4 GB.
+// 2^21 (the epilogue works with halves; LDS runs out first, so far), halo tiles that do not fit in LDS, tiles
+// whose rows of a plane span more than 4 GB, and banks of more than 3.75 GB where a halo tile of 128 voxels does not fit.
 // A tile holds all words of its voxels: 3 x 3 x 3 kernels fit up to 47 words (1504 channels) at stride 1, 19 with
 // dilation 2, 10 with 3, 14 at stride 2, 7 and 4 with dilation 2 and 3; from the next word on they take three
 // to eight times as long as their neighbours.
@@ -741,16 +741,15 @@ bool launch_conv_matrix(const ConvParams& p, const ConvPair* pair, hipStream_t s
     if (!choose_cached(shape, c, &settled)) return false;
     if (!p.tp_slots || c.vb == 4) c = settled;
     if (!tile_of(shape, c, q)) return false;
-    // A tile's planes within 4 GB (a volume's may be more), or else its rows of each: then with waves of 128 voxels on 32
-    // filters, as there is one form of that kernel (64 -> 64 channels, 3 x 3, on a plane of 16 400 x 16 400
+    // A tile's planes within 4 GB (a volume's may be more), or else its rows of each, and the filter bank: else waves of 128
+    // voxels on 32 filters, as there is one form of that kernel (64 -> 64 channels, 3 x 3, on a plane of 16 400 x 16 400
     // 6.9 ms; half of it, which one descriptor reaches, 3.4, with bit counts 17.6).
     const int64_t line_bytes = 8 * (int64_t)p.wd_in * p.w, plane_bytes = line_bytes * p.h;
-    const bool whole = plane_bytes * p.d * p.n <= 0xffff0000ll;
-    int64_t reach = pair ? t.pair.reach : whole ? plane_bytes * p.d * p.n : plane_bytes * (q.hz < p.d ? q.hz : p.d);
-    // (the bank is read through one, too, and a row past its end, which has to read as zeros, has to lie within 4 GB)
-    const int64_t bank_rows = p.tp_slots ? cdiv(taps, (int64_t)p.tp_slots) : taps * (p.wd_in / p.wc);
-    const int64_t bank_bytes = (bank_rows + 1) * p.co_pad * p.wc * (p.binary ? 4 : 8);
-    const bool far = reach > 0xffff0000ll || bank_bytes > 0xf0000000ll;
+    bool whole;
+    int64_t reach = input_reach(p.n, p.d, plane_bytes, q.hz, whole);
+    if (pair) reach = t.pair.reach;
+    const int64_t bank_rows = bank_rows_of(taps, p.wd_in, p.wc, p.tp_slots), row_bytes = (int64_t)p.co_pad * p.wc * (p.binary ? 4 : 8);
+    const bool far = reach > kReach || !bank_in_reach(bank_rows, row_bytes);
     if (far && pair) return false;
     if (far) {
         const bool flat = p.od == 1, deep = p.od > 1 && p.kd > 1;
@@ -763,7 +762,7 @@ bool launch_conv_matrix(const ConvParams& p, const ConvPair* pair, hipStream_t s
             if (!tile_of(shape, c, q)) return false;
         }
         reach = line_bytes * (q.hy < p.h ? q.hy : p.h);
-        if (reach > 0xffff0000ll) return false;
+        if (reach > kReach) return false;
     }
     const int X = 1 << c.lxb, Y = 1 << c.lyb, Z = (32 * c.vb) >> (c.lxb + c.lyb);
     const int64_t gy = q.wgs / q.tiles;
@@ -777,7 +776,7 @@ bool launch_conv_matrix(const ConvParams& p, const ConvPair* pair, hipStream_t s
     t.item = (uint32_t)(plane_bytes * p.d);
     t.nch = p.digits || odd ? words : words / 2;
     t.rows = (int32_t)bank_rows;
-    t.row_bytes = p.co_pad * p.wc * (p.binary ? 4 : 8);
+    t.row_bytes = (int32_t)row_bytes;
     t.plane = t.hx * t.hy;
     t.items = (int32_t)q.items;
     t.pl = (int32_t)(q.hx * q.hy * q.hz * 16);

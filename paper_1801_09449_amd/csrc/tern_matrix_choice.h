@@ -78,6 +78,22 @@ inline bool tile_of(const MatrixShape& s, const Choice& c, Tile& t)
     return true;
 }
 
+// What the kernel reads through buffer descriptors has to lie within reach of their 32-bit offsets.
+constexpr int64_t kReach = 0xffff0000ll;
+// Bytes that the input's descriptor spans: all of the input, or a tile's planes in it.
+inline int64_t input_reach(int32_t n, int32_t d, int64_t plane_bytes, int64_t hz, bool& whole)
+{
+    whole = plane_bytes * d * n <= kReach;
+    return whole ? plane_bytes * d * n : plane_bytes * (hz < d ? hz : d);
+}
+inline int64_t bank_rows_of(int64_t taps, int32_t wd_in, int32_t wc, int32_t tp_slots)
+{
+    return tp_slots ? cdiv(taps, (int64_t)tp_slots) : taps * (wd_in / wc);
+}
+// Rows past the end of the filter bank have to read as zeros (the absent partner of the last row) or are fetched and not used
+// (up to twelve, those of the six steps under way): a row is at most 8 MB (2^19 filters), and 256 MB are left for them.
+inline bool bank_in_reach(int64_t rows, int64_t row_bytes) { return (rows + 1) * row_bytes <= 0xf0000000ll; }
+
 // Estimated time of a launch in clock cycles, the 1.73-norm of two parts.  Throughput (busy): the fullest
 // compute unit's share of matrix instructions (32 cycles each) and of vector instructions (a wave's fixed
 // part, per 64 halo items, per step and its operands, per accumulator block of the epilogue).  Latency: as

@@ -214,6 +214,39 @@ int main()
 """
 
 
+REACH = r"""
+#include "tern_matrix_choice.h"
+#include <cstdio>
+using namespace tern;
+int main()
+{
+    int wrong = 0;
+    bool whole;
+    // input: all of it, a tile's planes of it, more than there are, planes that do not fit
+    wrong += input_reach(2, 8, 1 << 28, 4, whole) != (1ll << 30) || whole;
+    wrong += input_reach(1, 15, 1 << 28, 4, whole) != 15ll << 28 || !whole;
+    wrong += input_reach(1, 16, 1 << 28, 4, whole) != (1ll << 30) || whole;
+    wrong += input_reach(7, 2, 1 << 29, 4, whole) != (1ll << 30) || whole;
+    wrong += input_reach(1, 65535, 65536, 3, whole) != kReach || !whole;
+    wrong += input_reach(1, 65536, 65536, 3, whole) != 3 * 65536 || whole;
+    wrong += input_reach(1, 3, 1ll << 31, 3, whole) != 3ll << 31 || whole;
+    // bank: (taps, words of the input, words of a row, taps to a word) -> rows; plain even and odd, digits, tap-packed
+    wrong += bank_rows_of(27, 36, 2, 0) != 486 || bank_rows_of(27, 37, 1, 0) != 999 || bank_rows_of(9, 4, 2, 0) != 18;
+    wrong += bank_rows_of(27, 1, 1, 2) != 14 || bank_rows_of(9, 1, 1, 32) != 1 || bank_rows_of(128, 1, 1, 4) != 32;
+    // the most filters: rows of 8 and 4 MB (ternary, even and odd words), 4 and 2 MB (binary); the last row that fits and the next
+    const int64_t co = 1 << 19;
+    const int64_t bytes[4] = {co * 16, co * 8, co * 8, co * 4};
+    for (int64_t b : bytes) {
+        const int64_t rows = 0xf0000000ll / b - 1;
+        wrong += !bank_in_reach(rows, b) || bank_in_reach(rows + 1, b);
+        // the bank with the twelve rows fetched past its end, two words of 32 bits and two blocks of filters on
+        wrong += (rows + 13) * b + 1024 > kReach;
+    }
+    printf("%d", wrong);
+}
+"""
+
+
 ROWS = r"""
 #include "tern_matrix_choice.h"
 #include <cstdio>
@@ -388,3 +421,9 @@ def test_rows_of_int32_sums(tmp_path):
 def test_second_look_counts_the_fill_of_two_digit_input(tmp_path):
     """Launches that took 1.06 to 1.22 times as long with their steps split over fewer waves, which fill the tile alone."""
     assert build_and_run(tmp_path, DIGITS).split() == ["1"] * 4
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_reach_of_the_buffer_descriptors(tmp_path):
+    """Which inputs and filter banks the kernel's ordinary form takes, on both sides of the limits."""
+    assert build_and_run(tmp_path, REACH) == "0"
