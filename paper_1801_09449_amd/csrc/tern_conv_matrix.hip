@@ -108,7 +108,7 @@ __device__ __forceinline__ v4i expand_digits(uint32_t lm, uint32_t hm, uint32_t 
 
 // FAR: a tile's planes together span more than 4 GB, so a buffer descriptor takes the tile's rows of one plane at a time.
 template <int VB, int NB, bool PACKED, int KIND, bool ODD, bool SPLIT, bool FAR>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void conv_matrix_kernel(ConvParams p, MatrixPlan t)
+__global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPlan t)
 {
     extern __shared__ __align__(16) uint8_t lds8[];
     const int tid = threadIdx.x;
@@ -711,7 +711,7 @@ static bool pair_plan(const ConvPair& pair, int32_t n, PairPlan& u)
 }
 
 // Every convolution goes this way except those that one of the limits below sends to the bit-count
-// kernels: more than 128 taps (the tap offsets of a wave sit in two registers), sums that could pass
+// kernels: more than 128 taps (the bound of the reciprocals of kernel extents, and as far as it was measured), sums that could pass
 // 2^21 (the epilogue works with halves; LDS runs out first, so far), halo tiles that do not fit in LDS, tiles
 // whose rows of a plane span more than 4 GB, and banks of more than 3.75 GB where a halo tile of 128 voxels does not fit.
 // A tile holds all words of its voxels: 3 x 3 x 3 kernels fit up to 47 words (1504 channels) at stride 1, 19 with
