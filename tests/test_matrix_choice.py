@@ -202,8 +202,9 @@ using namespace tern;
 int main()
 {
     // (n, c_out, output, kernel, stride, dilation, words, digits, packed, LDS limit): two-digit input, a tile's fill against its steps
-    const MatrixShape s[] = {{4, 37, 40, 4, 34, 2, 2, 2, 2, 2, 2, 1, 1, 1, 2, 1, 1, 163840}, {16, 64, 1, 24, 64, 1, 3, 3, 1, 2, 2, 1, 1, 1, 3, 1, 1, 163840},
-                             {2, 64, 7, 79, 21, 2, 2, 2, 1, 1, 1, 1, 1, 1, 4, 1, 1, 163840}, {4, 32, 1, 107, 97, 1, 2, 2, 1, 1, 1, 1, 1, 1, 4, 1, 1, 163840}};
+    // (planes of a batch are planes of one volume)
+    const MatrixShape s[] = {{4, 37, 40, 4, 34, 2, 2, 2, 2, 2, 2, 1, 1, 1, 2, 1, 1, 163840}, {1, 64, 16, 24, 64, 1, 3, 3, 1, 2, 2, 1, 1, 1, 3, 1, 1, 163840},
+                             {2, 64, 7, 79, 21, 2, 2, 2, 1, 1, 1, 1, 1, 1, 4, 1, 1, 163840}, {1, 32, 4, 107, 97, 1, 2, 2, 1, 1, 1, 1, 1, 1, 4, 1, 1, 163840}};
     for (const MatrixShape& x : s) {
         Choice a, b;
         Tile ta, tb;
