@@ -49,7 +49,7 @@ ALGORITHMIC_OPS_PER_MAC = 5.0 / 32.0
 # HBM bytes per launch of the config[1] kernel: rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE scaled by
 # a 256 MiB copy under the same counters (profiles/conv_matrix_kernels.md).  A profiler figure,
 # not measured by this script.
-TRAFFIC_BYTES_CFG1 = 9.72e6
+TRAFFIC_BYTES_CFG1 = 9.68e6
 ALGORITHMIC_BYTES_CFG1 = 8.42e6
 SETTLE_MS = 40.0                          # GPU work in front of every timed region (clocks settle)
 

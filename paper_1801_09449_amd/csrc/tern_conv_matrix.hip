@@ -106,7 +106,8 @@ __device__ __forceinline__ v4i expand_digits(uint32_t lm, uint32_t hm, uint32_t 
     return o;
 }
 
-// FAR: a tile's planes together span more than 4 GB, so a buffer descriptor takes the tile's rows of one plane at a time.
+// FAR: a tile's planes together, or the filter bank, span more than 4 GB: a buffer descriptor takes the tile's rows of one plane
+// at a time, and bank rows are read by 64-bit addresses.
 template <int VB, int NB, bool PACKED, int KIND, bool ODD, bool SPLIT, bool FAR>
 __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPlan t)
 {
@@ -448,10 +449,10 @@ __global__ __launch_bounds__(512) void conv_matrix_kernel(ConvParams p, MatrixPl
     entry = 0;
     if constexpr (VB == 4) {
         // Operands of step i + 1 are fetched and widened between step i's matrix instructions, filter words two steps further
-        // ahead.  In front of all of them, both waves of a SIMD did that at the same time, with the matrix cores idle: 64 -> 64
-        // channels on 96^3 with dilation 2 46.1 -> 44.5 us, 256 -> 256 on 2 x 32^3 45.6 -> 42.1 (with a wave priority for that
-        // part 41.3 and 47.2).  (The barriers hold the order; a load moved above the last use of its registers has the compiler
-        // copy them and wait.)
+        // ahead.  In front of all of them, both waves of a SIMD do that at the same time, with the matrix cores idle: the same steps
+        // so ordered take 46.1 us for 44.5 on 64 -> 64 channels, 96^3 with dilation 2, and 45.6 for 42.1 on 256 -> 256, 2 x 32^3 (with
+        // a wave priority for that part 47.2 and 41.3).  The scalar walk before them, which had that order, took 47.6 and 42.8.
+        // (The barriers hold the order; a load moved above the last use of its registers has the compiler copy them and wait.)
         auto column = [&](const v4i (&F)[NB], const v4i (&x)[VB], int vb) {
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) acc[vb][nb] = multiply(F[nb], x[vb], acc[vb][nb]);

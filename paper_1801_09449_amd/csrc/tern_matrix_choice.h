@@ -2,8 +2,9 @@
 // take, chosen from sizes alone.  Host code without HIP, so that a test can compile it by itself.
 //
 // A program whose extents are new on every call pays for the choice on every call, so it has to cost little
-// beside a launch: 2.4 us on average over random geometries and 3.0 us for 256 -> 256 channels on 32^3, where
-// every candidate's whole estimate, two powers among them, took 6.3 us on the same host.
+// beside a launch: 2.4 us on average over random geometries and 4.0 us for 256 -> 256 channels on 32^3 (an EPYC core;
+// a Xeon at 2.7 GHz 4.6 and 6.9), the second look at small launches in it: 0.1 on average, 0.4 of the 2.4 us of 512 -> 256,
+// 3 x 3, on 52 x 36.  Every candidate's whole estimate, two powers among them, would take twice as long.
 #pragma once
 #include <stdint.h>
 #include <string.h>
@@ -99,9 +100,11 @@ inline bool bank_in_reach(int64_t rows, int64_t row_bytes) { return (rows + 1) *
 // part, per 64 halo items, per step and its operands, per accumulator block of the epilogue).  Latency: as
 // many rounds of workgroups as registers and LDS leave no room for at once, each as long as one wave takes by
 // itself.  The weights are a fit to 1400 launches on 54 shapes, from the 2-D layers of a U-Net to 96-cubed volumes
-// (workgroups of powers of two only; the search looks at more).  Of 2817 launches on those shapes, the choice took
-// 6 % longer than the best one in the geometric mean and 22 % at the most.
-// A choice looks at some two hundred launches, so nothing below is an integer division.
+// (workgroups of powers of two only; the search looks at more), of kernels whose small waves took twice as long
+// for a step as now and which added partial sums by whole blocks.  Of 1868 launches of the kernels as they are on those shapes, the choice, with the
+// second look and the rows of int32 sums below, takes 2.3 % longer than the best one in the geometric mean and 19 % at the most.
+// A choice looks at some two hundred launches, so no candidate of this search costs an integer division (the second look
+// divides: it has at most forty).
 inline int32_t steps_of(const MatrixShape& s, int lks)             // of a wave, the longest
 {
     return (int32_t)(((int64_t)s.kd * s.kh * s.kw * s.words + ((int64_t)2 << lks)) >> (lks + 1));
