@@ -713,8 +713,8 @@ static bool pair_plan(const ConvPair& pair, int32_t n, PairPlan& u)
 
 // Every convolution goes this way except those that one of the limits below sends to the bit-count
 // kernels: more than 128 taps (the bound of the reciprocals of kernel extents, and as far as it was measured), sums that could pass
-// 2^21 (the epilogue works with halves; LDS runs out first, so far), halo tiles that do not fit in LDS, tiles
-// whose rows of a plane span more than 4 GB, and banks of more than 3.75 GB where a halo tile of 128 voxels does not fit.
+// 2^21 (the epilogue works with halves; LDS runs out first, so far), halo tiles that do not fit in LDS, and tiles
+// whose rows of a plane span more than 4 GB.
 // A tile holds all words of its voxels: 3 x 3 x 3 kernels fit up to 47 words (1504 channels) at stride 1, 19 with
 // dilation 2, 10 with 3, 14 at stride 2, 7 and 4 with dilation 2 and 3; from the next word on they take three
 // to eight times as long as their neighbours.
@@ -742,17 +742,19 @@ bool launch_conv_matrix(const ConvParams& p, const ConvPair* pair, hipStream_t s
     if (!choose_cached(shape, c, &settled)) return false;
     if (!p.tp_slots || c.vb == 4) c = settled;
     if (!tile_of(shape, c, q)) return false;
-    // A tile's planes within 4 GB (a volume's may be more), or else its rows of each, and the filter bank: else waves of 128
-    // voxels on 32 filters, as there is one form of that kernel (64 -> 64 channels, 3 x 3, on a plane of 16 400 x 16 400
-    // 6.9 ms; half of it, which one descriptor reaches, 3.4, with bit counts 17.6).
+    // A tile's planes within 4 GB (a volume's may be more), or else its rows of each: then with waves of 128 voxels on 32
+    // filters (64 -> 64 channels, 3 x 3, on a plane of 16 400 x 16 400 6.9 ms; half of it, which one descriptor reaches, 3.4,
+    // with bit counts 17.6).
     const int64_t line_bytes = 8 * (int64_t)p.wd_in * p.w, plane_bytes = line_bytes * p.h;
     bool whole;
     int64_t reach = input_reach(p.n, p.d, plane_bytes, q.hz, whole);
     if (pair) reach = t.pair.reach;
+    // The filter bank within 4 GB, or else the launch as chosen, without a split (2^19 filters of 1152 channels, 3 x 3 x 3, on
+    // 4 x 6 x 9 3.8 ms, with bit counts 122; of 256, 11 x 11, on 90 x 100 53 ms, with waves of 128 voxels on 32 filters 69).
     const int64_t bank_rows = bank_rows_of(taps, p.wd_in, p.wc, p.tp_slots), row_bytes = (int64_t)p.co_pad * p.wc * (p.binary ? 4 : 8);
-    const bool far = reach > kReach || !bank_in_reach(bank_rows, row_bytes);
+    const bool far_input = reach > kReach, far = far_input || !bank_in_reach(bank_rows, row_bytes);
     if (far && pair) return false;
-    if (far) {
+    if (far_input) {
         const bool flat = p.od == 1, deep = p.od > 1 && p.kd > 1;
         const int8_t* sh = kWaveShape[1][flat][0];
         c = {4, 1, sh[0], sh[1], 1, 1, 1, 1};
@@ -762,6 +764,11 @@ bool launch_conv_matrix(const ConvParams& p, const ConvPair* pair, hipStream_t s
             c.nwy = c.nwz = 1;
             if (!tile_of(shape, c, q)) return false;
         }
+    } else if (far) {
+        c.nks = 1;
+        if (!tile_of(shape, c, q)) return false;
+    }
+    if (far) {
         reach = line_bytes * (q.hy < p.h ? q.hy : p.h);
         if (reach > kReach) return false;
     }
@@ -801,23 +808,24 @@ bool launch_conv_matrix(const ConvParams& p, const ConvPair* pair, hipStream_t s
     const dim3 grid((unsigned)q.tiles, (unsigned)gy);
     const size_t lds = (size_t)q.lds;
     note_launch(TERN_KERNEL_TILED, c.vb / 2, 32 * c.nb, c.nks, threads, grid.x, grid.y, lds);
-    if (far) {
-        *rc = packed ? launch_kind<4, 1, true, false, true>(p, t, odd, lds, grid, threads, s)
-                     : launch_kind<4, 1, false, false, true>(p, t, odd, lds, grid, threads, s);
-        return true;
-    }
-    const auto kind = [&](auto vb, auto nb, auto split) {
+    const auto kind = [&](auto vb, auto nb, auto split, auto beyond) {
         constexpr int VB = decltype(vb)::value, NB = decltype(nb)::value;
-        constexpr bool SPLIT = decltype(split)::value;
-        return packed ? launch_kind<VB, NB, true, SPLIT, false>(p, t, odd, lds, grid, threads, s)
-                      : launch_kind<VB, NB, false, SPLIT, false>(p, t, odd, lds, grid, threads, s);
+        constexpr bool SPLIT = decltype(split)::value, FAR = decltype(beyond)::value;
+        return packed ? launch_kind<VB, NB, true, SPLIT, FAR>(p, t, odd, lds, grid, threads, s)
+                      : launch_kind<VB, NB, false, SPLIT, FAR>(p, t, odd, lds, grid, threads, s);
     };
     const std::integral_constant<int, 1> one;
     const std::integral_constant<int, 2> two;
     const std::integral_constant<int, 4> four;
-    if (c.vb == 4) *rc = c.nb == 2 ? kind(four, two, std::false_type{}) : kind(four, one, std::false_type{});
-    else if (c.nks > 1) *rc = c.nb == 2 ? kind(two, two, std::true_type{}) : kind(two, one, std::true_type{});
-    else *rc = c.nb == 2 ? kind(two, two, std::false_type{}) : kind(two, one, std::false_type{});
+    const std::true_type yes;
+    const std::false_type no;
+    const auto unsplit = [&](auto beyond) {
+        if (c.vb == 4) return c.nb == 2 ? kind(four, two, no, beyond) : kind(four, one, no, beyond);
+        return c.nb == 2 ? kind(two, two, no, beyond) : kind(two, one, no, beyond);
+    };
+    if (far) *rc = unsplit(yes);
+    else if (c.nks > 1) *rc = c.nb == 2 ? kind(two, two, yes, no) : kind(two, one, yes, no);
+    else *rc = unsplit(no);
     return true;
 }
 

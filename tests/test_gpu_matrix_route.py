@@ -433,29 +433,34 @@ def test_planes_of_a_tile_beyond_four_gigabytes(G, ci, co, vol, k, stride, binar
     torch.cuda.empty_cache()
 
 
-@pytest.mark.parametrize("ci", [256, 288])                  # eight and nine words: rows of pairs; single words, an odd number of them
-def test_filter_bank_beyond_four_gigabytes(G, ci):
+@pytest.mark.parametrize("ci,vol,k,co,form", [
+    # even and odd words: rows of pairs; single words, an odd number of them
+    (256, (1, 4, 9), (1, 11, 11), 1 << 19, (1, 64)), (288, (1, 4, 9), (1, 11, 11), 1 << 19, (1, 64)), (288, (1, 4, 9), (1, 11, 11), (1 << 19) - 32, (1, 32)),
+    (1152, (2, 3, 5), (3, 3, 3), 1 << 19, (1, 64)), (1184, (2, 3, 5), (3, 3, 3), 1 << 19, (1, 64)), (1184, (2, 3, 5), (3, 3, 3), (1 << 19) - 40, (1, 32)),
+    (256, (1, 90, 100), (1, 11, 11), 1 << 19, (2, 64)), (576, (8, 12, 14), (3, 3, 6), (1 << 19) - 32, (2, 32))])   # (waves of 128 voxels)
+def test_filter_bank_beyond_four_gigabytes(G, ci, vol, k, co, form):
     """A bank that no buffer descriptor reaches, and the row past its end, against the same convolution with some of its filters."""
     import torch
     import paper_1801_09449_amd as T
-    co, part, k, pad = 1 << 19, 2048, (1, 11, 11), (0, 5, 5)
+    part, pad, cp = 2048, tuple(a // 2 for a in k), (co + 31) // 32 * 32
     gen = torch.Generator("cuda").manual_seed(ci)
-    act = T.tern_pack(torch.randint(-1, 2, (1, ci, 1, 4, 9), generator=gen, device="cuda", dtype=torch.int8))
+    act = T.tern_pack(torch.randint(-1, 2, (1, ci) + vol, generator=gen, device="cuda", dtype=torch.int8))
     words = ci // 32
     wc = 1 + (words + 1) % 2
-    bank = torch.randint(-2**31, 2**31 - 1, (121 * words // wc, co, 2, wc), generator=gen, device="cuda", dtype=torch.int32)
+    bank = torch.randint(-2**31, 2**31 - 1, (k[0] * k[1] * k[2] * words // wc, cp, 2, wc), generator=gen, device="cuda", dtype=torch.int32)
     bank[:, :, 1] &= bank[:, :, 0]
-    assert (bank.shape[0] + 1) * co * 8 * wc > 0xf0000000
+    assert (bank.shape[0] + 1) * cp * 8 * wc > 0xf0000000
     lo, hi = torch.full((co,), -40, device="cuda", dtype=torch.int32), torch.arange(co, device="cuda", dtype=torch.int32) % 60
-    acc = T.tern_conv3d(act, ci, bank.view(-1), co, k, 1, pad)
-    plan = T.tern_last_launch()
-    assert plan["kernel"] == T.KERNEL_TILED and (plan["voxels_per_lane"], plan["channels_per_pass"], plan["tap_split"]) == (2, 32, 1)
+    small = vol[1] < 50
+    acc = T.tern_conv3d(act, ci, bank.view(-1), co, k, 1, pad) if small else None
     packed = T.tern_conv3d(act, ci, bank.view(-1), co, k, 1, pad, thr_lo=lo, thr_hi=hi)
-    for a in (0, co // 2 - part // 2, co - part):
-        few = bank[:, a:a + part].contiguous().view(-1)
-        want = T.tern_conv3d(act, ci, few, part, k, 1, pad)
-        assert T.tern_last_launch()["voxels_per_lane"] == 1      # the ordinary form
-        assert torch.equal(acc[:, a:a + part], want)
-        assert torch.equal(packed[..., a // 32:(a + part) // 32], T.tern_threshold_pack(want, lo[a:a + part].contiguous(), hi[a:a + part].contiguous()))
-    del bank, acc, packed
+    plan = T.tern_last_launch()
+    assert plan["kernel"] == T.KERNEL_TILED and (plan["voxels_per_lane"], plan["channels_per_pass"], plan["tap_split"]) == form + (1,)
+    for a in (0, cp // 64 * 32 - part // 2, cp - part):
+        few, n = bank[:, a:a + part].contiguous().view(-1), min(part, co - a)
+        want = T.tern_conv3d(act, ci, few, n, k, 1, pad)
+        if small:
+            assert torch.equal(acc[:, a:a + n], want)
+        assert torch.equal(packed[..., a // 32:(a + part) // 32], T.tern_threshold_pack(want, lo[a:a + n].contiguous(), hi[a:a + n].contiguous()))
+    del bank, acc, packed, want
     torch.cuda.empty_cache()

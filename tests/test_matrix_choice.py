@@ -384,7 +384,7 @@ def test_resident_waves_of_the_matrix_kernels():
         if (vb, nb, kind) == (2, 1, 4):        # input in two tensors
             least = 20
         assert waves >= least and scratch == 0, (name, registers, scratch)
-    assert found == 104
+    assert found == 146
 
 
 @pytest.mark.skipif(not os.path.exists(READELF), reason="needs llvm-readelf")
